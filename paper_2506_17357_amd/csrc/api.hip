@@ -77,15 +77,11 @@ int props(DevProps *out) {
         // shared memory (their static LDS is a few bytes).  If the runtime
         // refuses, stay within the 64 KiB every launch may use.
         const int dyn = lds - 1024;
-        const void *fns[] = {(const void *)k_eval_inter<false, false>, (const void *)k_eval_inter<true, false>,
-                             (const void *)k_eval_inter<false, true>, (const void *)k_eval_inter<true, true>,
-                             (const void *)k_eval_batch<1>, (const void *)k_eval_batch<2>,
+        const void *fns[] = {(const void *)k_eval_batch<1>, (const void *)k_eval_batch<2>,
                              (const void *)k_eval_batch<3>, (const void *)k_eval_batch<5>,
                              (const void *)k_eval_batch<7>,
                              (const void *)k_eval_solution<false, false>, (const void *)k_eval_solution<true, false>,
-                             (const void *)k_eval_solution<false, true>, (const void *)k_eval_solution<true, true>,
-                             (const void *)k_eval_gran_fused<false, false>, (const void *)k_eval_gran_fused<true, false>,
-                             (const void *)k_eval_gran_fused<false, true>, (const void *)k_eval_gran_fused<true, true>};
+                             (const void *)k_eval_solution<false, true>, (const void *)k_eval_solution<true, true>};
         bool ok = dyn > 65536;
         for (const void *f : fns)
             if (ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dyn) != hipSuccess) ok = false;
@@ -165,8 +161,7 @@ long long count_items(int Q, int rows) {
 
 struct SolLayout {
     size_t desc, a4, b4, t4, w4, pf4, pb4, pl4, ql4, pdist, ref2slot, roff, rdist, nr_alt, roff_alt, rblk, best_key, rec,
-        state, acc, items, intra, total;
-    int max_items;
+        state, acc, total;
 };
 
 SolLayout sol_layout(int n, int R) {
@@ -200,10 +195,6 @@ SolLayout sol_layout(int n, int R) {
     L.rec = take(32 + 4 * 16 + 8 * kAccCount);
     L.state = L.rec + 32;
     L.acc = L.state + 4 * 16;
-    // room for one-row items (the smallest rows per item a schedule may give)
-    L.max_items = (int)Q;
-    L.items = take(sizeof(InterItem) * L.max_items);
-    L.intra = take(sizeof(IntraItem) * std::max(R, 1));  // at most one group per route
     L.total = off;
     return L;
 }
@@ -234,10 +225,6 @@ struct tga_solution {
     int32_t n, R, Q;
     SolDev h;          // host copy of the descriptor
     SolDev *d;         // device copy (1 entry)
-    InterItem *items;  // device
-    int nitems;
-    IntraItem *intra;  // device
-    int nintra;
     int tile_rows;   // rows one workgroup's LDS budget holds (batched form)
     int plain_rows;  // rows per item of the single-solution form
     int item_rows;   // rows per inter-route item of the batched form (0: the default rule)
@@ -483,20 +470,17 @@ extern "C" int tga_free_instance(tga_instance_t inst) {
 
 static int check_partition(int n, int R, const int32_t *offsets, const int32_t *customers);
 
-// Intra-route items: groups of consecutive routes whose customers typically
-// fill about 48 of a wavefront's 64 lanes (the kernel falls back to one route
-// at a time when a group has grown beyond what its wavefront can stage).
-static void push_intra_groups(int n, int R, int sol_index, std::vector<IntraItem> &intra) {
+// Routes per intra-route item: consecutive routes whose customers typically
+// fill about 48 of a wavefront's 64 lanes (the kernels fall back to one route
+// at a time when a group has grown beyond what is staged).
+static int group_routes(int n, int R) {
     const int avgL = std::max(1, n / std::max(1, R));
-    const int G = std::max(1, std::min(kIntraMaxGroup, 48 / (avgL + 1)));
-    for (int r = 0; r < R; r += G) intra.push_back(IntraItem{sol_index, r, std::min(R, r + G), 0});
+    return std::max(1, std::min(kIntraMaxGroup, 48 / (avgL + 1)));
 }
 
-static void build_plain_items(tga_solution *S, std::vector<InterItem> &items,
-                              std::vector<IntraItem> &intra, int sol_index) {
-    for_each_item(S->Q, S->plain_rows,
-                  [&](int s0, int s1) { items.push_back(InterItem{sol_index, s0, s1, 0}); });
-    push_intra_groups(S->n, S->R, sol_index, intra);
+static void push_intra_groups(int n, int R, int sol_index, std::vector<IntraItem> &intra) {
+    const int G = group_routes(n, R);
+    for (int r = 0; r < R; r += G) intra.push_back(IntraItem{sol_index, r, std::min(R, r + G), 0});
 }
 
 // Argument checks shared by every way of setting up a solution.
@@ -571,8 +555,6 @@ static int solution_init(tga_solution *S, tga_instance_t inst, int32_t R, const 
     h.state = (int32_t *)(base + L.state);
     h.acc = (long long *)(base + L.acc);
     S->d = (SolDev *)(base + L.desc);
-    S->items = (InterItem *)(base + L.items);
-    S->intra = (IntraItem *)(base + L.intra);
 
     // host-side layout: slots route-major with the start depot first
     std::vector<int2> nr(Q + 1);
@@ -585,12 +567,6 @@ static int solution_init(tga_solution *S, tga_instance_t inst, int32_t R, const 
     }
     roff[R] = s;
     nr[Q] = make_int2(0, R);
-    std::vector<InterItem> items;
-    std::vector<IntraItem> intra;
-    build_plain_items(S, items, intra, 0);
-    S->nitems = (int)items.size();
-    S->nintra = (int)intra.size();
-    if (S->nitems > L.max_items) return fail(TGA_ERANGE, "too many work items");
     std::vector<int32_t> state(16, 0);
     std::vector<long long> acc(kAccCount, 0);
     auto up = [&](void *dst, const void *src, size_t bytes) {
@@ -602,8 +578,6 @@ static int solution_init(tga_solution *S, tga_instance_t inst, int32_t R, const 
     if (e == hipSuccess) e = up(h.roff_alt, roff.data(), sizeof(int32_t) * (R + 1));
     if (e == hipSuccess) e = up(h.state, state.data(), sizeof(int32_t) * 16);
     if (e == hipSuccess) e = up(h.acc, acc.data(), sizeof(long long) * kAccCount);
-    if (e == hipSuccess) e = up(S->items, items.data(), sizeof(InterItem) * items.size());
-    if (e == hipSuccess) e = up(S->intra, intra.data(), sizeof(IntraItem) * intra.size());
     if (e == hipSuccess) {
         k_route_blocks_clear<<<(R + 255) / 256, 256, 0, st>>>(h.rblk, R);
         k_build<<<1, kApplyThreads, 0, st>>>(S->d);
@@ -643,12 +617,7 @@ extern "C" int tga_solution_set_rows(tga_solution_t sol, int32_t plain_rows_, in
     sol->item_rows = item_rows > 0 ? item_rows : t_item;
     sol->lds = rows_lds(sol->n + 1, sol->plain_rows, w16);
     sol->h.tile_rows = sol->plain_rows;
-    std::vector<InterItem> items;
-    std::vector<IntraItem> intra;
-    build_plain_items(sol, items, intra, 0);
-    sol->nitems = (int)items.size();
     hipStream_t st = (hipStream_t)stream;
-    HIPCHK(hipMemcpyAsync(sol->items, items.data(), sizeof(InterItem) * items.size(), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(sol->d, &sol->h, sizeof(SolDev), hipMemcpyHostToDevice, st));
     HIPCHK(hipStreamSynchronize(st));
     return TGA_OK;
@@ -737,123 +706,42 @@ extern "C" int tga_free_solution(tga_solution_t sol) {
 
 extern "C" uint32_t tga_solution_version(tga_solution_t sol) { return sol ? sol->version : 0; }
 
-// Granular mode: the inter-route moves of the granular pairs (one launch of
-// k_eval_gran), the intra-route ones complete (k_eval_intra).
-static void launch_eval_gran(const tga_instance *I, const SolDev *d, int R, const IntraItem *intra, int nintra,
-                             int has_tw, uint32_t op_mask, int32_t *dd, uint8_t *df, hipStream_t st) {
-    const bool dump = dd != nullptr;
-    const long long work = I->gcc + (long long)I->gdep * R;
-    if ((op_mask & 7) && work > 0 && (op_mask & (2 | 8 | 16)) && nintra > 0) {
-        // both kinds in one launch: the intra-route groups first, then the pairs
-        const int grid = nintra + (int)((work + kInterThreads - 1) / kInterThreads);
-        const size_t l = (size_t)kInterWaves * kIntraRegionBytes;
-        const int a = I->gcc, b = I->gdep;
-        if (has_tw) {
-            if (dump)
-                k_eval_gran_fused<true, true><<<grid, kInterThreads, l, st>>>(d, I->gsrc, I->gadj, a, b, intra, nintra,
-                                                                             op_mask, dd, df);
-            else
-                k_eval_gran_fused<true, false><<<grid, kInterThreads, l, st>>>(d, I->gsrc, I->gadj, a, b, intra,
-                                                                              nintra, op_mask, dd, df);
-        } else {
-            if (dump)
-                k_eval_gran_fused<false, true><<<grid, kInterThreads, l, st>>>(d, I->gsrc, I->gadj, a, b, intra,
-                                                                              nintra, op_mask, dd, df);
-            else
-                k_eval_gran_fused<false, false><<<grid, kInterThreads, l, st>>>(d, I->gsrc, I->gadj, a, b, intra,
-                                                                               nintra, op_mask, dd, df);
-        }
-        return;
-    }
-    if ((op_mask & 7) && work > 0) {
-        const int grid = (int)((work + 255) / 256);
-        const int a = I->gcc, b = I->gdep;
-        if (has_tw) {
-            if (dump)
-                k_eval_gran<true, true><<<grid, 256, 0, st>>>(d, I->gsrc, I->gadj, a, b, op_mask, dd, df);
-            else
-                k_eval_gran<true, false><<<grid, 256, 0, st>>>(d, I->gsrc, I->gadj, a, b, op_mask, dd, df);
-        } else {
-            if (dump)
-                k_eval_gran<false, true><<<grid, 256, 0, st>>>(d, I->gsrc, I->gadj, a, b, op_mask, dd, df);
-            else
-                k_eval_gran<false, false><<<grid, 256, 0, st>>>(d, I->gsrc, I->gadj, a, b, op_mask, dd, df);
-        }
-    }
-    if ((op_mask & (2 | 8 | 16)) && nintra > 0) {
-        const size_t ilds = (size_t)kInterWaves * kIntraRegionBytes;
-        if (has_tw) {
-            if (dump)
-                k_eval_intra<true, true><<<nintra, kInterThreads, ilds, st>>>(d, intra, nintra, op_mask, dd, df);
-            else
-                k_eval_intra<true, false><<<nintra, kInterThreads, ilds, st>>>(d, intra, nintra, op_mask, dd, df);
-        } else {
-            if (dump)
-                k_eval_intra<false, true><<<nintra, kInterThreads, ilds, st>>>(d, intra, nintra, op_mask, dd, df);
-            else
-                k_eval_intra<false, false><<<nintra, kInterThreads, ilds, st>>>(d, intra, nintra, op_mask, dd, df);
-        }
-    }
+// Launches of one evaluation take the workgroup counts of the enabled
+// operator kinds: intra-route groups of G routes, then inter-route work.
+struct EvalShape {
+    int nintra, G;
+};
+
+static EvalShape intra_shape(const tga_solution *sol, uint32_t op_mask) {
+    const int G = group_routes(sol->n, sol->R);
+    return EvalShape{(op_mask & (2 | 8 | 16)) ? (sol->R + G - 1) / G : 0, G};
 }
 
-static void launch_eval(const SolDev *d, const InterItem *items, int nitems, const IntraItem *intra,
-                        int nintra, int has_tw, uint32_t op_mask, size_t lds, int grid_inter,
-                        int32_t *dd, uint8_t *df, hipStream_t st) {
-    const bool dump = dd != nullptr;
-    if ((op_mask & 7) && nitems > 0 && (op_mask & (2 | 8 | 16)) && nintra > 0) {
-        // both kinds in one launch: one workgroup per intra-route group first
-        // (their walks are the launch's longest chains), then the inter-route
-        // workgroups
-        const int ninter = std::max(1, std::min(nitems, grid_inter));
-        const int nbintra = nintra;
-        const int grid = nbintra + ninter;
-        const size_t l = std::max(lds, (size_t)kInterWaves * kIntraRegionBytes);
-        if (has_tw) {
-            if (dump)
-                k_eval_solution<true, true><<<grid, kInterThreads, l, st>>>(d, items, nitems, intra, nintra, nbintra,
-                                                                            op_mask, dd, df);
-            else
-                k_eval_solution<true, false><<<grid, kInterThreads, l, st>>>(d, items, nitems, intra, nintra, nbintra,
-                                                                             op_mask, dd, df);
-        } else {
-            if (dump)
-                k_eval_solution<false, true><<<grid, kInterThreads, l, st>>>(d, items, nitems, intra, nintra, nbintra,
-                                                                             op_mask, dd, df);
-            else
-                k_eval_solution<false, false><<<grid, kInterThreads, l, st>>>(d, items, nitems, intra, nintra, nbintra,
-                                                                              op_mask, dd, df);
-        }
-        return;
-    }
-    if ((op_mask & 7) && nitems > 0) {
-        const int grid = std::max(1, std::min(nitems, grid_inter));
-        if (has_tw) {
-            if (dump)
-                k_eval_inter<true, true><<<grid, kInterThreads, lds, st>>>(d, items, nitems, op_mask, dd, df);
-            else
-                k_eval_inter<true, false><<<grid, kInterThreads, lds, st>>>(d, items, nitems, op_mask, dd, df);
-        } else {
-            if (dump)
-                k_eval_inter<false, true><<<grid, kInterThreads, lds, st>>>(d, items, nitems, op_mask, dd, df);
-            else
-                k_eval_inter<false, false><<<grid, kInterThreads, lds, st>>>(d, items, nitems, op_mask, dd, df);
-        }
-    }
-    if ((op_mask & (2 | 8 | 16)) && nintra > 0) {
-        const int grid = nintra;  // one workgroup per group: every walk has a compute unit to itself
-        const size_t ilds = (size_t)kInterWaves * kIntraRegionBytes;
-        if (has_tw) {
-            if (dump)
-                k_eval_intra<true, true><<<grid, kInterThreads, ilds, st>>>(d, intra, nintra, op_mask, dd, df);
-            else
-                k_eval_intra<true, false><<<grid, kInterThreads, ilds, st>>>(d, intra, nintra, op_mask, dd, df);
-        } else {
-            if (dump)
-                k_eval_intra<false, true><<<grid, kInterThreads, ilds, st>>>(d, intra, nintra, op_mask, dd, df);
-            else
-                k_eval_intra<false, false><<<grid, kInterThreads, ilds, st>>>(d, intra, nintra, op_mask, dd, df);
-        }
-    }
+// Granular mode: the inter-route moves of the granular pairs, the
+// intra-route ones complete.
+template <bool TW>
+static void launch_eval_gran(const tga_solution *sol, uint32_t op_mask, int32_t *dd, uint8_t *df, hipStream_t st) {
+    const tga_instance *I = sol->inst;
+    const long long work = (op_mask & 7) ? I->gcc + (long long)I->gdep * sol->R : 0;
+    const EvalShape e = intra_shape(sol, op_mask);
+    const int grid = e.nintra + (int)((work + kInterThreads - 1) / kInterThreads);
+    if (!grid) return;
+    if (dd)
+        k_eval_gran<TW, true><<<grid, kInterThreads, kIntraRegionBytes, st>>>(sol->h, I->gsrc, I->gadj, I->gcc, I->gdep,
+                                                                             e.nintra, e.G, op_mask, dd, df);
+    else
+        k_eval_gran<TW, false><<<grid, kInterThreads, kIntraRegionBytes, st>>>(sol->h, I->gsrc, I->gadj, I->gcc,
+                                                                              I->gdep, e.nintra, e.G, op_mask, dd, df);
+}
+
+template <bool TW>
+static void launch_eval(const tga_solution *sol, uint32_t op_mask, int32_t *dd, uint8_t *df, hipStream_t st) {
+    const EvalShape e = intra_shape(sol, op_mask);
+    const int grid = e.nintra + ((op_mask & 7) ? (sol->Q + sol->plain_rows - 1) / sol->plain_rows : 0);
+    if (!grid) return;
+    const size_t lds = std::max((op_mask & 7) ? sol->lds : 0, (size_t)kIntraRegionBytes);
+    if (dd) k_eval_solution<TW, true><<<grid, kInterThreads, lds, st>>>(sol->h, e.nintra, e.G, op_mask, dd, df);
+    else k_eval_solution<TW, false><<<grid, kInterThreads, lds, st>>>(sol->h, e.nintra, e.G, op_mask, dd, df);
 }
 
 static void to_move(const int32_t *rec, tga_move_t *m) {
@@ -900,13 +788,10 @@ static void launch_eval_pen(const tga_solution *sol, uint32_t op_mask, int32_t *
 // Launch one evaluation of a solution (penalised, granular or full
 // neighbourhood).
 static void launch_solution_eval(tga_solution *sol, uint32_t op_mask, int32_t *dd, uint8_t *df, hipStream_t st) {
-    if (sol->h.pen || sol->h.pd || sol->h.gen)
-        launch_eval_pen(sol, op_mask, dd, df, st);
-    else if (op_mask & TGA_OP_GRANULAR)
-        launch_eval_gran(sol->inst, sol->d, sol->R, sol->intra, sol->nintra, sol->h.has_tw, op_mask, dd, df, st);
-    else
-        launch_eval(sol->d, sol->items, sol->nitems, sol->intra, sol->nintra, sol->h.has_tw, op_mask, sol->lds,
-                    sol->nitems, dd, df, st);
+    const bool tw = sol->h.has_tw;
+    if (sol->h.pen || sol->h.pd || sol->h.gen) launch_eval_pen(sol, op_mask, dd, df, st);
+    else if (op_mask & TGA_OP_GRANULAR) (tw ? launch_eval_gran<true> : launch_eval_gran<false>)(sol, op_mask, dd, df, st);
+    else (tw ? launch_eval<true> : launch_eval<false>)(sol, op_mask, dd, df, st);
 }
 
 // Operator mask of a single-solution call: the five operators plus the
@@ -988,7 +873,7 @@ static int eval_record(tga_solution *sol, uint32_t op_mask, tga_move_t *best, in
                        uint8_t *dump_feas, hipStream_t st, int32_t *host, bool host_pinned) {
     int32_t *dev_view = host_pinned ? g_pin_dev : nullptr;  // where the kernel may write `host`
     launch_solution_eval(sol, op_mask, dump_delta, dump_feas, st);
-    k_finalize<<<1, kApplyThreads, 0, st>>>(sol->d, kModeRecord, op_mask, nullptr, dev_view);
+    k_finalize_one<<<1, kApplyThreads, 0, st>>>(sol->h, kModeRecord, op_mask, dev_view);
     HIPCHK(hipGetLastError());
     if (!dev_view)
         HIPCHK(hipMemcpyAsync(host, sol->h.rec, 32 + 16, hipMemcpyDeviceToHost, st));  // record, state[0..3]
@@ -1168,7 +1053,7 @@ extern "C" int tga_apply_move(tga_solution_t sol, const tga_move_t *move, int64_
     p[6] = (int32_t)move->id;
     p[7] = (int32_t)move->version;
     HIPCHK(hipMemcpyAsync(sol->h.rec, p, 32, hipMemcpyHostToDevice, st));
-    k_finalize<<<1, kApplyThreads, 0, st>>>(sol->d, kModeApplyRec, TGA_OP_ALL, nullptr);
+    k_finalize_one<<<1, kApplyThreads, 0, st>>>(sol->h, kModeApplyRec, TGA_OP_ALL, nullptr);
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(p + 8, sol->h.state, 4 * 16 + 8, hipMemcpyDeviceToHost, st));  // state, acc[0]
     HIPCHK(hipStreamSynchronize(st));
@@ -1209,7 +1094,7 @@ extern "C" int tga_ls_run(tga_solution_t sol, uint32_t op_mask, int32_t max_step
             if (multi)
                 k_multi_step<<<1, kApplyThreads, 0, st>>>(sol->d, kModeLS, op_mask);
             else
-                k_finalize<<<1, kApplyThreads, 0, st>>>(sol->d, kModeLS, op_mask, nullptr);
+                k_finalize_one<<<1, kApplyThreads, 0, st>>>(sol->h, kModeLS, op_mask, nullptr);
         }
         HIPCHK(hipGetLastError());
         launched += todo;

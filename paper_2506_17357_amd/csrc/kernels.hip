@@ -1228,10 +1228,18 @@ __device__ __forceinline__ void inter_item(const SolDev &S, const InterItem &ite
     __syncthreads();  // the previous item is done with LDS
     if (!DUMP && threadIdx.x == 0) *thr_sh = committed_delta(S);
     drow_issue<W16>(S, rows, s0 - 1, s0 - 1, min(h, s1 - s0) + 2, wave);
-    __builtin_amdgcn_s_waitcnt(0);
-
     ColRaw nxt;  // column attributes fetched ahead for the chunk at nxt_cb
     int nxt_cb = -1;
+    {  // the first run's, together with the rows
+        int lo0, hi0;
+        const int nr0 = min(h, s1 - s0);
+        wave_share(Q, s0, nr0, wave, lo0, hi0);
+        if (s0 + 1 < Q && lo0 < hi0) {
+            nxt_cb = s0 + 1 + (lo0 / nr0) * kColsPerWave;
+            nxt = col_fetch<TW>(S, nxt_cb);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0);
     for (int i = 0; i < nsb; ++i) {
         const int sb = s0 + i * h;
         const int nr = min(h, s1 - sb);  // rows of this sub-block
@@ -1399,26 +1407,6 @@ __device__ __forceinline__ void inter_item(const SolDev &S, const InterItem &ite
     block_argmin_commit(bd, bid, S.best_key, red);
 }
 
-template <bool TW, bool DUMP>
-__global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_inter(const SolDev *__restrict__ sols,
-                                                              const InterItem *__restrict__ items,
-                                                              int nitems, uint32_t op_mask,
-                                                              int32_t *__restrict__ dump_delta,
-                                                              uint8_t *__restrict__ dump_feas) {
-    extern __shared__ int4 smem4[];
-    __shared__ unsigned long long red[kInterWaves];
-    __shared__ int thr_sh;
-    for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
-        const InterItem item = items[it];
-        const SolDev &S = sols[item.sol];
-        if (skip_solution(S, op_mask)) continue;
-        if (S.D16)
-            inter_item<TW, DUMP, true>(S, item, op_mask, dump_delta, dump_feas, smem4, red, &thr_sh);
-        else
-            inter_item<TW, DUMP, false>(S, item, op_mask, dump_delta, dump_feas, smem4, red, &thr_sh);
-    }
-}
-
 // ------------------------------------------- granular inter-route eval ---
 // Edge-based extraction (Section 5.3.1): only the node pairs kept by the
 // granular mask, the symmetric closure of each node's theta nearest
@@ -1524,19 +1512,6 @@ __device__ __forceinline__ void gran_block(const SolDev &S, const int32_t *__res
     if ((threadIdx.x & 63) == 0 && cnt) atomicAdd((unsigned long long *)cnt_sh, (unsigned long long)cnt);
     block_argmin_commit(bd, bid, S.best_key, red);  // its barriers also order cnt_sh
     if (threadIdx.x == 0 && *cnt_sh) atomicAdd((unsigned long long *)(S.acc + kAccGranInter), (unsigned long long)*cnt_sh);
-}
-
-template <bool TW, bool DUMP>
-__global__ __launch_bounds__(256) void k_eval_gran(const SolDev *__restrict__ sols, const int32_t *__restrict__ gsrc,
-                                                   const int32_t *__restrict__ gadj, int gcc, int gdep,
-                                                   uint32_t op_mask, int32_t *__restrict__ dump_delta,
-                                                   uint8_t *__restrict__ dump_feas) {
-    __shared__ unsigned long long red[256 / 64];
-    __shared__ long long cnt_sh;
-    const SolDev &S = sols[0];
-    if (skip_solution(S, op_mask)) return;  // uniform for the grid
-    gran_block<TW, DUMP>(S, gsrc, gadj, gcc, gdep, blockIdx.x * blockDim.x + threadIdx.x, op_mask, dump_delta,
-                         dump_feas, red, &cnt_sh);
 }
 
 // ------------------------------------------- penalised-mode evaluation ---
@@ -2225,25 +2200,23 @@ constexpr int kGatherBatch = 8;    // distance gathers in flight per lane while 
 
 // The P x P distance sub-blocks of G staged routes (route k = r0 + k: P[k]
 // positions, staged at word offset at[k] of the region, nodes first):
-// element y of route k's block is D[node(y / P)][node(y % P)].  With cache,
-// a route whose cache entry holds the same P and nodes copies its block from
-// there (LDS DMA) and any other route gathers it from D and, when
-// P <= kRouteBlockMaxP, rewrites its entry; without it every block is
-// gathered and no entry is read or written.  Each lane keeps up to
-// kGatherBatch loads in flight before it stores them, so a group costs a
-// couple of memory round trips.
+// element y of route k's block is D[node(y / P)][node(y % P)].  A route whose
+// cache entry holds the same P and nodes copies its block from there (LDS
+// DMA) and any other route gathers it from D and, when P <= kRouteBlockMaxP,
+// rewrites its entry.  Each lane keeps up to kGatherBatch loads in flight
+// before it stores them, so a group costs a couple of memory round trips.
 __device__ __forceinline__ void gather_dist_blocks(const SolDev &S, int *region, const int (&P)[kIntraMaxGroup],
                                                    const int (&at)[kIntraMaxGroup], int G, int r0, uint32_t hit,
                                                    uint32_t fill);
 
 __device__ __forceinline__ void stage_dist_blocks(const SolDev &S, int *region, const int (&P)[kIntraMaxGroup],
-                                                  const int (&at)[kIntraMaxGroup], int G, int r0, bool cache) {
+                                                  const int (&at)[kIntraMaxGroup], int G, int r0) {
     const int lane = threadIdx.x & 63;
     // which routes' cached blocks are current (bit k), and which entries to rewrite
     uint32_t hit = 0, fill = 0;
 #pragma unroll
     for (int k = 0; k < kIntraMaxGroup; ++k) {
-        if (cache && k < G && P[k] <= kRouteBlockMaxP) {
+        if (k < G && P[k] <= kRouteBlockMaxP) {
             const int *c = S.rblk + (size_t)(r0 + k) * kRouteBlockWords;
             const bool same = lane >= P[k] || gld(c + kRouteBlockNodes + lane) == region[at[k] + lane];
             const bool ok = __builtin_amdgcn_readfirstlane(gld(c)) == P[k] && __builtin_amdgcn_ballot_w64(!same) == 0;
@@ -2336,18 +2309,13 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // One wavefront evaluates every intra-route move of routes [r0, r1) of one
-// solution (with SPLIT, only the moves of walk `walk`, so that seven
-// wavefronts share a group) and commits the best to the solution's key.
-// When all their positions fit (sum of L <= 64 first positions, staged data
-// within the wavefront's LDS region), lane l takes one (route, first
-// position) pair of the whole group; otherwise routes are taken one at a
-// time.  Only a wavefront that evaluates every walk of its routes (no SPLIT,
-// or walk 0) reads or rewrites the route distance-block cache, so no two
-// wavefronts of a launch ever touch the same entry.
-template <bool TW, bool DUMP, bool SPLIT = false>
-__device__ __forceinline__ void intra_group(const SolDev &S, const IntraItem &item, uint32_t op_mask, int walk,
-                                            int32_t *__restrict__ dump_delta, uint8_t *__restrict__ dump_feas,
-                                            int *region) {
+// solution and commits the best to the solution's key (the batched form's
+// path for a group that intra_group_flat does not stage).  When all their
+// positions fit (sum of L <= 64 first positions, staged data within the
+// wavefront's LDS region), lane l takes one (route, first position) pair of
+// the whole group; otherwise routes are taken one at a time.
+template <bool TW>
+__device__ __forceinline__ void intra_group(const SolDev &S, const IntraItem &item, uint32_t op_mask, int *region) {
     const int lane = threadIdx.x & 63;
     int bd = initial_bound(op_mask);
     uint32_t bid = 0xFFFFFFFFu;
@@ -2385,7 +2353,7 @@ __device__ __forceinline__ void intra_group(const SolDev &S, const IntraItem &it
                 at[k] = w;
                 w += 7 * Pk[k] + Pk[k] * Pk[k];
             }
-            stage_dist_blocks(S, region, Pk, at, G, item.r0, !SPLIT || walk == 0);
+            stage_dist_blocks(S, region, Pk, at, G, item.r0);
         }
         wave_lds_sync();
         // lane -> (route k, first position i) and that route's staged view
@@ -2410,8 +2378,8 @@ __device__ __forceinline__ void intra_group(const SolDev &S, const IntraItem &it
             int *b = region + myBase;
             const RouteLds V{b, b + P, b + 2 * P, b + 3 * P, b + 4 * P, b + 5 * P, b + 6 * P, b + 7 * P, P};
             const bool capOK = gld(S.b4 + myOff).z <= S.cap;
-            intra_moves<TW, DUMP, SPLIT>(S, V, item.r0 + myk, myL, myi, 1 << 30, capOK, op_mask, walk, dump_delta, dump_feas,
-                                  bd, bid);
+            intra_moves<TW, false, false>(S, V, item.r0 + myk, myL, myi, 1 << 30, capOK, op_mask, -1, nullptr, nullptr, bd,
+                                          bid);
         }
         wave_lds_sync();
     } else {
@@ -2431,14 +2399,14 @@ __device__ __forceinline__ void intra_group(const SolDev &S, const IntraItem &it
                         Pk[k] = k == 0 ? P : 0;
                         at[k] = 0;
                     }
-                    stage_dist_blocks(S, region, Pk, at, 1, r, !SPLIT || walk == 0);
+                    stage_dist_blocks(S, region, Pk, at, 1, r);
                 }
                 wave_lds_sync();
-                intra_moves<TW, DUMP, SPLIT>(S, V, r, L, lane + 1, 64, capOK, op_mask, walk, dump_delta, dump_feas, bd, bid);
+                intra_moves<TW, false, false>(S, V, r, L, lane + 1, 64, capOK, op_mask, -1, nullptr, nullptr, bd, bid);
                 wave_lds_sync();
             } else {
                 const RouteGlobal V{&S, off, L, l0};
-                intra_moves<TW, DUMP, SPLIT>(S, V, r, L, lane + 1, 64, capOK, op_mask, walk, dump_delta, dump_feas, bd, bid);
+                intra_moves<TW, false, false>(S, V, r, L, lane + 1, 64, capOK, op_mask, -1, nullptr, nullptr, bd, bid);
             }
         }
     }
@@ -2719,7 +2687,7 @@ __device__ __forceinline__ void intra_group_flat(const SolDev &S, const IntraIte
         cumP[k + 1] = cumP[k] + P[k];
     }
     if (!(sumL <= 64 && words <= kIntraRegionBytes / 4)) {
-        intra_group<TW, false>(S, item, op_mask, -1, nullptr, nullptr, region);
+        intra_group<TW>(S, item, op_mask, region);
         return;
     }
     const int l0 = TW ? S.node4[0].z : kTwOff;
@@ -2906,93 +2874,215 @@ __device__ __forceinline__ void intra_group_flat(const SolDev &S, const IntraIte
     if (lane == 0 && bd < kAdmissibleBound && bid != 0xFFFFFFFFu) atomicMin(S.best_key, pack_key(bd, bid));
 }
 
-template <bool TW, bool DUMP>
-__global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_intra(
-    const SolDev *__restrict__ sols, const IntraItem *__restrict__ items, int nitems, uint32_t op_mask,
-    int32_t *__restrict__ dump_delta, uint8_t *__restrict__ dump_feas) {
-    extern __shared__ int4 smem4[];
-    const int wave = threadIdx.x >> 6;
-    int *region = (int *)smem4 + wave * (kIntraRegionBytes / 4);
-    if ((int)gridDim.x >= nitems) {  // one workgroup per group: wavefront w < 7 takes walk w
-        if ((int)blockIdx.x >= nitems) return;
-        const IntraItem item = items[blockIdx.x];
-        const SolDev &S = sols[item.sol];
-        if (wave < kIntraWalks && !skip_solution(S, op_mask))
-            intra_group<TW, DUMP, true>(S, item, op_mask, wave, dump_delta, dump_feas, region);
-        return;
-    }
-    for (int itx = wave * gridDim.x + blockIdx.x; itx < nitems; itx += gridDim.x * kInterWaves) {
-        const IntraItem item = items[itx];
-        const SolDev &S = sols[item.sol];
-        if (skip_solution(S, op_mask)) continue;
-        intra_group<TW, DUMP>(S, item, op_mask, -1, dump_delta, dump_feas, region);
+// A group of consecutive routes staged in LDS by a whole workgroup: route k
+// (P[k] positions) at word offset at[k] of the region, seven per-position
+// arrays and its P x P distance sub-block.
+struct GroupStage {
+    int offs[kIntraMaxGroup + 1], P[kIntraMaxGroup], at[kIntraMaxGroup];
+    int NP, sumL, words;
+};
+
+// Layout of the routes [r0, r0 + G) (G <= kIntraMaxGroup), uniform.
+__device__ __forceinline__ void group_layout(const SolDev &S, int r0, int G, GroupStage &g) {
+#pragma unroll
+    for (int k = 0; k <= kIntraMaxGroup; ++k) g.offs[k] = sld1(S.roff + r0 + min(k, G));
+    g.NP = g.sumL = g.words = 0;
+#pragma unroll
+    for (int k = 0; k < kIntraMaxGroup; ++k) {
+        g.P[k] = k < G ? g.offs[k + 1] - g.offs[k] + 1 : 0;
+        g.at[k] = g.words;
+        g.NP += g.P[k];
+        g.sumL += k < G ? g.P[k] - 2 : 0;
+        g.words += 7 * g.P[k] + g.P[k] * g.P[k];
     }
 }
 
-// Single-solution form with both operator kinds: workgroups below nbintra
-// take the intra-route groups (as k_eval_intra; with one workgroup per group
-// every walk has a compute unit to itself), the others the inter-route items
-// (as k_eval_inter), so both run at once in one launch and the long
-// intra-route chains are dispatched first.  The dynamic LDS is the larger of
-// the two needs.
+// Stages the group: every position's attributes at once, then every distance
+// at once (the workgroup's eight wavefronts share them, so a group of 48
+// customers takes two memory round trips after its offsets).  Every thread
+// of the block calls it; it ends with a barrier.
+template <bool TW>
+__device__ __forceinline__ void stage_group(const SolDev &S, const GroupStage &g, int *region) {
+    const int T = blockDim.x;
+    const int l0 = TW ? sld(S.node4).z : kTwOff;
+    for (int f = threadIdx.x; f < g.NP; f += T) {
+        int pk = g.P[0], ak = g.at[0], ok = g.offs[0], c = 0, ck = 0;
+#pragma unroll
+        for (int k = 1; k < kIntraMaxGroup; ++k) {
+            c += g.P[k - 1];
+            if (g.P[k] && f >= c) {
+                pk = g.P[k];
+                ak = g.at[k];
+                ok = g.offs[k];
+                ck = c;
+            }
+        }
+        const int p = f - ck;
+        int *b = region + ak;
+        if (p <= pk - 2) {
+            const int4 a = gld(S.a4 + ok + p);
+            if (TW) {
+                const int4 t = gld(S.t4 + ok + p), w = gld(S.w4 + ok + p);
+                b[2 * pk + p] = t.x;
+                b[3 * pk + p] = t.w;
+                b[4 * pk + p] = w.x;
+                b[5 * pk + p] = w.y;
+                b[6 * pk + p] = w.z;
+            }
+            b[p] = nodeof(a.x);
+            b[pk + p] = a.z;
+        } else {
+            b[p] = 0;
+            b[pk + p] = 0;
+            b[3 * pk + p] = l0;
+        }
+    }
+    __syncthreads();
+    int E = 0;
+#pragma unroll
+    for (int k = 0; k < kIntraMaxGroup; ++k) E += g.P[k] * g.P[k];
+    constexpr int U = 4;  // gathers in flight per thread
+    for (int x0 = threadIdx.x; x0 < E; x0 += T * U) {
+        int val[U], dst[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int x = x0 + u * T;
+            dst[u] = -1;
+            if (x < E) {
+                int pk = g.P[0], ak = g.at[0], c = 0, ck = 0;
+#pragma unroll
+                for (int k = 1; k < kIntraMaxGroup; ++k) {
+                    c += g.P[k - 1] * g.P[k - 1];
+                    if (g.P[k] && x >= c) {
+                        pk = g.P[k];
+                        ak = g.at[k];
+                        ck = c;
+                    }
+                }
+                const int y = x - ck, pp = y / pk, qq = y - pp * pk;
+                val[u] = gld(S.D + (size_t)region[ak + pp] * S.np1 + region[ak + qq]);
+                dst[u] = ak + 7 * pk + y;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (dst[u] >= 0) region[dst[u]] = val[u];
+    }
+    __syncthreads();
+}
+
+// Single-solution form: one workgroup evaluates the intra-route moves of the
+// routes [r0, r1), wavefront w < 7 walk w of every first position (see
+// intra_moves), and commits the best.  The group is staged once for all
+// seven (one staging per wavefront gathered every distance seven times, and
+// each wavefront alone needed two rounds of gathers for it).  A group that
+// does not fit the region, or has more first positions than lanes, is taken
+// route by route; a route that does not fit reads the slot arrays directly.
+template <bool TW, bool DUMP>
+__device__ __forceinline__ void intra_block(const SolDev &S, int r0, int r1, uint32_t op_mask,
+                                            int32_t *__restrict__ dump_delta, uint8_t *__restrict__ dump_feas,
+                                            int *region) {
+    const int lane = threadIdx.x & 63;
+    const int walk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int bd = initial_bound(op_mask);
+    uint32_t bid = 0xFFFFFFFFu;
+    GroupStage g;
+    const int G = r1 - r0;
+    group_layout(S, r0, G, g);
+    if (g.sumL <= 64 && g.words <= kIntraRegionBytes / 4) {
+        // lane -> (route k, first position i) and that route's staged view
+        int myk = -1, myi = 0, myP = 0, myAt = 0, myOff = 0, cum = 0;
+#pragma unroll
+        for (int k = 0; k < kIntraMaxGroup; ++k) {
+            const int L = g.P[k] - 2;
+            if (k < G && myk < 0 && lane < cum + L) {
+                myk = k;
+                myi = lane - cum + 1;
+                myP = g.P[k];
+                myAt = g.at[k];
+                myOff = g.offs[k];
+            }
+            cum += k < G ? L : 0;
+        }
+        const bool capOK = myk >= 0 && gld(S.b4 + myOff).z <= S.cap;
+        stage_group<TW>(S, g, region);
+        if (myk >= 0 && walk < kIntraWalks) {
+            int *b = region + myAt;
+            const RouteLds V{b,           b + myP,     b + 2 * myP, b + 3 * myP, b + 4 * myP,
+                             b + 5 * myP, b + 6 * myP, b + 7 * myP, myP};
+            intra_moves<TW, DUMP, true>(S, V, r0 + myk, myP - 2, myi, 1 << 30, capOK, op_mask, walk, dump_delta,
+                                        dump_feas, bd, bid);
+        }
+    } else {
+        for (int k = 0; k < G; ++k) {
+            const int r = r0 + k;
+            group_layout(S, r, 1, g);
+            const int off = g.offs[0], P = g.P[0], L = P - 2;
+            const bool capOK = gld(S.b4 + off).z <= S.cap;
+            if (g.words <= kIntraRegionBytes / 4) {
+                __syncthreads();  // the previous route is done with the region
+                stage_group<TW>(S, g, region);
+                const RouteLds V{region,         region + P,     region + 2 * P, region + 3 * P, region + 4 * P,
+                                 region + 5 * P, region + 6 * P, region + 7 * P, P};
+                if (walk < kIntraWalks)
+                    intra_moves<TW, DUMP, true>(S, V, r, L, lane + 1, 64, capOK, op_mask, walk, dump_delta, dump_feas,
+                                                bd, bid);
+            } else if (walk < kIntraWalks) {
+                const RouteGlobal V{&S, off, L, S.has_tw ? sld(S.node4).z : kTwOff};
+                intra_moves<TW, DUMP, true>(S, V, r, L, lane + 1, 64, capOK, op_mask, walk, dump_delta, dump_feas, bd,
+                                            bid);
+            }
+        }
+    }
+    wave_argmin(bd, bid);
+    if (lane == 0 && bd < kAdmissibleBound && bid != 0xFFFFFFFFu) atomicMin(S.best_key, pack_key(bd, bid));
+}
+
+// Single-solution form: workgroups below nintra take the intra-route groups
+// (G routes each, the launch's longest chains, dispatched first), the others
+// the inter-route items (strips of S.tile_rows rows), so both run at once in
+// one launch.  With only one kind of operator enabled the other count is 0.
+// The launch is bound by its chains of dependent reads, not by its work, so
+// the descriptor comes by value (its pointers are there with the kernel's
+// arguments) and the items are computed instead of read.  Per launch, with
+// the groups staged by the whole workgroup: n = 1000 CVRP 11.7 us (18.8 with
+// descriptor and items in memory and a staging per wavefront), n = 201 VRPTW
+// 12.9 (18.3), granular n = 1000 VRPTW 13.4 (21.3).  The dynamic LDS is the
+// larger of the two needs.
 template <bool TW, bool DUMP>
 __global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_solution(
-    const SolDev *__restrict__ sols, const InterItem *__restrict__ items, int nitems,
-    const IntraItem *__restrict__ intra, int nintra, int nbintra, uint32_t op_mask, int32_t *__restrict__ dump_delta,
+    const SolDev S, int nintra, int G, uint32_t op_mask, int32_t *__restrict__ dump_delta,
     uint8_t *__restrict__ dump_feas) {
     extern __shared__ int4 smem4[];
     __shared__ unsigned long long red[kInterWaves];
     __shared__ int thr_sh;
-    if ((int)blockIdx.x >= nbintra) {
-        const int ninter = gridDim.x - nbintra;
-        for (int it = blockIdx.x - nbintra; it < nitems; it += ninter) {
-            const InterItem item = items[it];
-            const SolDev &S = sols[item.sol];
-            if (skip_solution(S, op_mask)) continue;
-            if (S.D16)
-                inter_item<TW, DUMP, true>(S, item, op_mask, dump_delta, dump_feas, smem4, red, &thr_sh);
-            else
-                inter_item<TW, DUMP, false>(S, item, op_mask, dump_delta, dump_feas, smem4, red, &thr_sh);
-        }
-    } else {
-        const int wave = threadIdx.x >> 6, b = blockIdx.x;
-        int *region = (int *)smem4 + wave * (kIntraRegionBytes / 4);
-        if (nbintra >= nintra) {  // one workgroup per group: wavefront w < 7 takes walk w
-            if (b >= nintra) return;
-            const IntraItem item = intra[b];
-            const SolDev &S = sols[item.sol];
-            if (wave < kIntraWalks && !skip_solution(S, op_mask))
-                intra_group<TW, DUMP, true>(S, item, op_mask, wave, dump_delta, dump_feas, region);
-        } else {
-            for (int itx = wave * nbintra + b; itx < nintra; itx += nbintra * kInterWaves) {
-                const IntraItem item = intra[itx];
-                const SolDev &S = sols[item.sol];
-                if (skip_solution(S, op_mask)) continue;
-                intra_group<TW, DUMP>(S, item, op_mask, -1, dump_delta, dump_feas, region);
-            }
-        }
+    if (skip_solution(S, op_mask)) return;  // uniform for the grid
+    if ((int)blockIdx.x < nintra) {
+        const int r0 = blockIdx.x * G;
+        intra_block<TW, DUMP>(S, r0, min(S.R, r0 + G), op_mask, dump_delta, dump_feas, (int *)smem4);
+        return;
     }
+    const int s0 = ((int)blockIdx.x - nintra) * S.tile_rows;
+    const InterItem item{0, s0, min(S.Q, s0 + S.tile_rows), 0};
+    if (S.D16)
+        inter_item<TW, DUMP, true>(S, item, op_mask, dump_delta, dump_feas, smem4, red, &thr_sh);
+    else
+        inter_item<TW, DUMP, false>(S, item, op_mask, dump_delta, dump_feas, smem4, red, &thr_sh);
 }
 
-// Granular mode with both operator kinds in one launch (as k_eval_solution):
-// workgroups below nintra take the intra-route groups (one per group, seven
-// wavefronts with one walk each), the others kInterThreads granular work
-// items each.
+// Granular mode (as k_eval_solution): workgroups below nintra take the
+// intra-route groups, the others kInterThreads granular work items each.
 template <bool TW, bool DUMP>
-__global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_gran_fused(
-    const SolDev *__restrict__ sols, const int32_t *__restrict__ gsrc, const int32_t *__restrict__ gadj, int gcc,
-    int gdep, const IntraItem *__restrict__ intra, int nintra, uint32_t op_mask, int32_t *__restrict__ dump_delta,
-    uint8_t *__restrict__ dump_feas) {
+__global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_gran(
+    const SolDev S, const int32_t *__restrict__ gsrc, const int32_t *__restrict__ gadj, int gcc, int gdep, int nintra,
+    int G, uint32_t op_mask, int32_t *__restrict__ dump_delta, uint8_t *__restrict__ dump_feas) {
     extern __shared__ int4 smem4[];
     __shared__ unsigned long long red[kInterWaves];
     __shared__ long long cnt_sh;
-    const SolDev &S = sols[0];
     if (skip_solution(S, op_mask)) return;  // uniform for the grid
     if ((int)blockIdx.x < nintra) {
-        const int wave = threadIdx.x >> 6;
-        int *region = (int *)smem4 + wave * (kIntraRegionBytes / 4);
-        if (wave < kIntraWalks)
-            intra_group<TW, DUMP, true>(S, intra[blockIdx.x], op_mask, wave, dump_delta, dump_feas, region);
+        const int r0 = blockIdx.x * G;
+        intra_block<TW, DUMP>(S, r0, min(S.R, r0 + G), op_mask, dump_delta, dump_feas, (int *)smem4);
         return;
     }
     gran_block<TW, DUMP>(S, gsrc, gadj, gcc, gdep, ((int)blockIdx.x - nintra) * blockDim.x + threadIdx.x, op_mask,
@@ -3424,7 +3514,9 @@ __device__ __forceinline__ void shift_slots(const SolDev &S, int lo, int hi, int
 // One block per solution.  kModeRecord: publish the best move (status 1 if
 // none) and reset the key.  kModeLS: also apply it when its delta is negative
 // and the step cap allows, else mark the solution converged.  kModeApplyRec:
-// apply the move record the host wrote into S.rec.
+// apply the move record the host wrote into S.rec.  host_out (nullable,
+// single solution): pinned host memory that receives the move record and
+// state[0..3] straight from the kernel (12 ints), so that no copy follows.
 //
 // The step is bound by the length of its chain of dependent memory reads
 // (one workgroup, a few KB), so it has as few links as the data allow: key,
@@ -3625,18 +3717,19 @@ __device__ __forceinline__ void finalize_block(const SolDev &S, int mode, uint32
 }
 
 // `steps` (nullable): a batch's step counter, advanced once per launch.
-// Empty slots of a slot batch (Q = 0) are skipped.  host_out (nullable,
-// single solution): pinned host memory that receives the move record and
-// state[0..3] straight from the kernel (12 ints), so that no copy follows.
+// Empty slots of a slot batch (Q = 0) are skipped.
 __global__ __launch_bounds__(kApplyThreads) void k_finalize(const SolDev *__restrict__ sols, int mode,
-                                                            uint32_t op_mask, int *__restrict__ steps,
-                                                            int32_t *__restrict__ host_out = nullptr) {
+                                                            uint32_t op_mask, int *__restrict__ steps) {
     if (steps && blockIdx.x == 0 && threadIdx.x == 0) *steps += 1;
     if (sols[blockIdx.x].Q == 0) return;
-    const SolDev &S = sols[blockIdx.x];
-    finalize_block(S, mode, op_mask, host_out);
+    finalize_block(sols[blockIdx.x], mode, op_mask, nullptr);
 }
 
+// The same for one solution, its descriptor by value (see k_eval_solution).
+__global__ __launch_bounds__(kApplyThreads) void k_finalize_one(const SolDev S, int mode, uint32_t op_mask,
+                                                                int32_t *__restrict__ host_out) {
+    finalize_block(S, mode, op_mask, host_out);
+}
 
 // ------------------------------------------------------------ multi-move --
 // Several independent moves per step (Section 7, after Dynasearch): the
