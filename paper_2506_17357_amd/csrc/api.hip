@@ -82,9 +82,21 @@ int props(DevProps *out) {
                              (const void *)k_eval_batch<7>,
                              (const void *)k_eval_solution<false, false>, (const void *)k_eval_solution<true, false>,
                              (const void *)k_eval_solution<false, true>, (const void *)k_eval_solution<true, true>};
+        // the general path's kernels also hold their move queues
+        const int dyn_gen = dyn - kInterWaves * (int)sizeof(GenQueue);
+        const void *gen[] = {(const void *)k_eval_general<false, false, false, true>,
+                             (const void *)k_eval_general<false, false, true, true>,
+                             (const void *)k_eval_general<false, true, false, true>,
+                             (const void *)k_eval_general<false, true, true, true>,
+                             (const void *)k_eval_general<true, false, false, true>,
+                             (const void *)k_eval_general<true, false, true, true>,
+                             (const void *)k_eval_general<true, true, false, true>,
+                             (const void *)k_eval_general<true, true, true, true>};
         bool ok = dyn > 65536;
         for (const void *f : fns)
             if (ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dyn) != hipSuccess) ok = false;
+        for (const void *f : gen)
+            if (ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_gen) != hipSuccess) ok = false;
         (void)hipGetLastError();  // do not leave a refused attribute as the sticky error
         g_props.attr_ok = ok;
         g_props.max_lds = ok ? dyn : std::min(lds, 65536);
@@ -160,7 +172,7 @@ long long count_items(int Q, int rows) {
 }
 
 struct SolLayout {
-    size_t desc, a4, b4, t4, w4, pf4, pb4, pl4, ql4, pdist, ref2slot, roff, rdist, nr_alt, roff_alt, rblk, best_key, rec,
+    size_t desc, a4, b4, t4, w4, pf4, pb4, pl4, ql4, g4, pdist, ref2slot, roff, rdist, nr_alt, roff_alt, rblk, best_key, rec,
         state, acc, total;
 };
 
@@ -182,6 +194,7 @@ SolLayout sol_layout(int n, int R) {
     L.pb4 = take(16 * S);
     L.pl4 = take(16 * S);
     L.ql4 = take(16 * S);
+    L.g4 = take(16 * S);
     L.pdist = take(4 * S);
     L.ref2slot = take(4 * Q);
     L.roff = take(4 * (R + 1));
@@ -541,6 +554,7 @@ static int solution_init(tga_solution *S, tga_instance_t inst, int32_t R, const 
     h.pb4 = (int4 *)(base + L.pb4);
     h.pl4 = (int4 *)(base + L.pl4);
     h.ql4 = (int4 *)(base + L.ql4);
+    h.g4 = (int4 *)(base + L.g4);
     h.pick = inst->pick;
     h.pd = inst->pick != nullptr;
     h.pdist = (int32_t *)(base + L.pdist);
@@ -755,34 +769,49 @@ static void to_move(const int32_t *rec, tga_move_t *m) {
     m->version = (uint32_t)rec[7];
 }
 
-// One evaluation of a solution whose workspace is set up: evaluation launch,
-// record-mode finalize, and one copy of the record and state[0..3] into
-// `host` (48 bytes; pinned or pageable).
-// Penalised mode: inter-route pairs (16 x 16 tiles on and above the
-// diagonal) and intra-route walks (one thread per slot).
-template <bool TW, bool PD>
-static void launch_eval_gen(const tga_solution *sol, uint32_t op_mask, int32_t *dd, uint8_t *df, hipStream_t st) {
-    const bool dump = dd != nullptr;
-    if (op_mask & (7 | TGA_OP_VARIANTS)) {
-        const int tiles = (sol->Q + 15) / 16, grid = tiles * (tiles + 1) / 2;
-        if (dump) k_eval_pen_pairs<TW, PD, true><<<grid, 256, 0, st>>>(sol->d, tiles, op_mask, dd, df);
-        else k_eval_pen_pairs<TW, PD, false><<<grid, 256, 0, st>>>(sol->d, tiles, op_mask, dd, df);
-    }
-    if (op_mask & (2 | 8 | 16)) {
-        const int grid = (7 * sol->Q + 255) / 256;  // seven walks per slot
-        if (dump) k_eval_pen_intra<TW, PD, true><<<grid, 256, 0, st>>>(sol->d, op_mask, dd, df);
-        else k_eval_pen_intra<TW, PD, false><<<grid, 256, 0, st>>>(sol->d, op_mask, dd, df);
-    }
+// General path (penalised mode, pickups, operator variants, multi-move).
+// The rows go in strips of equal work, as many as let two workgroups share
+// every compute unit with the intra-route groups, up to 24 rows staged at a
+// time where 56 KiB of LDS hold them with their halo (one row before, one
+// after, three with the variants).  Without a 16-bit copy of D, or where one
+// row and its halo do not fit, the distances are gathered from D and nothing
+// is staged.
+static size_t general_lds_limit() {
+    DevProps P;
+    if (props(&P) != TGA_OK) return 0;
+    return std::max(0, P.max_lds - (P.attr_ok ? kInterWaves * (int)sizeof(GenQueue) : 0));
 }
 
-// General path (penalised mode or pickups): gathers per pair and per walk,
-// every attribute of a new route concatenated from the stored summaries.
+template <bool TW, bool PD, bool EXT>
+static void launch_eval_general(const tga_solution *sol, uint32_t op_mask, int32_t *dd, uint8_t *df, hipStream_t st) {
+    const EvalShape e = intra_shape(sol, op_mask);
+    const int halo = EXT ? 4 : 2, np1 = sol->h.np1;
+    auto lds_of = [&](int rows) { return rows_lds(np1, rows + halo - 2, true); };
+    const bool w16 = sol->h.D16 && lds_of(1) <= general_lds_limit();
+    int rows = 24;
+    while (w16 && rows > 1 && lds_of(rows) > 57344) --rows;
+    DevProps P;
+    const int cus = props(&P) == TGA_OK ? P.cus : 256;
+    const int strips = std::min(std::max(2 * cus - e.nintra, cus / 2), (sol->Q + 1) / 2);
+    const int grid = e.nintra + ((op_mask & (7 | TGA_OP_VARIANTS)) ? strips : 0);
+    if (!grid) return;
+    const size_t lds = std::max(w16 ? lds_of(rows) : 0, (size_t)kGenRegionBytes);
+    if (w16) k_eval_general<TW, PD, EXT, true><<<grid, kInterThreads, lds, st>>>(sol->h, e.nintra, e.G, rows, op_mask, dd, df);
+    else k_eval_general<TW, PD, EXT, false><<<grid, kInterThreads, lds, st>>>(sol->h, e.nintra, e.G, rows, op_mask, dd, df);
+}
+
+template <bool TW, bool PD>
+static void launch_eval_ext(const tga_solution *sol, uint32_t op_mask, int32_t *dd, uint8_t *df, hipStream_t st) {
+    if (op_mask & TGA_OP_VARIANTS) launch_eval_general<TW, PD, true>(sol, op_mask, dd, df, st);
+    else launch_eval_general<TW, PD, false>(sol, op_mask, dd, df, st);
+}
+
 static void launch_eval_pen(const tga_solution *sol, uint32_t op_mask, int32_t *dd, uint8_t *df, hipStream_t st) {
     const bool tw = sol->h.has_tw, pd = sol->h.pd;
-    if (tw && pd) launch_eval_gen<true, true>(sol, op_mask, dd, df, st);
-    else if (tw) launch_eval_gen<true, false>(sol, op_mask, dd, df, st);
-    else if (pd) launch_eval_gen<false, true>(sol, op_mask, dd, df, st);
-    else launch_eval_gen<false, false>(sol, op_mask, dd, df, st);
+    if (tw && pd) launch_eval_ext<true, true>(sol, op_mask, dd, df, st);
+    else if (tw) launch_eval_ext<true, false>(sol, op_mask, dd, df, st);
+    else if (pd) launch_eval_ext<false, true>(sol, op_mask, dd, df, st);
+    else launch_eval_ext<false, false>(sol, op_mask, dd, df, st);
 }
 
 // Launch one evaluation of a solution (penalised, granular or full
@@ -866,6 +895,9 @@ extern "C" int tga_solution_violations(tga_solution_t sol, int64_t *load_excess,
     return TGA_OK;
 }
 
+// One evaluation of a solution whose workspace is set up: evaluation launch,
+// record-mode finalize, and the record and state[0..3] in `host` (48 bytes;
+// pinned or pageable).
 // `host_pinned`: `host` is this thread's pinned buffer, which the finalize
 // kernel writes directly (through its device address); otherwise (pageable
 // memory, or no device address) the record is copied after it.

@@ -148,6 +148,12 @@ __device__ __forceinline__ void wave_argmin(int &bd, uint32_t &bid) {
     }
 }
 
+// One wavefront's best folded into the solution's key.
+__device__ __forceinline__ void wave_argmin_commit(int bd, uint32_t bid, unsigned long long *key) {
+    wave_argmin(bd, bid);
+    if ((threadIdx.x & 63) == 0 && bd < kAdmissibleBound && bid != 0xFFFFFFFFu) atomicMin(key, pack_key(bd, bid));
+}
+
 // Reduce the per-lane bests of a workgroup and fold the result into the
 // solution's key.  Every thread of the block must call it.
 __device__ __forceinline__ void block_argmin_commit(int bd, uint32_t bid, unsigned long long *key,
@@ -258,7 +264,7 @@ __device__ __forceinline__ int bwd_apply(const BwdElem &m, int y) {
 struct ApplyShared {
     FwdElem fw[kApplyThreads / 64];
     BwdElem bw[kApplyThreads / 64];
-    long long red[kApplyThreads / 64][5];
+    long long red[kApplyThreads / 64][8];
 };
 
 __device__ __forceinline__ FwdElem shfl_f(const FwdElem &e, int src) {
@@ -360,34 +366,52 @@ __device__ __forceinline__ BwdElem bwd_elem(const SolDev &S, const int32_t *roff
     return e;
 }
 
+// Terms a route of L customers adds to |N(S)| of RELOCATE, to twice that of
+// 2OPT* (subtracted), to 2OPT and OR-OPT, and to the operator variants'
+// counts (see kAccExtSeg).
+struct RouteCounts {
+    long long rel, star2, two, oropt, seg, k, k2;
+};
+__device__ __forceinline__ RouteCounts route_counts(long long L, long long Q) {
+    RouteCounts c{L * (Q - L - 1), (L + 1) * (L + 1), L * (L - 1) / 2, 0, 0, 0, 0};
+    for (int k = 1; k <= 3; ++k)
+        if (k <= L) c.oropt += (L - k + 1) * (L - k);
+    const long long more = L >= 2 ? 2 * L - 3 : 0;  // sum of k(x) - 1
+    c.seg = more * (Q - L - 1);
+    c.k = more + L;
+    c.k2 = c.k * c.k - L * L;
+    return c;
+}
+
 // Cost (sum of route distances) and |N(S)| per operator from the route
 // offsets and distances.  Every thread of the block calls it.
 __device__ __forceinline__ void solution_totals(const SolDev &S, const int32_t *roffn, ApplyShared &sh) {
     const int Q = S.Q, R = S.R, n = S.n;
     const int tid = threadIdx.x, T = blockDim.x;
-    // cost and |N(S)| per operator
-    long long v[5] = {0, 0, 0, 0, 0};
+    long long v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int r = tid; r < R; r += T) {
-        const long long L = gld(roffn + r + 1) - gld(roffn + r) - 1;
+        const RouteCounts c = route_counts(gld(roffn + r + 1) - gld(roffn + r) - 1, Q);
         v[0] += gld(S.rdist + r);
-        v[1] += L * (Q - L - 1);
-        v[2] += (L + 1) * (L + 1);
-        v[3] += L * (L - 1) / 2;
-        for (int k = 1; k <= 3; ++k)
-            if (k <= L) v[4] += (L - k + 1) * (L - k);
+        v[1] += c.rel;
+        v[2] += c.star2;
+        v[3] += c.two;
+        v[4] += c.oropt;
+        v[5] += c.seg;
+        v[6] += c.k;
+        v[7] += c.k2;
     }
-    for (int i = 0; i < 5; ++i) {
+    for (int i = 0; i < 8; ++i) {
         long long x = v[i];
         for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
         v[i] = x;
     }
     if ((tid & 63) == 0)
-        for (int i = 0; i < 5; ++i) sh.red[tid >> 6][i] = v[i];
+        for (int i = 0; i < 8; ++i) sh.red[tid >> 6][i] = v[i];
     __syncthreads();
     if (tid == 0) {
-        long long t[5] = {0, 0, 0, 0, 0};
+        long long t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         for (int w = 0; w < T / 64; ++w)
-            for (int i = 0; i < 5; ++i) t[i] += sh.red[w][i];
+            for (int i = 0; i < 8; ++i) t[i] += sh.red[w][i];
         const long long qq = (long long)Q * Q;
         S.acc[kAccCost] = t[0];
         S.acc[kAccCnt0 + 0] = t[1];
@@ -395,6 +419,9 @@ __device__ __forceinline__ void solution_totals(const SolDev &S, const int32_t *
         S.acc[kAccCnt0 + 2] = (qq - t[2]) / 2;
         S.acc[kAccCnt0 + 3] = t[3];
         S.acc[kAccCnt0 + 4] = t[4];
+        S.acc[kAccExtSeg] = t[5];
+        S.acc[kAccExtK] = t[6];
+        S.acc[kAccExtK2] = t[7];
     }
     __threadfence_block();
     __syncthreads();
@@ -427,7 +454,7 @@ __device__ __forceinline__ void rebuild_range(const SolDev &S, int2 *nr, const i
         const int edge = gld(D + (size_t)node * np1 + succ);
         const bool cust = s != first;
         gst(S.a4 + s, make_int4(node | ((cust ? kFlagCustomer : 0) << 16), r, edge, 0));
-        gst(S.w4 + s, make_int4(q.y, q.z, q.w, 0));
+        gst(S.w4 + s, make_int4(q.y, q.z, q.w, S.pd && cust ? gld(S.pick + node) : 0));
         gst(S.b4 + s, make_int4(cust ? q.x : 0, 0, 0, 0));
         gst(S.ref2slot + (cust ? node - 1 : n + r), s);
     }
@@ -562,6 +589,7 @@ __device__ __forceinline__ SlotAttr route_attr(const SolDev &S, int node, int r,
     const int4 q0 = gld(S.node4);
     const int edge = on ? gld(D + (size_t)node * np1 + nsucc) : 0;
     const int dpw = cust ? gld(D + (size_t)pred * np1 + nsucc) : 0;  // c(pred, succ)
+    const int pick = S.pd && cust ? gld(S.pick + node) : 0;
     if (!tw) q = make_int4(q.x, 0, kTwOff, 0);
     const int demand = cust ? q.x : 0;
     const int epred = __shfl(edge, max(lane - 1, 0));
@@ -620,7 +648,7 @@ __device__ __forceinline__ SlotAttr route_attr(const SolDev &S, int node, int r,
     SlotAttr x;
     x.a = make_int4(node | (flags << 16), r, edge, cust ? dpw - epred - edge : 0);
     x.b = make_int4(demand, f.load, rload, cust ? epred + edge : 0);
-    x.w = make_int4(q.y, q.z, q.w, 0);
+    x.w = make_int4(q.y, q.z, q.w, pick);
     x.t = make_int4(dep, zn, adp, Z);
     x.pdist = f.dist;
     x.ref = cust ? node - 1 : S.n + r;
@@ -708,8 +736,7 @@ __device__ __forceinline__ Ld ld_cat(const Ld &a, const Ld &b) {
     return Ld{a.li + b.li, a.lo + b.lo, max(a.lm + b.li, a.lo + b.lm)};
 }
 __device__ __forceinline__ Ld ld_node_at(const SolDev &S, int x) {
-    const int node = nodeof(gld(S.a4 + x).x);
-    const int d = gld(S.b4 + x).x, p = node ? gld(S.pick + node) : 0;
+    const int d = gld(S.b4 + x).x, p = gld(S.w4 + x).w;
     return Ld{d, p, max(d, p)};
 }
 
@@ -795,15 +822,42 @@ __device__ __forceinline__ int route_peak(const SolDev &S, int r) {
 // Load excess of route r.
 __device__ __forceinline__ int route_excess(const SolDev &S, int r) { return max(route_peak(S, r) - S.cap, 0); }
 
-// Summaries the general evaluation path reads (penalised mode or pickups).
-__device__ __forceinline__ void gen_route(const SolDev &S, int r) {
-    if (S.has_tw) pen_route(S, r);
-    if (S.pd) pd_route(S, r);
-}
-
 // Time warp of route r (the suffix summary at its start depot).
 __device__ __forceinline__ int route_warp(const SolDev &S, int r) {
     return S.has_tw ? gld(S.pb4 + gld(S.roff + r)).w : 0;
+}
+
+// Removal deltas of the segments of two and three nodes that start at lane
+// p's node (`node`, `edge`: the lanes' nodes and the edges leaving them; L
+// customers follow the depot in lane 0); 0 where the route is too short.
+__device__ __forceinline__ int2 segment_removal(const SolDev &S, int node, int edge, int L) {
+    const int lane = threadIdx.x & 63, np1 = S.np1;
+    const int pred = __shfl(node, max(lane - 1, 0)), epred = __shfl(edge, max(lane - 1, 0));
+    const int n2 = __shfl(node, min(lane + 2, 63)), n3 = __shfl(node, min(lane + 3, 63));
+    const int e1 = __shfl(edge, min(lane + 1, 63)), e2 = __shfl(edge, min(lane + 2, 63));
+    int2 v = make_int2(0, 0);
+    if (lane >= 1 && lane + 1 <= L) v.x = gld(S.D + (size_t)pred * np1 + (lane + 2 <= L ? n2 : 0)) - epred - e1;
+    if (lane >= 1 && lane + 2 <= L) v.y = gld(S.D + (size_t)pred * np1 + (lane + 3 <= L ? n3 : 0)) - epred - e2;
+    return v;
+}
+
+// Summaries the general evaluation path reads, of route r, by one thread.
+__device__ __forceinline__ void gen_route(const SolDev &S, int r) {
+    if (S.has_tw) pen_route(S, r);
+    if (S.pd) pd_route(S, r);
+    const int off = gld(S.roff + r), L = gld(S.roff + r + 1) - off - 1;
+    auto node = [&](int p) { return p <= L ? nodeof(gld(S.a4 + off + p).x) : 0; };
+    int4 g = make_int4(0, 0, S.pd ? gld(S.ql4 + off).z : gld(S.b4 + off).z, S.has_tw ? gld(S.pb4 + off).w : 0);
+    for (int p = 0; p <= L; ++p) {
+        g.x = g.y = 0;
+        if (p >= 1) {
+            const int32_t *row = S.D + (size_t)node(p - 1) * S.np1;
+            const int ep = gld(S.a4 + off + p - 1).z;
+            if (p + 1 <= L) g.x = gld(row + node(p + 2)) - ep - gld(S.a4 + off + p + 1).z;
+            if (p + 2 <= L) g.y = gld(row + node(p + 3)) - ep - gld(S.a4 + off + p + 2).z;
+        }
+        gst(S.g4 + off + p, g);
+    }
 }
 
 // Totals of load excess and time warp over the routes (every thread of the
@@ -846,7 +900,10 @@ __device__ __forceinline__ void pen_all(const SolDev &S, ApplyShared &sh) {
             if (lane == 0) gen_route(S, r);
             continue;
         }
-        const int node = lane <= L ? nodeof(gld(S.a4 + off + lane).x) : 0;
+        const int4 a = lane <= L ? gld(S.a4 + off + lane) : make_int4(0, 0, 0, 0);
+        const int node = nodeof(a.x);
+        const int2 rem = segment_removal(S, node, a.z, L);
+        int4 g = make_int4(rem.x, rem.y, gld(S.b4 + off).z, 0);
         if (S.has_tw) {
             Tw f, b;
             tw_route_wave(S, node, L, f, b);
@@ -854,6 +911,7 @@ __device__ __forceinline__ void pen_all(const SolDev &S, ApplyShared &sh) {
                 gst(S.pf4 + off + lane, tw_pack(f));
                 gst(S.pb4 + off + lane, tw_pack(b));
             }
+            g.w = __shfl(b.v, 0);
         }
         if (S.pd) {
             Ld f, b;
@@ -862,7 +920,9 @@ __device__ __forceinline__ void pen_all(const SolDev &S, ApplyShared &sh) {
                 gst(S.pl4 + off + lane, ld_pack(f));
                 gst(S.ql4 + off + lane, ld_pack(b));
             }
+            g.z = __shfl(b.lm, 0);
         }
+        if (lane <= L) gst(S.g4 + off + lane, g);
     }
     __threadfence_block();
     __syncthreads();
@@ -1514,428 +1574,6 @@ __device__ __forceinline__ void gran_block(const SolDev &S, const int32_t *__res
     if (threadIdx.x == 0 && *cnt_sh) atomicAdd((unsigned long long *)(S.acc + kAccGranInter), (unsigned long long)*cnt_sh);
 }
 
-// ------------------------------------------- penalised-mode evaluation ---
-// Feasible and infeasible search (Alg. A2): every move of N(S) is admissible
-// and scores dD + w_L dL_V + w_T dT_V over the touched routes (Section 5.3.3
-// attribute deltas, eq. scoring_tensor).  New routes are concatenations of
-// the stored prefix / suffix summaries with the moved nodes (Section 4.3.3);
-// loads come from the prefix loads.  One thread per pair of slots (inter-
-// route) or per first position of an intra-route walk: the attributes are
-// gathered, nothing is staged (this mode serves the search, not the
-// headline rate).  The dumps hold the score and the hard capacity / window
-// bits of the touched routes (load excess and time warp both zero).
-
-// Suffix summary strictly after slot x (the end depot when x is last).
-__device__ __forceinline__ Tw tw_after(const SolDev &S, int x, const Tw &dep) {
-    return nodeof(gld(S.a4 + x + 1).x) == 0 ? dep : tw_of(gld(S.pb4 + x + 1));
-}
-
-__device__ __forceinline__ Tw tw_node_at(const SolDev &S, int x) {
-    const int4 w = gld(S.w4 + x);
-    return tw_node(w.x, w.y, w.z);
-}
-
-// Record one move of the general path.  Penalised mode: the score is
-// dD + w_L dL_V + w_T dT_V and every move is admissible.  Otherwise (pickups
-// with hard feasibility): the distance delta, admissible when the touched
-// routes have no load excess and no time warp.  The dumps hold the score
-// (penalised) or the delta, and the hard capacity / window bits.
-__device__ __forceinline__ void gen_record(const SolDev &S, int dD, int dlv, int dtv, bool capok, bool twok, uint32_t id,
-                                           bool dump, int32_t *dd, uint8_t *df, int &bd, uint32_t &bid) {
-    const int feas = (capok ? 1 : 0) | (twok ? 2 : 0);
-    const int score = S.pen ? dD + S.wL * dlv + S.wT * dtv : dD;
-    if (dump) {
-        dd[id] = score;
-        df[id] = (uint8_t)feas;
-    }
-    consider(S.pen || feas == 3 ? score : score + kPenalty, id, bd, bid);
-}
-
-// Load summary strictly after slot x (the end depot: empty, when x is last).
-__device__ __forceinline__ Ld ld_after(const SolDev &S, int x) {
-    return nodeof(gld(S.a4 + x + 1).x) == 0 ? Ld{0, 0, 0} : ld_of(gld(S.ql4 + x + 1));
-}
-
-// Distances of a 16 x 16 pair tile, staged in LDS: Dc[i][j] between the
-// row-side slot x0 - 1 + i and the column-side slot t0 - 1 + j (i, j < 20),
-// Rr[i][k - 1] between row-side slots x0 - 1 + i and x0 - 1 + i + k
-// (k = 1..4), Cc likewise on the column side.  Every distance a pair's
-// moves need is one of these (segments reach three slots past x or t).
-constexpr int kTileSpan = 20;
-struct PairTileD {
-    int Dc[kTileSpan][kTileSpan];
-    int Rr[kTileSpan][4];
-    int Cc[kTileSpan][4];
-};
-
-// The inter-route moves of slots x, t (route(x) < route(t)); T holds the
-// tile's distances, xi = x - x0 + 1 and tj = t - t0 + 1 locate the pair.
-template <bool TW, bool PD, bool DUMP>
-__device__ __forceinline__ void pen_pair(const SolDev &S, int x, int t, const PairTileD &T, int xi, int tj,
-                                         uint32_t op_mask, int32_t *dd, uint8_t *df, int &bd, uint32_t &bid,
-                                         int &cntExt) {
-    const int n = S.n, cap = S.cap;
-    const uint32_t uQ = (uint32_t)S.Q;
-    const int4 ax = gld(S.a4 + x), at = gld(S.a4 + t), bx = gld(S.b4 + x), bt = gld(S.b4 + t);
-    const bool cx = flagsof(ax.x) & kFlagCustomer, ct = flagsof(at.x) & kFlagCustomer;
-    const int nx = nodeof(ax.x), nt = nodeof(at.x);
-    // X(a, b): distance between slots x + a and t + b; RX(a, k): between
-    // x + a and x + a + k; CT likewise on t's side
-    auto X = [&](int a, int b) { return T.Dc[xi + a][tj + b]; };
-    auto RX = [&](int a, int k) { return T.Rr[xi + a][k - 1]; };
-    auto CT = [&](int b, int k) { return T.Cc[tj + b][k - 1]; };
-    const int refX = cx ? nx - 1 : n + ax.y, refT = ct ? nt - 1 : n + at.y;
-    const int Lx = bx.z, Lt = bt.z, dx = bx.x, dtt = bt.x;
-    const int lvOld = route_excess(S, ax.y) + route_excess(S, at.y);
-    int tvOld = 0;
-    Tw dep{}, Fx{}, Ft{}, Fpx{}, Fpt{}, Bax{}, Bat{}, Nx{}, Nt{};
-    if (TW) {
-        dep = tw_depot(S);
-        Fx = tw_of(gld(S.pf4 + x));
-        Ft = tw_of(gld(S.pf4 + t));
-        Fpx = tw_of(gld(S.pf4 + max(x - 1, 0)));
-        Fpt = tw_of(gld(S.pf4 + t - 1));
-        Bax = tw_after(S, x, dep);
-        Bat = tw_after(S, t, dep);
-        Nx = tw_node_at(S, x);
-        Nt = tw_node_at(S, t);
-        tvOld = route_warp(S, ax.y) + route_warp(S, at.y);
-    }
-    Ld Px{}, Pt{}, Ppx{}, Ppt{}, Sax{}, Sat{}, Mx{}, Mt{};
-    if (PD) {
-        Px = ld_of(gld(S.pl4 + x));
-        Pt = ld_of(gld(S.pl4 + t));
-        Ppx = ld_of(gld(S.pl4 + max(x - 1, 0)));
-        Ppt = ld_of(gld(S.pl4 + t - 1));
-        Sax = ld_after(S, x);
-        Sat = ld_after(S, t);
-        Mx = ld_node_at(S, x);
-        Mt = ld_node_at(S, t);
-    }
-    const int exx = RX(0, 1), ett = CT(0, 1);  // edges leaving x and t
-    // peak loads of the two new routes are passed in (lx, lt)
-    auto rec = [&](int dD, int lx, int lt, int tvx, int tvt, uint32_t id) {
-        const int lv = max(lx - cap, 0) + max(lt - cap, 0);
-        gen_record(S, dD, lv - lvOld, tvx + tvt - tvOld, lv == 0, tvx + tvt == 0, id, DUMP, dd, df, bd, bid);
-    };
-    if ((op_mask & 1) && cx) {  // RELOCATE x -> right after t
-        const int dD = X(0, 0) + X(0, 1) - ett + RX(-1, 2) - RX(-1, 1) - exx;
-        const int tvx = TW ? tw_cat(Fpx, RX(-1, 2), Bax).v : 0;
-        const int tvt = TW ? tw_cat(tw_cat(Ft, X(0, 0), Nx), X(0, 1), Bat).v : 0;
-        const int lx = PD ? ld_cat(Ppx, Sax).lm : Lx - dx;
-        const int lt = PD ? ld_cat(ld_cat(Pt, Mx), Sat).lm : Lt + dx;
-        rec(dD, lx, lt, tvx, tvt, (uQ + (uint32_t)refX) * uQ + (uint32_t)refT);
-    }
-    if ((op_mask & 1) && ct) {  // RELOCATE t -> right after x
-        const int dD = X(0, 0) + X(1, 0) - exx + CT(-1, 2) - CT(-1, 1) - ett;
-        const int tvx = TW ? tw_cat(tw_cat(Fx, X(0, 0), Nt), X(1, 0), Bax).v : 0;
-        const int tvt = TW ? tw_cat(Fpt, CT(-1, 2), Bat).v : 0;
-        const int lx = PD ? ld_cat(ld_cat(Px, Mt), Sax).lm : Lx + dtt;
-        const int lt = PD ? ld_cat(Ppt, Sat).lm : Lt - dtt;
-        rec(dD, lx, lt, tvx, tvt, (uQ + (uint32_t)refT) * uQ + (uint32_t)refX);
-    }
-    const uint32_t lo = min((uint32_t)refX, (uint32_t)refT), hi = max((uint32_t)refX, (uint32_t)refT);
-    if ((op_mask & 2) && cx && ct) {  // SWAP x <-> t
-        const int dD = X(-1, 0) + X(1, 0) + X(0, -1) + X(0, 1) - RX(-1, 1) - exx - CT(-1, 1) - ett;
-        const int tvx = TW ? tw_cat(tw_cat(Fpx, X(-1, 0), Nt), X(1, 0), Bax).v : 0;
-        const int tvt = TW ? tw_cat(tw_cat(Fpt, X(0, -1), Nx), X(0, 1), Bat).v : 0;
-        const int lx = PD ? ld_cat(ld_cat(Ppx, Mt), Sax).lm : Lx - dx + dtt;
-        const int lt = PD ? ld_cat(ld_cat(Ppt, Mx), Sat).lm : Lt - dtt + dx;
-        rec(dD, lx, lt, tvx, tvt, (5u * uQ + lo) * uQ + hi);
-    }
-    if (op_mask & 4) {  // 2OPT*: heads keep their routes, tails exchanged
-        const int dD = X(0, 1) + X(1, 0) - exx - ett;
-        const int tvx = TW ? tw_cat(Fx, X(0, 1), Bat).v : 0;
-        const int tvt = TW ? tw_cat(Ft, X(1, 0), Bax).v : 0;
-        const int lx = PD ? ld_cat(Px, Sat).lm : bx.y + (Lt - bt.y);
-        const int lt = PD ? ld_cat(Pt, Sax).lm : bt.y + (Lx - bx.y);
-        rec(dD, lx, lt, tvx, tvt, (8u * uQ + lo) * uQ + hi);
-    }
-    if (!(op_mask & 0xE0u)) return;
-    // ---- operator variants: segments of up to three customers starting at
-    // x and at t (kept and reversed summaries, the slot after each segment)
-    struct Seg3 {
-        int k;         // customers available from the slot on, within its route (<= 3)
-        int dem[3];    // deliveries of the first k customers
-        Tw f[3], r[3];
-        Ld lf[3], lr[3];
-        Tw sa[3];
-        Ld la[3];
-    };
-    auto seg3 = [&](int y, Seg3 &g) {
-        const int last = gld(S.roff + gld(S.a4 + y).y + 1) - 1;
-        g.k = min(3, last - y + 1);
-        int dsum = 0;
-        for (int q = 0; q < 3; ++q) {
-            const bool in = q < g.k;
-            dsum += in ? gld(S.b4 + y + q).x : 0;
-            g.dem[q] = dsum;
-            if (!in) continue;
-            if (TW) {
-                const Tw nq = tw_node_at(S, y + q);
-                g.f[q] = q == 0 ? nq : tw_cat(g.f[q - 1], gld(S.a4 + y + q - 1).z, nq);
-                g.r[q] = q == 0 ? nq : tw_cat(nq, gld(S.a4 + y + q - 1).z, g.r[q - 1]);
-                g.sa[q] = tw_after(S, y + q, dep);
-            }
-            if (PD) {
-                const Ld lq = ld_node_at(S, y + q);
-                g.lf[q] = q == 0 ? lq : ld_cat(g.lf[q - 1], lq);
-                g.lr[q] = q == 0 ? lq : ld_cat(lq, g.lr[q - 1]);
-                g.la[q] = ld_after(S, y + q);
-            }
-        }
-    };
-    Seg3 gx, gt;
-    if (cx) seg3(x, gx);
-    if (ct) seg3(t, gt);
-    // SEGMENT RELOCATE (op 5 kept, op 6 reversed), k = 2, 3: the segment
-    // starting at slot y of route `from` (prefix summaries before it Fp /
-    // Pp, route load Lf) moves right after slot z of route `to` (prefix Fy /
-    // Py, suffix after it Bay / Say, route load Lto); (y, z) = (x, t) when
-    // fromIsX, else (t, x).
-    auto segrel = [&](const Seg3 &g, const Tw &Fp, const Ld &Pp, int Lf, const Tw &Fy, const Ld &Py, const Tw &Bay,
-                      const Ld &Say, int Lto, bool fromIsX, uint32_t refA, uint32_t refB) {
-        auto rf = [&](int a, int k) { return fromIsX ? RX(a, k) : CT(a, k); };  // within `from`
-        auto rt = [&](int b, int k) { return fromIsX ? CT(b, k) : RX(b, k); };  // within `to`
-        auto cr = [&](int a, int b) { return fromIsX ? X(a, b) : X(b, a); };    // y + a and z + b
-        for (int k = 2; k <= g.k; ++k) {
-            const int cut = rf(-1, k + 1) - rf(-1, 1) - rf(k - 1, 1);
-            for (int op = 5; op <= 6; ++op) {
-                if (!(op_mask & (op == 5 ? 32u : 64u))) continue;
-                const int first = op == 5 ? 0 : k - 1, lastp = op == 5 ? k - 1 : 0;  // offsets from y
-                const int dD = cut + cr(first, 0) + cr(lastp, 1) - rt(0, 1);
-                int tvFrom = 0, tvTo = 0;
-                if (TW) {
-                    tvFrom = tw_cat(Fp, rf(-1, k + 1), g.sa[k - 1]).v;
-                    tvTo = tw_cat(tw_cat(Fy, cr(first, 0), op == 5 ? g.f[k - 1] : g.r[k - 1]), cr(lastp, 1), Bay).v;
-                }
-                const int lFrom = PD ? ld_cat(Pp, g.la[k - 1]).lm : Lf - g.dem[k - 1];
-                const int lTo = PD ? ld_cat(ld_cat(Py, op == 5 ? g.lf[k - 1] : g.lr[k - 1]), Say).lm : Lto + g.dem[k - 1];
-                const uint32_t id = (((uint32_t)op * 4u + (uint32_t)k) * uQ + refA) * uQ + refB;
-                if (fromIsX)
-                    rec(dD, lFrom, lTo, tvFrom, tvTo, id);
-                else
-                    rec(dD, lTo, lFrom, tvTo, tvFrom, id);
-                ++cntExt;
-            }
-        }
-    };
-    if (cx) segrel(gx, Fpx, Ppx, Lx, Ft, Pt, Bat, Sat, Lt, true, (uint32_t)refX, (uint32_t)refT);
-    if (ct) segrel(gt, Fpt, Ppt, Lt, Fx, Px, Bax, Sax, Lx, false, (uint32_t)refT, (uint32_t)refX);
-    // CROSS-EXCHANGE (ops 7..9): x's first ka customers and t's first kb
-    if ((op_mask & 128u) && cx && ct) {
-        for (int ka = 1; ka <= gx.k; ++ka)
-            for (int kb = 1; kb <= gt.k; ++kb) {
-                if (ka == 1 && kb == 1) continue;
-                // segment x .. x + ka - 1 and t .. t + kb - 1 exchanged
-                const int dD = X(-1, 0) + X(ka, kb - 1) + X(0, -1) + X(ka - 1, kb) - RX(-1, 1) - RX(ka - 1, 1) -
-                               CT(-1, 1) - CT(kb - 1, 1);
-                int tvx = 0, tvt = 0;
-                if (TW) {
-                    tvx = tw_cat(tw_cat(Fpx, X(-1, 0), gt.f[kb - 1]), X(ka, kb - 1), gx.sa[ka - 1]).v;
-                    tvt = tw_cat(tw_cat(Fpt, X(0, -1), gx.f[ka - 1]), X(ka - 1, kb), gt.sa[kb - 1]).v;
-                }
-                const int lx = PD ? ld_cat(ld_cat(Ppx, gt.lf[kb - 1]), gx.la[ka - 1]).lm
-                                  : Lx - gx.dem[ka - 1] + gt.dem[kb - 1];
-                const int lt = PD ? ld_cat(ld_cat(Ppt, gx.lf[ka - 1]), gt.la[kb - 1]).lm
-                                  : Lt - gt.dem[kb - 1] + gx.dem[ka - 1];
-                const bool xFirst = refX < refT;
-                const uint32_t op = 6u + (uint32_t)(xFirst ? ka : kb), k = (uint32_t)(xFirst ? kb : ka);
-                rec(dD, lx, lt, tvx, tvt, ((op * 4u + k) * uQ + lo) * uQ + hi);
-                ++cntExt;
-            }
-    }
-}
-
-// Inter-route pairs: 16 x 16 tiles of (row slot, column slot) on and above
-// the diagonal, blockIdx.x enumerating the tiles row by row.
-template <bool TW, bool PD, bool DUMP>
-__global__ __launch_bounds__(256) void k_eval_pen_pairs(const SolDev *__restrict__ sols, int tiles, uint32_t op_mask,
-                                                        int32_t *__restrict__ dd, uint8_t *__restrict__ df) {
-    __shared__ unsigned long long red[4];
-    const SolDev &S = sols[0];
-    if (skip_solution(S, op_mask)) return;
-    int bi = 0, rem = blockIdx.x;  // tile row bi holds tiles - bi tiles
-    while (rem >= tiles - bi) {
-        rem -= tiles - bi;
-        ++bi;
-    }
-    const int bj = bi + rem;
-    const int x0 = bi * 16, t0 = bj * 16;
-    const int x = x0 + (threadIdx.x >> 4), t = t0 + (threadIdx.x & 15);
-    // the tile's distances: nodes of slots x0 - 1 .. x0 + 22 and t0 - 1 ..
-    // t0 + 22 (clamped to [0, Q]), then one gather per distance
-    __shared__ PairTileD T;
-    __shared__ int nodeX[kTileSpan + 4], nodeT[kTileSpan + 4];
-    {
-        const int Q = S.Q, np1 = S.np1;
-        const int32_t *D = S.D;
-        const int i = threadIdx.x;
-        if (i < kTileSpan + 4) nodeX[i] = nodeof(gld(S.a4 + min(max(x0 - 1 + i, 0), Q)).x);
-        else if (i >= 32 && i < 32 + kTileSpan + 4)
-            nodeT[i - 32] = nodeof(gld(S.a4 + min(max(t0 - 1 + i - 32, 0), Q)).x);
-        __syncthreads();
-        for (int e = threadIdx.x; e < kTileSpan * kTileSpan; e += blockDim.x) {
-            const int a = e / kTileSpan, b = e - a * kTileSpan;
-            T.Dc[a][b] = gld(D + (size_t)nodeX[a] * np1 + nodeT[b]);
-        }
-        for (int e = threadIdx.x; e < 2 * kTileSpan * 4; e += blockDim.x) {
-            const int side = e / (kTileSpan * 4), a = (e / 4) % kTileSpan, k = e % 4 + 1;
-            const int *nd = side ? nodeT : nodeX;
-            const int v = gld(D + (size_t)nd[a] * np1 + nd[a + k]);
-            if (side) T.Cc[a][k - 1] = v;
-            else T.Rr[a][k - 1] = v;
-        }
-        __syncthreads();
-    }
-    int bd = DUMP ? kAdmissibleBound : initial_bound(op_mask);
-    uint32_t bid = 0xFFFFFFFFu;
-    int ext = 0;  // operator-variant moves of this thread's pair
-    if (x < S.Q && t < S.Q && gld(S.a4 + x).y < gld(S.a4 + t).y) {
-        pen_pair<TW, PD, DUMP>(S, x, t, T, x - x0 + 1, t - t0 + 1, op_mask, dd, df, bd, bid, ext);
-        // every move of this pair of slots touches exactly their two routes
-        if ((op_mask & kMulti) && bd < 0 && bid != 0xFFFFFFFFu)
-            atomicMin(S.pairkey + (size_t)gld(S.a4 + x).y * S.R + gld(S.a4 + t).y, pack_key(bd, bid));
-    }
-    if (op_mask & 0xE0u) {  // one atomic per workgroup
-        __shared__ int ext_sh;
-        if (threadIdx.x == 0) ext_sh = 0;
-        __syncthreads();
-        for (int off = 32; off >= 1; off >>= 1) ext += __shfl_xor(ext, off);
-        if ((threadIdx.x & 63) == 0 && ext) atomicAdd(&ext_sh, ext);
-        __syncthreads();
-        if (threadIdx.x == 0 && ext_sh) atomicAdd((unsigned long long *)(S.acc + kAccExtMoves), (unsigned long long)ext_sh);
-    }
-    block_argmin_commit(bd, bid, S.best_key, red);
-}
-
-// Intra-route moves whose first position is the customer at slot s: the
-// 2-opt / same-route swap walk and the or-opt walks, the middle summaries
-// (time warp and, with pickups, load) growing one node per step.  Seven
-// threads per slot, one walk each (walk 0: 2-opt / swap; 1..3: or-opt of
-// k = walk nodes moved forward; 4..6: k = walk - 3 moved backward), so that a
-// launch has seven times the threads and each its own short chain.
-template <bool TW, bool PD, bool DUMP>
-__global__ __launch_bounds__(256) void k_eval_pen_intra(const SolDev *__restrict__ sols, uint32_t op_mask,
-                                                        int32_t *__restrict__ dd, uint8_t *__restrict__ df) {
-    __shared__ unsigned long long red[4];
-    const SolDev &S = sols[0];
-    if (skip_solution(S, op_mask)) return;
-    int bd = DUMP ? kAdmissibleBound : initial_bound(op_mask);
-    uint32_t bid = 0xFFFFFFFFu;
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int walk = gid / S.Q, s = gid - walk * S.Q;
-    if (walk < 7 && (flagsof(gld(S.a4 + s).x) & kFlagCustomer)) {
-        const int r = gld(S.a4 + s).y, off = gld(S.roff + r), L = gld(S.roff + r + 1) - off - 1, i = s - off;
-        const int n = S.n, np1 = S.np1, cap = S.cap;
-        const uint32_t uQ = (uint32_t)S.Q;
-        const int32_t *D = S.D;
-        const bool opSwap = op_mask & 2, op2o = op_mask & 8, opOr = op_mask & 16;
-        auto node = [&](int p) { return (p == 0 || p > L) ? 0 : nodeof(gld(S.a4 + off + p).x); };
-        auto d = [&](int a, int b) { return gld(D + (size_t)a * np1 + b); };
-        auto ref = [&](int p) { return p == 0 ? (uint32_t)(n + r) : (uint32_t)(node(p) - 1); };
-        auto edge = [&](int p) { return gld(S.a4 + off + p).z; };  // position p to p + 1
-        const Tw dep = TW ? tw_depot(S) : Tw{};
-        auto Npos = [&](int p) { return TW ? tw_node_at(S, off + p) : Tw{}; };
-        auto Fpos = [&](int p) { return TW ? tw_of(gld(S.pf4 + off + p)) : Tw{}; };
-        auto Bafter = [&](int p) { return TW ? (p >= L ? dep : tw_of(gld(S.pb4 + off + p + 1))) : Tw{}; };
-        auto LNpos = [&](int p) { return PD ? ld_node_at(S, off + p) : Ld{}; };
-        auto LFpos = [&](int p) { return PD ? ld_of(gld(S.pl4 + off + p)) : Ld{}; };
-        auto LBafter = [&](int p) { return PD ? (p >= L ? Ld{0, 0, 0} : ld_of(gld(S.ql4 + off + p + 1))) : Ld{}; };
-        const int lvR = route_excess(S, r);
-        const int tvR = TW ? gld(S.pb4 + off).w : 0;
-        // new route: time warp tvNew, largest load peakNew (without pickups
-        // an intra-route move keeps the load)
-        auto rec = [&](int dD, int tvNew, int lvNew, uint32_t id) {
-            gen_record(S, dD, lvNew - lvR, tvNew - tvR, lvNew == 0, tvNew == 0, id, DUMP, dd, df, bd, bid);
-        };
-        auto excess = [&](const Ld &x) { return PD ? max(x.lm - cap, 0) : lvR; };
-        const int cI = node(i), cP = node(i - 1);
-        const int eP = edge(i - 1), eI = edge(i);
-        const Tw Fi1 = Fpos(i - 1);
-        const Ld LFi1 = LFpos(i - 1);
-        // ---- 2OPT(i, j) and SWAP(i, j), j > i
-        if ((op2o || opSwap) && walk == 0) {
-            Tw rev = Npos(i), mid{};
-            Ld lrev = LNpos(i), lmid{};
-            for (int j = i + 1; j <= L; ++j) {
-                const int cJ = node(j), cJ1 = node(j + 1), ej = edge(j), ejm = edge(j - 1);
-                if (TW) rev = tw_cat(Npos(j), ejm, rev);
-                if (PD) lrev = ld_cat(LNpos(j), lrev);
-                const int d1 = d(cP, cJ), d2 = d(cI, cJ1);
-                const uint32_t lo = min(ref(i), ref(j)), hi = max(ref(i), ref(j));
-                const Tw Ba = Bafter(j);
-                const Ld LBa = LBafter(j);
-                if (op2o) {
-                    const int tv = TW ? tw_cat(tw_cat(Fi1, d1, rev), d2, Ba).v : 0;
-                    const int lv = excess(ld_cat(ld_cat(LFi1, lrev), LBa));
-                    rec(d1 + d2 - eP - ej, tv, lv, (12u * uQ + lo) * uQ + hi);
-                }
-                if (opSwap) {
-                    int dS, tv = 0, lv;
-                    if (j == i + 1) {
-                        dS = d1 + d2 - eP - ej;
-                        if (TW) tv = tw_cat(tw_cat(tw_cat(Fi1, d1, Npos(j)), ejm, Npos(i)), d2, Ba).v;
-                        lv = excess(ld_cat(ld_cat(ld_cat(LFi1, LNpos(j)), LNpos(i)), LBa));
-                    } else {
-                        const int dA = d(cJ, node(i + 1)), dB = d(node(j - 1), cI);
-                        dS = d1 + dA + dB + d2 - eP - eI - ejm - ej;
-                        if (TW)
-                            tv = tw_cat(tw_cat(tw_cat(tw_cat(Fi1, d1, Npos(j)), dA, mid), dB, Npos(i)), d2, Ba).v;
-                        lv = excess(ld_cat(ld_cat(ld_cat(ld_cat(LFi1, LNpos(j)), lmid), LNpos(i)), LBa));
-                    }
-                    rec(dS, tv, lv, (5u * uQ + lo) * uQ + hi);
-                }
-                if (TW) mid = (j == i + 1) ? Npos(j) : tw_cat(mid, ejm, Npos(j));  // c_{i+1} .. c_j
-                if (PD) lmid = (j == i + 1) ? LNpos(j) : ld_cat(lmid, LNpos(j));
-            }
-        }
-        // ---- OR-OPT: segment c_i .. c_{i+k-1} moved right after c_j
-        if (opOr && walk >= 1) {
-            const int k = walk <= 3 ? walk : walk - 3;
-            const bool fwd = walk <= 3;
-            if (i + k - 1 <= L) {
-                const int g = i + k - 1, w = i + k, cG = node(g), cW = node(w);
-                const int base = d(cP, cW) - eP - edge(g);
-                Tw sig{};
-                Ld lsig{};
-                if (TW) {
-                    sig = Npos(i);
-                    for (int q = 1; q < k; ++q) sig = tw_cat(sig, edge(i + q - 1), Npos(i + q));
-                }
-                if (PD) {
-                    lsig = LNpos(i);
-                    for (int q = 1; q < k; ++q) lsig = ld_cat(lsig, LNpos(i + q));
-                }
-                Tw mid{};
-                Ld lmid{};
-                for (int j = w; fwd && j <= L; ++j) {  // forward: middle c_{i+k} .. c_j
-                    const int cJ = node(j), cJ1 = node(j + 1);
-                    if (TW) mid = (j == w) ? Npos(j) : tw_cat(mid, edge(j - 1), Npos(j));
-                    if (PD) lmid = (j == w) ? LNpos(j) : ld_cat(lmid, LNpos(j));
-                    const int dVF = d(cJ, cI), dGV = d(cG, cJ1);
-                    const int tv = TW ? tw_cat(tw_cat(tw_cat(Fi1, d(cP, cW), mid), dVF, sig), dGV, Bafter(j)).v : 0;
-                    const int lv = excess(ld_cat(ld_cat(ld_cat(LFi1, lmid), lsig), LBafter(j)));
-                    rec(base + dVF + dGV - edge(j), tv, lv, ((16u + k) * uQ + ref(i)) * uQ + ref(j));
-                }
-                for (int j = i - 2; !fwd && j >= 0; --j) {  // backward: middle c_{j+1} .. c_{i-1}
-                    const int cJ = node(j), cJ1 = node(j + 1);
-                    if (TW) mid = (j == i - 2) ? Npos(i - 1) : tw_cat(Npos(j + 1), edge(j + 1), mid);
-                    if (PD) lmid = (j == i - 2) ? LNpos(i - 1) : ld_cat(LNpos(j + 1), lmid);
-                    const int dVF = d(cJ, cI), dGV = d(cG, cJ1);
-                    const int tv =
-                        TW ? tw_cat(tw_cat(tw_cat(Fpos(j), dVF, sig), dGV, mid), d(cP, cW), Bafter(g)).v : 0;
-                    const int lv = excess(ld_cat(ld_cat(ld_cat(LFpos(j), lsig), lmid), LBafter(g)));
-                    rec(base + dVF + dGV - edge(j), tv, lv, ((16u + k) * uQ + ref(i)) * uQ + ref(j));
-                }
-            }
-        }
-        if ((op_mask & kMulti) && bd < 0 && bid != 0xFFFFFFFFu)  // moves inside route r
-            atomicMin(S.pairkey + (size_t)r * S.R + r, pack_key(bd, bid));
-    }
-    block_argmin_commit(bd, bid, S.best_key, red);
-}
-
 // theta nearest neighbours of every node (distance, then node id; the node
 // itself excluded), one workgroup per node: the theta-th smallest key
 // (d << 14 | j) is found by bisection over the key range with block-wide
@@ -2410,8 +2048,7 @@ __device__ __forceinline__ void intra_group(const SolDev &S, const IntraItem &it
             }
         }
     }
-    wave_argmin(bd, bid);
-    if (lane == 0 && bd < kAdmissibleBound && bid != 0xFFFFFFFFu) atomicMin(S.best_key, pack_key(bd, bid));
+    wave_argmin_commit(bd, bid, S.best_key);
 }
 
 // The intra-route moves of one (i, j) cell of route r (L customers, staged
@@ -2841,8 +2478,7 @@ __device__ __forceinline__ void intra_group_flat(const SolDev &S, const IntraIte
             intra_moves_joint<TW>(S, V, item.r0 + myk, pk - 2, myi, (capOK >> myk) & 1, op_mask, bd, bid);
         }
         wave_lds_sync();
-        wave_argmin(bd, bid);
-        if (lane == 0 && bd < kAdmissibleBound && bid != 0xFFFFFFFFu) atomicMin(S.best_key, pack_key(bd, bid));
+        wave_argmin_commit(bd, bid, S.best_key);
         return;
     }
     const bool opSwap = op_mask & 2, op2o = op_mask & 8, opOr = op_mask & 16;
@@ -2870,19 +2506,19 @@ __device__ __forceinline__ void intra_group_flat(const SolDev &S, const IntraIte
         }
     }
     wave_lds_sync();  // the region is free for the next group
-    wave_argmin(bd, bid);
-    if (lane == 0 && bd < kAdmissibleBound && bid != 0xFFFFFFFFu) atomicMin(S.best_key, pack_key(bd, bid));
+    wave_argmin_commit(bd, bid, S.best_key);
 }
 
 // A group of consecutive routes staged in LDS by a whole workgroup: route k
-// (P[k] positions) at word offset at[k] of the region, seven per-position
-// arrays and its P x P distance sub-block.
+// (P[k] positions) at word offset at[k] of the region, NA per-position
+// arrays (seven, more on the general path) and its P x P distance sub-block.
 struct GroupStage {
     int offs[kIntraMaxGroup + 1], P[kIntraMaxGroup], at[kIntraMaxGroup];
     int NP, sumL, words;
 };
 
 // Layout of the routes [r0, r0 + G) (G <= kIntraMaxGroup), uniform.
+template <int NA = 7>
 __device__ __forceinline__ void group_layout(const SolDev &S, int r0, int G, GroupStage &g) {
 #pragma unroll
     for (int k = 0; k <= kIntraMaxGroup; ++k) g.offs[k] = sld1(S.roff + r0 + min(k, G));
@@ -2893,16 +2529,23 @@ __device__ __forceinline__ void group_layout(const SolDev &S, int r0, int G, Gro
         g.at[k] = g.words;
         g.NP += g.P[k];
         g.sumL += k < G ? g.P[k] - 2 : 0;
-        g.words += 7 * g.P[k] + g.P[k] * g.P[k];
+        g.words += NA * g.P[k] + g.P[k] * g.P[k];
     }
 }
+
+// Per-position arrays of a group staged for the general path: the seven with
+// deliveries and pickups in the place of departures and latest arrivals, then
+// the time-warp (TW) and load (PD) summaries of prefix and suffix.
+template <bool TW, bool PD>
+constexpr int gen_arrays() { return 7 + (TW ? 8 : 0) + (PD ? 6 : 0); }
 
 // Stages the group: every position's attributes at once, then every distance
 // at once (the workgroup's eight wavefronts share them, so a group of 48
 // customers takes two memory round trips after its offsets).  Every thread
 // of the block calls it; it ends with a barrier.
-template <bool TW>
+template <bool TW, bool GEN = false, bool PD = false>
 __device__ __forceinline__ void stage_group(const SolDev &S, const GroupStage &g, int *region) {
+    constexpr int NA = GEN ? gen_arrays<TW, PD>() : 7;
     const int T = blockDim.x;
     const int l0 = TW ? sld(S.node4).z : kTwOff;
     for (int f = threadIdx.x; f < g.NP; f += T) {
@@ -2917,24 +2560,57 @@ __device__ __forceinline__ void stage_group(const SolDev &S, const GroupStage &g
                 ck = c;
             }
         }
-        const int p = f - ck;
-        int *b = region + ak;
+        const int p = f - ck, x = ok + p;
+        int *b = region + ak + p;
         if (p <= pk - 2) {
-            const int4 a = gld(S.a4 + ok + p);
-            if (TW) {
-                const int4 t = gld(S.t4 + ok + p), w = gld(S.w4 + ok + p);
-                b[2 * pk + p] = t.x;
-                b[3 * pk + p] = t.w;
-                b[4 * pk + p] = w.x;
-                b[5 * pk + p] = w.y;
-                b[6 * pk + p] = w.z;
+            const int4 a = gld(S.a4 + x);
+            if (TW || PD) {
+                const int4 w = gld(S.w4 + x);
+                if (TW && !GEN) {
+                    const int4 t = gld(S.t4 + x);
+                    b[2 * pk] = t.x;
+                    b[3 * pk] = t.w;
+                }
+                if (PD) {
+                    b[2 * pk] = gld(S.b4 + x).x;
+                    b[3 * pk] = w.w;
+                }
+                b[4 * pk] = w.x;
+                b[5 * pk] = w.y;
+                b[6 * pk] = w.z;
             }
-            b[p] = nodeof(a.x);
-            b[pk + p] = a.z;
+            b[0] = nodeof(a.x);
+            b[pk] = a.z;
         } else {
-            b[p] = 0;
-            b[pk + p] = 0;
-            b[3 * pk + p] = l0;
+            b[0] = 0;
+            b[pk] = 0;
+            if (!GEN) b[3 * pk] = l0;
+        }
+        if (GEN && TW) {
+            const bool in = p <= pk - 2;
+            const int4 q = gld(S.node4);
+            const int4 f4 = in ? gld(S.pf4 + x) : make_int4(0, 0, 0, 0);
+            const int4 b4 = in ? gld(S.pb4 + x) : make_int4(q.w, q.y, q.z, 0);  // the end depot
+            b[7 * pk] = f4.x;
+            b[8 * pk] = f4.y;
+            b[9 * pk] = f4.z;
+            b[10 * pk] = f4.w;
+            b[11 * pk] = b4.x;
+            b[12 * pk] = b4.y;
+            b[13 * pk] = b4.z;
+            b[14 * pk] = b4.w;
+        }
+        if (GEN && PD) {
+            constexpr int o = TW ? 15 : 7;
+            const bool in = p <= pk - 2;
+            const int4 f4 = in ? gld(S.pl4 + x) : make_int4(0, 0, 0, 0);
+            const int4 b4 = in ? gld(S.ql4 + x) : make_int4(0, 0, 0, 0);
+            b[o * pk] = f4.x;
+            b[(o + 1) * pk] = f4.y;
+            b[(o + 2) * pk] = f4.z;
+            b[(o + 3) * pk] = b4.x;
+            b[(o + 4) * pk] = b4.y;
+            b[(o + 5) * pk] = b4.z;
         }
     }
     __syncthreads();
@@ -2961,7 +2637,7 @@ __device__ __forceinline__ void stage_group(const SolDev &S, const GroupStage &g
                 }
                 const int y = x - ck, pp = y / pk, qq = y - pp * pk;
                 val[u] = gld(S.D + (size_t)region[ak + pp] * S.np1 + region[ak + qq]);
-                dst[u] = ak + 7 * pk + y;
+                dst[u] = ak + NA * pk + y;
             }
         }
 #pragma unroll
@@ -3034,8 +2710,7 @@ __device__ __forceinline__ void intra_block(const SolDev &S, int r0, int r1, uin
             }
         }
     }
-    wave_argmin(bd, bid);
-    if (lane == 0 && bd < kAdmissibleBound && bid != 0xFFFFFFFFu) atomicMin(S.best_key, pack_key(bd, bid));
+    wave_argmin_commit(bd, bid, S.best_key);
 }
 
 // Single-solution form: workgroups below nintra take the intra-route groups
@@ -3087,6 +2762,743 @@ __global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4
     }
     gran_block<TW, DUMP>(S, gsrc, gadj, gcc, gdep, ((int)blockIdx.x - nintra) * blockDim.x + threadIdx.x, op_mask,
                          dump_delta, dump_feas, red, &cnt_sh);
+}
+
+// ------------------------------------------------------- general path ---
+// Penalised mode, pickups, the operator variants and multi-move steps: new
+// routes are concatenations of the stored prefix / suffix summaries with the
+// moved nodes (Section 4.3.2, Section 4.3.3).  Penalised mode (feasible and
+// infeasible search, Alg. A2): every move is admissible and scores
+// dD + w_L dL_V + w_T dT_V over the touched routes (Section 5.3.3 attribute
+// deltas, eq. scoring_tensor).  The dumps hold the score (penalised) or the
+// delta, and the hard capacity / window bits of the touched routes.
+//
+// As on the plain path the deltas come first and the concatenations only
+// where a move can still be the best: a score is at least
+// dD - w_L L_V - w_T T_V of the routes as they are (new excess and warp are
+// >= 0), and the deliveries of a new route bound its largest load from
+// below.
+
+// Suffix summary strictly after slot x (the end depot when x is last).
+__device__ __forceinline__ Tw tw_after(const SolDev &S, int x, const Tw &dep) {
+    return nodeof(gld(S.a4 + x + 1).x) == 0 ? dep : tw_of(gld(S.pb4 + x + 1));
+}
+
+__device__ __forceinline__ Tw tw_node_at(const SolDev &S, int x) {
+    const int4 w = gld(S.w4 + x);
+    return tw_node(w.x, w.y, w.z);
+}
+
+// Load summary strictly after slot x (the end depot: empty, when x is last).
+__device__ __forceinline__ Ld ld_after(const SolDev &S, int x) {
+    return nodeof(gld(S.a4 + x + 1).x) == 0 ? Ld{0, 0, 0} : ld_of(gld(S.ql4 + x + 1));
+}
+
+// Record one move of the general path.  Penalised mode: every move is
+// admissible.  Otherwise the distance delta, admissible when the touched
+// routes have no load excess and no time warp.
+__device__ __forceinline__ void gen_record(const SolDev &S, int dD, int dlv, int dtv, bool capok, bool twok, uint32_t id,
+                                           int32_t *dd, uint8_t *df, int &bd, uint32_t &bid) {
+    const int feas = (capok ? 1 : 0) | (twok ? 2 : 0);
+    const int score = S.pen ? dD + S.wL * dlv + S.wT * dtv : dD;
+    if (dd) {
+        dd[id] = score;
+        df[id] = (uint8_t)feas;
+    }
+    consider(S.pen || feas == 3 ? score : score + kPenalty, id, bd, bid);
+}
+
+// An inter-route move as a queue entry: cx customers starting at slot x and
+// ct customers starting at slot t leave their routes and take each other's
+// place (a side that gives nothing receives right after its slot); rev: the
+// moved segment is reversed; star: 2OPT*, the tails after x and t change
+// places.
+constexpr int kGenTBits = 14;  // t < 2^14 (TGA_MAX_Q)
+constexpr int gen_code(int cx, int ct, int rev, int star) { return cx | (ct << 2) | (rev << 4) | (star << 5); }
+constexpr int kGenStar = gen_code(0, 0, 0, 1);
+
+// One side's new route: the prefix ending at slot p, then the c customers
+// that start at slot y (reversed when rev), then what follows slot q.
+// Returns its time warp; peak receives its largest load, del the deliveries
+// of the inserted customers.
+template <bool TW, bool PD>
+__device__ __forceinline__ int gen_new_route(const SolDev &S, int p, int y, int c, bool rev, int q, const Tw &dep,
+                                             int &peak, int &del) {
+    const int32_t *D = S.D;
+    const int np1 = S.np1;
+    int last = nodeof(gld(S.a4 + p).x);
+    const int after = nodeof(gld(S.a4 + q + 1).x);  // node 0 when the route ends at q
+    Tw f{};
+    Ld lf{};
+    if (TW) f = tw_of(gld(S.pf4 + p));
+    if (PD) lf = ld_of(gld(S.pl4 + p));
+    del = 0;
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+        if (u < c) {
+            const int s = rev ? y + c - 1 - u : y + u;
+            const int node = nodeof(gld(S.a4 + s).x);
+            del += gld(S.b4 + s).x;
+            if (TW) f = tw_cat(f, gld(D + (size_t)last * np1 + node), tw_node_at(S, s));
+            if (PD) lf = ld_cat(lf, ld_node_at(S, s));
+            last = node;
+        }
+    }
+    if (PD) peak = ld_cat(lf, after ? ld_of(gld(S.ql4 + q + 1)) : Ld{0, 0, 0}).lm;
+    if (!TW) return 0;
+    const Tw b = after ? tw_of(gld(S.pb4 + q + 1)) : dep;
+    return tw_cat(f, gld(D + (size_t)last * np1 + after), b).v;
+}
+
+// The move `code` of the slot pair (x, t), distance delta dD.
+template <bool TW, bool PD>
+__device__ __forceinline__ void gen_eval_move(const SolDev &S, int x, int t, int code, int dD, int32_t *dd, uint8_t *df,
+                                              int &bd, uint32_t &bid) {
+    const int cx = code & 3, ct = (code >> 2) & 3;
+    const bool rev = code & 16, star = code & 32;
+    const int4 ax = gld(S.a4 + x), at = gld(S.a4 + t), bx = gld(S.b4 + x), bt = gld(S.b4 + t), gx = gld(S.g4 + x),
+               gt = gld(S.g4 + t);
+    const int px = cx ? x - 1 : x, qx = cx ? x + cx - 1 : x, pt = ct ? t - 1 : t, qt = ct ? t + ct - 1 : t;
+    const Tw dep = TW ? tw_depot(S) : Tw{};
+    int lx = 0, lt = 0, intoX, intoT;
+    const int tvx = gen_new_route<TW, PD>(S, px, t, ct, rev, star ? t : qx, dep, lx, intoX);
+    const int tvt = gen_new_route<TW, PD>(S, pt, x, cx, rev, star ? x : qt, dep, lt, intoT);
+    if (!PD) {  // loads: what leaves one route enters the other
+        lx = star ? bx.y + (bt.z - bt.y) : bx.z - intoT + intoX;
+        lt = star ? bt.y + (bx.z - bx.y) : bt.z - intoX + intoT;
+    }
+    const int cap = S.cap, lv = max(lx - cap, 0) + max(lt - cap, 0);
+    const int lvOld = max(gx.z - cap, 0) + max(gt.z - cap, 0);
+    const uint32_t uQ = (uint32_t)S.Q;
+    const uint32_t refX = (flagsof(ax.x) & kFlagCustomer) ? nodeof(ax.x) - 1 : S.n + ax.y;
+    const uint32_t refT = (flagsof(at.x) & kFlagCustomer) ? nodeof(at.x) - 1 : S.n + at.y;
+    const uint32_t lo = min(refX, refT), hi = max(refX, refT);
+    uint32_t opk, a = lo, b = hi;
+    if (star) {
+        opk = 8u;
+    } else if (!cx || !ct) {  // relocation of a segment: op 0, or op 5 / op 6
+        const uint32_t k = (uint32_t)(cx + ct);
+        opk = (k == 1 ? 0u : (rev ? 24u : 20u)) + k;
+        a = cx ? refX : refT;
+        b = cx ? refT : refX;
+    } else if (cx == 1 && ct == 1) {
+        opk = 5u;
+    } else {  // cross-exchange, the lower ref's segment length in the operator
+        opk = (6u + (uint32_t)(refX < refT ? cx : ct)) * 4u + (uint32_t)(refX < refT ? ct : cx);
+    }
+    gen_record(S, dD, lv - lvOld, tvx + tvt - gx.w - gt.w, lv == 0, tvx + tvt == 0, (opk * uQ + a) * uQ + b, dd, df, bd,
+               bid);
+}
+
+// Per wavefront: moves waiting to be evaluated (slots and code, lower bound of
+// the score, distance delta).
+constexpr int kGenQueue = 192, kGenSteps = 64;
+struct GenQueue {
+    int move[kGenQueue], bound[kGenQueue], delta[kGenQueue];
+    int step_min[kGenSteps];  // least lower bound of each of the wavefront's steps
+};
+
+// Whole-workgroup evaluation of the inter-route moves of the row slots
+// [s0, s1) (fewer than 256) against every column slot of a later route.
+// The (64-column chunk, row) steps are dealt to the wavefronts in equal
+// contiguous runs, chunk-major; lane = column, the distances between the slots x - 1 .. x + 3 and
+// t - 1 .. t + 3 in a register window (x - 1 .. x + 1 and t - 1 .. t + 1
+// without the operator variants), one row of it gathered per step: from the
+// rows staged in LDS (16-bit distances), else from D.
+//
+// A step forms the deltas of every move of the pair (4, with the variants up
+// to 20).  The wavefront goes over its steps twice, because evaluating a move
+// costs some 30 scattered reads per lane, which the compute unit's address
+// path takes one lane at a time: with thresholds that start at 0 the 90,000
+// improving moves of an early step were evaluated, 20 us of the launch.
+// First each lane keeps the move with the least lower bound (delta, the
+// loads' exact or least excess, less what the pair's routes could shed), and
+// the best of every eight lanes is evaluated: the workgroup's 64 candidates
+// give a threshold that hardly any move passes the second time.  The second
+// pass takes only the steps whose least lower bound reaches it; in them the
+// least delta of the pair is compared with the threshold; only where some
+// lane passes are the moves taken one by one and those that can still be the
+// best queued.  The queue is evaluated 64 moves at a time, one per lane, so
+// the long concatenations run on full wavefronts whatever the share of lanes
+// that passed.  A queue that fills up in the middle of a step is drained and
+// the step taken again from the move that did not fit.  Dumps and multi-move
+// steps (which need every improving move) start with the second pass.
+//
+// The evaluation launch (with the intra-route groups) against one thread per
+// pair evaluating all of its moves, and one per walk gathering from memory, in
+// two launches: n = 1000 VRPTW penalised 21.8 us (58.7), n = 997 CVRP with the
+// variants 22.8 (77.3), n = 603 with pickups 17.2 (43.4); multi-move, where
+// nothing is screened against the best, 18.8 (57.4).  The first pass is bound
+// by its arithmetic, the rest by the latency of one batch and by the longest
+// intra-route walk (16 us).
+template <bool TW, bool PD, bool EXT, bool W16>
+__device__ __forceinline__ void gen_strip(const SolDev &S, int s0, int s1, uint32_t op_mask, int32_t *__restrict__ dd,
+                                          uint8_t *__restrict__ df, int4 *smem4, unsigned long long *red, int *thr_sh,
+                                          GenQueue *queues) {
+    constexpr int A = EXT ? 3 : 1;  // slots read ahead of x and t
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int Q = S.Q, cap = S.cap, wL = S.wL;
+    const bool pen = S.pen, multi = op_mask & kMulti;
+    const uint16_t *rows = (const uint16_t *)smem4;
+    const int rs = S.stride16;
+    if (threadIdx.x == 0) *thr_sh = committed_delta(S);
+    if (W16) drow_issue<true>(S, smem4, s0 - 1, s0 - 1, s1 - s0 + 1 + A, wave);
+    int bd = initial_bound(op_mask);
+    uint32_t bid = 0xFFFFFFFFu;
+    GenQueue &q = queues[wave];
+    int cnt = 0;  // queued moves
+    auto threshold = [&]() {
+        if (dd) return 0x7FFFFFFF;
+        const int v = min(__hip_atomic_load(thr_sh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP),
+                          initial_bound(op_mask));
+        return multi ? max(v, 0) : v;  // multi-move: every improving move counts, for its pair of routes
+    };
+    auto node_at = [&](int s) { return nodeof(gld(S.a4 + min(max(s, 0), Q)).x); };
+    // added to the delta of a move that does not exist (at most three times);
+    // real deltas are below 2^27 in magnitude
+    constexpr int big = kAdmissibleBound, exists = big / 2;
+    const int offRel = (op_mask & 1) ? 0 : big, offSwap = (op_mask & 2) ? 0 : big, offStar = (op_mask & 4) ? 0 : big,
+              offKept = (op_mask & 32) ? 0 : big, offRev = (op_mask & 64) ? 0 : big,
+              offCross = (op_mask & 128) ? 0 : big;
+    // the wavefront's steps, and the columns of the current chunk
+    const int nr = s1 - s0, T = ((Q - s0 - 1 + 63) / 64) * nr;
+    const int first = T * wave / kInterWaves, end = T * (wave + 1) / kInterWaves;
+    int idx = first;
+    int cb = s0 + 1 + first / nr * 64;
+    int nd[A + 2];  // nodes of t - 1 .. t + A
+    int4 ta, tb, tg;
+    int et1 = 0, et2 = 0, lt1 = 0, lt2 = 0, slackT = 0;  // edges leaving t + 1, t + 2; deliveries of t's first 2 / 3 customers
+    auto columns = [&]() {
+        const int t = cb + lane, tc = min(t, Q);
+        ta = gld(S.a4 + tc);
+        tb = gld(S.b4 + tc);
+        tg = gld(S.g4 + tc);
+        nd[0] = node_at(t - 1);
+        nd[1] = nodeof(ta.x);
+        nd[2] = node_at(t + 1);
+        if (EXT) {
+            nd[3] = node_at(t + 2);
+            nd[A + 1] = node_at(t + 3);
+            et1 = gld(S.a4 + min(t + 1, Q)).z;
+            et2 = gld(S.a4 + min(t + 2, Q)).z;
+            lt1 = gld(S.b4 + min(t + 1, Q)).y - tb.y + tb.x;
+            lt2 = gld(S.b4 + min(t + 2, Q)).y - tb.y + tb.x;
+        }
+        slackT = pen ? wL * max(tg.z - cap, 0) + S.wT * tg.w : 0;
+    };
+    if (idx < end) columns();
+    // row attributes, read one step ahead
+    int4 ra = sld(S.a4 + s0 + first % nr), rb = sld(S.b4 + s0 + first % nr), rg = sld(S.g4 + s0 + first % nr);
+    if (W16) __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();  // rows and threshold in place
+    // D between slot x + a (uniform) and the lane's node
+    auto dist = [&](int x, int node) -> int {
+        if (W16) return rows[(x - s0 + 1) * rs + node];
+        const int rn = nodeof(sld(S.a4 + min(max(x, 0), Q)).x);
+        return gld(S.D + (size_t)rn * S.np1 + node);
+    };
+    int w[A + 2][A + 2];  // w[1 + a][1 + b]: between x + a and t + b
+    int x = s0 + first % nr, m0 = 0;  // row; first move of the step still to be taken
+    bool fresh = true;       // the window and the row attributes are not those of row x yet
+    bool fresh_cols = false;  // the columns are not those of chunk cb yet
+    bool scan = !dd && !multi;
+    int scan_lb = threshold(), scan_d = big, scan_mv = 0;  // the lane's most promising move of the first pass
+    while (true) {
+        const bool fin = idx >= end;
+        const bool visit = !fin && (scan || dd || multi || m0 != 0 || idx - first >= kGenSteps ||
+                                    q.step_min[idx - first] <= threshold());
+        if (!fin && !visit) {  // no move of the step can be the best any more
+            ++idx;
+            fresh = true;
+            if (++x == s1) {
+                x = s0;
+                cb += 64;
+                fresh_cols = true;
+            }
+        }
+        if (visit) {
+            if (fresh_cols) {
+                columns();
+                fresh_cols = false;
+            }
+            if (fresh) {
+                ra = sld(S.a4 + x);
+                rb = sld(S.b4 + x);
+                rg = sld(S.g4 + x);
+#pragma unroll
+                for (int a = 0; a <= A; ++a)
+#pragma unroll
+                    for (int b = 0; b < A + 2; ++b)
+                        if (EXT || a == 1 || b == 1) w[a][b] = dist(x - 1 + a, nd[b]);
+                fresh = false;
+            }
+            if (m0 == 0) {
+#pragma unroll
+                for (int b = 0; b < A + 2; ++b)
+                    if (EXT || b == 1) w[A + 1][b] = dist(x + A, nd[b]);
+            }
+            const int xn = x + 1 == s1 ? s0 : x + 1;
+            const int4 na = sld(S.a4 + xn), nb = sld(S.b4 + xn), ng = sld(S.g4 + xn);
+            const bool cx = flagsof(ra.x) & kFlagCustomer, ctv = flagsof(ta.x) & kFlagCustomer;
+            const int bx = cx ? 0 : big, bt = ctv ? 0 : big;
+            const int ex = ra.z, et = ta.z;
+            const bool valid = cb + lane < Q && ta.y > ra.y;
+            const int thr = threshold();
+            const int slack = slackT + (pen ? wL * max(rg.z - cap, 0) + S.wT * rg.w : 0);
+            int d[20];
+            d[0] = w[1][1] + w[1][2] - et + (ra.w + bx + offRel);
+            d[1] = w[1][1] + w[2][1] + (ta.w + bt) + (offRel - ex);
+            d[2] = w[0][1] + w[2][1] + w[1][0] + w[1][2] - tb.w + bt + (bx + offSwap - rb.w);
+            d[3] = w[1][2] + w[2][1] - et + (offStar - ex);
+            int lx1 = 0, lx2 = 0;  // deliveries of x's first 2 / 3 customers
+            int m = min(min(d[0], d[1]), min(d[2], d[3]));
+            if constexpr (EXT) {
+                const int4 r1 = sld(S.a4 + min(x + 1, Q)), r2 = sld(S.a4 + min(x + 2, Q));
+                const int kx = cx ? (nodeof(r1.x) == 0 ? 1 : (nodeof(r2.x) == 0 ? 2 : 3)) : 0;
+                const int kt = ctv ? (nd[2] == 0 ? 1 : (nd[3] == 0 ? 2 : 3)) : 0;
+                lx1 = sld(S.b4 + min(x + 1, Q)).y - rb.y + rb.x;
+                lx2 = sld(S.b4 + min(x + 2, Q)).y - rb.y + rb.x;
+                const int x2 = rg.x - et + (kx >= 2 ? 0 : big), x3 = rg.y - et + (kx >= 3 ? 0 : big);
+                const int t2 = tg.x - ex + (kt >= 2 ? 0 : big), t3 = tg.y - ex + (kt >= 3 ? 0 : big);
+                d[4] = w[1][1] + w[2][2] + x2 + offKept;
+                d[5] = w[2][1] + w[1][2] + x2 + offRev;
+                d[6] = w[1][1] + w[3][2] + x3 + offKept;
+                d[7] = w[3][1] + w[1][2] + x3 + offRev;
+                d[8] = w[1][1] + w[2][2] + t2 + offKept;
+                d[9] = w[1][2] + w[2][1] + t2 + offRev;
+                d[10] = w[1][1] + w[2][3] + t3 + offKept;
+                d[11] = w[1][3] + w[2][1] + t3 + offRev;
+                const int c0 = w[0][1] + w[1][0] + offCross;
+                const int epx = rb.w - ra.z, ept = tb.w - ta.z;  // edges entering x and t
+                const int ox[3] = {-epx - ex + bx, -epx - r1.z + (kx >= 2 ? 0 : big), -epx - r2.z + (kx >= 3 ? 0 : big)};
+                const int ot[3] = {-ept - et + bt, -ept - et1 + (kt >= 2 ? 0 : big), -ept - et2 + (kt >= 3 ? 0 : big)};
+#pragma unroll
+                for (int j = 1; j <= 8; ++j) {
+                    const int ka = j / 3 + 1, kb = j % 3 + 1;
+                    d[11 + j] = c0 + w[1 + ka][kb] + w[ka][1 + kb] + ox[ka - 1] + ot[kb - 1];
+                }
+#pragma unroll
+                for (int j = 4; j < 20; ++j) m = min(m, d[j]);
+            }
+            int next = 0x7FFFFFFF;  // the move to resume from when the queue is full
+            const int Lx = rb.z, Lt = tb.z;
+            // every move of the pair: f(j, deliveries that x's route gains from t's, code)
+            auto each_move = [&](auto f) {
+                f(0, -rb.x, gen_code(1, 0, 0, 0));
+                f(1, tb.x, gen_code(0, 1, 0, 0));
+                f(2, tb.x - rb.x, gen_code(1, 1, 0, 0));
+                f(3, (Lt - tb.y) - (Lx - rb.y), kGenStar);
+                if constexpr (EXT) {
+                    f(4, -lx1, gen_code(2, 0, 0, 0));
+                    f(5, -lx1, gen_code(2, 0, 1, 0));
+                    f(6, -lx2, gen_code(3, 0, 0, 0));
+                    f(7, -lx2, gen_code(3, 0, 1, 0));
+                    f(8, lt1, gen_code(0, 2, 0, 0));
+                    f(9, lt1, gen_code(0, 2, 1, 0));
+                    f(10, lt2, gen_code(0, 3, 0, 0));
+                    f(11, lt2, gen_code(0, 3, 1, 0));
+#pragma unroll
+                    for (int j = 1; j <= 8; ++j) {
+                        const int ka = j / 3 + 1, kb = j % 3 + 1;
+                        f(11 + j, (kb == 1 ? tb.x : (kb == 2 ? lt1 : lt2)) - (ka == 1 ? rb.x : (ka == 2 ? lx1 : lx2)),
+                          gen_code(ka, kb, 0, 0));
+                    }
+                }
+            };
+            if (scan) {
+                int step = valid && m < exists ? m - slack : 0x7FFFFFFF;
+                if (__builtin_amdgcn_ballot_w64(step < scan_lb)) {
+                    int lb = big, dj = big, code = 0;
+                    if (pen)
+                        each_move([&](int j, int load, int c) {
+                            const int over = max(Lx + load - cap, 0) + max(Lt - load - cap, 0);
+                            const int v = d[j] < exists ? d[j] + wL * over : big;
+                            if (v < lb) {
+                                lb = v;
+                                dj = d[j];
+                                code = c;
+                            }
+                        });
+                    else
+                        each_move([&](int j, int load, int c) {
+                            const int v = ((cap - Lx - load) | (cap - Lt + load)) >= 0 ? d[j] : big;
+                            if (v < lb) {
+                                lb = v;
+                                code = c;
+                            }
+                        });
+                    if (!pen) dj = lb;
+                    lb -= slack;
+                    step = valid && dj < exists ? lb : 0x7FFFFFFF;
+                    if (step < scan_lb) {
+                        scan_lb = lb;
+                        scan_d = dj;
+                        scan_mv = (cb + lane) | ((x - s0) << kGenTBits) | (code << (kGenTBits + 8));
+                    }
+                }
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1) step = min(step, __shfl_xor(step, o));
+                if (lane == 0 && idx - first < kGenSteps) q.step_min[idx - first] = step;
+            } else if (__builtin_amdgcn_ballot_w64(valid && m < exists && m - slack <= thr)) {
+                each_move([&](int j, int load, int code) {
+                    if (j < m0) return;
+                    const int over = max(Lx + load - cap, 0) + max(Lt - load - cap, 0);
+                    const int lb = pen ? d[j] - slack + wL * over : (over ? big : d[j]);
+                    const bool p = valid && d[j] < exists && lb <= thr;
+                    const unsigned long long mask = __builtin_amdgcn_ballot_w64(p);
+                    if (!mask) return;
+                    if (cnt > kGenQueue - 64) {
+                        next = min(next, j);
+                        return;
+                    }
+                    const int at = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+                    if (p) {
+                        q.move[at] = (cb + lane) | ((x - s0) << kGenTBits) | (code << (kGenTBits + 8));
+                        q.bound[at] = lb;
+                        q.delta[at] = d[j];
+                    }
+                    cnt += __builtin_popcountll(mask);
+                });
+            }
+            if (next == 0x7FFFFFFF) {  // on to the next row, or the next chunk
+                m0 = 0;
+                ++idx;
+                ra = na;
+                rb = nb;
+                rg = ng;
+                if (++x == s1) {
+                    x = s0;
+                    cb += 64;
+                    fresh = true;
+                    fresh_cols = true;
+                } else {
+#pragma unroll
+                    for (int a = 0; a <= A; ++a)
+#pragma unroll
+                        for (int b = 0; b < A + 2; ++b)
+                            if (EXT || b == 1) w[a][b] = w[a + 1][b];
+                    if (!EXT) {
+                        w[1][0] = dist(x, nd[0]);
+                        w[1][2] = dist(x, nd[2]);
+                    }
+                }
+            } else {
+                m0 = next;
+            }
+        }
+        if (fin && scan) {  // the best of every eight lanes become the queue; then once more over the steps
+            int g = scan_d < exists ? scan_lb : 0x7FFFFFFF;
+#pragma unroll
+            for (int o = 1; o <= 4; o <<= 1) g = min(g, __shfl_xor(g, o));
+            const unsigned long long eq = __builtin_amdgcn_ballot_w64(scan_d < exists && scan_lb == g);
+            const bool first = (eq >> lane & 1) && !(eq >> (lane & ~7) & ((1ull << (lane & 7)) - 1));
+            const unsigned long long mask = __builtin_amdgcn_ballot_w64(first);
+            const int at = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+            if (first) {
+                q.move[at] = scan_mv;
+                q.bound[at] = scan_lb;
+                q.delta[at] = scan_d;
+            }
+            cnt = __builtin_popcountll(mask);
+        }
+        if (cnt >= 64 || (fin && cnt > 0)) {  // evaluate the last (up to) 64 queued moves
+            const int take = min(cnt, 64), e = cnt - take + lane;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the queue is this wavefront's own
+            __builtin_amdgcn_wave_barrier();
+            if (lane < take && q.bound[e] <= threshold()) {
+                const int mv = q.move[e];
+                const int xx = s0 + ((mv >> kGenTBits) & 255), tt = mv & ((1 << kGenTBits) - 1);
+                const int code = (mv >> (kGenTBits + 8)) & 63;
+                if (multi) {  // the best improving move of each pair of routes
+                    int b1 = kAdmissibleBound;
+                    uint32_t i1 = 0xFFFFFFFFu;
+                    gen_eval_move<TW, PD>(S, xx, tt, code, q.delta[e], dd, df, b1, i1);
+                    if (b1 < 0 && i1 != 0xFFFFFFFFu)
+                        atomicMin(S.pairkey + (size_t)gld(S.a4 + xx).y * S.R + gld(S.a4 + tt).y, pack_key(b1, i1));
+                    if (i1 != 0xFFFFFFFFu) consider(b1, i1, bd, bid);
+                } else {
+                    gen_eval_move<TW, PD>(S, xx, tt, code, q.delta[e], dd, df, bd, bid);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            cnt -= take;
+            if (!dd) {  // publish what was found
+                int wmin = bd;
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) wmin = min(wmin, __shfl_xor(wmin, off));
+                if (lane == 0) atomicMin(thr_sh, wmin);
+            }
+        }
+        if (fin && cnt == 0) {
+            if (!scan) break;
+            scan = false;
+            if (first == end) break;
+            idx = first;
+            x = s0 + first % nr;
+            cb = s0 + 1 + first / nr * 64;
+            fresh = fresh_cols = true;
+        }
+    }
+    block_argmin_commit(bd, bid, S.best_key, red);
+}
+
+// Views of a route on the general path: staged (gen_arrays), and direct.
+template <bool TW, bool PD>
+struct GenLds {
+    const int *b;
+    int P;
+    __device__ int node(int p) const { return b[p]; }
+    __device__ int edge(int p) const { return b[P + p]; }
+    __device__ Ld load(int p) const { return Ld{b[2 * P + p], b[3 * P + p], max(b[2 * P + p], b[3 * P + p])}; }
+    __device__ Tw at(int p) const { return tw_node(b[4 * P + p], b[5 * P + p], b[6 * P + p]); }
+    __device__ Tw sum(int o, int p) const { return Tw{b[o * P + p], b[(o + 1) * P + p], b[(o + 2) * P + p], b[(o + 3) * P + p]}; }
+    __device__ Ld lsum(int o, int p) const { return Ld{b[o * P + p], b[(o + 1) * P + p], b[(o + 2) * P + p]}; }
+    __device__ Tw pre(int p) const { return sum(7, p); }          // prefix ending at p
+    __device__ Tw post(int p) const { return sum(11, p + 1); }    // suffix after p
+    __device__ Ld lpre(int p) const { return lsum(TW ? 15 : 7, p); }
+    __device__ Ld lpost(int p) const { return lsum(TW ? 18 : 10, p + 1); }
+    __device__ int dd(int p, int q) const { return b[gen_arrays<TW, PD>() * P + p * P + q]; }
+};
+
+struct GenGlobal {
+    const SolDev &S;
+    int off, L;
+    __device__ int node(int p) const { return p <= L ? nodeof(gld(S.a4 + off + p).x) : 0; }
+    __device__ int edge(int p) const { return gld(S.a4 + off + p).z; }
+    __device__ Ld load(int p) const { return ld_node_at(S, off + p); }
+    __device__ Tw at(int p) const { return tw_node_at(S, off + p); }
+    __device__ Tw pre(int p) const { return tw_of(gld(S.pf4 + off + p)); }
+    __device__ Tw post(int p) const { return p >= L ? tw_depot(S) : tw_of(gld(S.pb4 + off + p + 1)); }
+    __device__ Ld lpre(int p) const { return ld_of(gld(S.pl4 + off + p)); }
+    __device__ Ld lpost(int p) const { return p >= L ? Ld{0, 0, 0} : ld_of(gld(S.ql4 + off + p + 1)); }
+    __device__ int dd(int p, int q) const { return gld(S.D + (size_t)node(p) * S.np1 + node(q)); }
+};
+
+// Intra-route moves of route r (slots off .., L customers, view V) whose
+// first position is i: walk 0 the 2-opt walk, 1..3 or-opt of k = walk nodes
+// moved forward, 4..6 k = walk - 3 moved backward, 7 the same-route swap walk.
+// The middle summaries grow one node per step; a move is concatenated only
+// when its delta, less what the route could shed in penalties, can reach the
+// lane's best or the workgroup's (thr_sh; null: the lane's alone).
+template <bool TW, bool PD, class RV>
+__device__ __forceinline__ void gen_moves(const SolDev &S, const RV &V, int r, int off, int L, int i, uint32_t op_mask,
+                                          int walk, int32_t *dd, uint8_t *df, int *thr_sh, int &bd, uint32_t &bid) {
+    const int n = S.n, cap = S.cap;
+    const uint32_t uQ = (uint32_t)S.Q;
+    const bool opSwap = (op_mask & 2) && walk == 7, op2o = (op_mask & 8) && walk == 0, opOr = op_mask & 16;
+    auto ref = [&](int p) { return p == 0 ? (uint32_t)(n + r) : (uint32_t)(V.node(p) - 1); };
+    auto Npos = [&](int p) { return TW ? V.at(p) : Tw{}; };
+    auto Fpos = [&](int p) { return TW ? V.pre(p) : Tw{}; };
+    auto Bafter = [&](int p) { return TW ? V.post(p) : Tw{}; };
+    auto LNpos = [&](int p) { return PD ? V.load(p) : Ld{}; };
+    auto LFpos = [&](int p) { return PD ? V.lpre(p) : Ld{}; };
+    auto LBafter = [&](int p) { return PD ? V.lpost(p) : Ld{}; };
+    const int4 g = gld(S.g4 + off);
+    const int lvR = max(g.z - cap, 0), tvR = g.w;
+    const int slack = S.pen ? S.wL * lvR + S.wT * tvR : 0;
+    const bool hopeless = !S.pen && !PD && lvR > 0;  // an intra-route move keeps the load
+    int thr = bd;
+    auto can = [&](int dD) { return dd || (!hopeless && dD - slack <= thr); };
+    auto refresh = [&]() {
+        thr = bd;
+        if (thr_sh) thr = min(bd, __hip_atomic_load(thr_sh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    };
+    // new route: time warp tvNew, load excess lvNew
+    auto rec = [&](int dD, int tvNew, int lvNew, uint32_t id) {
+        const int was = bd;
+        gen_record(S, dD, lvNew - lvR, tvNew - tvR, lvNew == 0, tvNew == 0, id, dd, df, bd, bid);
+        if (thr_sh && bd < was) atomicMin(thr_sh, bd);
+    };
+    auto excess = [&](const Ld &x) { return PD ? max(x.lm - cap, 0) : lvR; };
+    const int eP = V.edge(i - 1), eI = V.edge(i);
+    const Tw Fi1 = Fpos(i - 1);
+    const Ld LFi1 = LFpos(i - 1);
+    if (walk == 0 || walk == 7) {  // ---- 2OPT(i, j) or SWAP(i, j), j > i
+        if (!op2o && !opSwap) return;
+        Tw rev = Npos(i), mid{};
+        Ld lrev = LNpos(i), lmid{};
+#pragma unroll 1
+        for (int j = i + 1; j <= L; ++j) {
+            const int ej = V.edge(j), ejm = V.edge(j - 1);
+            refresh();
+            if (TW && op2o) rev = tw_cat(Npos(j), ejm, rev);
+            if (PD && op2o) lrev = ld_cat(LNpos(j), lrev);
+            const int d1 = V.dd(i - 1, j), d2 = V.dd(i, j + 1);
+            const int dO = d1 + d2 - eP - ej;
+            int dA = 0, dB = 0, dS = dO;
+            if (j > i + 1) {
+                dA = V.dd(j, i + 1);
+                dB = V.dd(j - 1, i);
+                dS = d1 + dA + dB + d2 - eP - eI - ejm - ej;
+            }
+            const uint32_t lo = min(ref(i), ref(j)), hi = max(ref(i), ref(j));
+            if (op2o && can(dO)) {
+                const int tv = TW ? tw_cat(tw_cat(Fi1, d1, rev), d2, Bafter(j)).v : 0;
+                rec(dO, tv, excess(ld_cat(ld_cat(LFi1, lrev), LBafter(j))), (12u * uQ + lo) * uQ + hi);
+            }
+            if (opSwap && can(dS)) {
+                Tw f = TW ? tw_cat(Fi1, d1, Npos(j)) : Tw{};
+                Ld lf = PD ? ld_cat(LFi1, LNpos(j)) : Ld{};
+                if (j > i + 1) {
+                    if (TW) f = tw_cat(f, dA, mid);
+                    if (PD) lf = ld_cat(lf, lmid);
+                }
+                const int tv = TW ? tw_cat(tw_cat(f, j > i + 1 ? dB : ejm, Npos(i)), d2, Bafter(j)).v : 0;
+                rec(dS, tv, excess(ld_cat(ld_cat(lf, LNpos(i)), LBafter(j))), (5u * uQ + lo) * uQ + hi);
+            }
+            if (TW && opSwap) mid = (j == i + 1) ? Npos(j) : tw_cat(mid, ejm, Npos(j));  // c_{i+1} .. c_j
+            if (PD && opSwap) lmid = (j == i + 1) ? LNpos(j) : ld_cat(lmid, LNpos(j));
+        }
+        return;
+    }
+    // ---- OR-OPT: segment c_i .. c_{i+k-1} moved right after c_j
+    const int k = walk <= 3 ? walk : walk - 3;
+    if (!opOr || i + k - 1 > L) return;
+    const int gi = i + k - 1, wi = i + k;
+    const int dPW = V.dd(i - 1, wi), base = dPW - eP - V.edge(gi);
+    Tw sig{};
+    Ld lsig{};
+    if (TW) sig = Npos(i);
+    if (PD) lsig = LNpos(i);
+#pragma unroll 1
+    for (int u = 1; u < k; ++u) {
+        if (TW) sig = tw_cat(sig, V.edge(i + u - 1), Npos(i + u));
+        if (PD) lsig = ld_cat(lsig, LNpos(i + u));
+    }
+    Tw mid{};
+    Ld lmid{};
+    if (walk <= 3) {
+#pragma unroll 1
+        for (int j = wi; j <= L; ++j) {  // forward: middle c_{i+k} .. c_j
+            refresh();
+            if (TW) mid = (j == wi) ? Npos(j) : tw_cat(mid, V.edge(j - 1), Npos(j));
+            if (PD) lmid = (j == wi) ? LNpos(j) : ld_cat(lmid, LNpos(j));
+            const int dVF = V.dd(j, i), dGV = V.dd(gi, j + 1), dO = base + dVF + dGV - V.edge(j);
+            if (can(dO)) {
+                const int tv = TW ? tw_cat(tw_cat(tw_cat(Fi1, dPW, mid), dVF, sig), dGV, Bafter(j)).v : 0;
+                rec(dO, tv, excess(ld_cat(ld_cat(ld_cat(LFi1, lmid), lsig), LBafter(j))),
+                    ((16u + k) * uQ + ref(i)) * uQ + ref(j));
+            }
+        }
+        return;
+    }
+#pragma unroll 1
+    for (int j = i - 2; j >= 0; --j) {  // backward: middle c_{j+1} .. c_{i-1}
+        refresh();
+        if (TW) mid = (j == i - 2) ? Npos(i - 1) : tw_cat(Npos(j + 1), V.edge(j + 1), mid);
+        if (PD) lmid = (j == i - 2) ? LNpos(i - 1) : ld_cat(LNpos(j + 1), lmid);
+        const int dVF = V.dd(j, i), dGV = V.dd(gi, j + 1), dO = base + dVF + dGV - V.edge(j);
+        if (can(dO)) {
+            const int tv = TW ? tw_cat(tw_cat(tw_cat(Fpos(j), dVF, sig), dGV, mid), dPW, Bafter(gi)).v : 0;
+            rec(dO, tv, excess(ld_cat(ld_cat(ld_cat(LFpos(j), lsig), lmid), LBafter(gi))),
+                ((16u + k) * uQ + ref(i)) * uQ + ref(j));
+        }
+    }
+}
+
+constexpr int kGenRegionBytes = 16384;  // LDS of a staged group on the general path
+
+// One workgroup evaluates the intra-route moves of the routes [r0, r1) on the
+// general path, wavefront w walk w (as intra_block).
+template <bool TW, bool PD>
+__device__ __forceinline__ void gen_intra_block(const SolDev &S, int r0, int r1, uint32_t op_mask,
+                                                int32_t *__restrict__ dd, uint8_t *__restrict__ df, int *region, int *thr_sh) {
+    const int lane = threadIdx.x & 63;
+    const int walk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool multi = op_mask & kMulti;
+    int bd = initial_bound(op_mask);
+    if (threadIdx.x == 0) *thr_sh = bd;
+    if (dd || multi) thr_sh = nullptr;  // every move, or every route's best, is wanted
+    __syncthreads();
+    uint32_t bid = 0xFFFFFFFFu;
+    GroupStage g;
+    const int G = r1 - r0;
+    constexpr int NA = gen_arrays<TW, PD>();
+    group_layout<NA>(S, r0, G, g);
+    // the routes' moves; multi-move: also the route's best improving move
+    auto moves = [&](const auto &V, int r, int off, int L, int i, int step) {
+        int b1 = multi ? initial_bound(op_mask) : bd;
+        uint32_t i1 = multi ? 0xFFFFFFFFu : bid;
+#pragma unroll 1
+        for (; i <= L; i += step) gen_moves<TW, PD>(S, V, r, off, L, i, op_mask, walk, dd, df, thr_sh, b1, i1);
+        if (multi) {
+            if (b1 < 0 && i1 != 0xFFFFFFFFu) atomicMin(S.pairkey + (size_t)r * S.R + r, pack_key(b1, i1));
+            if (i1 != 0xFFFFFFFFu) consider(b1, i1, bd, bid);
+        } else {
+            bd = b1;
+            bid = i1;
+        }
+    };
+    if (g.sumL <= 64 && g.words <= kGenRegionBytes / 4) {
+        int myk = -1, myi = 0, myP = 0, myAt = 0, myOff = 0, cum = 0;
+#pragma unroll
+        for (int k = 0; k < kIntraMaxGroup; ++k) {
+            const int L = g.P[k] - 2;
+            if (k < G && myk < 0 && lane < cum + L) {
+                myk = k;
+                myi = lane - cum + 1;
+                myP = g.P[k];
+                myAt = g.at[k];
+                myOff = g.offs[k];
+            }
+            cum += k < G ? L : 0;
+        }
+        stage_group<TW, true, PD>(S, g, region);
+        const GenLds<TW, PD> V{region + myAt, myP};
+        if (myk >= 0) moves(V, r0 + myk, myOff, myP - 2, myi, 1 << 30);
+    } else {
+        for (int k = 0; k < G; ++k) {
+            const int r = r0 + k;
+            group_layout<NA>(S, r, 1, g);
+            const int off = g.offs[0], P = g.P[0], L = P - 2;
+            if (g.words <= kGenRegionBytes / 4) {
+                __syncthreads();  // the previous route is done with the region
+                stage_group<TW, true, PD>(S, g, region);
+                const GenLds<TW, PD> V{region, P};
+                moves(V, r, off, L, lane + 1, 64);
+            } else {
+                const GenGlobal V{S, off, L};
+                moves(V, r, off, L, lane + 1, 64);
+            }
+        }
+    }
+    wave_argmin_commit(bd, bid, S.best_key);
+}
+
+// First row slot of strip k of n (k = n gives Q): rows grow as (1 - k/n)^(-1/4),
+// between strips of equal work (whose last ones had so many rows that they
+// took several rounds of staging and ended last) and of equal rows.
+__device__ __forceinline__ int strip_begin(int Q, int k, int n) {
+    if (k >= n) return Q;
+    const float r = sqrtf(1.0f - (float)k / (float)n);
+    return Q - min(Q, (int)ceilf((float)Q * r * sqrtf(r)));
+}
+
+// One evaluation on the general path (as k_eval_solution): workgroups below
+// nintra take the intra-route groups of G routes, the others one strip of row
+// slots each, at most `rows` of them staged at a time.
+template <bool TW, bool PD, bool EXT, bool W16>
+__global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_general(
+    const SolDev S, int nintra, int G, int rows, uint32_t op_mask, int32_t *__restrict__ dd,
+    uint8_t *__restrict__ df) {
+    extern __shared__ int4 smem4[];
+    __shared__ unsigned long long red[kInterWaves];
+    __shared__ int thr_sh;
+    __shared__ GenQueue queues[kInterWaves];
+    if (skip_solution(S, op_mask)) return;  // uniform for the grid
+    if ((int)blockIdx.x < nintra) {
+        const int r0 = blockIdx.x * G;
+        gen_intra_block<TW, PD>(S, r0, min(S.R, r0 + G), op_mask, dd, df, (int *)smem4, &thr_sh);
+        return;
+    }
+    const int k = blockIdx.x - nintra, n = gridDim.x - nintra;
+    const int s0 = __builtin_amdgcn_readfirstlane(strip_begin(S.Q, k, n));
+    const int s1 = __builtin_amdgcn_readfirstlane(strip_begin(S.Q, k + 1, n));
+    for (int x = s0; x < s1; x += rows)
+        gen_strip<TW, PD, EXT, W16>(S, x, min(s1, x + rows), op_mask, dd, df, smem4, red, &thr_sh, queues);
 }
 
 // Batched form: persistent launches evaluate every solution of the batch.
@@ -3364,7 +3776,7 @@ __device__ __forceinline__ void apply_move_block(const SolDev &S, const MoveInfo
                 const int rk = d < 0 ? k : rounds - 1 - k;
                 const int src = lo + rk * T + tid;
                 const bool on = src < hi;
-                int4 a = make_int4(0, 0, 0, 0), b = a, t = a, w = a, pf = a, pb = a, pl = a, ql = a;
+                int4 a = make_int4(0, 0, 0, 0), b = a, t = a, w = a, pf = a, pb = a, pl = a, ql = a, g = a;
                 int pd = 0;
                 if (on) {
                     a = S.a4[src];
@@ -3377,6 +3789,7 @@ __device__ __forceinline__ void apply_move_block(const SolDev &S, const MoveInfo
                         pb = S.pb4[src];
                         pl = S.pl4[src];
                         ql = S.ql4[src];
+                        g = S.g4[src];
                     }
                 }
                 __syncthreads();
@@ -3392,6 +3805,7 @@ __device__ __forceinline__ void apply_move_block(const SolDev &S, const MoveInfo
                         S.pb4[dst] = pb;
                         S.pl4[dst] = pl;
                         S.ql4[dst] = ql;
+                        S.g4[dst] = g;
                     }
                     const int node = nodeof(a.x);
                     S.ref2slot[(flagsof(a.x) & kFlagCustomer) ? node - 1 : S.n + a.y] = dst;
@@ -3419,13 +3833,16 @@ __device__ __forceinline__ void apply_move_block(const SolDev &S, const MoveInfo
 }
 
 // Local-search accounting of one evaluation (one thread): |N(S)| of the
-// enabled operators (granular: the inter-route moves as counted; variants:
-// as counted) into acc[kAccMoves], and with kCountFull the slot pairs the
+// enabled operators (granular: the inter-route moves as counted) into
+// acc[kAccMoves], and with kCountFull the slot pairs the
 // screens visited.  `acc` holds the accumulators as they were before the
 // step's move.
 __device__ __forceinline__ void ls_count_moves(const SolDev &S, uint32_t op_mask, const long long *acc) {
     long long m = 0;
-    if (op_mask & 0xE0u) m += acc[kAccExtMoves];  // operator variants, as counted
+    if (op_mask & 32u) m += acc[kAccExtSeg];
+    if (op_mask & 64u) m += acc[kAccExtSeg];
+    if (op_mask & 128u)  // ordered pairs of customers of different routes: k(x) k(t) exchanges less the swap
+        m += (acc[kAccExtK] * acc[kAccExtK] - (long long)S.n * S.n - acc[kAccExtK2]) / 2;
     if (op_mask & kGranular) {  // inter-route moves as counted; intra-route ones complete
         m = acc[kAccGranInter];
         if (op_mask & 2) m += acc[kAccCnt0 + 3];  // same-route swaps: L(L-1)/2 per route, as 2-opt
@@ -3438,18 +3855,6 @@ __device__ __forceinline__ void ls_count_moves(const SolDev &S, uint32_t op_mask
     S.acc[kAccMoves] = acc[kAccMoves] + m;
     if ((op_mask & kCountFull) && (op_mask & 7))
         S.acc[kAccScreenPairs] = acc[kAccScreenPairs] + acc[kAccCnt0 + 2];  // = slot pairs of different routes
-}
-
-// Terms a route of L customers adds to |N(S)| of RELOCATE, twice that of
-// 2OPT* (subtracted), and to 2OPT and OR-OPT.
-struct RouteCounts {
-    long long rel, star2, two, oropt;
-};
-__device__ __forceinline__ RouteCounts route_counts(long long L, long long Q) {
-    RouteCounts c{L * (Q - L - 1), (L + 1) * (L + 1), L * (L - 1) / 2, 0};
-    for (int k = 1; k <= 3; ++k)
-        if (k <= L) c.oropt += (L - k + 1) * (L - k);
-    return c;
 }
 
 __device__ __forceinline__ void acc_add(const SolDev &S, int k, long long v) {
@@ -3468,7 +3873,7 @@ __device__ __forceinline__ void shift_slots(const SolDev &S, int lo, int hi, int
     const int per = T * U, rounds = max(1, (hi - lo + per - 1) / per);
     for (int k = 0; k < rounds; ++k) {
         const int first = lo + (d < 0 ? k : rounds - 1 - k) * per + tid;
-        int4 a[U], b[U], t[U], w[U], pf[U], pb[U], pl[U], ql[U];
+        int4 a[U], b[U], t[U], w[U], pf[U], pb[U], pl[U], ql[U], g[U];
         int pd[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -3484,6 +3889,7 @@ __device__ __forceinline__ void shift_slots(const SolDev &S, int lo, int hi, int
                     pb[u] = gld(S.pb4 + src);
                     pl[u] = gld(S.pl4 + src);
                     ql[u] = gld(S.ql4 + src);
+                    g[u] = gld(S.g4 + src);
                 }
             }
         }
@@ -3503,6 +3909,7 @@ __device__ __forceinline__ void shift_slots(const SolDev &S, int lo, int hi, int
                     gst(S.pb4 + dst, pb[u]);
                     gst(S.pl4 + dst, pl[u]);
                     gst(S.ql4 + dst, ql[u]);
+                    gst(S.g4 + dst, g[u]);
                 }
                 gst(S.ref2slot + ((flagsof(a[u].x) & kFlagCustomer) ? nodeof(a[u].x) - 1 : S.n + a[u].y), dst);
             }
@@ -3599,7 +4006,6 @@ __device__ __forceinline__ void finalize_block(const SolDev &S, int mode, uint32
             *S.best_key = ~0ull;
             if (mode == kModeLS) ls_count_moves(S, op_mask, acc);
             S.acc[kAccGranInter] = 0;
-            S.acc[kAccExtMoves] = 0;
             int rec[8] = {0, 0, 0, 0, 0, 0, 0, version};
             if (found) {
                 rec[0] = m.op;
@@ -3636,6 +4042,9 @@ __device__ __forceinline__ void finalize_block(const SolDev &S, int mode, uint32
             S.acc[kAccCnt0 + 2] = acc[kAccCnt0 + 2] - ((a1.star2 - a0.star2) + (b1.star2 - b0.star2)) / 2;
             S.acc[kAccCnt0 + 3] = acc[kAccCnt0 + 3] + (a1.two - a0.two) + (b1.two - b0.two);
             S.acc[kAccCnt0 + 4] = acc[kAccCnt0 + 4] + (a1.oropt - a0.oropt) + (b1.oropt - b0.oropt);
+            S.acc[kAccExtSeg] = acc[kAccExtSeg] + (a1.seg - a0.seg) + (b1.seg - b0.seg);
+            S.acc[kAccExtK] = acc[kAccExtK] + (a1.k - a0.k) + (b1.k - b0.k);
+            S.acc[kAccExtK2] = acc[kAccExtK2] + (a1.k2 - a0.k2) + (b1.k2 - b0.k2);
         }
     }
     if (max(max(m.La, m.Lb), max(m.nLa, m.nLb)) >= 64) {
@@ -3658,6 +4067,7 @@ __device__ __forceinline__ void finalize_block(const SolDev &S, int mode, uint32
     const bool works = (!isB || inter) && (role == 0 || (role == 1 && gen && S.has_tw) || (role == 2 && S.pd));
     const int L = isB ? m.nLb : m.nLa, base = isB ? baseB : baseA, r = isB ? m.rb : m.ra, off = isB ? offB : offA;
     SlotAttr x;  // role 0: the slot's attributes; roles 1 and 2: prefix summary in x.a, suffix summary in x.b
+    int2 rem = make_int2(0, 0);
     int old = 0, old_load = 0;
     auto route = [&]() {
         if (!works) return;
@@ -3675,6 +4085,7 @@ __device__ __forceinline__ void finalize_block(const SolDev &S, int mode, uint32
         const int node = lane == 0 || lane > L ? 0 : (fromB && inter ? qb : qa);
         if (role == 0) {
             x = route_attr(S, node, r, L);
+            if (gen) rem = segment_removal(S, node, x.a.z, L);
         } else if (role == 1) {
             Tw f, b;
             tw_route_wave(S, node, L, f, b);
@@ -3694,6 +4105,12 @@ __device__ __forceinline__ void finalize_block(const SolDev &S, int mode, uint32
     if (works) {
         if (role == 0) {
             store_attr(S, x, r, base, L);
+            if (gen && lane <= L) {  // the other wavefronts add what they know
+                int *g = (int *)(S.g4 + base + lane);
+                gst((int2 *)g, rem);
+                if (!S.pd) gst(g + 2, x.b.z);
+                if (!S.has_tw) gst(g + 3, 0);
+            }
             if (lane == L) acc_add(S, kAccCost, (long long)x.rdist - old);
             if (lane == 0 && gen && !S.pd)
                 acc_add(S, kAccLoadExcess, (long long)max(x.b.z - S.cap, 0) - max(old_load - S.cap, 0));
@@ -3701,12 +4118,14 @@ __device__ __forceinline__ void finalize_block(const SolDev &S, int mode, uint32
             if (lane <= L) {
                 gst(S.pf4 + base + lane, x.a);
                 gst(S.pb4 + base + lane, x.b);
+                gst((int *)(S.g4 + base + lane) + 3, __shfl(x.b.w, 0));
             }
             if (lane == 0) acc_add(S, kAccTimeWarp, (long long)x.b.w - old);
         } else {
             if (lane <= L) {
                 gst(S.pl4 + base + lane, x.a);
                 gst(S.ql4 + base + lane, x.b);
+                gst((int *)(S.g4 + base + lane) + 2, __shfl(x.b.z, 0));
             }
             if (lane == 0) acc_add(S, kAccLoadExcess, (long long)max(x.b.z - S.cap, 0) - max(old - S.cap, 0));
         }
@@ -3765,7 +4184,6 @@ __global__ __launch_bounds__(kApplyThreads) void k_multi_step(const SolDev *__re
         nsel_sh = 0;
         if (mode == kModeLS) ls_count_moves(S, op_mask, S.acc);
         S.acc[kAccGranInter] = 0;
-        S.acc[kAccExtMoves] = 0;
         *S.best_key = ~0ull;
     }
     for (int r = tid; r < R; r += T) used[r] = 0;

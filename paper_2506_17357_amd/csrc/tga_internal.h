@@ -37,7 +37,7 @@ struct SolDev {
     int4 *a4;    // {node | flags << 16, route, edge to successor, removal delta}
     int4 *b4;    // {demand, prefix load (incl.), route load, sum of the two incident edges}
     int4 *t4;    // {departure time, latest arrival at successor, departure of predecessor, latest arrival here}
-    int4 *w4;    // {e, l, s, 0}
+    int4 *w4;    // {e, l, s, pickup (0 without)}
     int32_t *pdist;   // distance from the start depot along the route
     // per ref (Q)
     int32_t *ref2slot;
@@ -63,6 +63,9 @@ struct SolDev {
     const int32_t *pick;
     int4 *pl4;
     int4 *ql4;
+    // general path: per slot {removal delta of the two- and of the three-node
+    // segment starting there, largest load and time warp of its route}
+    int4 *g4;
     // multi-move (caller workspace, null when off): per pair of route slots
     // r1 <= r2 the best improving key of the last evaluation (R x R, entry
     // r1 * R + r2), and the selection {count, (id, delta) per move}
@@ -92,11 +95,16 @@ enum {
     kAccGranInter = 7,  // inter-route moves of the granular neighbourhood counted by the last evaluation
     kAccLoadExcess = 8, // penalised mode: total load above capacity
     kAccTimeWarp = 9,   // penalised mode: total time warp
-    kAccExtMoves = 10,  // operator-variant moves counted by the last evaluation
+    // operator variants, from the route lengths: with k(x) <= 3 the customers
+    // from x on in its route, the moves of op 5 (op 6 has as many), the sum of
+    // k(x), and per route the square of that sum less its length's
+    kAccExtSeg = 10,
     kAccFullPairs = 11, // local search: slot pairs of different routes evaluated in full (past the screens)
     kAccScreenPairs = 12, // local search: slot pairs of different routes visited by those evaluations
     kAccMultiApplied = 13, // multi-move local search: moves applied
-    kAccCount = 14
+    kAccExtK = 14,
+    kAccExtK2 = 15,
+    kAccCount = 16
 };
 
 // Inter-route work item: rows [s0, s1) against column slots [c0, c0 + the

@@ -36,8 +36,9 @@ LENGTHS = [[38, 39, 40, 41], [16, 17, 15, 16, 0, 1], [70, 3, 0, 5], [1] * 9, [8,
 def compare(T, S, inst, sol, mask, pen=None):
     ob, odd, odf = oracle.eval_neighbourhood(inst, sol, mask, dump=True, threads=0, penalty=pen)
     gb, gdd, gdf = S.eval(mask, dump=True)
-    assert np.array_equal(gdf.cpu().numpy(), odf)
-    assert np.array_equal(gdd.cpu().numpy(), odd)
+    for got, want in ((gdf.cpu().numpy(), odf), (gdd.cpu().numpy(), odd)):
+        bad = np.nonzero(got != want)[0]
+        assert bad.size == 0, (bad.size, [(oracle.decode(S.Q, int(i)), int(want[i]), int(got[i])) for i in bad[:12]])
     for b in (gb, S.eval(mask)):  # with the dump every move is evaluated, without it the screens decide
         assert (b is not None) == bool(ob.found)
         assert b is None or (b.delta, b.id) == (ob.delta, ob.id)
@@ -53,3 +54,50 @@ def test_plain_forms(tga, case, problem, mask):
     for rows in (0, 1, 5):
         S.set_rows(rows)
         compare(tga, S, inst, sol, mask)
+
+
+def widen(inst):
+    """The instance with distances (and times) beyond 16 bits."""
+    inst.dist = np.ascontiguousarray(inst.dist * 100)
+    inst.node4 = inst.node4.copy()
+    if inst.has_tw:
+        inst.node4[:, 1:] *= 100
+    assert inst.dist.max() >= 1 << 16
+    return inst
+
+
+@pytest.mark.parametrize("mode", ["hard", "penalised", "heavy"])
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("problem", ["cvrp", "vrptw", "vrpspdtw"])
+@pytest.mark.parametrize("case", range(len(LENGTHS)))
+def test_general_forms(tga, case, problem, wide, mode):
+    print("general", problem, LENGTHS[case], "wide" if wide else "", mode, flush=True)
+    inst, sol = make(problem, LENGTHS[case], 400 + case)
+    if wide:
+        inst = widen(inst)
+    S = tga.Solution(tga.Instance.from_workload(inst), sol.offsets, sol.customers)
+    assert S.inst.dist_bytes == (4 if wide else 2)
+    # light penalties, where most moves are screened, and ones that outweigh every distance
+    pen = None if mode == "hard" else ((1, 1) if mode == "penalised" else (40, 3))
+    if pen is not None:
+        pen = (pen[0], 0 if problem == "cvrp" else (1 if wide else pen[1]))
+    if pen is None:
+        S.set_general(True)
+    else:
+        S.set_penalty(*pen)
+    for mask in (0xFF, 0x1F, 0x60 if case % 2 else 0x82, 0x05):
+        compare(tga, S, inst, sol, mask, pen)
+
+
+@pytest.mark.parametrize("problem", ["cvrp", "vrptw", "vrpspdtw"])
+def test_general_steps(tga, problem):
+    """Local-search steps on the general path (screens from 0 on), all operators, against the oracle's."""
+    inst, sol = make(problem, [13, 2, 9, 11, 0, 12, 10, 8, 14, 21], 500)
+    for pen in (None, (2, 0) if problem == "cvrp" else (2, 3)):
+        S = tga.Solution(tga.Instance.from_workload(inst), sol.offsets, sol.customers)
+        S.set_general(True) if pen is None else S.set_penalty(*pen)
+        fin, ids, deltas, moves = oracle.local_search(inst, sol, 0xFF, max_steps=25, penalty=pen)
+        steps, mv, _ = S.ls_run(25, 0xFF)
+        off, cust, _ = S.get()
+        assert (steps, mv) == (len(ids), moves)
+        assert np.array_equal(off, fin.offsets) and np.array_equal(cust, fin.customers)
