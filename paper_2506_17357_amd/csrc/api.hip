@@ -21,8 +21,20 @@ using namespace tga;
 namespace {
 
 thread_local std::string g_err;
-thread_local tga_move_t *g_pin = nullptr;  // pinned staging, 4 KiB per host thread
-thread_local int32_t *g_pin_dev = nullptr;  // the same memory as kernels address it (null: copy instead)
+
+// Pinned staging of one host thread: the record and state of single-solution
+// calls (first 4 KiB), then the routes a call sends or receives (offsets and
+// customers of the largest solution).  Every call that uses it synchronises
+// before it returns; the thread's end gives it back.
+constexpr size_t kPinRecord = 4096, kPinBytes = kPinRecord + 16 + 4 * (2 * (size_t)TGA_MAX_Q + 2);
+struct PinnedBuf {
+    char *host = nullptr;
+    char *dev = nullptr;  // the same memory as kernels address it (null: copy instead)
+    ~PinnedBuf() {
+        if (host) (void)hipHostFree(host);
+    }
+};
+thread_local PinnedBuf g_pin;
 
 int fail(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 int fail(int code, const char *fmt, ...) {
@@ -42,19 +54,19 @@ int fail(int code, const char *fmt, ...) {
     } while (0)
 
 int pinned(void **p) {
-    if (!g_pin) {
-        hipError_t e = hipHostMalloc((void **)&g_pin, 4096, hipHostMallocDefault);
+    if (!g_pin.host) {
+        hipError_t e = hipHostMalloc((void **)&g_pin.host, kPinBytes, hipHostMallocDefault);
         if (e != hipSuccess) {
-            g_pin = nullptr;
+            g_pin.host = nullptr;
             return fail(TGA_EDEVICE, "hipHostMalloc: %s", hipGetErrorString(e));
         }
         void *dp = nullptr;
-        if (hipHostGetDevicePointer(&dp, g_pin, 0) == hipSuccess)
-            g_pin_dev = (int32_t *)dp;
+        if (hipHostGetDevicePointer(&dp, g_pin.host, 0) == hipSuccess)
+            g_pin.dev = (char *)dp;
         else
             (void)hipGetLastError();
     }
-    *p = g_pin;
+    *p = g_pin.host;
     return TGA_OK;
 }
 
@@ -172,7 +184,7 @@ long long count_items(int Q, int rows) {
 }
 
 struct SolLayout {
-    size_t desc, a4, b4, t4, w4, pf4, pb4, pl4, ql4, g4, pdist, ref2slot, roff, rdist, nr_alt, roff_alt, rblk, best_key, rec,
+    size_t a4, b4, t4, w4, pf4, pb4, pl4, ql4, g4, pdist, ref2slot, roff, rdist, nr_alt, roff_alt, part, rblk, best_key, rec,
         state, acc, total;
 };
 
@@ -185,7 +197,6 @@ SolLayout sol_layout(int n, int R) {
         off = align_up(off + bytes, 256);
         return o;
     };
-    L.desc = take(sizeof(SolDev));
     L.a4 = take(16 * S);
     L.b4 = take(16 * S);
     L.t4 = take(16 * S);
@@ -201,6 +212,7 @@ SolLayout sol_layout(int n, int R) {
     L.rdist = take(4 * std::max(R, 1));
     L.nr_alt = take(8 * S);
     L.roff_alt = take(4 * (R + 1));
+    L.part = take(8 * (1 + 3 * ((R + kBuildRoutes - 1) / kBuildRoutes)));
     L.rblk = take(4 * (size_t)kRouteBlockWords * std::max(R, 1));
     L.best_key = take(8);
     // last record, state and accumulators back to back, so that every host
@@ -236,8 +248,7 @@ struct tga_instance {
 struct tga_solution {
     tga_instance *inst;
     int32_t n, R, Q;
-    SolDev h;          // host copy of the descriptor
-    SolDev *d;         // device copy (1 entry)
+    SolDev h;          // the descriptor, passed to the kernels by value
     int tile_rows;   // rows one workgroup's LDS budget holds (batched form)
     int plain_rows;  // rows per item of the single-solution form
     int item_rows;   // rows per inter-route item of the batched form (0: the default rule)
@@ -507,11 +518,57 @@ static int check_solution_args(tga_instance_t inst, int32_t R, const int32_t *of
     return check_partition(n, R, offsets, customers);
 }
 
+// Send the routes (checked by the caller) to the device and build every
+// attribute from them; synchronises `st`.  The kernels read them from this
+// thread's pinned buffer; without use_pinned, or where the device cannot
+// address it, they are copied into the workspace first.
+static int upload_routes(tga_solution *S, const int32_t *offsets, const int32_t *customers, bool use_pinned,
+                         hipStream_t st) {
+    const int n = S->n, R = S->R;
+    const long long Q = S->Q;
+    int maxL = 0;
+    BuildCounts c{};
+    c.cnt[1] = (long long)n * (n - 1) / 2;
+    for (int r = 0; r < R; ++r) {
+        const int L = offsets[r + 1] - offsets[r];
+        maxL = std::max(maxL, L);
+        const RouteCounts t = route_counts(L, Q);
+        c.cnt[0] += t.rel;
+        c.cnt[2] += t.star2;
+        c.cnt[3] += t.two;
+        c.cnt[4] += t.oropt;
+        c.seg += t.seg;
+        c.k += t.k;
+        c.k2 += t.k2;
+    }
+    c.cnt[2] = (Q * Q - c.cnt[2]) / 2;
+    const int32_t *off = S->h.roff_alt, *cust = (const int32_t *)S->h.nr_alt;
+    void *pin;
+    if (use_pinned && pinned(&pin) == TGA_OK && g_pin.dev) {
+        int32_t *p = (int32_t *)((char *)pin + kPinRecord);
+        memcpy(p, offsets, 4 * ((size_t)R + 1));
+        memcpy(p + R + 1, customers, 4 * (size_t)n);
+        off = (const int32_t *)(g_pin.dev + kPinRecord);
+        cust = off + R + 1;
+    } else {
+        HIPCHK(hipMemcpyAsync(S->h.roff_alt, offsets, 4 * ((size_t)R + 1), hipMemcpyHostToDevice, st));
+        HIPCHK(hipMemcpyAsync(S->h.nr_alt, customers, 4 * (size_t)n, hipMemcpyHostToDevice, st));
+    }
+    if (maxL < 64)
+        k_build_routes<<<(R + kBuildRoutes - 1) / kBuildRoutes, kBuildRoutes * 64, 0, st>>>(S->h, off, cust, 1, c);
+    else
+        k_build_long<<<1, kApplyThreads, 0, st>>>(S->h, off, cust);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipStreamSynchronize(st));
+    return TGA_OK;
+}
+
 // Lay a solution out in the workspace at `ws` (checked by the caller: large
 // enough, 256-byte aligned), upload its routes and build its attributes.
-// Fills *S; synchronises `st`.  Allocates no device or pinned memory.
+// Fills *S; synchronises `st`.  Allocates no device memory, and pinned memory
+// only with use_pinned.
 static int solution_init(tga_solution *S, tga_instance_t inst, int32_t R, const int32_t *offsets,
-                         const int32_t *customers, void *ws, hipStream_t st) {
+                         const int32_t *customers, void *ws, bool use_pinned, hipStream_t st) {
     const int n = inst->n;
     const SolLayout L = sol_layout(n, R);
     DevProps P;
@@ -568,38 +625,15 @@ static int solution_init(tga_solution *S, tga_instance_t inst, int32_t R, const 
     h.rec = (int32_t *)(base + L.rec);
     h.state = (int32_t *)(base + L.state);
     h.acc = (long long *)(base + L.acc);
-    S->d = (SolDev *)(base + L.desc);
-
-    // host-side layout: slots route-major with the start depot first
-    std::vector<int2> nr(Q + 1);
-    std::vector<int32_t> roff(R + 1);
-    int s = 0;
-    for (int r = 0; r < R; ++r) {
-        roff[r] = s;
-        nr[s++] = make_int2(0, r);
-        for (int i = offsets[r]; i < offsets[r + 1]; ++i) nr[s++] = make_int2(customers[i], r);
-    }
-    roff[R] = s;
-    nr[Q] = make_int2(0, R);
-    std::vector<int32_t> state(16, 0);
-    std::vector<long long> acc(kAccCount, 0);
-    auto up = [&](void *dst, const void *src, size_t bytes) {
-        return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st);
-    };
+    h.part = (long long *)(base + L.part);
     hipError_t e = hipSuccess;
-    if (e == hipSuccess) e = up(S->d, &h, sizeof h);
-    if (e == hipSuccess) e = up(h.nr_alt, nr.data(), sizeof(int2) * (Q + 1));
-    if (e == hipSuccess) e = up(h.roff_alt, roff.data(), sizeof(int32_t) * (R + 1));
-    if (e == hipSuccess) e = up(h.state, state.data(), sizeof(int32_t) * 16);
-    if (e == hipSuccess) e = up(h.acc, acc.data(), sizeof(long long) * kAccCount);
-    if (e == hipSuccess) {
-        k_route_blocks_clear<<<(R + 255) / 256, 256, 0, st>>>(h.rblk, R);
-        k_build<<<1, kApplyThreads, 0, st>>>(S->d);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    // the fields the kernels only ever add to or test start at zero: record,
+    // state and accumulators, and the build's counter
+    k_zero_i32<<<1, 128, 0, st>>>(h.rec, (32 + 4 * 16 + 8 * kAccCount) / 4);
+    k_zero_i32<<<1, 64, 0, st>>>((int32_t *)h.part, 2);
+    e = hipGetLastError();
     if (e != hipSuccess) return fail(TGA_EDEVICE, "set_solution: %s", hipGetErrorString(e));
-    return TGA_OK;
+    return upload_routes(S, offsets, customers, use_pinned, st);
 }
 
 extern "C" int tga_set_tuning(const tga_tune_entry_t *entries, int32_t count) {
@@ -631,9 +665,7 @@ extern "C" int tga_solution_set_rows(tga_solution_t sol, int32_t plain_rows_, in
     sol->item_rows = item_rows > 0 ? item_rows : t_item;
     sol->lds = rows_lds(sol->n + 1, sol->plain_rows, w16);
     sol->h.tile_rows = sol->plain_rows;
-    hipStream_t st = (hipStream_t)stream;
-    HIPCHK(hipMemcpyAsync(sol->d, &sol->h, sizeof(SolDev), hipMemcpyHostToDevice, st));
-    HIPCHK(hipStreamSynchronize(st));
+    HIPCHK(hipStreamSynchronize((hipStream_t)stream));
     return TGA_OK;
 }
 
@@ -656,7 +688,7 @@ extern "C" int tga_set_solution(tga_instance_t inst, int32_t R, const int32_t *o
     if (ws_bytes < L.total) return fail(TGA_ENOMEM, "solution workspace %zu < %zu", ws_bytes, L.total);
     if (((uintptr_t)ws) & 255) return fail(TGA_EINVAL, "workspace must be 256-byte aligned");
     tga_solution *S = new tga_solution();
-    if ((rc = solution_init(S, inst, R, offsets, customers, ws, (hipStream_t)stream))) {
+    if ((rc = solution_init(S, inst, R, offsets, customers, ws, true, (hipStream_t)stream))) {
         delete S;
         return rc;
     }
@@ -680,27 +712,9 @@ static int check_partition(int n, int R, const int32_t *offsets, const int32_t *
 extern "C" int tga_solution_reload(tga_solution_t sol, const int32_t *offsets, const int32_t *customers,
                                    void *stream) {
     if (!sol || !offsets || !customers) return fail(TGA_EINVAL, "null argument");
-    const int n = sol->n, R = sol->R, Q = sol->Q;
-    int rc = check_partition(n, R, offsets, customers);
+    int rc = check_partition(sol->n, sol->R, offsets, customers);
     if (rc) return rc;
-    std::vector<int2> nr(Q + 1);
-    std::vector<int32_t> roff(R + 1);
-    int s = 0;
-    for (int r = 0; r < R; ++r) {
-        roff[r] = s;
-        nr[s++] = make_int2(0, r);
-        for (int i = offsets[r]; i < offsets[r + 1]; ++i) nr[s++] = make_int2(customers[i], r);
-    }
-    roff[R] = s;
-    nr[Q] = make_int2(0, R);
-    hipStream_t st = (hipStream_t)stream;
-    HIPCHK(hipMemcpyAsync(sol->h.nr_alt, nr.data(), sizeof(int2) * (Q + 1), hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(sol->h.roff_alt, roff.data(), sizeof(int32_t) * (R + 1), hipMemcpyHostToDevice, st));
-    k_reset_state<<<1, 64, 0, st>>>(sol->d, 1, 0);
-    k_route_blocks_clear<<<(R + 255) / 256, 256, 0, st>>>(sol->h.rblk, R);  // start cold, as a new solution
-    k_build<<<1, kApplyThreads, 0, st>>>(sol->d);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(st));
+    if ((rc = upload_routes(sol, offsets, customers, true, (hipStream_t)stream))) return rc;
     sol->version = 0;
     return TGA_OK;
 }
@@ -708,7 +722,7 @@ extern "C" int tga_solution_reload(tga_solution_t sol, const int32_t *offsets, c
 extern "C" int tga_solution_begin(tga_solution_t sol, int32_t max_steps, void *stream) {
     if (!sol) return fail(TGA_EINVAL, "null solution");
     if (max_steps < 0) return fail(TGA_EINVAL, "max_steps < 0");
-    k_reset_state<<<1, 64, 0, (hipStream_t)stream>>>(sol->d, 1, max_steps);
+    k_reset_one<<<1, 1, 0, (hipStream_t)stream>>>(sol->h, max_steps);
     HIPCHK(hipGetLastError());
     return TGA_OK;
 }
@@ -863,8 +877,7 @@ extern "C" int tga_solution_set_penalty(tga_solution_t sol, int32_t w_load, int3
     sol->h.wL = pen ? w_load : 0;
     sol->h.wT = pen ? w_tw : 0;
     hipStream_t st = (hipStream_t)stream;
-    HIPCHK(hipMemcpyAsync(sol->d, &sol->h, sizeof(SolDev), hipMemcpyHostToDevice, st));
-    k_pen_init<<<1, kApplyThreads, 0, st>>>(sol->d);
+    k_pen_init<<<1, kApplyThreads, 0, st>>>(sol->h);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
     return TGA_OK;
@@ -876,8 +889,7 @@ extern "C" int tga_solution_set_general(tga_solution_t sol, int32_t on, void *st
     if (on != 0 && on != 1) return fail(TGA_EINVAL, "on must be 0 or 1");
     sol->h.gen = on;
     hipStream_t st = (hipStream_t)stream;
-    HIPCHK(hipMemcpyAsync(sol->d, &sol->h, sizeof(SolDev), hipMemcpyHostToDevice, st));
-    k_pen_init<<<1, kApplyThreads, 0, st>>>(sol->d);
+    k_pen_init<<<1, kApplyThreads, 0, st>>>(sol->h);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
     return TGA_OK;
@@ -903,7 +915,7 @@ extern "C" int tga_solution_violations(tga_solution_t sol, int64_t *load_excess,
 // memory, or no device address) the record is copied after it.
 static int eval_record(tga_solution *sol, uint32_t op_mask, tga_move_t *best, int32_t *dump_delta,
                        uint8_t *dump_feas, hipStream_t st, int32_t *host, bool host_pinned) {
-    int32_t *dev_view = host_pinned ? g_pin_dev : nullptr;  // where the kernel may write `host`
+    int32_t *dev_view = host_pinned ? (int32_t *)g_pin.dev : nullptr;  // where the kernel may write `host`
     launch_solution_eval(sol, op_mask, dump_delta, dump_feas, st);
     k_finalize_one<<<1, kApplyThreads, 0, st>>>(sol->h, kModeRecord, op_mask, dev_view);
     HIPCHK(hipGetLastError());
@@ -964,8 +976,7 @@ extern "C" int tga_solution_set_multi(tga_solution_t sol, void *ws, size_t ws_by
         k_fill_u64<<<(int)std::min<size_t>((RR + 255) / 256, 1024), 256, 0, st>>>(sol->h.pairkey, RR);
         HIPCHK(hipGetLastError());
     }
-    HIPCHK(hipMemcpyAsync(sol->d, &sol->h, sizeof(SolDev), hipMemcpyHostToDevice, st));
-    k_pen_init<<<1, kApplyThreads, 0, st>>>(sol->d);
+    k_pen_init<<<1, kApplyThreads, 0, st>>>(sol->h);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
     return TGA_OK;
@@ -976,7 +987,7 @@ extern "C" int tga_solution_select_moves(tga_solution_t sol, tga_move_t *moves, 
     if (!sol || !count || (cap > 0 && !moves) || cap < 0) return fail(TGA_EINVAL, "bad argument");
     if (!sol->h.pairkey) return fail(TGA_EINVAL, "tga_solution_set_multi first");
     hipStream_t st = (hipStream_t)stream;
-    k_multi_step<<<1, kApplyThreads, 0, st>>>(sol->d, kModeRecord, TGA_OP_ALL);
+    k_multi_step<<<1, kApplyThreads, 0, st>>>(sol->h, kModeRecord, TGA_OP_ALL);
     HIPCHK(hipGetLastError());
     std::vector<int32_t> sel(1 + 2 * (size_t)sol->R);
     HIPCHK(hipMemcpyAsync(sel.data(), sol->h.msel, sel.size() * 4, hipMemcpyDeviceToHost, st));
@@ -1059,7 +1070,7 @@ extern "C" int tga_eval_routes_static(tga_instance_t inst, int32_t R, const int3
     if ((rc = scratch_ptr(&ws))) return rc;
     hipStream_t st = (hipStream_t)stream;
     tga_solution S{};  // lives for this call only; its arrays are in the scratch
-    if ((rc = solution_init(&S, inst, R, offsets, customers, ws, st))) return rc;
+    if ((rc = solution_init(&S, inst, R, offsets, customers, ws, false, st))) return rc;
     int32_t host[12];  // record and state[0..3]: pageable, so nothing is allocated
     return eval_record(&S, op_mask, best, nullptr, nullptr, st, host, false);
 }
@@ -1106,7 +1117,7 @@ extern "C" int tga_ls_run(tga_solution_t sol, uint32_t op_mask, int32_t max_step
     void *pin;
     if ((rc = pinned(&pin))) return rc;
     int32_t *p = (int32_t *)pin;
-    k_reset_state<<<1, 64, 0, st>>>(sol->d, 1, max_steps);
+    k_reset_one<<<1, 1, 0, st>>>(sol->h, max_steps);
     HIPCHK(hipGetLastError());
     const bool multi = (op_mask & TGA_OP_MULTI) != 0;
     if (multi) {  // the per-route-pair table starts empty
@@ -1123,9 +1134,11 @@ extern "C" int tga_ls_run(tga_solution_t sol, uint32_t op_mask, int32_t max_step
         const int todo = std::min(chunk, max_steps - launched);
         for (int i = 0; i < todo; ++i) {
             launch_solution_eval(sol, op_mask | kImprovingOnly, nullptr, nullptr, st);
-            if (multi)
-                k_multi_step<<<1, kApplyThreads, 0, st>>>(sol->d, kModeLS, op_mask);
-            else
+            if (multi) {
+                k_multi_step<<<1, kApplyThreads, 0, st>>>(sol->h, kModeLS, op_mask);
+                k_build_routes<<<(sol->R + kBuildRoutes - 1) / kBuildRoutes, kBuildRoutes * 64, 0, st>>>(
+                    sol->h, sol->h.roff_alt, (const int32_t *)sol->h.nr_alt, 0, BuildCounts{});
+            } else
                 k_finalize_one<<<1, kApplyThreads, 0, st>>>(sol->h, kModeLS, op_mask, nullptr);
         }
         HIPCHK(hipGetLastError());
@@ -1148,21 +1161,22 @@ extern "C" int tga_get_solution(tga_solution_t sol, int32_t *offsets, int32_t *c
                                 void *stream) {
     if (!sol || !offsets || !customers) return fail(TGA_EINVAL, "null argument");
     hipStream_t st = (hipStream_t)stream;
-    const int Q = sol->Q, R = sol->R;
-    std::vector<int4> a4(Q);
-    std::vector<int32_t> roff(R + 1);
-    long long c = 0;
-    HIPCHK(hipMemcpyAsync(a4.data(), sol->h.a4, sizeof(int4) * Q, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(roff.data(), sol->h.roff, sizeof(int32_t) * (R + 1), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(&c, sol->h.acc + kAccCost, 8, hipMemcpyDeviceToHost, st));
+    const int n = sol->n, R = sol->R;
+    // written by one kernel into this thread's pinned buffer (or, where the
+    // device cannot address it, into the staging arrays and copied)
+    const size_t ints = 2 + (size_t)(R + 1) + n;
+    void *pin;
+    int rc = pinned(&pin);
+    if (rc) return rc;
+    int32_t *p = (int32_t *)((char *)pin + kPinRecord);
+    int32_t *out = g_pin.dev ? (int32_t *)(g_pin.dev + kPinRecord) : (int32_t *)sol->h.nr_alt;
+    k_export<<<(sol->Q + 255) / 256, 256, 0, st>>>(sol->h, out);
+    HIPCHK(hipGetLastError());
+    if (!g_pin.dev) HIPCHK(hipMemcpyAsync(p, out, 4 * ints, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    int w = 0;
-    for (int r = 0; r < R; ++r) {
-        offsets[r] = w;
-        for (int s = roff[r] + 1; s < roff[r + 1]; ++s) customers[w++] = a4[s].x & 0xFFFF;
-    }
-    offsets[R] = w;
-    if (cost) *cost = c;
+    if (cost) *cost = *(const long long *)p;
+    memcpy(offsets, p + 2, 4 * ((size_t)R + 1));
+    memcpy(customers, p + 2 + R + 1, 4 * (size_t)n);
     return TGA_OK;
 }
 

@@ -372,7 +372,7 @@ __device__ __forceinline__ BwdElem bwd_elem(const SolDev &S, const int32_t *roff
 struct RouteCounts {
     long long rel, star2, two, oropt, seg, k, k2;
 };
-__device__ __forceinline__ RouteCounts route_counts(long long L, long long Q) {
+__host__ __device__ __forceinline__ RouteCounts route_counts(long long L, long long Q) {
     RouteCounts c{L * (Q - L - 1), (L + 1) * (L + 1), L * (L - 1) / 2, 0, 0, 0, 0};
     for (int k = 1; k <= 3; ++k)
         if (k <= L) c.oropt += (L - k + 1) * (L - k);
@@ -890,6 +890,36 @@ __device__ __forceinline__ void pen_totals(const SolDev &S, ApplyShared &sh) {
     __syncthreads();
 }
 
+// The general path's summaries of route r (slots off .., L < 64 customers) by
+// one wavefront: lane p's node and the edge leaving it, the route's load.
+// peak and warp receive the route's largest load and time warp.
+__device__ __forceinline__ void gen_route_wave(const SolDev &S, int off, int L, int node, int edge, int load, int &peak,
+                                               int &warp) {
+    const int lane = threadIdx.x & 63;
+    const int2 rem = segment_removal(S, node, edge, L);
+    peak = load;
+    warp = 0;
+    if (S.has_tw) {
+        Tw f, b;
+        tw_route_wave(S, node, L, f, b);
+        if (lane <= L) {
+            gst(S.pf4 + off + lane, tw_pack(f));
+            gst(S.pb4 + off + lane, tw_pack(b));
+        }
+        warp = __shfl(b.v, 0);
+    }
+    if (S.pd) {
+        Ld f, b;
+        ld_route_wave(S, node, L, f, b);
+        if (lane <= L) {
+            gst(S.pl4 + off + lane, ld_pack(f));
+            gst(S.ql4 + off + lane, ld_pack(b));
+        }
+        peak = __shfl(b.lm, 0);
+    }
+    if (lane <= L) gst(S.g4 + off + lane, make_int4(rem.x, rem.y, peak, warp));
+}
+
 // Summaries of every route and the totals (one block): a wavefront per
 // route, one thread for a route too long for it.
 __device__ __forceinline__ void pen_all(const SolDev &S, ApplyShared &sh) {
@@ -901,53 +931,190 @@ __device__ __forceinline__ void pen_all(const SolDev &S, ApplyShared &sh) {
             continue;
         }
         const int4 a = lane <= L ? gld(S.a4 + off + lane) : make_int4(0, 0, 0, 0);
-        const int node = nodeof(a.x);
-        const int2 rem = segment_removal(S, node, a.z, L);
-        int4 g = make_int4(rem.x, rem.y, gld(S.b4 + off).z, 0);
-        if (S.has_tw) {
-            Tw f, b;
-            tw_route_wave(S, node, L, f, b);
-            if (lane <= L) {
-                gst(S.pf4 + off + lane, tw_pack(f));
-                gst(S.pb4 + off + lane, tw_pack(b));
-            }
-            g.w = __shfl(b.v, 0);
-        }
-        if (S.pd) {
-            Ld f, b;
-            ld_route_wave(S, node, L, f, b);
-            if (lane <= L) {
-                gst(S.pl4 + off + lane, ld_pack(f));
-                gst(S.ql4 + off + lane, ld_pack(b));
-            }
-            g.z = __shfl(b.lm, 0);
-        }
-        if (lane <= L) gst(S.g4 + off + lane, g);
+        int peak, warp;
+        gen_route_wave(S, off, L, nodeof(a.x), a.z, gld(S.b4 + off).z, peak, warp);
     }
     __threadfence_block();
     __syncthreads();
     pen_totals(S, sh);
 }
 
-// Build the attributes of a freshly uploaded layout (nr_alt, roff_alt).
-__global__ __launch_bounds__(kApplyThreads) void k_build(const SolDev *__restrict__ sols) {
-    __shared__ ApplyShared sh;
-    const SolDev &S = sols[blockIdx.x];
-    rebuild(S, S.nr_alt, S.roff_alt, sh);
-    if (S.pen || S.pd || S.gen) pen_all(S, sh);
+// Local-search state and counters of a solution, for a new run.
+__device__ __forceinline__ void reset_run(const SolDev &S, int max_steps) {
+    S.state[kStDone] = 0;
+    S.state[kStSteps] = 0;
+    S.state[kStStatus] = 0;
+    S.state[kStMaxSteps] = max_steps;
+    S.acc[kAccMoves] = 0;
+    S.acc[kAccFullPairs] = 0;
+    S.acc[kAccScreenPairs] = 0;
+    S.acc[kAccMultiApplied] = 0;
+    *S.best_key = ~0ull;
+}
+
+// Attributes of a new layout: route r holds cust[off[r] .. off[r + 1]), every
+// route fewer than 64 customers.  One wavefront per route, every attribute in
+// registers (route_attr) and, on the general path, the summaries; the totals
+// are summed over the workgroup, and the last workgroup to finish adds up the
+// others' (part[0] counts them).  off and cust may lie in pinned host memory:
+// each route is read once, straight from there, so that a new solution takes
+// this one launch: 9 us (11 with n up to 10^4) and one synchronisation, a
+// reload 26 us of host time, in place of two copies, three launches and one
+// workgroup that scanned all slots (20 us, 58 us), a reload 50 us.
+// fresh: a solution set or reloaded by the host, which gives |N(S)|; its state
+// and the route distance-block cache start empty.  Otherwise a multi-move
+// step's layout (its launch keeps the counts), if there is one.
+struct BuildCounts {
+    long long cnt[5], seg, k, k2;
+};
+
+__global__ __launch_bounds__(kBuildRoutes * 64) void k_build_routes(const SolDev S, const int32_t *__restrict__ off,
+                                                                    const int32_t *__restrict__ cust, int fresh,
+                                                                    const BuildCounts c) {
+    __shared__ long long sum_sh[kBuildRoutes][3];
+    __shared__ int last_sh;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = blockIdx.x * kBuildRoutes + wave, R = S.R, Q = S.Q;
+    const bool gen = S.pen || S.pd || S.gen;
+    if (!fresh && !S.state[kStBuild]) return;  // uniform for the grid
+    long long cost = 0, excess = 0, warps = 0;
+    if (r < R) {
+        const int c0 = __builtin_amdgcn_readfirstlane(off[r]), L = __builtin_amdgcn_readfirstlane(off[r + 1]) - c0;
+        const int base = c0 + r;  // one start depot per route before it, and its own
+        const int node = lane >= 1 && lane <= L ? cust[c0 + lane - 1] : 0;
+        const SlotAttr x = route_attr(S, node, r, L);
+        store_attr(S, x, r, base, L);
+        cost = __shfl(x.rdist, L);
+        if (gen) {
+            int peak, warp;
+            gen_route_wave(S, base, L, node, x.a.z, x.b.z, peak, warp);
+            excess = max(peak - S.cap, 0);
+            warps = warp;
+        }
+        if (lane == 0) {
+            gst(S.roff + r, base);
+            if (fresh) gst(S.rblk + (size_t)r * kRouteBlockWords, -1);
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const bool tw = S.has_tw;
+        const int4 q = gld(S.node4);
+        gst(S.roff + R, Q);
+        gst(S.a4 + Q, make_int4(0, R, 0, 0));
+        gst(S.b4 + Q, make_int4(0, 0, 0, 0));
+        gst(S.w4 + Q, make_int4(tw ? q.y : 0, tw ? q.z : kTwOff, 0, 0));
+        gst(S.t4 + Q, make_int4(kInf, kNeg, kInf, kNeg));
+        gst(S.pdist + Q, 0);
+        if (fresh) {
+            reset_run(S, 0);
+            for (int i = 0; i < 5; ++i) S.acc[kAccCnt0 + i] = c.cnt[i];
+            S.acc[kAccExtSeg] = c.seg;
+            S.acc[kAccExtK] = c.k;
+            S.acc[kAccExtK2] = c.k2;
+            S.acc[kAccGranInter] = 0;
+        }
+    }
+    if (lane == 0) {
+        sum_sh[wave][0] = cost;
+        sum_sh[wave][1] = excess;
+        sum_sh[wave][2] = warps;
+    }
+    __syncthreads();
+    const int nb = gridDim.x;
     if (threadIdx.x == 0) {
-        *S.best_key = ~0ull;
-        S.state[kStDone] = 0;
-        S.state[kStStatus] = 0;
+        long long t[3] = {0, 0, 0};
+        for (int w = 0; w < kBuildRoutes; ++w)
+            for (int i = 0; i < 3; ++i) t[i] += sum_sh[w][i];
+        for (int i = 0; i < 3; ++i) {
+            sum_sh[0][i] = t[i];
+            if (nb > 1)
+                __hip_atomic_store(S.part + 1 + 3 * blockIdx.x + i, t[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        int last = 1;
+        if (nb > 1) {
+            __threadfence();
+            last = atomicAdd((unsigned long long *)S.part, 1ull) == (unsigned long long)(nb - 1);
+            __threadfence();
+        }
+        last_sh = last;
+    }
+    __syncthreads();
+    if (!last_sh || threadIdx.x >= 3) return;
+    long long t = nb > 1 ? 0 : sum_sh[0][threadIdx.x];
+    if (nb > 1)
+        for (int b = 0; b < nb; ++b)
+            t += __hip_atomic_load(S.part + 1 + 3 * b + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) {
+        S.part[0] = 0;
+        S.acc[kAccCost] = t;
+        S.state[kStBuild] = 0;
+    } else if (gen) {
+        S.acc[threadIdx.x == 1 ? kAccLoadExcess : kAccTimeWarp] = t;
     }
 }
 
-// Switch penalised mode on for a solution whose descriptor now says so:
-// summaries of every route and the totals.
-__global__ __launch_bounds__(kApplyThreads) void k_pen_init(const SolDev *__restrict__ sols) {
+// The same for a layout with a route of 64 customers or more, by the block
+// scans of one workgroup (always fresh).
+__global__ __launch_bounds__(kApplyThreads) void k_build_long(const SolDev S, const int32_t *__restrict__ off,
+                                                              const int32_t *__restrict__ cust) {
     __shared__ ApplyShared sh;
-    const SolDev &S = sols[blockIdx.x];
+    const int R = S.R, T = blockDim.x, tid = threadIdx.x;
+    // slot s of route r takes customer s - r - 1; from the last slots down, as
+    // cust may be the front of nr_alt itself, each round read before it is written
+    for (int q1 = S.Q; q1 > 0; q1 -= T) {
+        const int s = q1 - 1 - tid;
+        int2 v = make_int2(0, 0);
+        if (s >= 0) {
+            int lo = 0, hi = R - 1;  // the route whose slots [off[r] + r, off[r + 1] + r + 1) hold s
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (off[mid] + mid <= s) lo = mid;
+                else hi = mid - 1;
+            }
+            v = make_int2(s == off[lo] + lo ? 0 : cust[s - lo - 1], lo);
+        }
+        __syncthreads();
+        if (s >= 0) S.nr_alt[s] = v;
+        __threadfence_block();
+        __syncthreads();
+    }
+    // the slot offsets (off may be roff_alt itself)
+    for (int r = tid; r <= R; r += T) {
+        const int o = off[r] + r;
+        S.roff_alt[r] = r < R ? o : S.Q;
+        if (r < R) S.rblk[(size_t)r * kRouteBlockWords] = -1;
+    }
+    if (tid == 0) S.nr_alt[S.Q] = make_int2(0, R);
+    __threadfence_block();
+    __syncthreads();
+    rebuild(S, S.nr_alt, S.roff_alt, sh);
     if (S.pen || S.pd || S.gen) pen_all(S, sh);
+    if (tid == 0) {
+        reset_run(S, 0);
+        S.acc[kAccGranInter] = 0;
+    }
+}
+
+// Switch the general path on for a solution whose descriptor now says so:
+// summaries of every route and the totals.
+__global__ __launch_bounds__(kApplyThreads) void k_pen_init(const SolDev S) {
+    __shared__ ApplyShared sh;
+    if (S.pen || S.pd || S.gen) pen_all(S, sh);
+}
+
+// The current routes as the caller's arrays: offsets (R + 1), customers (n),
+// and the cost in front of them; out may lie in pinned host memory.
+__global__ __launch_bounds__(256) void k_export(const SolDev S, int32_t *__restrict__ out) {
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    int32_t *offsets = out + 2, *customers = offsets + S.R + 1;
+    if (s == 0) {
+        *(long long *)out = S.acc[kAccCost];
+        offsets[S.R] = S.n;
+    }
+    if (s >= S.Q) return;
+    const int4 a = gld(S.a4 + s);
+    if (flagsof(a.x) & kFlagCustomer) customers[s - a.y - 1] = nodeof(a.x);
+    else offsets[a.y] = s - a.y;
 }
 
 // ------------------------------------------------------ inter-route eval ---
@@ -4156,139 +4323,134 @@ __global__ __launch_bounds__(kApplyThreads) void k_finalize_one(const SolDev S, 
 // (S.pairkey); taken in (delta, id) order, a candidate is selected when
 // neither of its routes is used by an earlier selection.  Moves on disjoint
 // routes keep their deltas and feasibility when applied one after another.
-// Up to kMultiCands improving candidates are compacted into LDS and sorted
-// (bitonic); with more, rounds of locally dominant candidates give the same
-// set.  Requires R <= kMultiMaxR.
-constexpr int kMultiCands = 4096;
+// The greedy set is found in rounds of locally dominant candidates: a
+// candidate whose key is the smallest among the candidates at each of its
+// (free) routes is taken by the sequential greedy too (no smaller key can
+// take one of its routes first), and the candidates dominant in one round
+// share no route; repeating on the routes still free gives the greedy set in
+// a few rounds (sorting the candidates and going down them in one thread took
+// most of a launch of 170 us at n = 1000, against 37 us, and 11 us for the
+// layout's build).  Up to kMultiCands candidates are kept in LDS for
+// the rounds, more are read from the table each time.  Requires
+// R <= kMultiMaxR.
+constexpr int kMultiCands = 2048;
 constexpr int kMultiMaxR = 4096;
 
 __device__ __forceinline__ bool key_improving(unsigned long long k) { return k < 0x8000000000000000ull; }
 
-// kModeRecord: selection only, written to S.msel.  kModeLS: also apply the
-// selected moves in order, count the step, and mark the solution converged
+struct MultiShared {
+    unsigned long long best[kMultiMaxR];   // per route: least key of its candidates
+    unsigned long long key[kMultiCands];   // candidates
+    int pair[kMultiCands];                 // their routes, r1 << 16 | r2
+};
+// the selected moves decoded, and per route the selected move touching it
+constexpr int kMultiMoves = (int)((sizeof(MultiShared) - 4 * kMultiMaxR) / sizeof(MoveInfo));
+struct MultiApply {
+    int mov_of[kMultiMaxR];
+    MoveInfo mv[kMultiMoves];
+};
+static_assert(sizeof(MultiApply) <= sizeof(MultiShared), "multi-move LDS");
+
+// kModeRecord: selection only, written to S.msel in (delta, id) order.
+// kModeLS: also put the new layout of the routes into roff_alt and nr_alt for
+// k_build_routes (kStBuild), count the step, and mark the solution converged
 // when nothing is selected or the step cap is reached.  Clears S.pairkey.
-__global__ __launch_bounds__(kApplyThreads) void k_multi_step(const SolDev *__restrict__ sols, int mode,
-                                                              uint32_t op_mask) {
+__global__ __launch_bounds__(kApplyThreads) void k_multi_step(const SolDev S, int mode, uint32_t op_mask) {
     __shared__ ApplyShared sh;
     __shared__ MoveInfo mi;
-    __shared__ unsigned long long keys[kMultiCands];
-    __shared__ int pidx[kMultiCands];
+    __shared__ MultiShared ms;
     __shared__ unsigned char used[kMultiMaxR];
-    __shared__ int cnt_sh, nsel_sh, stop_sh;
-    const SolDev &S = sols[0];
-    const int tid = threadIdx.x, T = blockDim.x, R = S.R;
+    __shared__ int cnt_sh, nsel_sh, long_sh;
+    __shared__ unsigned long long first_sh;
+    const int tid = threadIdx.x, T = blockDim.x, R = S.R, lane = tid & 63, wave = tid >> 6;
     const size_t RR = (size_t)R * R;
     if (mode == kModeLS && S.state[kStDone]) return;
     if (tid == 0) {
-        cnt_sh = 0;
-        nsel_sh = 0;
+        cnt_sh = nsel_sh = long_sh = 0;
+        first_sh = ~0ull;
         if (mode == kModeLS) ls_count_moves(S, op_mask, S.acc);
         S.acc[kAccGranInter] = 0;
         *S.best_key = ~0ull;
     }
     for (int r = tid; r < R; r += T) used[r] = 0;
     __syncthreads();
-    // 1. compact the improving candidates
-    for (size_t q = tid; q < RR; q += T) {
-        const unsigned long long k = S.pairkey[q];
-        if (key_improving(k)) {
-            const int slot = atomicAdd(&cnt_sh, 1);
-            if (slot < kMultiCands) {
-                keys[slot] = k;
-                pidx[slot] = (int)q;
-            }
+    // 1. compact the improving candidates (one LDS atomic per wavefront), and
+    // clear the table for the next evaluation when they all fit
+    for (size_t q0 = 0; q0 < RR; q0 += T) {
+        const size_t q = q0 + tid;
+        const unsigned long long k = q < RR ? S.pairkey[q] : ~0ull;
+        const bool on = key_improving(k);
+        const unsigned long long mask = __builtin_amdgcn_ballot_w64(on);
+        if (!mask) continue;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&cnt_sh, __builtin_popcountll(mask));
+        at = __builtin_amdgcn_readfirstlane(at) +
+             __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+        if (on && at < kMultiCands) {
+            const int r1 = (int)((uint32_t)q / (uint32_t)R);
+            ms.key[at] = k;
+            ms.pair[at] = (r1 << 16) | ((int)q - r1 * R);
         }
     }
     __syncthreads();
-    const int cnt = cnt_sh;
+    const bool in_lds = cnt_sh <= kMultiCands;
+    const size_t count = in_lds ? (size_t)cnt_sh : RR;
+    if (in_lds)
+        for (size_t q = tid; q < RR; q += T) S.pairkey[q] = ~0ull;
+    // 2. rounds of locally dominant candidates
     int32_t *sel = S.msel + 1;  // (id, delta) per selected move
-    if (cnt <= kMultiCands) {
-        // 2a. sort (key, pair) ascending: bitonic over the next power of two
-        int np2 = 1;
-        while (np2 < cnt) np2 <<= 1;
-        for (int q = cnt + tid; q < np2; q += T) {
-            keys[q] = ~0ull;
-            pidx[q] = 0;
+    auto candidate = [&](size_t q, unsigned long long &k, int &r1, int &r2) {
+        if (in_lds) {
+            k = ms.key[q];
+            r1 = ms.pair[q] >> 16;
+            r2 = ms.pair[q] & 0xFFFF;
+        } else {
+            k = S.pairkey[q];
+            if (!key_improving(k)) return false;
+            r1 = (int)((uint32_t)q / (uint32_t)R);
+            r2 = (int)q - r1 * R;
         }
+        return !used[r1] && !used[r2];
+    };
+    for (int before = 0;;) {
+        for (int r = tid; r < R; r += T) ms.best[r] = ~0ull;
         __syncthreads();
-        for (int kk = 2; kk <= np2; kk <<= 1)
-            for (int j = kk >> 1; j > 0; j >>= 1) {
-                for (int q = tid; q < np2; q += T) {
-                    const int p = q ^ j;
-                    if (p > q) {
-                        const bool up = (q & kk) == 0;
-                        const unsigned long long a = keys[q], b = keys[p];
-                        if ((a > b) == up) {
-                            keys[q] = b;
-                            keys[p] = a;
-                            const int t2 = pidx[q];
-                            pidx[q] = pidx[p];
-                            pidx[p] = t2;
-                        }
-                    }
-                }
-                __syncthreads();
+        unsigned long long k;
+        int r1, r2;
+        for (size_t q = tid; q < count; q += T)
+            if (candidate(q, k, r1, r2)) {
+                if (k < ms.best[r1]) atomicMin(&ms.best[r1], k);
+                if (k < ms.best[r2]) atomicMin(&ms.best[r2], k);
             }
-        // greedy scan in order (one thread)
-        if (tid == 0) {
-            int ns = 0;
-            for (int q = 0; q < cnt; ++q) {
-                const int r1 = pidx[q] / R, r2 = pidx[q] - r1 * R;
-                if (used[r1] || used[r2]) continue;
-                used[r1] = used[r2] = 1;
-                sel[2 * ns] = (int32_t)(uint32_t)(keys[q] & 0xFFFFFFFFu);
-                sel[2 * ns + 1] = (int)((uint32_t)(keys[q] >> 32) ^ 0x80000000u);
-                ++ns;
-            }
-            nsel_sh = ns;
-        }
-    } else {
-        // 2b. rounds of locally dominant candidates: a candidate whose key is
-        // the smallest among the candidates at each of its (free) routes is
-        // taken by the sequential greedy too (no smaller key can take one of
-        // its routes first), and the candidates dominant in one round share
-        // no route; repeating on the routes still free gives the greedy set
-        // in a few passes.  The set is then sorted into (delta, id) order.
-        unsigned long long *bestr = keys;  // per route (R <= kMultiCands)
-        for (;;) {
-            for (int r = tid; r < R; r += T) bestr[r] = ~0ull;
-            if (tid == 0) stop_sh = 1;
-            __syncthreads();
-            for (size_t q = tid; q < RR; q += T) {
-                const unsigned long long k = S.pairkey[q];
-                if (!key_improving(k)) continue;
-                const int r1 = (int)(q / R), r2 = (int)(q - (size_t)r1 * R);
-                if (used[r1] || used[r2]) continue;
-                atomicMin(&bestr[r1], k);
-                if (r2 != r1) atomicMin(&bestr[r2], k);
-            }
-            __syncthreads();
-            const int before = nsel_sh;
-            for (size_t q = tid; q < RR; q += T) {
-                const unsigned long long k = S.pairkey[q];
-                if (!key_improving(k)) continue;
-                const int r1 = (int)(q / R), r2 = (int)(q - (size_t)r1 * R);
-                if (used[r1] || used[r2] || bestr[r1] != k || bestr[r2] != k) continue;
+        __syncthreads();
+        // a dominant candidate's routes are its own in this round, so marking
+        // them disturbs no other dominant one
+        for (size_t q = tid; q < count; q += T)
+            if (candidate(q, k, r1, r2) && ms.best[r1] == k && ms.best[r2] == k) {
                 const int slot = atomicAdd(&nsel_sh, 1);  // < R: the taken candidates share no route
-                pidx[slot] = (int)q;
                 sel[2 * slot] = (int32_t)(uint32_t)(k & 0xFFFFFFFFu);
                 sel[2 * slot + 1] = (int)((uint32_t)(k >> 32) ^ 0x80000000u);
-                stop_sh = 0;
-            }
-            __syncthreads();
-            for (int q = before + tid; q < nsel_sh; q += T) {
-                const int r1 = pidx[q] / R, r2 = pidx[q] - (pidx[q] / R) * R;
                 used[r1] = used[r2] = 1;
+                atomicMin(&first_sh, k);
             }
-            __syncthreads();
-            if (stop_sh) break;
-        }
-        // (delta, id) order: sort the selection's keys (bitonic, in LDS)
-        const int cntSel = nsel_sh;
+        __syncthreads();
+        const int now = nsel_sh;
+        if (now == before) break;
+        before = now;
+    }
+    const int ns = nsel_sh;
+    if (!in_lds)
+        for (size_t q = tid; q < RR; q += T) S.pairkey[q] = ~0ull;
+    __threadfence_block();
+    __syncthreads();
+    if (tid == 0) S.msel[0] = ns;
+    if (mode != kModeLS) {
+        // (delta, id) order: sort the selection's keys (bitonic, in LDS; ns <= R)
+        unsigned long long *keys = ms.best;
         int np2 = 1;
-        while (np2 < cntSel) np2 <<= 1;
+        while (np2 < ns) np2 <<= 1;
         for (int q = tid; q < np2; q += T)
-            keys[q] = q < cntSel ? pack_key(sel[2 * q + 1], (uint32_t)sel[2 * q]) : ~0ull;
+            keys[q] = q < ns ? pack_key(sel[2 * q + 1], (uint32_t)sel[2 * q]) : ~0ull;
         __syncthreads();
         for (int kk = 2; kk <= np2; kk <<= 1)
             for (int jj = kk >> 1; jj > 0; jj >>= 1) {
@@ -4305,80 +4467,106 @@ __global__ __launch_bounds__(kApplyThreads) void k_multi_step(const SolDev *__re
                 }
                 __syncthreads();
             }
-        for (int q = tid; q < cntSel; q += T) {
+        for (int q = tid; q < ns; q += T) {
             sel[2 * q] = (int32_t)(uint32_t)(keys[q] & 0xFFFFFFFFu);
             sel[2 * q + 1] = (int)((uint32_t)(keys[q] >> 32) ^ 0x80000000u);
         }
+        return;
     }
-    __syncthreads();
-    const int ns = nsel_sh;
-    if (tid == 0) S.msel[0] = ns;
-    // 3. clear the table for the next evaluation
-    for (size_t q = tid; q < RR; q += T) S.pairkey[q] = ~0ull;
-    __syncthreads();
-    if (mode != kModeLS) return;
-    // 4. apply the selection.  Routes are disjoint, so the new layout is the
-    // old one with each touched route replaced by its new node sequence: its
-    // nodes go into nr_alt (with the new route offsets), then one rebuild of
-    // every attribute.  The decoded moves reuse the key array; a selection
-    // too large for it is applied move by move instead.
-    MoveInfo *mv = reinterpret_cast<MoveInfo *>(keys);
-    constexpr int kBatchApply = (int)(sizeof(keys) / (sizeof(MoveInfo)));
-    if (ns <= kBatchApply) {
-        int *mov_of = pidx;  // per route: the selected move touching it, or -1
+    // 3. the new layout.  Routes are disjoint, so it is the old one with each
+    // touched route replaced by its new node sequence, whatever the order of
+    // the moves.  A selection too large for the LDS, or one that makes a route
+    // too long for k_build_routes, is applied move by move instead.
+    MultiApply &ma = reinterpret_cast<MultiApply &>(ms);
+    bool one_by_one = ns > kMultiMoves;
+    if (ns > 0 && !one_by_one) {
+        int *mov_of = ma.mov_of;
         for (int r = tid; r < R; r += T) mov_of[r] = -1;
         __syncthreads();
         for (int q = tid; q < ns; q += T) {
-            decode_move(S, (uint32_t)sel[2 * q], mv[q]);
-            mv[q].delta = sel[2 * q + 1];
-        }
-        __syncthreads();
-        for (int q = tid; q < ns; q += T)
-            if (mv[q].valid) {
-                mov_of[mv[q].ra] = q;
-                mov_of[mv[q].rb] = q;
+            MoveInfo m;
+            decode_move(S, (uint32_t)sel[2 * q], m);
+            m.delta = sel[2 * q + 1];
+            ma.mv[q] = m;
+            if (m.valid) {
+                mov_of[m.ra] = q;
+                mov_of[m.rb] = q;
             }
+        }
         __syncthreads();
         auto newL = [&](int r) {
             const int q = mov_of[r];
             if (q < 0) return S.roff[r + 1] - S.roff[r] - 1;
-            return r == mv[q].ra ? mv[q].nLa : mv[q].nLb;
+            return r == ma.mv[q].ra ? ma.mv[q].nLa : ma.mv[q].nLb;
         };
-        // new offsets: an exclusive scan of newL + 1 over the routes (each
-        // thread a contiguous run of routes, then the threads' totals)
+        // new offsets: an exclusive scan of newL over the routes (each thread
+        // a contiguous run of routes, then the threads' totals)
         const int per = (R + T - 1) / T, r0 = min(tid * per, R), r1 = min(r0 + per, R);
         int own = 0;
-        for (int r = r0; r < r1; ++r) own += newL(r) + 1;
+        for (int r = r0; r < r1; ++r) {
+            const int l = newL(r);
+            own += l;
+            if (l >= 64) long_sh = 1;
+        }
         int incl = own;
-        const int lane = tid & 63, wave = tid >> 6;
         for (int off = 1; off < 64; off <<= 1) {
             const int v = __shfl_up(incl, off);
             if (lane >= off) incl += v;
         }
         if (lane == 63) sh.red[wave][0] = incl;
         __syncthreads();
-        int before = incl - own;
-        for (int w = 0; w < wave; ++w) before += (int)sh.red[w][0];
-        for (int r = r0; r < r1; ++r) {
-            S.roff_alt[r] = before;
-            before += newL(r) + 1;
+        one_by_one = long_sh;
+        if (!one_by_one) {
+            int before = incl - own;
+            for (int w = 0; w < wave; ++w) before += (int)sh.red[w][0];
+            for (int r = r0; r < r1; ++r) {
+                S.roff_alt[r] = before;
+                before += newL(r);
+            }
+            if (tid == 0) S.roff_alt[R] = S.n;
+            __threadfence_block();
+            __syncthreads();
+            // customers of the new layout, one wavefront per route
+            int32_t *cust = (int32_t *)S.nr_alt;
+            for (int r = wave; r < R; r += T / 64) {
+                const int q = mov_of[r], base = S.roff_alt[r], nl = newL(r);
+                if (lane < nl) cust[base + lane] = q < 0 ? old_node(S, r, lane + 1) : new_node(S, ma.mv[q], r, lane + 1);
+            }
+            // |N(S)| changes by the touched routes' terms
+            long long d[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            for (int q = tid; q < ns; q += T) {
+                const MoveInfo &m = ma.mv[q];
+                if (!m.valid) continue;
+                d[0] += 1;
+                if (m.ra == m.rb) continue;
+                const RouteCounts a0 = route_counts(m.La, S.Q), a1 = route_counts(m.nLa, S.Q),
+                                  b0 = route_counts(m.Lb, S.Q), b1 = route_counts(m.nLb, S.Q);
+                d[1] += a1.rel - a0.rel + b1.rel - b0.rel;
+                d[2] -= (a1.star2 - a0.star2 + b1.star2 - b0.star2) / 2;
+                d[3] += a1.two - a0.two + b1.two - b0.two;
+                d[4] += a1.oropt - a0.oropt + b1.oropt - b0.oropt;
+                d[5] += a1.seg - a0.seg + b1.seg - b0.seg;
+                d[6] += a1.k - a0.k + b1.k - b0.k;
+                d[7] += a1.k2 - a0.k2 + b1.k2 - b0.k2;
+            }
+            __syncthreads();
+            for (int i = 0; i < 8; ++i) {
+                long long v = d[i];
+                for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+                if (lane == 0) sh.red[wave][i] = v;
+            }
+            __syncthreads();
+            if (tid < 8) {
+                long long v = 0;
+                for (int w = 0; w < T / 64; ++w) v += sh.red[w][tid];
+                const int to[8] = {-1, kAccCnt0, kAccCnt0 + 2, kAccCnt0 + 3, kAccCnt0 + 4, kAccExtSeg, kAccExtK, kAccExtK2};
+                if (tid == 0) S.state[kStVersion] += (int)v;
+                else S.acc[to[tid]] += v;
+            }
+            if (tid == 0) S.state[kStBuild] = 1;
         }
-        if (tid == 0) S.roff_alt[R] = S.Q;
-        __syncthreads();
-        // nodes of the new layout, one wavefront per route
-        for (int r = wave; r < R; r += T / 64) {
-            const int q = mov_of[r], base = S.roff_alt[r], nl = newL(r);
-            for (int p = lane; p <= nl; p += 64)
-                S.nr_alt[base + p] = make_int2(q < 0 ? old_node(S, r, p) : new_node(S, mv[q], r, p), r);
-        }
-        if (tid == 0) S.nr_alt[S.Q] = make_int2(0, R);
-        __threadfence_block();
-        __syncthreads();
-        rebuild(S, S.nr_alt, S.roff_alt, sh);
-        if (S.pen || S.pd || S.gen) pen_all(S, sh);
-        if (tid == 0)
-            for (int q = 0; q < ns; ++q) S.state[kStVersion] += mv[q].valid ? 1 : 0;
-    } else {
+    }
+    if (one_by_one)
         for (int q = 0; q < ns; ++q) {
             if (tid == 0) {
                 decode_move(S, (uint32_t)sel[2 * q], mi);
@@ -4390,12 +4578,10 @@ __global__ __launch_bounds__(kApplyThreads) void k_multi_step(const SolDev *__re
             __syncthreads();
             if (tid == 0 && m.valid) S.state[kStVersion] += 1;
         }
-    }
     if (tid == 0) {
-        if (ns > 0) {
-            const int q = 0;  // the record holds the first (best) selected move
-            S.rec[4] = sel[2 * q + 1];
-            S.rec[6] = sel[2 * q];
+        if (ns > 0) {  // the record holds the first (best) selected move
+            S.rec[4] = (int)((uint32_t)(first_sh >> 32) ^ 0x80000000u);
+            S.rec[6] = (int32_t)(uint32_t)(first_sh & 0xFFFFFFFFu);
             S.state[kStSteps] += 1;
             S.acc[kAccMultiApplied] += ns;
             S.state[kStStatus] = 0;
@@ -4461,7 +4647,6 @@ __global__ __launch_bounds__(256) void k_check_nodes(const int4 *__restrict__ nd
     atomicMax(&out[5], q.x);
 }
 
-// Marks every route's distance-block cache entry empty.
 // Pickup amounts: chk[0] |= 1 for a negative amount or a nonzero depot
 // entry; chk[1] = the largest amount.
 __global__ __launch_bounds__(256) void k_check_pick(const int32_t *__restrict__ pick, int np1, int32_t *chk) {
@@ -4470,11 +4655,6 @@ __global__ __launch_bounds__(256) void k_check_pick(const int32_t *__restrict__ 
     const int v = pick[i];
     if (v < 0 || (i == 0 && v != 0)) atomicOr(chk, 1);
     atomicMax(chk + 1, v);
-}
-
-__global__ void k_route_blocks_clear(int32_t *rblk, int R) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < R) rblk[(size_t)r * kRouteBlockWords] = -1;
 }
 
 __global__ void k_fill_u64(unsigned long long *p, size_t count) {
@@ -4520,17 +4700,10 @@ __global__ void k_collect(const SolDev *__restrict__ sols, int nsols, long long 
 __global__ void k_reset_state(const SolDev *__restrict__ sols, int nsols, int max_steps) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nsols || sols[i].Q == 0) return;
-    const SolDev &S = sols[i];
-    S.state[kStDone] = 0;
-    S.state[kStSteps] = 0;
-    S.state[kStStatus] = 0;
-    S.state[kStMaxSteps] = max_steps;
-    S.acc[kAccMoves] = 0;
-    S.acc[kAccFullPairs] = 0;
-    S.acc[kAccScreenPairs] = 0;
-    S.acc[kAccMultiApplied] = 0;
-    *S.best_key = ~0ull;
+    reset_run(sols[i], max_steps);
 }
+
+__global__ void k_reset_one(const SolDev S, int max_steps) { reset_run(S, max_steps); }
 
 // Measurement aid: reads `chunks` KiB from src into LDS with the 16-byte
 // LDS DMA that stages 16-bit distance rows (one KiB per wavefront

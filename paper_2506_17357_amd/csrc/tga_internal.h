@@ -45,8 +45,9 @@ struct SolDev {
     int32_t *roff;    // R+1
     int32_t *rdist;   // R
     // apply / build staging
-    int2 *nr_alt;     // Q+1 {node, route} of the next layout
-    int32_t *roff_alt;// R+1
+    int2 *nr_alt;     // Q+1 {node, route} of the next layout (k_build_routes: its customers, one int each)
+    int32_t *roff_alt;// R+1 slot offsets of the next layout (k_build_routes: customer offsets)
+    long long *part;  // k_build_routes: workgroups done, then per workgroup its sums
     // per route: the route's distance sub-block as last staged (see kRouteBlock*)
     int32_t *rblk;
     // penalised mode (feasible and infeasible search): per slot the
@@ -85,6 +86,7 @@ enum {
     kStStatus = 2,     // 0 ok, 1 no admissible move, -1 invalid move
     kStVersion = 3,    // applied moves (host-visible version)
     kStMaxSteps = 4,   // step cap for LS mode
+    kStBuild = 5,      // multi-move: the selection left a new layout for k_build_routes
     kStCount
 };
 // acc[] entries
@@ -112,6 +114,8 @@ enum {
 // Row stride (elements) of the 16-bit copy of D: a multiple of 8 keeps every
 // row 16-byte aligned.
 constexpr int stride16_of(int np1) { return (np1 + 7) & ~7; }
+
+constexpr int kBuildRoutes = 16;  // routes per workgroup of k_build_routes (one wavefront each)
 
 constexpr int kMaxXcds = 8;  // accelerator dies (each with its own L2) the batched items are spread over
 constexpr int kMaxBatchGrid = 4096;  // workgroups of one batched evaluation launch

@@ -91,3 +91,50 @@ def test_apply_forms(tga, case, problem, form):
         assert np.array_equal(S.move_counts(), F.move_counts())
         if form != "plain":
             assert S.violations() == F.violations()
+
+
+@pytest.mark.parametrize("problem", ["cvrp", "vrptw", "vrpspdtw"])
+@pytest.mark.parametrize("lengths", [[1], [0, 0, 3], [63] * 3, [63, 64, 1], [9] * 16, [9] * 17, [200, 3], [4, 0] * 40])
+def test_set_reload_get(tga, problem, lengths):
+    """Setting, reloading and reading back routes where the build changes form (one and several workgroups of 16
+    routes, a route too long for a wavefront): evaluations and counts equal the oracle's for the routes given."""
+    inst, sol = make(problem, lengths, 1200 + len(lengths))
+    other = make(problem, lengths, 1300 + len(lengths))[1]
+    S = tga.Solution(tga.Instance.from_workload(inst), sol.offsets, sol.customers)
+    print("set / reload / get", problem, len(lengths), flush=True)
+    for k, s in enumerate((sol, other, sol)):
+        if k > 0:
+            S.reload(s.offsets, s.customers)
+        off, cust, cost = S.get()
+        assert np.array_equal(off, s.offsets) and np.array_equal(cust, s.customers)
+        assert cost == oracle.cost(inst, s)[0]
+        ob = oracle.eval_neighbourhood(inst, s, 0x1F, threads=0)
+        b = S.eval()
+        assert (b is not None) == bool(ob.found) and (b is None or (b.id, b.delta) == (ob.id, ob.delta))
+        assert int(S.move_counts().sum()) == ob.moves
+        if problem == "vrpspdtw":
+            assert S.violations() == oracle.violations(inst, s)
+        if b is not None:
+            S.apply(b)  # the next reload replaces changed routes
+
+
+@pytest.mark.parametrize("lengths", [[12] * 9, [60, 62, 3, 5, 58, 1, 0], [2] * 300])
+@pytest.mark.parametrize("problem", ["cvrp", "vrptw", "vrpspdtw"])
+def test_multi_steps(tga, problem, lengths):
+    """Multi-move steps: candidates kept in LDS and read from the table, routes that outgrow a wavefront."""
+    inst, sol = make(problem, lengths, 1400 + len(lengths))
+    S = tga.Solution(tga.Instance.from_workload(inst), sol.offsets, sol.customers)
+    S.set_multi(True)
+    print("multi", problem, len(lengths), flush=True)
+    steps = 4
+    fin, applied, per, evaluated = oracle.local_search_multi(inst, sol, 0x1F, max_steps=steps)
+    got, moves, cost = S.ls_run(steps, 0x1F | tga.OP_MULTI)
+    assert (got, moves) == (len(per), evaluated) and S.multi_stats() == (len(per), len(applied))
+    off, cust, c = S.get()
+    assert np.array_equal(off, fin.offsets) and np.array_equal(cust, fin.customers)
+    assert cost == c == oracle.cost(inst, fin)[0]
+    F = tga.Solution(S.inst, off, cust)
+    F.set_general(True)
+    a, b = S.eval(), F.eval()
+    assert (a is None) == (b is None) and (a is None or (a.id, a.delta) == (b.id, b.delta))
+    assert np.array_equal(S.move_counts(), F.move_counts()) and S.violations() == F.violations()
