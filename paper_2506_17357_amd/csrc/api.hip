@@ -234,11 +234,9 @@ struct tga_instance {
     const int4 *node4;
     int32_t maxD, maxE, maxL, maxS, maxDem;
     // granular neighbourhood (tga_instance_set_granular), in a caller
-    // workspace: the customer-customer adjacency entries (source and
-    // neighbour node, both orders) first, then the customers paired with the
-    // depot (gsrc only)
-    int32_t theta = 0, gnnz = 0, gcc = 0, gdep = 0;
-    const int32_t *gsrc = nullptr, *gadj = nullptr;
+    // workspace; gnnz counts a pair of customers twice, one with the depot once
+    int32_t theta = 0, gnnz = 0;
+    GranPairs gran{};
     // pickups (tga_instance_set_pickups), borrowed; null without
     const int32_t *pick = nullptr;
     int32_t maxPick = 0;
@@ -346,14 +344,16 @@ extern "C" int tga_load_instance(int32_t n, const int32_t *dist, const int32_t *
     hipStream_t st = (hipStream_t)stream;
     const int np1 = n + 1;
     int32_t *chk = (int32_t *)ws;
+    const int stride16 = stride16_of(np1);
+    uint16_t *d16 = (uint16_t *)((char *)ws + 256);
     k_zero_i32<<<1, 64, 0, st>>>(chk, 8);
-    const int tiles = (np1 + 31) / 32;
-    k_check_dist<<<dim3(tiles, tiles), 256, 0, st>>>(dist, np1, chk);
-    k_check_nodes<<<(np1 + 255) / 256, 256, 0, st>>>((const int4 *)node4, np1, has_tw, chk);
-    HIPCHK(hipGetLastError());
+    const int tiles = (np1 + kCheckTile - 1) / kCheckTile;
+    k_check_instance<<<dim3(tiles, tiles), 256, 0, st>>>(dist, np1, stride16, d16, (const int4 *)node4, has_tw, chk);
     void *pin;
     if ((rc = pinned(&pin))) return rc;
-    HIPCHK(hipMemcpyAsync(pin, chk, 32, hipMemcpyDeviceToHost, st));
+    if (g_pin.dev) k_check_done<<<1, 64, 0, st>>>(chk, (int32_t *)g_pin.dev);
+    HIPCHK(hipGetLastError());
+    if (!g_pin.dev) HIPCHK(hipMemcpyAsync(pin, chk, 32, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     int32_t r[8];
     memcpy(r, pin, 32);
@@ -365,14 +365,7 @@ extern "C" int tga_load_instance(int32_t n, const int32_t *dist, const int32_t *
     if ((int64_t)n * maxDem >= (1 << 30)) return fail(TGA_ERANGE, "total demand may exceed 2^30");
     if (has_tw && (int64_t)np1 * (maxS + maxD) + maxL + maxE >= (1 << 28))
         return fail(TGA_ERANGE, "route durations may exceed 2^28");
-    const int stride16 = stride16_of(np1);
-    uint16_t *d16 = nullptr;
-    if (maxD < 65536) {  // every distance fits 16 bits: keep a packed copy for the inter-route kernels
-        d16 = (uint16_t *)((char *)ws + 256);
-        k_pack16<<<dim3((stride16 + 255) / 256, np1), 256, 0, st>>>(dist, np1, stride16, d16);
-        HIPCHK(hipGetLastError());
-        HIPCHK(hipStreamSynchronize(st));
-    }
+    if (maxD >= 65536) d16 = nullptr;  // the 16-bit copy serves only distances that fit
     tga_instance *I = new tga_instance;
     I->n = n;
     I->cap = capacity;
@@ -391,12 +384,34 @@ extern "C" int tga_load_instance(int32_t n, const int32_t *dist, const int32_t *
     return TGA_OK;
 }
 
+// Workspace of the granular pairs: theta nearest of every node and the bound
+// of their keys, the pairs of customers (at most one per list entry), the
+// customers paired with the depot, the two counts.
+struct GranLayout {
+    size_t nn, bound, src, adj, dep, cnt, total;
+};
+static GranLayout gran_layout(size_t np1, size_t theta) {
+    GranLayout L;
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        const size_t o = off;
+        off = align_up(off + bytes, 256);
+        return o;
+    };
+    L.nn = take(4 * np1 * theta);
+    L.bound = take(8 * np1);
+    L.src = take(4 * np1 * theta);
+    L.adj = take(4 * np1 * theta);
+    L.dep = take(4 * np1);
+    L.cnt = take(8);
+    L.total = off;
+    return L;
+}
+
 extern "C" size_t tga_granular_workspace_bytes(int32_t n, int32_t theta) {
     if (n < 1 || n > TGA_MAX_Q - 1 || theta < 1 || theta > n || theta > kKnnMax) return 0;
     const size_t np1 = (size_t)n + 1;
-    // theta nearest of every node, then source and neighbour of up to
-    // 2 theta (n+1) adjacency entries
-    return align_up(4 * np1 * theta, 256) + 2 * align_up(4 * 2 * np1 * (size_t)theta, 256);
+    return gran_layout(np1, theta).total;
 }
 
 extern "C" int tga_instance_set_granular(tga_instance_t inst, int32_t theta, void *ws, size_t ws_bytes,
@@ -408,52 +423,29 @@ extern "C" int tga_instance_set_granular(tga_instance_t inst, int32_t theta, voi
     if (ws_bytes < need) return fail(TGA_ENOMEM, "granular workspace %zu < %zu", ws_bytes, need);
     if (((uintptr_t)ws) & 255) return fail(TGA_EINVAL, "workspace must be 256-byte aligned");
     hipStream_t st = (hipStream_t)stream;
-    int32_t *nn = (int32_t *)ws;
-    k_knn<<<np1, 256, 0, st>>>(inst->D, np1, theta, nn);
+    const GranLayout L = gran_layout(np1, theta);
+    char *base = (char *)ws;
+    int32_t *nn = (int32_t *)(base + L.nn), *cnt = (int32_t *)(base + L.cnt);
+    unsigned long long *bound = (unsigned long long *)(base + L.bound);
+    GranPairs G;
+    G.src = (int32_t *)(base + L.src);
+    G.adj = (int32_t *)(base + L.adj);
+    G.dep = (int32_t *)(base + L.dep);
+    k_zero_i32<<<1, 64, 0, st>>>(cnt, 2);
+    k_knn<<<np1, 256, 4 * (size_t)np1, st>>>(inst->D, np1, theta, nn, bound);
+    k_gran_pairs<<<(int)(((long long)np1 * theta + 1023) / 1024), 1024, 0, st>>>(
+        inst->D, np1, theta, nn, bound, (int32_t *)G.src, (int32_t *)G.adj, (int32_t *)G.dep, cnt);
     HIPCHK(hipGetLastError());
-    std::vector<int32_t> h((size_t)np1 * theta);
-    HIPCHK(hipMemcpyAsync(h.data(), nn, 4 * h.size(), hipMemcpyDeviceToHost, st));
+    void *pin;
+    int rc = pinned(&pin);
+    if (rc) return rc;
+    HIPCHK(hipMemcpyAsync(pin, cnt, 8, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    // symmetric closure: j is listed under i when either is among the other's
-    // theta nearest; only the rows of customers are kept (the depot's pairs
-    // are walked from its customers)
-    std::vector<std::vector<int32_t>> adj(np1);
-    for (int i = 0; i < np1; ++i)
-        for (int k = 0; k < theta; ++k) {
-            const int j = h[(size_t)i * theta + k];
-            if (j < 0 || j > n || j == i) return fail(TGA_EDEVICE, "neighbour list of node %d is corrupt", i);
-            adj[i].push_back(j);
-            adj[j].push_back(i);
-        }
-    std::vector<int32_t> src, dst, dep;
-    for (int i = 1; i < np1; ++i) {
-        std::sort(adj[i].begin(), adj[i].end());
-        adj[i].erase(std::unique(adj[i].begin(), adj[i].end()), adj[i].end());
-        for (int j : adj[i]) {
-            if (j == 0) {
-                dep.push_back(i);
-                continue;
-            }
-            src.push_back(i);
-            dst.push_back(j);
-        }
-    }
-    const int32_t gcc = (int32_t)src.size(), gdep = (int32_t)dep.size();
-    src.insert(src.end(), dep.begin(), dep.end());
-    dst.resize(src.size(), 0);
-    int32_t *gsrc = (int32_t *)((char *)ws + align_up(4 * (size_t)np1 * theta, 256));
-    int32_t *gadj = (int32_t *)((char *)gsrc + align_up(4 * 2 * (size_t)np1 * theta, 256));
-    if (!src.empty()) {
-        HIPCHK(hipMemcpyAsync(gsrc, src.data(), 4 * src.size(), hipMemcpyHostToDevice, st));
-        HIPCHK(hipMemcpyAsync(gadj, dst.data(), 4 * dst.size(), hipMemcpyHostToDevice, st));
-    }
-    HIPCHK(hipStreamSynchronize(st));
+    G.gcc = ((const int32_t *)pin)[0];
+    G.gdep = ((const int32_t *)pin)[1];
     inst->theta = theta;
-    inst->gnnz = (int32_t)src.size();
-    inst->gcc = gcc;
-    inst->gdep = gdep;
-    inst->gsrc = gsrc;
-    inst->gadj = gadj;
+    inst->gnnz = 2 * G.gcc + G.gdep;
+    inst->gran = G;
     return TGA_OK;
 }
 
@@ -749,17 +741,15 @@ static EvalShape intra_shape(const tga_solution *sol, uint32_t op_mask) {
 // intra-route ones complete.
 template <bool TW>
 static void launch_eval_gran(const tga_solution *sol, uint32_t op_mask, int32_t *dd, uint8_t *df, hipStream_t st) {
-    const tga_instance *I = sol->inst;
-    const long long work = (op_mask & 7) ? I->gcc + (long long)I->gdep * sol->R : 0;
+    const GranPairs &P = sol->inst->gran;
+    const long long work = (op_mask & 7) ? P.gcc + (long long)P.gdep * sol->R : 0;
     const EvalShape e = intra_shape(sol, op_mask);
     const int grid = e.nintra + (int)((work + kInterThreads - 1) / kInterThreads);
     if (!grid) return;
     if (dd)
-        k_eval_gran<TW, true><<<grid, kInterThreads, kIntraRegionBytes, st>>>(sol->h, I->gsrc, I->gadj, I->gcc, I->gdep,
-                                                                             e.nintra, e.G, op_mask, dd, df);
+        k_eval_gran<TW, true><<<grid, kInterThreads, kIntraRegionBytes, st>>>(sol->h, P, e.nintra, e.G, op_mask, dd, df);
     else
-        k_eval_gran<TW, false><<<grid, kInterThreads, kIntraRegionBytes, st>>>(sol->h, I->gsrc, I->gadj, I->gcc,
-                                                                              I->gdep, e.nintra, e.G, op_mask, dd, df);
+        k_eval_gran<TW, false><<<grid, kInterThreads, kIntraRegionBytes, st>>>(sol->h, P, e.nintra, e.G, op_mask, dd, df);
 }
 
 template <bool TW>

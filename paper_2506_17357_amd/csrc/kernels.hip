@@ -1637,16 +1637,14 @@ __device__ __forceinline__ void inter_item(const SolDev &S, const InterItem &ite
 // ------------------------------------------- granular inter-route eval ---
 // Edge-based extraction (Section 5.3.1): only the node pairs kept by the
 // granular mask, the symmetric closure of each node's theta nearest
-// neighbours, get their inter-route moves evaluated.  The mask is an
-// adjacency list over nodes 0..n (CSR; node 0 is the depot and stands for
-// the start depot of every route).  One thread per adjacency entry (u, v) of
-// a customer u: the pair of slots (slot(u), slot(v)) is evaluated by the
-// entry whose row route comes first (each pair once, as in the full kernel:
-// row route < column route); an entry (u, depot) evaluates u against the
-// start depot of every other route.  The depot's own row is never walked:
-// its pairs are those of its customers.  Attributes are gathered per thread
-// (no LDS staging): E is small next to the Q^2 pairs of the full
-// neighbourhood.
+// neighbours, get their inter-route moves evaluated.  The mask is a list of
+// pairs of customers, each pair once, and of the customers paired with the
+// depot, which stands for the start depot of every route.  One thread per
+// pair (u, v): the slot of the route that comes first is the row (as in the
+// full kernel, row route < column route); one thread per (customer paired
+// with the depot, route): the customer against that route's start depot.
+// Attributes are gathered per thread (no LDS staging): E is small next to
+// the Q^2 pairs of the full neighbourhood.
 
 // Column attributes of slot t for one thread (the fields pair_moves reads).
 __device__ __forceinline__ void lane_col_single(const SolDev &S, int t, LaneCol &L) {
@@ -1703,38 +1701,38 @@ __device__ __forceinline__ int gran_pair(const SolDev &S, int x, int t, uint32_t
     return (opRel ? (int)cx + (int)ct : 0) + (opSwap && cx && ct ? 1 : 0) + (op2s ? 1 : 0);
 }
 
-// Work items: e < gcc, a customer-customer adjacency entry (gsrc[e],
-// gadj[e]); gcc <= e < gcc + gdep * R, customer gsrc[gcc + (e - gcc) / R]
-// (one the depot is paired with) against the start depot of route
+// The granular pairs of an instance (device lists).
+struct GranPairs {
+    const int32_t *src, *adj, *dep;  // gcc pairs of customers; gdep customers paired with the depot
+    int gcc, gdep;
+};
+
+// Work items: e < gcc, a pair of customers; gcc <= e < gcc + gdep * R,
+// customer dep[(e - gcc) / R] against the start depot of route
 // (e - gcc) % R, so that no thread walks every route.  The inter-route moves
 // of N_theta(S) evaluated are added to S.acc[kAccGranInter].
 // One block of work items, item e for this thread (every thread of the
 // block calls it; red holds blockDim / 64 keys).
 template <bool TW, bool DUMP>
-__device__ __forceinline__ void gran_block(const SolDev &S, const int32_t *__restrict__ gsrc,
-                                           const int32_t *__restrict__ gadj, int gcc, int gdep, int e,
-                                           uint32_t op_mask, int32_t *__restrict__ dump_delta,
-                                           uint8_t *__restrict__ dump_feas, unsigned long long *red,
-                                           long long *cnt_sh) {
+__device__ __forceinline__ void gran_block(const SolDev &S, const GranPairs &P, int e, uint32_t op_mask,
+                                           int32_t *__restrict__ dump_delta, uint8_t *__restrict__ dump_feas,
+                                           unsigned long long *red, long long *cnt_sh) {
     if (threadIdx.x == 0) *cnt_sh = 0;
     __syncthreads();
     int bd = DUMP ? kAdmissibleBound : initial_bound(op_mask);
     uint32_t bid = 0xFFFFFFFFu;
     long long cnt = 0;
-    if (e < gcc) {
-        const int x = gld(S.ref2slot + gsrc[e] - 1), t = gld(S.ref2slot + gadj[e] - 1);
-        if (gld(S.a4 + t).y > gld(S.a4 + x).y)
-            cnt += gran_pair<TW, DUMP>(S, x, t, op_mask, dump_delta, dump_feas, bd, bid);
-    } else if (e - gcc < gdep * S.R) {
-        const int k = (e - gcc) / S.R, r = (e - gcc) - k * S.R;
-        const int x = gld(S.ref2slot + gsrc[gcc + k] - 1);
-        const int rx = gld(S.a4 + x).y;
-        if (r != rx) {
-            const int d = gld(S.roff + r);  // start depot slot of route r
-            cnt += r > rx ? gran_pair<TW, DUMP>(S, x, d, op_mask, dump_delta, dump_feas, bd, bid)
-                          : gran_pair<TW, DUMP>(S, d, x, op_mask, dump_delta, dump_feas, bd, bid);
-        }
+    int x = 0, t = 0;
+    if (e < P.gcc) {
+        x = gld(S.ref2slot + gld(P.src + e) - 1);
+        t = gld(S.ref2slot + gld(P.adj + e) - 1);
+    } else if (e - P.gcc < P.gdep * S.R) {
+        const int k = (e - P.gcc) / S.R, r = (e - P.gcc) - k * S.R;
+        x = gld(S.ref2slot + gld(P.dep + k) - 1);
+        t = gld(S.roff + r);  // start depot slot of route r
     }
+    if (x != t && gld(S.a4 + x).y != gld(S.a4 + t).y)
+        cnt += gran_pair<TW, DUMP>(S, min(x, t), max(x, t), op_mask, dump_delta, dump_feas, bd, bid);
     for (int off = 32; off >= 1; off >>= 1) cnt += __shfl_xor(cnt, off);
     if ((threadIdx.x & 63) == 0 && cnt) atomicAdd((unsigned long long *)cnt_sh, (unsigned long long)cnt);
     block_argmin_commit(bd, bid, S.best_key, red);  // its barriers also order cnt_sh
@@ -1742,46 +1740,127 @@ __device__ __forceinline__ void gran_block(const SolDev &S, const int32_t *__res
 }
 
 // theta nearest neighbours of every node (distance, then node id; the node
-// itself excluded), one workgroup per node: the theta-th smallest key
-// (d << 14 | j) is found by bisection over the key range with block-wide
-// counts, then the theta keys at or below it are collected and ranked.
-// out: (n+1) x theta node ids, nearest first.  Requires theta <= n and
-// theta <= kKnnMax.
+// itself excluded), one workgroup per node.  The row of D is read once into
+// LDS; the theta-th smallest key (d << 14 | j) is found digit by digit from
+// the top: a histogram of the next eight bits of the keys that share the
+// digits found so far, then the bin that holds the theta-th.  It ends when
+// every key of the bin is wanted.  (Bisecting the key range instead read the
+// row some 38 times: 206 us at n = 2500 against 21.)
+// out: theta node ids per node, in no order; bound: per node a value that
+// exactly its theta neighbours' keys do not exceed.  Requires theta <= n;
+// dynamic LDS of np1 ints.
 constexpr int kKnnMax = 512;
 
 __global__ __launch_bounds__(256) void k_knn(const int32_t *__restrict__ D, int np1, int theta,
-                                             int32_t *__restrict__ out) {
-    __shared__ unsigned long long keys[kKnnMax];
-    __shared__ int cnt_w[4];
-    __shared__ int nsel;
-    const int i = blockIdx.x, tid = threadIdx.x;
-    const int32_t *row = D + (size_t)i * np1;
-    auto key = [&](int j) { return ((unsigned long long)(uint32_t)gld(row + j) << 14) | (unsigned)j; };
-    unsigned long long lo = 0, hi = (1ull << 38) - 1;  // the answer is in [lo, hi]
-    while (lo < hi) {
-        const unsigned long long mid = lo + (hi - lo) / 2;
-        int c = 0;
-        for (int j = tid; j < np1; j += 256) c += (j != i && key(j) <= mid) ? 1 : 0;
-        for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
-        if ((tid & 63) == 0) cnt_w[tid >> 6] = c;
-        __syncthreads();
-        const int total = cnt_w[0] + cnt_w[1] + cnt_w[2] + cnt_w[3];
-        __syncthreads();
-        if (total >= theta)
-            hi = mid;
-        else
-            lo = mid + 1;
+                                             int32_t *__restrict__ out, unsigned long long *__restrict__ bound) {
+    extern __shared__ int row[];
+    __shared__ int hist[256];
+    __shared__ int max_w[4], bin_sh, below_sh, nsel;
+    const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int mx = 0;
+    for (int j = tid; j < np1; j += 256) {
+        const int d = gld(D + (size_t)i * np1 + j);
+        row[j] = d;
+        mx = max(mx, d);
     }
+    for (int off = 32; off >= 1; off >>= 1) mx = max(mx, __shfl_xor(mx, off));
+    if (lane == 0) max_w[wave] = mx;
     if (tid == 0) nsel = 0;
     __syncthreads();
-    for (int j = tid; j < np1; j += 256)
-        if (j != i && key(j) <= lo) keys[atomicAdd(&nsel, 1)] = key(j);
-    __syncthreads();
-    for (int a = tid; a < theta; a += 256) {
-        int rank = 0;
-        for (int b = 0; b < theta; ++b) rank += keys[b] < keys[a] ? 1 : 0;
-        out[(size_t)i * theta + rank] = (int32_t)(keys[a] & 0x3FFF);
+    mx = max(max(max_w[0], max_w[1]), max(max_w[2], max_w[3]));
+    auto key = [&](int j) { return ((unsigned long long)(uint32_t)row[j] << 14) | (unsigned)j; };
+    int bits = 32 - __clz(mx | 1) + 14, rem = theta;  // bits still to be found, rank among the keys that share the rest
+    unsigned long long prefix = 0, limit = 0;
+    while (true) {
+        const int w = min(8, bits), shift = bits - w;
+        hist[tid] = 0;
+        __syncthreads();
+        for (int j = tid; j < np1; j += 256) {
+            const unsigned long long k = key(j);
+            if (j != i && (k >> bits) == prefix) atomicAdd(&hist[(int)(k >> shift) & ((1 << w) - 1)], 1);
+        }
+        __syncthreads();
+        if (wave == 0) {  // four bins per lane
+            int c[4], t = 0;
+            for (int u = 0; u < 4; ++u) t += c[u] = hist[4 * lane + u];
+            int incl = t;
+            for (int off = 1; off < 64; off <<= 1) {
+                const int v = __shfl_up(incl, off);
+                if (lane >= off) incl += v;
+            }
+            int below = incl - t;
+            for (int u = 0; u < 4; ++u) {
+                if (below < rem && rem <= below + c[u]) {
+                    bin_sh = 4 * lane + u;
+                    below_sh = below;
+                }
+                below += c[u];
+            }
+        }
+        __syncthreads();
+        const int bin = bin_sh, inbin = hist[bin];
+        rem -= below_sh;
+        prefix = (prefix << w) | (unsigned)bin;
+        bits = shift;
+        limit = ((prefix + 1) << shift) - 1;
+        if (inbin == rem || shift == 0) break;  // the same for the whole workgroup
+        __syncthreads();
     }
+    for (int j = tid; j < np1; j += 256)
+        if (j != i && key(j) <= limit) out[(size_t)i * theta + atomicAdd(&nsel, 1)] = j;
+    if (tid == 0) bound[i] = limit;
+}
+
+// The granular pairs: the symmetric closure of the neighbour lists, every
+// pair of customers once (src, adj), the customers paired with the depot in
+// dep; cnt[0] and cnt[1] (zero before) receive how many.  One thread per list
+// entry (i, j): a pair that is in both lists is emitted by its lower node's
+// entry, which i's key against j's bound tells.  One atomic per workgroup.
+__global__ __launch_bounds__(1024) void k_gran_pairs(const int32_t *__restrict__ D, int np1, int theta,
+                                                     const int32_t *__restrict__ nn,
+                                                     const unsigned long long *__restrict__ bound,
+                                                     int32_t *__restrict__ src, int32_t *__restrict__ adj,
+                                                     int32_t *__restrict__ dep, int *__restrict__ cnt) {
+    __shared__ int n_sh[16][2], base_sh[2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const long long e = (long long)blockIdx.x * 1024 + tid;
+    int u = 0, v = 0;
+    bool pair = false, depot = false;
+    if (e < (long long)np1 * theta) {
+        const int i = (int)(e / theta), j = nn[e];
+        const unsigned long long k = ((unsigned long long)(uint32_t)gld(D + (size_t)j * np1 + i) << 14) | (unsigned)i;
+        const bool mutual = k <= bound[j];
+        u = i;
+        v = j;
+        depot = j == 0 || (i == 0 && !mutual);
+        pair = i != 0 && j != 0 && (!mutual || i < j);
+        if (i == 0) u = j;  // the customer of a depot pair
+    }
+    const unsigned long long mp = __builtin_amdgcn_ballot_w64(pair), md = __builtin_amdgcn_ballot_w64(depot);
+    if (lane == 0) {
+        n_sh[wave][0] = __builtin_popcountll(mp);
+        n_sh[wave][1] = __builtin_popcountll(md);
+    }
+    __syncthreads();
+    if (tid < 2) {
+        int t = 0;
+        for (int w = 0; w < 16; ++w) {
+            const int c = n_sh[w][tid];
+            n_sh[w][tid] = t;
+            t += c;
+        }
+        base_sh[tid] = t ? atomicAdd(cnt + tid, t) : 0;
+    }
+    __syncthreads();
+    const auto rank = [&](unsigned long long m) {
+        return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+    };
+    if (pair) {
+        const int at = base_sh[0] + n_sh[wave][0] + rank(mp);
+        src[at] = u;
+        adj[at] = v;
+    }
+    if (depot) dep[base_sh[1] + n_sh[wave][1] + rank(md)] = u;
 }
 
 // ------------------------------------------------------ intra-route eval ---
@@ -2916,8 +2995,8 @@ __global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4
 // intra-route groups, the others kInterThreads granular work items each.
 template <bool TW, bool DUMP>
 __global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_gran(
-    const SolDev S, const int32_t *__restrict__ gsrc, const int32_t *__restrict__ gadj, int gcc, int gdep, int nintra,
-    int G, uint32_t op_mask, int32_t *__restrict__ dump_delta, uint8_t *__restrict__ dump_feas) {
+    const SolDev S, const GranPairs P, int nintra, int G, uint32_t op_mask, int32_t *__restrict__ dump_delta,
+    uint8_t *__restrict__ dump_feas) {
     extern __shared__ int4 smem4[];
     __shared__ unsigned long long red[kInterWaves];
     __shared__ long long cnt_sh;
@@ -2927,8 +3006,8 @@ __global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4
         intra_block<TW, DUMP>(S, r0, min(S.R, r0 + G), op_mask, dump_delta, dump_feas, (int *)smem4);
         return;
     }
-    gran_block<TW, DUMP>(S, gsrc, gadj, gcc, gdep, ((int)blockIdx.x - nintra) * blockDim.x + threadIdx.x, op_mask,
-                         dump_delta, dump_feas, red, &cnt_sh);
+    gran_block<TW, DUMP>(S, P, ((int)blockIdx.x - nintra) * blockDim.x + threadIdx.x, op_mask, dump_delta, dump_feas,
+                         red, &cnt_sh);
 }
 
 // ------------------------------------------------------- general path ---
@@ -4595,56 +4674,95 @@ __global__ __launch_bounds__(kApplyThreads) void k_multi_step(const SolDev S, in
 // ------------------------------------------------------ instance checks ----
 // out[0] |= 1 value out of range, 2 asymmetric, 4 nonzero diagonal,
 //           8 bad node data; out[1] = max distance; out[2] = max e;
-// out[3] = max l; out[4] = max s; out[5] = max demand.
-__global__ __launch_bounds__(256) void k_check_dist(const int32_t *__restrict__ D, int np1,
-                                                    int32_t *out) {
-    __shared__ int ta[32][33], tb[32][33];
-    const int I = blockIdx.y * 32, J = blockIdx.x * 32;
-    const int x = threadIdx.x & 31, y0 = threadIdx.x >> 5;
-    int bad = 0, mx = 0;
-    for (int y = y0; y < 32; y += 8) {
-        const int i = I + y, j = J + x;
-        ta[y][x] = (i < np1 && j < np1) ? D[(size_t)i * np1 + j] : 0;
-        const int i2 = J + y, j2 = I + x;
-        tb[y][x] = (i2 < np1 && j2 < np1) ? D[(size_t)i2 * np1 + j2] : 0;
-    }
-    __syncthreads();
-    for (int y = y0; y < 32; y += 8) {
-        const int i = I + y, j = J + x;
-        if (i >= np1 || j >= np1) continue;
-        const int d = ta[y][x];
-        if (d < 0 || d >= (1 << 24)) bad |= 1;
-        if (d != tb[x][y]) bad |= 2;
-        if (i == j && d != 0) bad |= 4;
-        mx = max(mx, d);
-    }
-    if (bad) atomicOr(&out[0], bad);
-    atomicMax(&out[1], mx);
+// out[3] = max l; out[4] = max s; out[5] = max demand (all zero before).
+//
+// One pass over D: workgroup (I, J), I <= J, takes the 64 x 64 tiles (I, J)
+// and (J, I), compares them across the diagonal, and writes both into the
+// 16-bit copy (rows padded to `stride` with zeros; of no use when a distance
+// turns out wider).  Bound by memory: 4 bytes read and 2 written per entry.
+// The maxima go to one address, where atomics are taken one after the other,
+// so only a larger value is sent, once per workgroup.  (Tiles of 32 read from
+// both sides, an atomic per wavefront and a second pass for the copy: 308 us
+// at n = 2500 against 17.)  Diagonal workgroups also check the nodes of their
+// rows.
+constexpr int kCheckTile = 64;
+
+__device__ __forceinline__ void raise(int32_t *p, int v) {
+    if (v > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, v);
 }
 
-// 16-bit copy of D (every value < 2^16), rows padded to `stride` with zeros.
-__global__ __launch_bounds__(256) void k_pack16(const int32_t *__restrict__ D, int np1, int stride,
-                                                uint16_t *__restrict__ out) {
-    const int u = blockIdx.y;
-    for (int v = blockIdx.x * 256 + threadIdx.x; v < stride; v += gridDim.x * 256)
-        out[(size_t)u * stride + v] = v < np1 ? (uint16_t)D[(size_t)u * np1 + v] : (uint16_t)0;
+__global__ __launch_bounds__(256) void k_check_instance(const int32_t *__restrict__ D, int np1, int stride,
+                                                        uint16_t *__restrict__ D16, const int4 *__restrict__ nd,
+                                                        int has_tw, int32_t *__restrict__ out) {
+    __shared__ int ta[kCheckTile][kCheckTile + 1];
+    __shared__ int red[4][2];
+    const int I = blockIdx.y, J = blockIdx.x;
+    const int tid = threadIdx.x, x = tid & 63, wave = tid >> 6;
+    if (I <= J) {  // uniform for the workgroup
+        int bad = 0, mx = 0;
+        auto tile = [&](int bi, int bj, bool second) {
+            const int j = bj * kCheckTile + x;
+            int v[kCheckTile / 4];
+#pragma unroll
+            for (int u = 0; u < kCheckTile / 4; ++u) {
+                const int i = bi * kCheckTile + 4 * u + wave;
+                v[u] = i < np1 && j < np1 ? gld(D + (size_t)i * np1 + j) : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kCheckTile / 4; ++u) {
+                const int y = 4 * u + wave, i = bi * kCheckTile + y;
+                if (v[u] < 0 || v[u] >= (1 << 24)) bad |= 1;
+                mx = max(mx, v[u]);
+                if (!second) ta[y][x] = v[u];
+                else if (v[u] != ta[x][y]) bad |= 2;
+                if (i == j && v[u] != 0) bad |= 4;
+                if (i < np1 && j < stride) D16[(size_t)i * stride + j] = (uint16_t)v[u];
+            }
+        };
+        tile(I, J, false);
+        __syncthreads();
+        if (I != J) {
+            tile(J, I, true);
+        } else {
+            for (int y = wave; y < kCheckTile; y += 4)
+                if (ta[y][x] != ta[x][y]) bad |= 2;
+            const int i = I * kCheckTile + x;
+            if (wave == 0) {
+                const int4 q = i < np1 ? nd[i] : make_int4(0, 0, 0, 0);
+                const int lim = 1 << 26;
+                bool wrong = q.x < 0 || q.x >= lim || (i == 0 && q.x != 0);
+                if (has_tw)
+                    wrong = wrong || q.y < 0 || q.z < q.y || q.w < 0 || q.z >= lim || q.w >= lim || (i == 0 && q.w != 0);
+                if (wrong) bad |= 8;
+                int m[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    for (int off = 32; off >= 1; off >>= 1) m[k] = max(m[k], __shfl_xor(m[k], off));
+                    if (x == 0 && (k == 0 || has_tw)) raise(&out[k == 0 ? 5 : 1 + k], m[k]);
+                }
+            }
+        }
+        for (int off = 32; off >= 1; off >>= 1) {
+            bad |= __shfl_xor(bad, off);
+            mx = max(mx, __shfl_xor(mx, off));
+        }
+        if (x == 0) {
+            red[wave][0] = bad;
+            red[wave][1] = mx;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            bad = red[0][0] | red[1][0] | red[2][0] | red[3][0];
+            mx = max(max(red[0][1], red[1][1]), max(red[2][1], red[3][1]));
+            if (bad) atomicOr(&out[0], bad);
+            raise(&out[1], mx);
+        }
+    }
 }
 
-__global__ __launch_bounds__(256) void k_check_nodes(const int4 *__restrict__ nd, int np1, int has_tw,
-                                                     int32_t *out) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= np1) return;
-    const int4 q = nd[i];
-    const int lim = 1 << 26;
-    bool bad = q.x < 0 || q.x >= lim || (i == 0 && q.x != 0);
-    if (has_tw) {
-        bad = bad || q.y < 0 || q.z < q.y || q.w < 0 || q.z >= lim || q.w >= lim || (i == 0 && q.w != 0);
-        atomicMax(&out[2], q.y);
-        atomicMax(&out[3], q.z);
-        atomicMax(&out[4], q.w);
-    }
-    if (bad) atomicOr(&out[0], 8);
-    atomicMax(&out[5], q.x);
+// Check results to pinned host memory.
+__global__ void k_check_done(const int32_t *__restrict__ out, int32_t *__restrict__ host_out) {
+    if (threadIdx.x < 8) host_out[threadIdx.x] = out[threadIdx.x];
 }
 
 // Pickup amounts: chk[0] |= 1 for a negative amount or a nonzero depot
