@@ -1908,7 +1908,8 @@ struct RouteGlobal {
 // i = i0, i0 + di, ... <= L.  Without SPLIT: all of them; with it only walk per
 // first position: 0 the 2-opt / same-route swap walk, 1..3 the forward and
 // 4..6 the backward or-opt walk of segment length 1..3 (the seven walks
-// cover each move exactly once).
+// cover each move exactly once).  A step reads everything it may need at its
+// start, so that it waits for the staged values once, not once per test.
 template <bool TW, bool DUMP, bool SPLIT, class RV>
 __device__ __forceinline__ void intra_moves(const SolDev &S, const RV &V, int r, int L, int i0, int di,
                                             bool capOK, uint32_t op_mask, int walk_arg,
@@ -1916,6 +1917,7 @@ __device__ __forceinline__ void intra_moves(const SolDev &S, const RV &V, int r,
                                             uint32_t &bid) {
     const int walk = SPLIT ? walk_arg : -1;  // a compile-time -1 without the split
     const bool opSwap = op_mask & 2, op2o = op_mask & 8, opOr = op_mask & 16;
+    if (SPLIT && walk > 6) return;
     const int n = S.n;
     const uint32_t uQ = (uint32_t)S.Q;
     auto ref = [&](int p) { return p == 0 ? (uint32_t)(n + r) : (uint32_t)(V.node(p) - 1); };
@@ -1926,40 +1928,40 @@ __device__ __forceinline__ void intra_moves(const SolDev &S, const RV &V, int r,
         const int eI = V.edge(i);      // c(c_i, c_{i+1})
         const int depP = TW ? V.dep(i - 1) : 0;
         const uint32_t refI = ref(i);
+        const int bI = TW ? V.e(i) : 0, lI = TW ? V.l(i) : 0, sI = TW ? V.s(i) : 0;
         // Every step computes the deltas (and carries the segment summaries
         // along); feasibility, ids and the running minimum are evaluated
         // only where a delta can still reach the lane's best.
         // ---- 2OPT(i, j) and SWAP(i, j), j > i
         if ((op2o || opSwap) && walk <= 0) {
-            Seg rev = TW ? segAt(i) : Seg{0, 0, 0, true};
+            Seg rev = TW ? seg_node(bI, lI, sI) : Seg{0, 0, 0, true};
             Seg mid = Seg{0, 0, 0, true};
+            int ejm = eI;
 #pragma unroll 1
             for (int j = i + 1; j <= L; ++j) {
-                const int ej = V.edge(j), ejm = V.edge(j - 1);
-                if (TW) rev = seg_cat(segAt(j), ejm, rev);
+                const int ej = V.edge(j);
                 const int d1 = V.dd(i - 1, j), d2 = V.dd(i, j + 1);
+                const int dA = V.dd(j, i + 1), dB = V.dd(j - 1, i);
+                const uint32_t refJ = ref(j);
+                const int bJ = TW ? V.e(j) : 0, lJ = TW ? V.l(j) : 0, sJ = TW ? V.s(j) : 0, zJ1 = TW ? V.z(j + 1) : 0;
+                const Seg nj = seg_node(bJ, lJ, sJ);
+                if (TW) rev = seg_cat(nj, ejm, rev);
                 const int dlt2 = d1 + d2 - eP - ej;
-                int dS = dlt2, dA = 0, dB = 0;
-                if (j > i + 1) {
-                    dA = V.dd(j, i + 1);
-                    dB = V.dd(j - 1, i);
-                    dS = d1 + dA + dB + d2 - eP - eI - ejm - ej;
-                }
+                const int dS = j > i + 1 ? d1 + dA + dB + d2 - eP - eI - ejm - ej : dlt2;
                 if (DUMP || (capOK && min(op2o ? dlt2 : kNoDelta, opSwap ? dS : kNoDelta) <= bd)) {
                     bool tw2 = true;
-                    if (TW) tw2 = seg_pass(rev, depP + d1) + d2 <= V.z(j + 1);
+                    if (TW) tw2 = seg_pass(rev, depP + d1) + d2 <= zJ1;
                     bool twS = tw2;
                     if (TW && j > i + 1) {
                         const int arr0 = depP + d1;
-                        bool ok = arr0 <= V.l(j);
-                        const int t0 = max(arr0, V.e(j)) + V.s(j);
+                        bool ok = arr0 <= lJ;
+                        const int t0 = max(arr0, bJ) + sJ;
                         const int dM = seg_pass(mid, t0 + dA);
                         const int arrI = dM + dB;
-                        ok = ok && dM < kInf && arrI <= V.l(i);
-                        const int t2 = max(arrI, V.e(i)) + V.s(i);
-                        twS = ok && (t2 + d2 <= V.z(j + 1));
+                        ok = ok && dM < kInf && arrI <= lI;
+                        const int t2 = max(arrI, bI) + sI;
+                        twS = ok && (t2 + d2 <= zJ1);
                     }
-                    const uint32_t refJ = ref(j);
                     const uint32_t lo = min(refI, refJ), hi = max(refI, refJ);
                     if (op2o) {
                         const uint32_t id = (12u * uQ + lo) * uQ + hi;
@@ -1979,7 +1981,8 @@ __device__ __forceinline__ void intra_moves(const SolDev &S, const RV &V, int r,
                     }
                 }
                 // middle c_{i+1} .. c_j for the next j
-                if (TW) mid = (j == i + 1) ? segAt(j) : seg_cat(mid, ejm, segAt(j));
+                if (TW) mid = (j == i + 1) ? nj : seg_cat(mid, ejm, nj);
+                ejm = ej;
             }
         }
         if (!opOr || walk == 0) continue;
@@ -1994,25 +1997,29 @@ __device__ __forceinline__ void intra_moves(const SolDev &S, const RV &V, int r,
             const int base = dPW - eP - eG;
             Seg sig = Seg{0, 0, 0, true};
             if (TW) {
-                sig = segAt(i);
+                sig = seg_node(bI, lI, sI);
 #pragma unroll 1
                 for (int q = 1; q < k; ++q) sig = seg_cat(sig, V.edge(i + q - 1), segAt(i + q));
             }
             // ---- forward: right after c_j, j >= i+k (middle c_{i+k} .. c_j)
             Seg mid = Seg{0, 0, 0, true};
+            int ejm = eG;
 #pragma unroll 1
             for (int j = w; j <= (walk <= 3 ? L : w - 1); ++j) {
-                if (TW) mid = (j == w) ? segAt(j) : seg_cat(mid, V.edge(j - 1), segAt(j));
-                const int dVF = V.dd(j, i), dGV = V.dd(g, j + 1);
-                const int dlt = base + dVF + dGV - V.edge(j);
+                const int ej = V.edge(j), dVF = V.dd(j, i), dGV = V.dd(g, j + 1);
+                const uint32_t refJ = ref(j);
+                const int zJ1 = TW ? V.z(j + 1) : 0;
+                if (TW) mid = (j == w) ? segAt(j) : seg_cat(mid, ejm, segAt(j));
+                ejm = ej;
+                const int dlt = base + dVF + dGV - ej;
                 if (DUMP || (capOK && dlt <= bd)) {
                     bool tw = true;
                     if (TW) {
                         const int dm = seg_pass(mid, depP + dPW);
                         const int ds = dm >= kInf ? kInf : seg_pass(sig, dm + dVF);
-                        tw = ds < kInf && ds + dGV <= V.z(j + 1);
+                        tw = ds < kInf && ds + dGV <= zJ1;
                     }
-                    const uint32_t id = ((16u + k) * uQ + refI) * uQ + ref(j);
+                    const uint32_t id = ((16u + k) * uQ + refI) * uQ + refJ;
                     if (DUMP) {
                         dump_delta[id] = dlt;
                         dump_feas[id] = (uint8_t)(capOK | (tw << 1));
@@ -2023,19 +2030,23 @@ __device__ __forceinline__ void intra_moves(const SolDev &S, const RV &V, int r,
             // ---- backward: right after c_j, j <= i-2 (middle c_{j+1} .. c_{i-1})
             const int zW = TW ? V.z(w) : 0;
             mid = Seg{0, 0, 0, true};
+            int ej1 = 0;  // c(c_{j+1}, c_{j+2})
 #pragma unroll 1
             for (int j = i - 2; j >= (walk < 0 || walk >= 4 ? 0 : i - 1); --j) {
-                if (TW) mid = (j == i - 2) ? segAt(i - 1) : seg_cat(segAt(j + 1), V.edge(j + 1), mid);
-                const int dVF = V.dd(j, i), dGV = V.dd(g, j + 1);
-                const int dlt = base + dVF + dGV - V.edge(j);
+                const int ej = V.edge(j), dVF = V.dd(j, i), dGV = V.dd(g, j + 1);
+                const uint32_t refJ = ref(j);
+                const int depJ = TW ? V.dep(j) : 0;
+                if (TW) mid = (j == i - 2) ? segAt(i - 1) : seg_cat(segAt(j + 1), ej1, mid);
+                ej1 = ej;
+                const int dlt = base + dVF + dGV - ej;
                 if (DUMP || (capOK && dlt <= bd)) {
                     bool tw = true;
                     if (TW) {
-                        const int ds = seg_pass(sig, V.dep(j) + dVF);
+                        const int ds = seg_pass(sig, depJ + dVF);
                         const int dmm = ds >= kInf ? kInf : seg_pass(mid, ds + dGV);
                         tw = dmm < kInf && dmm + dPW <= zW;
                     }
-                    const uint32_t id = ((16u + k) * uQ + refI) * uQ + ref(j);
+                    const uint32_t id = ((16u + k) * uQ + refI) * uQ + refJ;
                     if (DUMP) {
                         dump_delta[id] = dlt;
                         dump_feas[id] = (uint8_t)(capOK | (tw << 1));
@@ -2079,7 +2090,6 @@ __device__ __forceinline__ RouteLds stage_route(const SolDev &S, int off, int L,
 }
 
 constexpr int kIntraMaxGroup = 8;  // routes per intra-route work item
-constexpr int kIntraWalks = 7;     // walks per first position (2-opt / swap, 3 forward and 3 backward or-opt)
 constexpr int kGatherBatch = 8;    // distance gathers in flight per lane while staging
 
 // The P x P distance sub-blocks of G staged routes (route k = r0 + k: P[k]
@@ -2298,17 +2308,16 @@ __device__ __forceinline__ void intra_group(const SolDev &S, const IntraItem &it
 }
 
 // The intra-route moves of one (i, j) cell of route r (L customers, staged
-// view V, 1 <= i <= L, 0 <= j <= L): 2OPT(i, j) and SWAP(i, j) when i < j,
-// and the or-opt moves of the segments of length k = 1..3 that start at c_i
-// to right after c_j (j >= i + k forward, j <= i - 2 backward).  The cells of
-// the grid hold every intra-route move exactly once, with the deltas,
-// feasibility and ids of intra_moves; the deltas come first (every position
-// clamped into the route, invalid moves masked), and the time-window
-// summaries of a move are built only when its delta can still reach bd, in
-// the order intra_moves builds them.
-template <bool TW>
-__device__ __forceinline__ void intra_cell(const SolDev &S, const RouteLds &V, int r, int L, int i, int j,
-                                           bool opSwap, bool op2o, bool opOr, int &bd, uint32_t &bid) {
+// view V, 1 <= i <= L, 0 <= j <= L) without windows: 2OPT(i, j) and
+// SWAP(i, j) when i < j, and the or-opt moves of the segments of length
+// k = 1..3 that start at c_i to right after c_j (j >= i + k forward,
+// j <= i - 2 backward).  The cells of the grid hold every intra-route move
+// exactly once, with the deltas and ids of intra_moves (every position
+// clamped into the route, invalid moves masked).
+template <bool DUMP>
+__device__ __forceinline__ void intra_cell(const SolDev &S, const RouteLds &V, int r, int L, int i, int j, bool capOK,
+                                           bool opSwap, bool op2o, bool opOr, int32_t *__restrict__ dump_delta,
+                                           uint8_t *__restrict__ dump_feas, int &bd, uint32_t &bid) {
     const int jm = max(j - 1, 0);
     const int eP = V.edge(i - 1), eI = V.edge(i), eJ = V.edge(j), eJm = V.edge(jm);
     const int d1 = V.dd(i - 1, j), d2 = V.dd(i, j + 1);  // j + 1 <= L + 1
@@ -2329,64 +2338,26 @@ __device__ __forceinline__ void intra_cell(const SolDev &S, const RouteLds &V, i
         vOr[k - 1] = opOr && i + k - 1 <= L && (j >= i + k || j <= i - 2);
         if (vOr[k - 1]) m = min(m, dOr[k - 1]);
     }
-    if (m > bd) return;  // rare late in a search: no move of the cell can reach the lane's best
+    if (!DUMP && m > bd) return;  // rare late in a search: no move of the cell can reach the lane's best
 
     const uint32_t uQ = (uint32_t)S.Q;
     const uint32_t refI = (uint32_t)(V.node(i) - 1);
     const uint32_t refJ = j == 0 ? (uint32_t)(S.n + r) : (uint32_t)(V.node(j) - 1);
-    const int depP = TW ? V.dep(i - 1) : 0;
-    auto segAt = [&](int p) { return seg_node(V.e(p), V.l(p), V.s(p)); };
-    if (up && min(op2o ? dlt2 : kNoDelta, opSwap ? dS : kNoDelta) <= bd) {
-        bool tw2 = true, twS = true;
-        if (TW) {
-            // c_i .. c_j reversed
-            Seg rev = segAt(i);
-            for (int q = i + 1; q <= j; ++q) rev = seg_cat(segAt(q), V.edge(q - 1), rev);
-            tw2 = seg_pass(rev, depP + d1) + d2 <= V.z(j + 1);
-            twS = tw2;
-            if (j > i + 1) {
-                const int arr0 = depP + d1;
-                bool ok = arr0 <= V.l(j);
-                const int t0 = max(arr0, V.e(j)) + V.s(j);
-                // middle c_{i+1} .. c_{j-1}
-                Seg mid = segAt(i + 1);
-                for (int q = i + 2; q <= j - 1; ++q) mid = seg_cat(mid, V.edge(q - 1), segAt(q));
-                const int dM = seg_pass(mid, t0 + dA);
-                const int arrI = dM + dB;
-                ok = ok && dM < kInf && arrI <= V.l(i);
-                const int t2 = max(arrI, V.e(i)) + V.s(i);
-                twS = ok && (t2 + d2 <= V.z(j + 1));
-            }
+    auto record = [&](int d, uint32_t id) {
+        if (DUMP) {
+            dump_delta[id] = d;
+            dump_feas[id] = (uint8_t)(capOK | 2);
         }
+        if (capOK) consider(d, id, bd, bid);
+    };
+    if (up) {
         const uint32_t lo = min(refI, refJ), hi = max(refI, refJ);
-        if (op2o && tw2) consider(dlt2, (12u * uQ + lo) * uQ + hi, bd, bid);
-        if (opSwap && twS) consider(dS, (5u * uQ + lo) * uQ + hi, bd, bid);
+        if (op2o) record(dlt2, (12u * uQ + lo) * uQ + hi);
+        if (opSwap) record(dS, (5u * uQ + lo) * uQ + hi);
     }
 #pragma unroll
-    for (int k = 1; k <= 3; ++k) {
-        if (!vOr[k - 1] || dOr[k - 1] > bd) continue;
-        bool tw = true;
-        if (TW) {
-            const int g = i + k - 1, w = i + k;
-            Seg sig = segAt(i);
-            for (int q = 1; q < k; ++q) sig = seg_cat(sig, V.edge(i + q - 1), segAt(i + q));
-            const int dPW = V.dd(i - 1, w), dGV = V.dd(g, j + 1);
-            if (j >= w) {  // forward: middle c_w .. c_j
-                Seg mid = segAt(w);
-                for (int q = w + 1; q <= j; ++q) mid = seg_cat(mid, V.edge(q - 1), segAt(q));
-                const int dm = seg_pass(mid, depP + dPW);
-                const int ds = dm >= kInf ? kInf : seg_pass(sig, dm + dVF);
-                tw = ds < kInf && ds + dGV <= V.z(j + 1);
-            } else {  // backward: middle c_{j+1} .. c_{i-1}
-                Seg mid = segAt(i - 1);
-                for (int q = i - 2; q >= j + 1; --q) mid = seg_cat(segAt(q), V.edge(q), mid);
-                const int ds = seg_pass(sig, V.dep(j) + dVF);
-                const int dmm = ds >= kInf ? kInf : seg_pass(mid, ds + dGV);
-                tw = dmm < kInf && dmm + dPW <= V.z(w);
-            }
-        }
-        if (tw) consider(dOr[k - 1], ((16u + k) * uQ + refI) * uQ + refJ, bd, bid);
-    }
+    for (int k = 1; k <= 3; ++k)
+        if (vOr[k - 1]) record(dOr[k - 1], ((16u + k) * uQ + refI) * uQ + refJ);
 }
 
 // A route staged in a region has fewer than 64 positions, so a row of its
@@ -2748,7 +2719,8 @@ __device__ __forceinline__ void intra_group_flat(const SolDev &S, const IntraIte
 #pragma unroll 1
         for (int i0 = 1; i0 <= L; i0 += rpi) {
             const int i = i0 + di;
-            if (di < rpi && i <= L) intra_cell<TW>(S, V, item.r0 + k, L, i, j, opSwap, op2o, opOr, bd, bid);
+            if (di < rpi && i <= L)
+                intra_cell<false>(S, V, item.r0 + k, L, i, j, true, opSwap, op2o, opOr, nullptr, nullptr, bd, bid);
         }
     }
     wave_lds_sync();  // the region is free for the next group
@@ -2894,12 +2866,17 @@ __device__ __forceinline__ void stage_group(const SolDev &S, const GroupStage &g
 }
 
 // Single-solution form: one workgroup evaluates the intra-route moves of the
-// routes [r0, r1), wavefront w < 7 walk w of every first position (see
-// intra_moves), and commits the best.  The group is staged once for all
-// seven (one staging per wavefront gathered every distance seven times, and
-// each wavefront alone needed two rounds of gathers for it).  A group that
-// does not fit the region, or has more first positions than lanes, is taken
-// route by route; a route that does not fit reads the slot arrays directly.
+// routes [r0, r1) and commits the best.  The group is staged once for all its
+// wavefronts (one staging per wavefront gathered every distance seven times,
+// in two rounds).  Without windows every (i, j) cell is then a thread's own;
+// with them wavefront w takes walk w of every first position (see
+// intra_moves), the segment summaries carried along: the launch waits for its
+// longest chain, and for CVRP routes of about 20 customers the cells end
+// 2.8 us after the staging where the walks took 5.6.  (With windows, tables of
+// every segment's summary in LDS and cells that read them took as long as the
+// walks, 8 us.)  A group that does not fit the region, or has more first
+// positions than lanes, is taken route by route; a route that does not fit
+// reads the slot arrays directly.
 template <bool TW, bool DUMP>
 __device__ __forceinline__ void intra_block(const SolDev &S, int r0, int r1, uint32_t op_mask,
                                             int32_t *__restrict__ dump_delta, uint8_t *__restrict__ dump_feas,
@@ -2909,52 +2886,58 @@ __device__ __forceinline__ void intra_block(const SolDev &S, int r0, int r1, uin
     int bd = initial_bound(op_mask);
     uint32_t bid = 0xFFFFFFFFu;
     GroupStage g;
-    const int G = r1 - r0;
-    group_layout(S, r0, G, g);
-    if (g.sumL <= 64 && g.words <= kIntraRegionBytes / 4) {
-        // lane -> (route k, first position i) and that route's staged view
-        int myk = -1, myi = 0, myP = 0, myAt = 0, myOff = 0, cum = 0;
-#pragma unroll
-        for (int k = 0; k < kIntraMaxGroup; ++k) {
-            const int L = g.P[k] - 2;
-            if (k < G && myk < 0 && lane < cum + L) {
-                myk = k;
-                myi = lane - cum + 1;
-                myP = g.P[k];
-                myAt = g.at[k];
-                myOff = g.offs[k];
-            }
-            cum += k < G ? L : 0;
+    for (int ra = r0; ra < r1;) {
+        // the rest of the group when it fits, else its next route
+        int G = r1 - ra;
+        group_layout(S, ra, G, g);
+        if (G > 1 && (g.sumL > 64 || g.words > kIntraRegionBytes / 4)) {
+            G = 1;
+            group_layout(S, ra, 1, g);
         }
-        const bool capOK = myk >= 0 && gld(S.b4 + myOff).z <= S.cap;
+        if (ra != r0) __syncthreads();  // the previous route is done with the region
+        const int load = lane < G ? gld(S.b4 + gld(S.roff + ra + lane)).z : 0;
+        if (g.words > kIntraRegionBytes / 4) {
+            const int L = g.P[0] - 2;
+            const RouteGlobal V{&S, g.offs[0], L, S.has_tw ? sld(S.node4).z : kTwOff};
+            intra_moves<TW, DUMP, true>(S, V, ra, L, lane + 1, 64, __builtin_amdgcn_readfirstlane(load) <= S.cap, op_mask,
+                                        walk, dump_delta, dump_feas, bd, bid);
+            ra += G;
+            continue;
+        }
         stage_group<TW>(S, g, region);
-        if (myk >= 0 && walk < kIntraWalks) {
-            int *b = region + myAt;
-            const RouteLds V{b,           b + myP,     b + 2 * myP, b + 3 * myP, b + 4 * myP,
-                             b + 5 * myP, b + 6 * myP, b + 7 * myP, myP};
-            intra_moves<TW, DUMP, true>(S, V, r0 + myk, myP - 2, myi, 1 << 30, capOK, op_mask, walk, dump_delta,
-                                        dump_feas, bd, bid);
-        }
-    } else {
-        for (int k = 0; k < G; ++k) {
-            const int r = r0 + k;
-            group_layout(S, r, 1, g);
-            const int off = g.offs[0], P = g.P[0], L = P - 2;
-            const bool capOK = gld(S.b4 + off).z <= S.cap;
-            if (g.words <= kIntraRegionBytes / 4) {
-                __syncthreads();  // the previous route is done with the region
-                stage_group<TW>(S, g, region);
-                const RouteLds V{region,         region + P,     region + 2 * P, region + 3 * P, region + 4 * P,
-                                 region + 5 * P, region + 6 * P, region + 7 * P, P};
-                if (walk < kIntraWalks)
-                    intra_moves<TW, DUMP, true>(S, V, r, L, lane + 1, 64, capOK, op_mask, walk, dump_delta, dump_feas,
-                                                bd, bid);
-            } else if (walk < kIntraWalks) {
-                const RouteGlobal V{&S, off, L, S.has_tw ? sld(S.node4).z : kTwOff};
-                intra_moves<TW, DUMP, true>(S, V, r, L, lane + 1, 64, capOK, op_mask, walk, dump_delta, dump_feas, bd,
-                                            bid);
+        const unsigned long long caps = __builtin_amdgcn_ballot_w64(load <= S.cap);  // bit k: route ra + k
+        // element f of the group (first positions with windows, else cells) ->
+        // route k and the index within it; one pass, or several
+        auto per_route = [&](int P) { return P == 0 ? 0 : (TW ? P - 2 : (P - 1) * (P - 2)); };
+        int count = 0;
+#pragma unroll
+        for (int k = 0; k < kIntraMaxGroup; ++k) count += per_route(g.P[k]);
+        for (int f = TW ? lane : (int)threadIdx.x; f < count; f += TW ? 64 : (int)blockDim.x) {
+            int pk = g.P[0], ak = g.at[0], kk = 0, c = 0, ck = 0;
+#pragma unroll
+            for (int k = 1; k < kIntraMaxGroup; ++k) {
+                c += per_route(g.P[k - 1]);
+                if (g.P[k] && f >= c) {
+                    pk = g.P[k];
+                    ak = g.at[k];
+                    kk = k;
+                    ck = c;
+                }
+            }
+            int *b = region + ak;
+            const RouteLds V{b, b + pk, b + 2 * pk, b + 3 * pk, b + 4 * pk, b + 5 * pk, b + 6 * pk, b + 7 * pk, pk};
+            const bool capOK = caps >> kk & 1;
+            const int W = pk - 1;
+            if constexpr (TW) {
+                intra_moves<TW, DUMP, true>(S, V, ra + kk, W - 1, f - ck + 1, 1 << 30, capOK, op_mask, walk, dump_delta,
+                                            dump_feas, bd, bid);
+            } else if (DUMP || capOK) {
+                const int i = (f - ck) / W + 1, j = f - ck - (i - 1) * W;
+                intra_cell<DUMP>(S, V, ra + kk, W - 1, i, j, capOK, op_mask & 2, op_mask & 8, op_mask & 16, dump_delta,
+                                 dump_feas, bd, bid);
             }
         }
+        ra += G;
     }
     wave_argmin_commit(bd, bid, S.best_key);
 }
@@ -2966,10 +2949,10 @@ __device__ __forceinline__ void intra_block(const SolDev &S, int r0, int r1, uin
 // The launch is bound by its chains of dependent reads, not by its work, so
 // the descriptor comes by value (its pointers are there with the kernel's
 // arguments) and the items are computed instead of read.  Per launch, with
-// the groups staged by the whole workgroup: n = 1000 CVRP 11.7 us (18.8 with
-// descriptor and items in memory and a staging per wavefront), n = 201 VRPTW
-// 12.9 (18.3), granular n = 1000 VRPTW 13.4 (21.3).  The dynamic LDS is the
-// larger of the two needs.
+// the groups staged by the whole workgroup: n = 1000 CVRP 11.1 us (18.8 with
+// descriptor and items in memory and a staging per wavefront; 11.8 with walks
+// for the intra-route moves), n = 201 VRPTW 12.3 (18.3), granular n = 1000
+// VRPTW 13.2 (21.3).  The dynamic LDS is the larger of the two needs.
 template <bool TW, bool DUMP>
 __global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_solution(
     const SolDev S, int nintra, int G, uint32_t op_mask, int32_t *__restrict__ dump_delta,
