@@ -158,7 +158,8 @@ __device__ __forceinline__ void wave_argmin_commit(int bd, uint32_t bid, unsigne
 // solution's key.  Every thread of the block must call it.
 __device__ __forceinline__ void block_argmin_commit(int bd, uint32_t bid, unsigned long long *key,
                                     unsigned long long *red) {
-    wave_argmin(bd, bid);
+    // (a wavefront that found nothing, most of them late in a search, has nothing to reduce)
+    if (__builtin_amdgcn_ballot_w64(bid != 0xFFFFFFFFu)) wave_argmin(bd, bid);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) red[wave] = (bd >= kAdmissibleBound || bid == 0xFFFFFFFFu) ? ~0ull : pack_key(bd, bid);
     __syncthreads();
@@ -1141,6 +1142,9 @@ __device__ __forceinline__ int from_next_lane(int v) { return __builtin_amdgcn_m
 // lane i receives lane i-1 (lane 0 receives 0)
 __device__ __forceinline__ int from_prev_lane(int v) { return __builtin_amdgcn_mov_dpp(v, 0x138, 0xF, 0xF, true); }
 
+constexpr int kPenalty = 1 << 30;     // added to the delta of an inadmissible move
+constexpr int kAdmissible = 1 << 29;  // every admissible delta is below this
+
 // Column-side (lane) values of one chunk, kept in registers while the
 // wavefront walks rows against it.  Every feasibility condition below is
 // written as a difference that must be >= 0; "bad" values are 0 when a
@@ -1168,16 +1172,21 @@ struct ColRaw {
     int4 ta, tb, tt, tw;
 };
 
+// The slot arrays, their addresses read once per item.
+struct SlotPtrs {
+    const int4 *a4, *b4, *t4, *w4;
+};
+
 template <bool TW>
-__device__ __forceinline__ ColRaw col_fetch(const SolDev &S, int cb) {
+__device__ __forceinline__ ColRaw col_fetch(const SlotPtrs &P, int Q, int cb) {
     const int lane = threadIdx.x & 63;
-    const int tc = min(max(cb - 1 + lane, 0), S.Q);
+    const int tc = min(max(cb - 1 + lane, 0), Q);
     ColRaw c;
-    c.ta = gld(S.a4 + tc);
-    c.tb = gld(S.b4 + tc);
+    c.ta = gld(P.a4 + tc);
+    c.tb = gld(P.b4 + tc);
     if (TW) {
-        c.tt = gld(S.t4 + tc);
-        c.tw = gld(S.w4 + tc);
+        c.tt = gld(P.t4 + tc);
+        c.tw = gld(P.w4 + tc);
     } else {
         c.tt = make_int4(0, 0, 0, 0);
         c.tw = make_int4(0, 0, 0, 0);
@@ -1187,10 +1196,9 @@ __device__ __forceinline__ ColRaw col_fetch(const SolDev &S, int cb) {
 
 // Lane values of the chunk at cb from its raw attributes.  routeLast: route
 // of the last owned column (-1 if none), wave-uniform.
-__device__ __forceinline__ void col_setup(const SolDev &S, int cb, const ColRaw &c, uint32_t op_mask, LaneCol &L,
+__device__ __forceinline__ void col_setup(int Q, int n, int cb, const ColRaw &c, uint32_t op_mask, LaneCol &L,
                                           int &routeLast) {
     const int lane = threadIdx.x & 63;
-    const int Q = S.Q, n = S.n;
     const int t = cb - 1 + lane;
     L.ta = c.ta;
     L.tb = c.tb;
@@ -1217,8 +1225,7 @@ __device__ __forceinline__ void col_setup(const SolDev &S, int cb, const ColRaw 
     L.cSwap = L.negTw + offSwap;
     L.c2s = L.negTz + off2s;
     const int lastLane = min(kColsPerWave, Q - cb);
-    const int rl = __shfl(L.ta.y, max(lastLane, 0));
-    routeLast = __builtin_amdgcn_readfirstlane(lastLane >= 1 ? rl : -1);
+    routeLast = lastLane >= 1 ? __builtin_amdgcn_readlane(L.ta.y, lastLane) : -1;
 }
 
 // ---- LDS block of distance rows of an inter-route item.  While the rows of
@@ -1233,13 +1240,19 @@ __device__ __forceinline__ void col_setup(const SolDev &S, int cb, const ColRaw 
 // (vmcnt) before a barrier publishes them.  `wave` is the wavefront index
 // (uniform).
 template <bool W16>
-__device__ __forceinline__ void drow_issue(const SolDev &S, void *rows, int base, int x0, int cnt, int wave) {
+__device__ __forceinline__ void drow_issue(const SolDev &S, const int4 *a4, int Q, void *rows, int base, int x0,
+                                           int cnt, int wave) {
     const int lane = threadIdx.x & 63;
-    const int words = W16 ? S.stride16 / 2 : S.np1;  // dwords per row
-    for (int r = wave; r < cnt; r += kInterWaves) {
+    const int stride = W16 ? S.stride16 : S.np1;  // elements per row
+    const int words = W16 ? stride / 2 : stride;  // dwords per row
+    const char *const D = W16 ? (const char *)S.D16 : (const char *)S.D;
+    // lane k: the node of this wavefront's k-th row (cnt <= 64 * kInterWaves),
+    // read together: a scalar read per row had each row wait for the last
+    const int nodes = nodeof(gld(&a4[min(max(x0 + min(wave + lane * kInterWaves, cnt - 1), 0), Q)].x));
+    for (int r = wave, k = 0; r < cnt; r += kInterWaves, ++k) {
         const int x = x0 + r;
-        const int node = nodeof(sld(S.a4 + min(max(x, 0), S.Q)).x);
-        const int *src = W16 ? (const int *)(S.D16 + (size_t)node * S.stride16) : S.D + (size_t)node * S.np1;
+        const int node = __builtin_amdgcn_readlane(nodes, k);
+        const int *src = (const int *)(D + (size_t)node * stride * (W16 ? 2 : 4));
         int *dst = (int *)rows + (x - base) * words;
         if (W16) {  // rows are 16-byte aligned multiples of 16 bytes: four dwords per lane
             for (int c = 0; c < words; c += 256) {
@@ -1261,8 +1274,6 @@ template <bool W16> struct DistElem { typedef int type; };
 template <> struct DistElem<true> { typedef uint16_t type; };
 
 constexpr int kSign = (int)0x80000000;
-constexpr int kPenalty = 1 << 30;     // added to the delta of an inadmissible move
-constexpr int kAdmissible = 1 << 29;  // every admissible delta is below this
 
 // delta, plus kPenalty when viol < 0
 __device__ __forceinline__ int penalise(int d, int viol) {
@@ -1399,16 +1410,6 @@ __device__ __forceinline__ int committed_delta(const SolDev &S) {
     return k == ~0ull ? kAdmissibleBound : (int)((uint32_t)(k >> 32) ^ 0x80000000u);
 }
 
-// The (column chunk, row) pairs of the sub-block of nr rows starting at slot
-// sb, chunk-major, with chunks of kColsPerWave columns from slot sb + 1:
-// [lo, hi) is the equal share of wavefront `wave`.
-__device__ __forceinline__ void wave_share(int Q, int sb, int nr, int wave, int &lo, int &hi) {
-    const int k = (Q - sb - 1 + kColsPerWave - 1) / kColsPerWave;
-    const long long T = (long long)k * nr;
-    lo = (int)(T * wave / kInterWaves);
-    hi = (int)(T * (wave + 1) / kInterWaves);
-}
-
 // Whole-workgroup evaluation of one inter-route item: the row slots
 // [s0, s1) against every column slot after the row.  The distance rows
 // (16-bit when W16) are staged in LDS in sub-blocks of h = S.tile_rows rows
@@ -1428,9 +1429,21 @@ __device__ __forceinline__ void wave_share(int Q, int sb, int nr, int wave, int 
 // initial bound.  Every threshold is the delta of an admissible move of this
 // neighbourhood (or the bound), so no move that could be the minimum (or tie
 // with it) is ever skipped.
-// With dump arrays every move is evaluated.  smem4 is the dynamic LDS area;
-// red holds kInterWaves keys.
-template <bool TW, bool DUMP, bool W16, bool CNT = false>
+// With dump arrays every move is evaluated.  smem4 is the dynamic LDS area,
+// free when the call starts; red holds kInterWaves keys (BATCH: unused).
+//
+// Per item the time goes to chains, not to bytes or instructions: of 12 us for
+// about 18 rows of 2000 columns, 2.7 until the rows are in LDS, 6 for some 40
+// passes per wavefront, 2.5 for its barriers and the commit.  Hence the rows'
+// nodes in one read (each row's own scalar read waited for the one before),
+// the next chunk's columns fetched on one path only (where two paths met, the
+// wait for this run's columns became one for the next run's), no read for the
+// rows' routes, and for a batch a commit without barriers: the evaluation
+// launch of 256 solutions of 100..2000 customers 165 -> 150 us, of one of
+// 1000 (CVRP) 11.1 -> 10.7 us.  (Fewer instructions per pass gained nothing:
+// four rows at a time without a branch 164 us, 13 instead of 17 vector
+// instructions 154.)
+template <bool TW, bool DUMP, bool W16, bool CNT = false, bool BATCH = false>
 __device__ __forceinline__ void inter_item(const SolDev &S, const InterItem &item, uint32_t op_mask,
                            int32_t *__restrict__ dump_delta, uint8_t *__restrict__ dump_feas,
                            int4 *smem4, unsigned long long *red, int *thr_sh) {
@@ -1440,6 +1453,7 @@ __device__ __forceinline__ void inter_item(const SolDev &S, const InterItem &ite
     const bool opRel = op_mask & 1, opSwap = op_mask & 2, op2s = op_mask & 4;
     const int Q = S.Q, np1 = S.np1, n = S.n, cap = S.cap, h = S.tile_rows;
     const uint32_t uQ = (uint32_t)Q;
+    const SlotPtrs P{S.a4, S.b4, S.t4, S.w4};
     const int s0 = item.s0, s1 = item.s1;
     const int nsb = (s1 - s0 + h - 1) / h;
     const int NB = h + 2;
@@ -1451,21 +1465,26 @@ __device__ __forceinline__ void inter_item(const SolDev &S, const InterItem &ite
     uint32_t bid = 0xFFFFFFFFu;
     uint32_t nfull = 0;  // CNT: this wavefront's pairs evaluated in full (wave-uniform)
 
+    // this wavefront's share of the sub-block: (chunk, row) pairs from chunk j,
+    // row r0 on, `left` of them; the first chunk's column attributes; lane k:
+    // the route of the sub-block's k-th row (at most 64 rows)
+    int j = 0, r0 = 0, left = 0, rowRoute = 0;
+    ColRaw nxt;
+    // everything a sub-block reads besides its distance rows, together with them
+    auto sub_block = [&](int sb, int nr) {
+        const int T = max(0, (Q - sb - 1 + kColsPerWave - 1) / kColsPerWave) * nr;  // below 2^14
+        const int lo = T * wave / kInterWaves;
+        left = T * (wave + 1) / kInterWaves - lo;
+        j = lo / nr;
+        r0 = lo - j * nr;
+        rowRoute = gld(&P.a4[sb + min(lane, nr - 1)].y);
+        nxt = col_fetch<TW>(P, Q, sb + 1 + j * kColsPerWave);
+    };
+
     // prologue: the distance rows of sub-block 0 (with its halo rows)
-    __syncthreads();  // the previous item is done with LDS
     if (!DUMP && threadIdx.x == 0) *thr_sh = committed_delta(S);
-    drow_issue<W16>(S, rows, s0 - 1, s0 - 1, min(h, s1 - s0) + 2, wave);
-    ColRaw nxt;  // column attributes fetched ahead for the chunk at nxt_cb
-    int nxt_cb = -1;
-    {  // the first run's, together with the rows
-        int lo0, hi0;
-        const int nr0 = min(h, s1 - s0);
-        wave_share(Q, s0, nr0, wave, lo0, hi0);
-        if (s0 + 1 < Q && lo0 < hi0) {
-            nxt_cb = s0 + 1 + (lo0 / nr0) * kColsPerWave;
-            nxt = col_fetch<TW>(S, nxt_cb);
-        }
-    }
+    drow_issue<W16>(S, P.a4, Q, rows, s0 - 1, s0 - 1, min(h, s1 - s0) + 2, wave);
+    sub_block(s0, min(h, s1 - s0));
     __builtin_amdgcn_s_waitcnt(0);
     for (int i = 0; i < nsb; ++i) {
         const int sb = s0 + i * h;
@@ -1493,48 +1512,31 @@ __device__ __forceinline__ void inter_item(const SolDev &S, const InterItem &ite
                 }
             }
             __syncthreads();
-            drow_issue<W16>(S, rows, sb - 1, sb + 1, nr, wave);
+            drow_issue<W16>(S, P.a4, Q, rows, sb - 1, sb + 1, nr, wave);
+            sub_block(sb, nr);
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
         }
         // columns: every slot after the sub-block's first row (pairs in the
-        // same route are skipped per pair)
-        if (sb + 1 < Q) {
-            int idx, hi;
-            wave_share(Q, sb, nr, wave, idx, hi);
-            // run = (chunk j, rows [r0, r1)); every run after the first of a
-            // share starts the next chunk at row 0
-            int j = idx / nr, r0 = idx - j * nr;
-            for (; idx < hi; ++j, r0 = 0) {
-                const int r1 = min(nr, r0 + (hi - idx));
-                idx += r1 - r0;
+        // same route are skipped per pair).  Runs = (chunk j, rows [r0, r1));
+        // every run after the first of a share starts the next chunk at row 0.
+        if (left > 0) {
+            for (; left > 0; ++j, r0 = 0) {
+                const int r1 = min(nr, r0 + left);
+                left -= r1 - r0;
                 const int cb = sb + 1 + j * kColsPerWave;
-                const ColRaw cur = nxt_cb == cb ? nxt : col_fetch<TW>(S, cb);
-                // fetch the chunk of this wavefront's next run (here or in a
-                // later sub-block) while this one is evaluated
-                int cb2 = -1;
-                if (idx < hi) {
-                    cb2 = cb + kColsPerWave;
-                } else {
-                    for (int i2 = i + 1; i2 < nsb && cb2 < 0; ++i2) {
-                        const int sb2 = s0 + i2 * h, nr2 = min(h, s1 - sb2);
-                        int lo2, hi2;
-                        if (sb2 + 1 >= Q) break;
-                        wave_share(Q, sb2, nr2, wave, lo2, hi2);
-                        if (lo2 < hi2) cb2 = sb2 + 1 + (lo2 / nr2) * kColsPerWave;
-                    }
-                }
-                if (cb2 >= 0 && cb2 != cb) nxt = col_fetch<TW>(S, cb2);
-                else if (cb2 == cb) nxt = cur;
-                nxt_cb = cb2;
+                // the next run's chunk is fetched while this one is evaluated
+                const ColRaw cur = nxt;
+                if (left > 0) nxt = col_fetch<TW>(P, Q, cb + kColsPerWave);
                 LaneCol L;
                 int routeLast;
-                col_setup(S, cb, cur, op_mask, L, routeLast);
+                col_setup(Q, n, cb, cur, op_mask, L, routeLast);
                 int x = sb + r0;  // row slot
                 // rows whose route precedes the chunk's last route (slots are
-                // route-major, so those before that route's first slot), at
-                // most up to the end of the run
-                const int xlim = routeLast >= 0 ? min(sb + r1, sld1(S.roff + routeLast)) : x;
+                // route-major, so they come first), at most up to the end of
+                // the run
+                const int before = (int)__builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < nr && rowRoute < routeLast));
+                const int xlim = sb + min(r1, before);
                 // register window over the distance rows: x - 1, x, x + 1
                 const DT *pp = rows + (x - sb) * rs;
                 int gp = pp[L.node];
@@ -1543,7 +1545,7 @@ __device__ __forceinline__ void inter_item(const SolDev &S, const InterItem &ite
                 pp += rs;
                 int gn = pp[L.node];
                 uint32_t ro = (uint32_t)x * 16u;  // byte offset of row x's slot attributes
-                int4 ra = sld_at(S.a4, ro), rb = sld_at(S.b4, ro);
+                int4 ra = sld_at(P.a4, ro), rb = sld_at(P.b4, ro);
                 const int thrRun = DUMP ? 0 : __hip_atomic_load(thr_sh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 // The passes screen against the run's threshold alone (the delta
                 // of an admissible move, or the initial bound): a lane's own
@@ -1561,8 +1563,8 @@ __device__ __forceinline__ void inter_item(const SolDev &S, const InterItem &ite
                                 int &wnn) {
                     pp = min(pp + rs, rowsLast);
                     wnn = pp[L.node];  // row x + 2 (past the halo on the last row: unused)
-                    rAn = sld_at(S.a4, ro + 16u);  // x + 1 <= Q
-                    rBn = sld_at(S.b4, ro + 16u);
+                    rAn = sld_at(P.a4, ro + 16u);  // x + 1 <= Q
+                    rBn = sld_at(P.b4, ro + 16u);
                     const int gR = from_next_lane(w0);  // D[s][succ(t)]
                     const int gL = from_prev_lane(w0);  // D[s][pred(t)]
                     bool full = true;
@@ -1591,8 +1593,8 @@ __device__ __forceinline__ void inter_item(const SolDev &S, const InterItem &ite
                     if (full) {
                         int4 rt = make_int4(0, 0, 0, 0), rw = make_int4(0, 0, 0, 0);
                         if (TW) {
-                            rt = sld_at(S.t4, ro);
-                            rw = sld_at(S.w4, ro);
+                            rt = sld_at(P.t4, ro);
+                            rw = sld_at(P.w4, ro);
                         }
                         const RowVals R = row_vals(rA, rB, cap, n);
                         pair_moves<TW, DUMP>(L, R, rt, rw, wp, w0, wn, gR, gL, uQ, opRel, opSwap, op2s, dump_delta,
@@ -1631,7 +1633,14 @@ __device__ __forceinline__ void inter_item(const SolDev &S, const InterItem &ite
     }
     if (CNT && !DUMP && (op_mask & kImprovingOnly) && lane == 0 && nfull)
         atomicAdd((unsigned long long *)(S.acc + kAccFullPairs), (unsigned long long)nfull);
-    block_argmin_commit(bd, bid, S.best_key, red);
+    if (BATCH) {
+        // an item of many: a wavefront commits by itself, without the
+        // workgroup's barriers, and only what is still the workgroup's best
+        const int best = __hip_atomic_load(thr_sh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (__builtin_amdgcn_ballot_w64(bid != 0xFFFFFFFFu && bd <= best)) wave_argmin_commit(bd, bid, S.best_key);
+    } else {
+        block_argmin_commit(bd, bid, S.best_key, red);
+    }
 }
 
 // ------------------------------------------- granular inter-route eval ---
@@ -3171,7 +3180,7 @@ __device__ __forceinline__ void gen_strip(const SolDev &S, int s0, int s1, uint3
     const uint16_t *rows = (const uint16_t *)smem4;
     const int rs = S.stride16;
     if (threadIdx.x == 0) *thr_sh = committed_delta(S);
-    if (W16) drow_issue<true>(S, smem4, s0 - 1, s0 - 1, s1 - s0 + 1 + A, wave);
+    if (W16) drow_issue<true>(S, S.a4, S.Q, smem4, s0 - 1, s0 - 1, s1 - s0 + 1 + A, wave);
     int bd = initial_bound(op_mask);
     uint32_t bid = 0xFFFFFFFFu;
     GenQueue &q = queues[wave];
@@ -3755,7 +3764,6 @@ __global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4
     uint32_t *__restrict__ qctr, const IntraItem *__restrict__ intra, const int *__restrict__ ixoff, int nx,
     uint32_t op_mask) {
     extern __shared__ int4 smem4[];
-    __shared__ unsigned long long red[kInterWaves];
     __shared__ int thr_sh;
     const int wave = threadIdx.x >> 6;
     const int x = blockIdx.x % nx, j = blockIdx.x / nx, step = gridDim.x / nx;
@@ -3794,14 +3802,14 @@ __global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4
             constexpr bool CNT = (PH & 4) != 0;
             if (S.has_tw) {
                 if (S.D16)
-                    inter_item<true, false, true, CNT>(S, item, op_mask, nullptr, nullptr, smem4, red, &thr_sh);
+                    inter_item<true, false, true, CNT, true>(S, item, op_mask, nullptr, nullptr, smem4, nullptr, &thr_sh);
                 else
-                    inter_item<true, false, false, CNT>(S, item, op_mask, nullptr, nullptr, smem4, red, &thr_sh);
+                    inter_item<true, false, false, CNT, true>(S, item, op_mask, nullptr, nullptr, smem4, nullptr, &thr_sh);
             } else {
                 if (S.D16)
-                    inter_item<false, false, true, CNT>(S, item, op_mask, nullptr, nullptr, smem4, red, &thr_sh);
+                    inter_item<false, false, true, CNT, true>(S, item, op_mask, nullptr, nullptr, smem4, nullptr, &thr_sh);
                 else
-                    inter_item<false, false, false, CNT>(S, item, op_mask, nullptr, nullptr, smem4, red, &thr_sh);
+                    inter_item<false, false, false, CNT, true>(S, item, op_mask, nullptr, nullptr, smem4, nullptr, &thr_sh);
             }
             // slot (round + 1) & 1 was last read in the previous round, before
             // that round's closing barrier
