@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdlib>
@@ -24,8 +25,8 @@ thread_local std::string g_err;
 
 // Pinned staging of one host thread: the record and state of single-solution
 // calls (first 4 KiB), then the routes a call sends or receives (offsets and
-// customers of the largest solution).  Every call that uses it synchronises
-// before it returns; the thread's end gives it back.
+// customers of the largest solution).  Every call that uses it returns only
+// once the device has written the last of it; the thread's end gives it back.
 constexpr size_t kPinRecord = 4096, kPinBytes = kPinRecord + 16 + 4 * (2 * (size_t)TGA_MAX_Q + 2);
 struct PinnedBuf {
     char *host = nullptr;
@@ -897,6 +898,24 @@ extern "C" int tga_solution_violations(tga_solution_t sol, int64_t *load_excess,
     return TGA_OK;
 }
 
+// Wait for the last word of a record in pinned memory, for a short while (true
+// when it came: the finalize launch, the last on the stream, has written all
+// it writes).  The stream's own synchronisation sees the end of a launch only
+// through the runtime's signal, 4 us later (a call on 100 customers 23.1 us
+// with it, 19.2 without; on 1000 with windows 33.7 and 28.3); it stays for what
+// takes longer (a long queue before the call, a dump) and for errors, a capture
+// among them.
+static bool record_arrived(const int32_t *host) {
+    const auto start = std::chrono::steady_clock::now();
+    do {
+        for (int k = 0; k < 64; ++k) {
+            if (__atomic_load_n(host + kHostDone, __ATOMIC_ACQUIRE)) return true;
+            __builtin_ia32_pause();
+        }
+    } while (std::chrono::steady_clock::now() - start < std::chrono::microseconds(200));
+    return false;
+}
+
 // One evaluation of a solution whose workspace is set up: evaluation launch,
 // record-mode finalize, and the record and state[0..3] in `host` (48 bytes;
 // pinned or pageable).
@@ -906,12 +925,13 @@ extern "C" int tga_solution_violations(tga_solution_t sol, int64_t *load_excess,
 static int eval_record(tga_solution *sol, uint32_t op_mask, tga_move_t *best, int32_t *dump_delta,
                        uint8_t *dump_feas, hipStream_t st, int32_t *host, bool host_pinned) {
     int32_t *dev_view = host_pinned ? (int32_t *)g_pin.dev : nullptr;  // where the kernel may write `host`
+    if (dev_view) __atomic_store_n(host + kHostDone, 0, __ATOMIC_RELAXED);
     launch_solution_eval(sol, op_mask, dump_delta, dump_feas, st);
     k_finalize_one<<<1, kApplyThreads, 0, st>>>(sol->h, kModeRecord, op_mask, dev_view);
     HIPCHK(hipGetLastError());
     if (!dev_view)
         HIPCHK(hipMemcpyAsync(host, sol->h.rec, 32 + 16, hipMemcpyDeviceToHost, st));  // record, state[0..3]
-    HIPCHK(hipStreamSynchronize(st));
+    if (!dev_view || !record_arrived(host)) HIPCHK(hipStreamSynchronize(st));
     if (host[8 + kStStatus] == 1) {
         memset(best, 0, sizeof *best);
         best->version = sol->version;

@@ -4262,7 +4262,11 @@ __device__ __forceinline__ void finalize_block(const SolDev &S, int mode, uint32
                 host_out[8 + kStSteps] = steps;
                 host_out[8 + kStStatus] = found ? 0 : 1;
                 host_out[8 + kStVersion] = version;
+                // then the word the host waits for: everything this thread
+                // wrote, here and in the workspace, is visible before it, and
+                // in record mode nothing is written after it
                 __threadfence_system();
+                __hip_atomic_store(host_out + kHostDone, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             }
         }
     }

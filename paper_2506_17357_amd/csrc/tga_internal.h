@@ -79,6 +79,9 @@ struct SolDev {
     long long *acc;   // kAcc* below
 };
 
+// word of a host record that is set last (see finalize_block)
+constexpr int kHostDone = 15;
+
 // state[] entries
 enum {
     kStDone = 0,       // local optimum (or step cap) reached in LS mode

@@ -101,3 +101,32 @@ def test_general_steps(tga, problem):
         off, cust, _ = S.get()
         assert (steps, mv) == (len(ids), moves)
         assert np.array_equal(off, fin.offsets) and np.array_equal(cust, fin.customers)
+
+
+@pytest.mark.parametrize("queued", [False, True])
+def test_record_on_several_streams(tga, queued):
+    """Evaluations and moves in turn on three streams, each behind a queue of other work that outlasts the
+    short wait for the record or behind none."""
+    import torch
+    print("streams", "queued" if queued else "idle", flush=True)
+    inst, sol = make("vrptw", [13, 2, 9, 11, 0, 12, 10, 8, 14, 21], 600)
+    S = tga.Solution(tga.Instance.from_workload(inst), sol.offsets, sol.customers)
+    final, ids, _, _ = oracle.local_search(inst, sol, max_steps=6)
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    work = torch.zeros(1 << 26, device="cuda")  # 256 MiB: a pass takes about 0.1 ms
+    torch.cuda.synchronize()
+    for k, want in enumerate(ids):
+        st = streams[k % 3]
+        if queued:
+            with torch.cuda.stream(st):
+                for _ in range(8):
+                    work.add_(1.0)
+        best = S.eval(0x1F, stream=st)
+        assert best is not None and best.id == want
+        again = S.eval(0x1F, stream=streams[(k + 1) % 3])
+        assert (again.delta, again.id) == (best.delta, best.id)
+        S.apply(best, stream=streams[(k + 2) % 3])
+    off, cust, cost = S.get()
+    assert np.array_equal(off, final.offsets) and np.array_equal(cust, final.customers)
+    assert cost == oracle.cost(inst, final)[0]
+    torch.cuda.synchronize()
