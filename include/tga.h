@@ -116,8 +116,8 @@ typedef struct {
 
 /* Device workspace sizes (bytes) for an instance of n customers and for a
  * solution with R route slots.  Returns 0 when n or R is out of range.  A
- * solution workspace holds the slot attributes, the work lists of the
- * single-solution form and, per route, the route's distance sub-block as
+ * solution workspace holds the slot attributes, the staging of a new or
+ * rewritten route layout and, per route, the route's distance sub-block as
  * last staged by the intra-route evaluation (6.5 KB per route; an entry is
  * used only while the route's node sequence is unchanged). */
 size_t tga_instance_workspace_bytes(int32_t n);
@@ -205,8 +205,9 @@ int tga_solution_reload(tga_solution_t sol, const int32_t *offsets, const int32_
  * Optional per-move dump (testing): dump_delta (int32) and dump_feas (uint8)
  * are device arrays of 20*Q*Q entries indexed by move id; the library writes
  * only entries that are moves, the caller pre-fills the rest.  Both NULL, or
- * both set.  Synchronises `stream` (the returned record is the best-move
- * latency). */
+ * both set.  On return everything queued on `stream` before the call and by
+ * it has taken effect (the call waits for its record, the last thing its
+ * launches write, or for the stream). */
 int tga_eval_neighborhood(tga_solution_t sol, uint32_t op_mask, tga_move_t *best,
                           int32_t *dump_delta, uint8_t *dump_feas, void *stream);
 
@@ -214,7 +215,7 @@ int tga_eval_neighborhood(tga_solution_t sol, uint32_t op_mask, tga_move_t *best
  * a HIP graph, tight serving loops, harnesses that forbid hipMalloc): the
  * result of tga_set_solution followed by tga_eval_neighborhood(op_mask, no
  * dump) on the routes given, without a caller workspace.  The solution's
- * attribute arrays and work lists go into a library-owned static device
+ * arrays go into a library-owned static device
  * buffer of TGA_STATIC_SCRATCH_BYTES per GPU (held from the library's load
  * until the process ends); the call allocates no device or pinned memory.
  *   inst      a loaded instance (its buffers as for tga_load_instance).

@@ -171,15 +171,6 @@ __device__ __forceinline__ void block_argmin_commit(int bd, uint32_t bid, unsign
     __syncthreads();
 }
 
-// Insert one node with window [e, l] and service s: arrive from a departure
-// time `dep` over `cin`, leave over `cout` to a successor whose latest
-// feasible arrival is `z`.
-__device__ __forceinline__ bool tw_insert(int dep, int cin, int e, int l, int s, int cout, int z) {
-    const int arr = dep + cin;
-    const int st = arr > e ? arr : e;
-    return (arr <= l) & (st + s + cout <= z);
-}
-
 // (duration, earliest finish, latest arrival) summary of a segment under hard
 // windows: arriving at time a <= la, the segment is served and left at
 // max(a + dur, ef).
@@ -3017,19 +3008,9 @@ __global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4
 // >= 0), and the deliveries of a new route bound its largest load from
 // below.
 
-// Suffix summary strictly after slot x (the end depot when x is last).
-__device__ __forceinline__ Tw tw_after(const SolDev &S, int x, const Tw &dep) {
-    return nodeof(gld(S.a4 + x + 1).x) == 0 ? dep : tw_of(gld(S.pb4 + x + 1));
-}
-
 __device__ __forceinline__ Tw tw_node_at(const SolDev &S, int x) {
     const int4 w = gld(S.w4 + x);
     return tw_node(w.x, w.y, w.z);
-}
-
-// Load summary strictly after slot x (the end depot: empty, when x is last).
-__device__ __forceinline__ Ld ld_after(const SolDev &S, int x) {
-    return nodeof(gld(S.a4 + x + 1).x) == 0 ? Ld{0, 0, 0} : ld_of(gld(S.ql4 + x + 1));
 }
 
 // Record one move of the general path.  Penalised mode: every move is
