@@ -1046,9 +1046,9 @@ __global__ __launch_bounds__(kBuildRoutes * 64) void k_build_routes(const SolDev
 }
 
 // The same for a layout with a route of 64 customers or more, by the block
-// scans of one workgroup (always fresh).
-__global__ __launch_bounds__(kApplyThreads) void k_build_long(const SolDev S, const int32_t *__restrict__ off,
-                                                              const int32_t *__restrict__ cust) {
+// scans of one workgroup (always fresh).  off and cust may be the staging
+// arrays this kernel writes, so they are not __restrict__.
+__global__ __launch_bounds__(kApplyThreads) void k_build_long(const SolDev S, const int32_t *off, const int32_t *cust) {
     __shared__ ApplyShared sh;
     const int R = S.R, T = blockDim.x, tid = threadIdx.x;
     // slot s of route r takes customer s - r - 1; from the last slots down, as
