@@ -54,6 +54,16 @@ int fail(int code, const char *fmt, ...) {
         if (e_ != hipSuccess) return fail(TGA_EDEVICE, "%s: %s", #x, hipGetErrorString(e_)); \
     } while (0)
 
+// After launches that use this thread's pinned buffer: on an error (of a launch,
+// or left by an earlier call of the caller's) nothing of them may still be under
+// way when the call returns, or it would write into a later call's record.
+int launched(hipStream_t st) {
+    const hipError_t e = hipGetLastError();
+    if (e == hipSuccess) return TGA_OK;
+    (void)hipStreamSynchronize(st);
+    return fail(TGA_EDEVICE, "launch: %s", hipGetErrorString(e));
+}
+
 int pinned(void **p) {
     if (!g_pin.host) {
         hipError_t e = hipHostMalloc((void **)&g_pin.host, kPinBytes, hipHostMallocDefault);
@@ -353,7 +363,7 @@ extern "C" int tga_load_instance(int32_t n, const int32_t *dist, const int32_t *
     void *pin;
     if ((rc = pinned(&pin))) return rc;
     if (g_pin.dev) k_check_done<<<1, 64, 0, st>>>(chk, (int32_t *)g_pin.dev);
-    HIPCHK(hipGetLastError());
+    if ((rc = launched(st))) return rc;
     if (!g_pin.dev) HIPCHK(hipMemcpyAsync(pin, chk, 32, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     int32_t r[8];
@@ -551,7 +561,7 @@ static int upload_routes(tga_solution *S, const int32_t *offsets, const int32_t 
         k_build_routes<<<(R + kBuildRoutes - 1) / kBuildRoutes, kBuildRoutes * 64, 0, st>>>(S->h, off, cust, 1, c);
     else
         k_build_long<<<1, kApplyThreads, 0, st>>>(S->h, off, cust);
-    HIPCHK(hipGetLastError());
+    if (int rc = launched(st)) return rc;
     HIPCHK(hipStreamSynchronize(st));
     return TGA_OK;
 }
@@ -619,13 +629,11 @@ static int solution_init(tga_solution *S, tga_instance_t inst, int32_t R, const 
     h.state = (int32_t *)(base + L.state);
     h.acc = (long long *)(base + L.acc);
     h.part = (long long *)(base + L.part);
-    hipError_t e = hipSuccess;
     // the fields the kernels only ever add to or test start at zero: record,
     // state and accumulators, and the build's counter
     k_zero_i32<<<1, 128, 0, st>>>(h.rec, (32 + 4 * 16 + 8 * kAccCount) / 4);
     k_zero_i32<<<1, 64, 0, st>>>((int32_t *)h.part, 2);
-    e = hipGetLastError();
-    if (e != hipSuccess) return fail(TGA_EDEVICE, "set_solution: %s", hipGetErrorString(e));
+    if ((rc = launched(st))) return rc;
     return upload_routes(S, offsets, customers, use_pinned, st);
 }
 
@@ -928,7 +936,7 @@ static int eval_record(tga_solution *sol, uint32_t op_mask, tga_move_t *best, in
     if (dev_view) __atomic_store_n(host + kHostDone, 0, __ATOMIC_RELAXED);
     launch_solution_eval(sol, op_mask, dump_delta, dump_feas, st);
     k_finalize_one<<<1, kApplyThreads, 0, st>>>(sol->h, kModeRecord, op_mask, dev_view);
-    HIPCHK(hipGetLastError());
+    if (int rc = launched(st)) return rc;
     if (!dev_view)
         HIPCHK(hipMemcpyAsync(host, sol->h.rec, 32 + 16, hipMemcpyDeviceToHost, st));  // record, state[0..3]
     if (!dev_view || !record_arrived(host)) HIPCHK(hipStreamSynchronize(st));
@@ -1181,7 +1189,7 @@ extern "C" int tga_get_solution(tga_solution_t sol, int32_t *offsets, int32_t *c
     int32_t *p = (int32_t *)((char *)pin + kPinRecord);
     int32_t *out = g_pin.dev ? (int32_t *)(g_pin.dev + kPinRecord) : (int32_t *)sol->h.nr_alt;
     k_export<<<(sol->Q + 255) / 256, 256, 0, st>>>(sol->h, out);
-    HIPCHK(hipGetLastError());
+    if ((rc = launched(st))) return rc;
     if (!g_pin.dev) HIPCHK(hipMemcpyAsync(p, out, 4 * ints, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (cost) *cost = *(const long long *)p;
