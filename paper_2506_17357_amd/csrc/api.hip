@@ -82,7 +82,9 @@ int pinned(void **p) {
 }
 
 struct DevProps {
-    int ok = 0, cus = 0, max_lds = 0, attr_ok = 0;
+    int ok = 0, cus = 0;
+    int max_lds = 0;    // dynamic LDS of an evaluation workgroup
+    int lds_total = 0;  // static and dynamic LDS of a workgroup
 };
 
 DevProps g_props;
@@ -106,7 +108,7 @@ int props(DevProps *out) {
                              (const void *)k_eval_solution<false, false>, (const void *)k_eval_solution<true, false>,
                              (const void *)k_eval_solution<false, true>, (const void *)k_eval_solution<true, true>};
         // the general path's kernels also hold their move queues
-        const int dyn_gen = dyn - kInterWaves * (int)sizeof(GenQueue);
+        const int dyn_gen = dyn - (int)kGenQueueBytes;
         const void *gen[] = {(const void *)k_eval_general<false, false, false, true>,
                              (const void *)k_eval_general<false, false, true, true>,
                              (const void *)k_eval_general<false, true, false, true>,
@@ -121,8 +123,8 @@ int props(DevProps *out) {
         for (const void *f : gen)
             if (ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_gen) != hipSuccess) ok = false;
         (void)hipGetLastError();  // do not leave a refused attribute as the sticky error
-        g_props.attr_ok = ok;
         g_props.max_lds = ok ? dyn : std::min(lds, 65536);
+        g_props.lds_total = ok ? lds : std::min(lds, 65536);
         g_props.ok = 1;
     }
     *out = g_props;
@@ -784,31 +786,24 @@ static void to_move(const int32_t *rec, tga_move_t *m) {
 
 // General path (penalised mode, pickups, operator variants, multi-move).
 // The rows go in strips of equal work, as many as let two workgroups share
-// every compute unit with the intra-route groups, up to 24 rows staged at a
-// time where 56 KiB of LDS hold them with their halo (one row before, one
-// after, three with the variants).  Without a 16-bit copy of D, or where one
-// row and its halo do not fit, the distances are gathered from D and nothing
-// is staged.
-static size_t general_lds_limit() {
-    DevProps P;
-    if (props(&P) != TGA_OK) return 0;
-    return std::max(0, P.max_lds - (P.attr_ok ? kInterWaves * (int)sizeof(GenQueue) : 0));
-}
-
+// every compute unit with the intra-route groups, as many staged at a time as
+// general_rows says, with their halo (one row before, one after, three with
+// the variants).  Without a 16-bit copy of D, or where one row and its halo do
+// not fit, the distances are gathered from D and nothing is staged.
 template <bool TW, bool PD, bool EXT>
 static void launch_eval_general(const tga_solution *sol, uint32_t op_mask, int32_t *dd, uint8_t *df, hipStream_t st) {
     const EvalShape e = intra_shape(sol, op_mask);
     const int halo = EXT ? 4 : 2, np1 = sol->h.np1;
-    auto lds_of = [&](int rows) { return rows_lds(np1, rows + halo - 2, true); };
-    const bool w16 = sol->h.D16 && lds_of(1) <= general_lds_limit();
-    int rows = 24;
-    while (w16 && rows > 1 && lds_of(rows) > 57344) --rows;
     DevProps P;
-    const int cus = props(&P) == TGA_OK ? P.cus : 256;
+    const bool known = props(&P) == TGA_OK;
+    const int cus = known ? P.cus : 256;
+    const int staged = sol->h.D16 && known ? general_rows(np1, halo, P.lds_total) : 0;
+    const bool w16 = staged > 0;
+    const int rows = w16 ? staged : kGenRows;
     const int strips = std::min(std::max(2 * cus - e.nintra, cus / 2), (sol->Q + 1) / 2);
     const int grid = e.nintra + ((op_mask & (7 | TGA_OP_VARIANTS)) ? strips : 0);
     if (!grid) return;
-    const size_t lds = std::max(w16 ? lds_of(rows) : 0, (size_t)kGenRegionBytes);
+    const size_t lds = std::max(w16 ? general_rows_lds(np1, halo, rows) : 0, (size_t)kGenRegionBytes);
     if (w16) k_eval_general<TW, PD, EXT, true><<<grid, kInterThreads, lds, st>>>(sol->h, e.nintra, e.G, rows, op_mask, dd, df);
     else k_eval_general<TW, PD, EXT, false><<<grid, kInterThreads, lds, st>>>(sol->h, e.nintra, e.G, rows, op_mask, dd, df);
 }
@@ -1043,8 +1038,8 @@ extern "C" int tga_solution_multi_stats(tga_solution_t sol, int64_t out[2], void
 
 // ------------------------------------------------- no-allocation variant ----
 
-// Per-device scratch of tga_eval_routes_static: the solution workspace
-// (descriptor, slot attributes, work lists) of the call.  Each GPU the
+// Per-device scratch of tga_eval_routes_static: the solution workspace (slot
+// attributes, staging, route blocks, state) of the call.  Each GPU the
 // library runs on holds one copy until the process ends.  In host code the
 // name stands for the host-side shadow, not a device address: kernels and
 // copies take the address hipGetSymbolAddress returns for the current device.

@@ -3116,6 +3116,7 @@ struct GenQueue {
     int move[kGenQueue], bound[kGenQueue], delta[kGenQueue];
     int step_min[kGenSteps];  // least lower bound of each of the wavefront's steps
 };
+static_assert(kInterWaves * sizeof(GenQueue) == kGenQueueBytes, "move queues");
 
 // Whole-workgroup evaluation of the inter-route moves of the row slots
 // [s0, s1) (fewer than 256) against every column slot of a later route.

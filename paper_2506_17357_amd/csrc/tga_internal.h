@@ -144,6 +144,29 @@ struct IntraItem {
     int32_t sol, r0, r1, pad;
 };
 
+// General path: a workgroup's move queues (static LDS), and the room left for
+// the other static words of any kernel.
+constexpr size_t kGenQueueBytes = 20480, kStaticWordsBytes = 1024;
+constexpr int kGenRows = 24;               // rows of a strip taken at a time
+constexpr size_t kGenStageBytes = 57344;   // LDS the staged rows take (two workgroups share a compute unit)
+
+// LDS of `rows` staged rows of 16-bit distances and their halo rows.
+inline size_t general_rows_lds(int np1, int halo, int rows) {
+    return (size_t)(rows + halo) * 2 * (size_t)stride16_of(np1);
+}
+
+// Rows the general path stages at a time when a workgroup may hold lds_total
+// bytes of static and dynamic LDS: as many as kGenStageBytes hold, or one
+// where only that fits at all; 0 when it does not.
+inline int general_rows(int np1, int halo, size_t lds_total) {
+    const size_t fixed = kGenQueueBytes + kStaticWordsBytes;
+    const size_t limit = lds_total > fixed ? lds_total - fixed : 0;
+    const size_t want = limit < kGenStageBytes ? limit : kGenStageBytes;
+    int rows = kGenRows;
+    while (rows > 1 && general_rows_lds(np1, halo, rows) > want) --rows;
+    return general_rows_lds(np1, halo, rows) <= limit ? rows : 0;
+}
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 }  // namespace tga
