@@ -559,10 +559,9 @@ static int upload_routes(tga_solution *S, const int32_t *offsets, const int32_t 
         HIPCHK(hipMemcpyAsync(S->h.roff_alt, offsets, 4 * ((size_t)R + 1), hipMemcpyHostToDevice, st));
         HIPCHK(hipMemcpyAsync(S->h.nr_alt, customers, 4 * (size_t)n, hipMemcpyHostToDevice, st));
     }
-    if (maxL < 64)
-        k_build_routes<<<(R + kBuildRoutes - 1) / kBuildRoutes, kBuildRoutes * 64, 0, st>>>(S->h, off, cust, 1, c);
-    else
-        k_build_long<<<1, kApplyThreads, 0, st>>>(S->h, off, cust);
+    const int grid = (R + kBuildRoutes - 1) / kBuildRoutes;
+    if (maxL < 64) k_build_routes<false><<<grid, kBuildRoutes * 64, 0, st>>>(S->h, off, cust, 1, c);
+    else k_build_routes<true><<<grid, kBuildRoutes * 64, 0, st>>>(S->h, off, cust, 1, c);
     if (int rc = launched(st)) return rc;
     HIPCHK(hipStreamSynchronize(st));
     return TGA_OK;
@@ -1149,7 +1148,7 @@ extern "C" int tga_ls_run(tga_solution_t sol, uint32_t op_mask, int32_t max_step
             launch_solution_eval(sol, op_mask | kImprovingOnly, nullptr, nullptr, st);
             if (multi) {
                 k_multi_step<<<1, kApplyThreads, 0, st>>>(sol->h, kModeLS, op_mask);
-                k_build_routes<<<(sol->R + kBuildRoutes - 1) / kBuildRoutes, kBuildRoutes * 64, 0, st>>>(
+                k_build_routes<false><<<(sol->R + kBuildRoutes - 1) / kBuildRoutes, kBuildRoutes * 64, 0, st>>>(
                     sol->h, sol->h.roff_alt, (const int32_t *)sol->h.nr_alt, 0, BuildCounts{});
             } else
                 k_finalize_one<<<1, kApplyThreads, 0, st>>>(sol->h, kModeLS, op_mask, nullptr);

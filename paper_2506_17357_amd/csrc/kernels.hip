@@ -420,27 +420,24 @@ __device__ __forceinline__ void solution_totals(const SolDev &S, const int32_t *
 }
 
 // Attributes of the slots [lo, hi) of the layout (nr, roffn), a union of
-// whole routes, from their nodes (nr[s] = {node, route}; nr is then reused
-// as scratch for the scans' A and Z).  `full`: the whole layout (also the
-// route offsets and the sentinel slot Q); otherwise the other slots are
-// already right.  Route distances, cost and |N(S)| are refreshed either way.
+// whole routes, from their nodes (nr[ST * s] = {node, route} for slot s; it is
+// then reused as scratch for the scans' A and Z), and those routes' distances.
 // Requires blockDim.x == kApplyThreads.
+template <int ST>
 __device__ __forceinline__ void rebuild_range(const SolDev &S, int2 *nr, const int32_t *roffn, int lo, int hi,
-                                              bool full, ApplyShared &sh) {
-    const int Q = S.Q, R = S.R, n = S.n, np1 = S.np1;
+                                              ApplyShared &sh) {
+    const int n = S.n, np1 = S.np1;
     const int tid = threadIdx.x, T = blockDim.x;
     const int32_t *D = S.D;
     const int4 *nd = S.node4;
     const bool tw = S.has_tw;
 
-    if (full)
-        for (int r = tid; r <= R; r += T) gst(S.roff + r, gld(roffn + r));
     // pass 1: node, route, edge, per-node data, ref map
     for (int s = lo + tid; s < hi; s += T) {
-        const int2 x = gld(nr + s);
+        const int2 x = gld(nr + ST * s);
         const int node = x.x, r = x.y;
         const int first = gld(roffn + r), last = gld(roffn + r + 1) - 1;
-        const int succ = s < last ? gld(nr + s + 1).x : 0;
+        const int succ = s < last ? gld(nr + ST * (s + 1)).x : 0;
         int4 q = gld(nd + node);
         if (!tw) q = make_int4(q.x, 0, kTwOff, 0);
         const int edge = gld(D + (size_t)node * np1 + succ);
@@ -450,13 +447,6 @@ __device__ __forceinline__ void rebuild_range(const SolDev &S, int2 *nr, const i
         gst(S.b4 + s, make_int4(cust ? q.x : 0, 0, 0, 0));
         gst(S.ref2slot + (cust ? node - 1 : n + r), s);
     }
-    if (full && tid == 0) {
-        gst(S.a4 + Q, make_int4(0, R, 0, 0));
-        gst(S.b4 + Q, make_int4(0, 0, 0, 0));
-        gst(S.w4 + Q, make_int4(tw ? gld(nd).y : 0, tw ? gld(nd).z : kTwOff, 0, 0));
-        gst(S.t4 + Q, make_int4(kInf, kNeg, kInf, kNeg));
-        gst(S.pdist + Q, 0);
-    }
     __threadfence_block();
     __syncthreads();
     // pass 2: removal delta and incident-edge sums (customers)
@@ -464,7 +454,7 @@ __device__ __forceinline__ void rebuild_range(const SolDev &S, int2 *nr, const i
         int4 a = gld(S.a4 + s);
         if (s == gld(roffn + a.y)) continue;
         const int4 ap = gld(S.a4 + s - 1);
-        const int succ = s + 1 < gld(roffn + a.y + 1) ? gld(nr + s + 1).x : 0;
+        const int succ = s + 1 < gld(roffn + a.y + 1) ? gld(nr + ST * (s + 1)).x : 0;
         const int dpw = gld(D + (size_t)nodeof(ap.x) * np1 + succ);
         a.w = dpw - ap.z - a.z;
         gst(S.a4 + s, a);
@@ -489,9 +479,9 @@ __device__ __forceinline__ void rebuild_range(const SolDev &S, int2 *nr, const i
             b.y = run.load;
             gst(S.b4 + s, b);
             gst(S.pdist + s, run.dist);
-            int2 z = gld(nr + s);
+            int2 z = gld(nr + ST * s);
             z.x = tw ? fwd_apply(run, e0) : 0;  // A[s]
-            gst(nr + s, z);
+            gst(nr + ST * s, z);
         }
     }
     __threadfence_block();
@@ -499,9 +489,9 @@ __device__ __forceinline__ void rebuild_range(const SolDev &S, int2 *nr, const i
     // backward scan: latest feasible arrival Z (windows only)
     if (!tw) {
         for (int s = beg; s < end; ++s) {
-            int2 z = gld(nr + s);
+            int2 z = gld(nr + ST * s);
             z.y = kTwOff;
-            gst(nr + s, z);
+            gst(nr + ST * s, z);
         }
     } else {
         BwdElem agg = bwd_identity();
@@ -510,9 +500,9 @@ __device__ __forceinline__ void rebuild_range(const SolDev &S, int2 *nr, const i
         const int l0 = gld(nd).z;
         for (int s = end - 1; s >= beg; --s) {
             run = bwd_cat(bwd_elem(S, roffn, s), run);
-            int2 z = gld(nr + s);
+            int2 z = gld(nr + ST * s);
             z.y = bwd_apply(run, l0);  // Z[s]
-            gst(nr + s, z);
+            gst(nr + ST * s, z);
         }
     }
     __threadfence_block();
@@ -530,15 +520,15 @@ __device__ __forceinline__ void rebuild_range(const SolDev &S, int2 *nr, const i
         const int first = gld(roffn + a.y), last = gld(roffn + a.y + 1) - 1;
         const int rload = gld(S.b4 + last).y;
         const int4 w = gld(S.w4 + s);
-        const int2 az = gld(nr + s);
+        const int2 az = gld(nr + ST * s);
         const int A = az.x;
         const int dep = A >= kInf ? kInf : A + w.z;
-        const int zn = s < last ? gld(nr + s + 1).y : l0;
+        const int zn = s < last ? gld(nr + ST * (s + 1)).y : l0;
         int adp = kInf;
         int flags = flagsof(a.x);
         int4 b = gld(S.b4 + s);
         if (s != first) {
-            const int Ap = gld(nr + s - 1).x;
+            const int Ap = gld(nr + ST * (s - 1)).x;
             adp = Ap >= kInf ? kInf : Ap + gld(S.w4 + s - 1).z;
             if (rload - b.x <= cap) flags |= kFlagRemCap;
             // without this node: predecessor departure + c(pred, succ) <= Z(succ)
@@ -553,7 +543,6 @@ __device__ __forceinline__ void rebuild_range(const SolDev &S, int2 *nr, const i
     }
     __threadfence_block();
     __syncthreads();
-    solution_totals(S, roffn, sh);
 }
 
 // Attributes of one slot of a route, as route_attr computes them.
@@ -661,10 +650,6 @@ __device__ __forceinline__ void store_attr(const SolDev &S, const SlotAttr &x, i
     gst(S.pdist + s, x.pdist);
     gst(S.ref2slot + x.ref, s);
     if (lane == L) gst(S.rdist + r, x.rdist);
-}
-
-__device__ __forceinline__ void rebuild(const SolDev &S, int2 *nr, const int32_t *roffn, ApplyShared &sh) {
-    rebuild_range(S, nr, roffn, 0, S.Q, true, sh);
 }
 
 // ------------------------------------------------------ penalised mode ---
@@ -912,20 +897,24 @@ __device__ __forceinline__ void gen_route_wave(const SolDev &S, int off, int L, 
     if (lane <= L) gst(S.g4 + off + lane, make_int4(rem.x, rem.y, peak, warp));
 }
 
-// Summaries of every route and the totals (one block): a wavefront per
-// route, one thread for a route too long for it.
-__device__ __forceinline__ void pen_all(const SolDev &S, ApplyShared &sh) {
+// Summaries of route r by one wavefront (one thread of it when the route is
+// too long), from its slots' attributes.
+__device__ __forceinline__ void gen_route_any(const SolDev &S, int r) {
     const int lane = threadIdx.x & 63;
-    for (int r = threadIdx.x >> 6; r < S.R; r += blockDim.x >> 6) {
-        const int off = gld(S.roff + r), L = gld(S.roff + r + 1) - off - 1;
-        if (L >= 64) {
-            if (lane == 0) gen_route(S, r);
-            continue;
-        }
-        const int4 a = lane <= L ? gld(S.a4 + off + lane) : make_int4(0, 0, 0, 0);
-        int peak, warp;
-        gen_route_wave(S, off, L, nodeof(a.x), a.z, gld(S.b4 + off).z, peak, warp);
+    const int off = gld(S.roff + r), L = gld(S.roff + r + 1) - off - 1;
+    if (L >= 64) {
+        if (lane == 0) gen_route(S, r);
+        __threadfence_block();
+        return;
     }
+    const int4 a = lane <= L ? gld(S.a4 + off + lane) : make_int4(0, 0, 0, 0);
+    int peak, warp;
+    gen_route_wave(S, off, L, nodeof(a.x), a.z, gld(S.b4 + off).z, peak, warp);
+}
+
+// Summaries of every route and the totals (one block).
+__device__ __forceinline__ void pen_all(const SolDev &S, ApplyShared &sh) {
+    for (int r = threadIdx.x >> 6; r < S.R; r += blockDim.x >> 6) gen_route_any(S, r);
     __threadfence_block();
     __syncthreads();
     pen_totals(S, sh);
@@ -944,22 +933,31 @@ __device__ __forceinline__ void reset_run(const SolDev &S, int max_steps) {
     *S.best_key = ~0ull;
 }
 
-// Attributes of a new layout: route r holds cust[off[r] .. off[r + 1]), every
-// route fewer than 64 customers.  One wavefront per route, every attribute in
-// registers (route_attr) and, on the general path, the summaries; the totals
-// are summed over the workgroup, and the last workgroup to finish adds up the
-// others' (part[0] counts them).  off and cust may lie in pinned host memory:
-// each route is read once, straight from there, so that a new solution takes
-// this one launch: 9 us (11 with n up to 10^4) and one synchronisation, a
-// reload 26 us of host time, in place of two copies, three launches and one
-// workgroup that scanned all slots (20 us, 58 us), a reload 50 us.
+// Attributes of a new layout: route r holds cust[off[r] .. off[r + 1]).  One
+// wavefront per route, every attribute in registers (route_attr) and, on the
+// general path, the summaries; the totals are summed over the workgroup, and
+// the last workgroup to finish adds up the others' (part[0] counts them).
+// off and cust may lie in pinned host memory: each route is read once,
+// straight from there, so that a new solution takes this one launch: 9 us (11
+// with n up to 10^4) and one synchronisation, a reload 26 us of host time, in
+// place of two copies, three launches and one workgroup that scanned all slots
+// (20 us, 58 us), a reload 50 us.
+// A workgroup that holds a route of 64 customers or more builds its slots by
+// the block scans instead (rebuild_range, with the slots' own entries of pf4,
+// which are not set yet, as scratch); the other workgroups' routes keep to
+// their wavefronts.  A reload of 10^4 customers with one route of 64: 44 us
+// (203 before the wavefront form, 242 when one workgroup took every slot and
+// looked its route up in host memory).
 // fresh: a solution set or reloaded by the host, which gives |N(S)|; its state
 // and the route distance-block cache start empty.  Otherwise a multi-move
-// step's layout (its launch keeps the counts), if there is one.
+// step's layout (its launch keeps the counts), if there is one.  LONG: some
+// route may hold 64 customers or more (the other instance has no code for
+// that, which costs a reload of short routes 0.8 of its 29 us).
 struct BuildCounts {
     long long cnt[5], seg, k, k2;
 };
 
+template <bool LONG>
 __global__ __launch_bounds__(kBuildRoutes * 64) void k_build_routes(const SolDev S, const int32_t *__restrict__ off,
                                                                     const int32_t *__restrict__ cust, int fresh,
                                                                     const BuildCounts c) {
@@ -970,24 +968,59 @@ __global__ __launch_bounds__(kBuildRoutes * 64) void k_build_routes(const SolDev
     const bool gen = S.pen || S.pd || S.gen;
     if (!fresh && !S.state[kStBuild]) return;  // uniform for the grid
     long long cost = 0, excess = 0, warps = 0;
+    int c0 = 0, L = 0;
     if (r < R) {
-        const int c0 = __builtin_amdgcn_readfirstlane(off[r]), L = __builtin_amdgcn_readfirstlane(off[r + 1]) - c0;
-        const int base = c0 + r;  // one start depot per route before it, and its own
-        const int node = lane >= 1 && lane <= L ? cust[c0 + lane - 1] : 0;
-        const SlotAttr x = route_attr(S, node, r, L);
-        store_attr(S, x, r, base, L);
-        cost = __shfl(x.rdist, L);
-        if (gen) {
-            int peak, warp;
-            gen_route_wave(S, base, L, node, x.a.z, x.b.z, peak, warp);
-            excess = max(peak - S.cap, 0);
-            warps = warp;
+        c0 = __builtin_amdgcn_readfirstlane(off[r]);
+        L = __builtin_amdgcn_readfirstlane(off[r + 1]) - c0;
+    }
+    const int base = c0 + r;  // one start depot per route before it, and its own
+    if (!LONG || !__syncthreads_or(L >= 64)) {
+        if (r < R) {
+            const int node = lane >= 1 && lane <= L ? cust[c0 + lane - 1] : 0;
+            const SlotAttr x = route_attr(S, node, r, L);
+            store_attr(S, x, r, base, L);
+            cost = __shfl(x.rdist, L);
+            if (gen) {
+                int peak, warp;
+                gen_route_wave(S, base, L, node, x.a.z, x.b.z, peak, warp);
+                excess = max(peak - S.cap, 0);
+                warps = warp;
+            }
+            if (lane == 0) gst(S.roff + r, base);
         }
-        if (lane == 0) {
+    } else if constexpr (LONG) {
+        __shared__ ApplyShared sh;
+        __shared__ int base_sh[kBuildRoutes + 1];
+        const int r0 = blockIdx.x * kBuildRoutes, r1 = min(r0 + kBuildRoutes, R);
+        int2 *nr = (int2 *)S.pf4;
+        if (r < R && lane == 0) {
+            base_sh[wave] = base;
             gst(S.roff + r, base);
-            if (fresh) gst(S.rblk + (size_t)r * kRouteBlockWords, -1);
+            if (r == r1 - 1) {
+                base_sh[wave + 1] = base + L + 1;
+                gst(S.roff + r1, base + L + 1);  // (the next workgroup writes the same)
+            }
+        }
+        __syncthreads();
+        const int lo = base_sh[0], hi = base_sh[r1 - r0];
+        for (int s = lo + threadIdx.x; s < hi; s += kBuildRoutes * 64) {
+            int k = 0;  // the slot's route, r0 + k
+            for (int u = 1; u < r1 - r0; ++u) k += base_sh[u] <= s;
+            gst(nr + 2 * s, make_int2(s == base_sh[k] ? 0 : cust[s - (r0 + k) - 1], r0 + k));
+        }
+        __threadfence_block();
+        __syncthreads();
+        rebuild_range<2>(S, nr, S.roff, lo, hi, sh);
+        if (r < R) {
+            cost = gld(S.rdist + r);
+            if (gen) {
+                gen_route_any(S, r);
+                excess = route_excess(S, r);
+                warps = route_warp(S, r);
+            }
         }
     }
+    if (r < R && lane == 0 && fresh) gst(S.rblk + (size_t)r * kRouteBlockWords, -1);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         const bool tw = S.has_tw;
         const int4 q = gld(S.node4);
@@ -1042,48 +1075,6 @@ __global__ __launch_bounds__(kBuildRoutes * 64) void k_build_routes(const SolDev
         S.state[kStBuild] = 0;
     } else if (gen) {
         S.acc[threadIdx.x == 1 ? kAccLoadExcess : kAccTimeWarp] = t;
-    }
-}
-
-// The same for a layout with a route of 64 customers or more, by the block
-// scans of one workgroup (always fresh).  off and cust may be the staging
-// arrays this kernel writes, so they are not __restrict__.
-__global__ __launch_bounds__(kApplyThreads) void k_build_long(const SolDev S, const int32_t *off, const int32_t *cust) {
-    __shared__ ApplyShared sh;
-    const int R = S.R, T = blockDim.x, tid = threadIdx.x;
-    // slot s of route r takes customer s - r - 1; from the last slots down, as
-    // cust may be the front of nr_alt itself, each round read before it is written
-    for (int q1 = S.Q; q1 > 0; q1 -= T) {
-        const int s = q1 - 1 - tid;
-        int2 v = make_int2(0, 0);
-        if (s >= 0) {
-            int lo = 0, hi = R - 1;  // the route whose slots [off[r] + r, off[r + 1] + r + 1) hold s
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (off[mid] + mid <= s) lo = mid;
-                else hi = mid - 1;
-            }
-            v = make_int2(s == off[lo] + lo ? 0 : cust[s - lo - 1], lo);
-        }
-        __syncthreads();
-        if (s >= 0) S.nr_alt[s] = v;
-        __threadfence_block();
-        __syncthreads();
-    }
-    // the slot offsets (off may be roff_alt itself)
-    for (int r = tid; r <= R; r += T) {
-        const int o = off[r] + r;
-        S.roff_alt[r] = r < R ? o : S.Q;
-        if (r < R) S.rblk[(size_t)r * kRouteBlockWords] = -1;
-    }
-    if (tid == 0) S.nr_alt[S.Q] = make_int2(0, R);
-    __threadfence_block();
-    __syncthreads();
-    rebuild(S, S.nr_alt, S.roff_alt, sh);
-    if (S.pen || S.pd || S.gen) pen_all(S, sh);
-    if (tid == 0) {
-        reset_run(S, 0);
-        S.acc[kAccGranInter] = 0;
     }
 }
 
@@ -4038,8 +4029,9 @@ __device__ __forceinline__ void apply_move_block(const SolDev &S, const MoveInfo
     __threadfence_block();
     __syncthreads();
     // 3. rebuild the touched routes in place
-    rebuild_range(S, S.nr_alt, S.roff_alt, baseA, baseA + m.nLa + 1, false, sh);
-    if (inter) rebuild_range(S, S.nr_alt, S.roff_alt, baseB, baseB + m.nLb + 1, false, sh);
+    rebuild_range<1>(S, S.nr_alt, S.roff_alt, baseA, baseA + m.nLa + 1, sh);
+    if (inter) rebuild_range<1>(S, S.nr_alt, S.roff_alt, baseB, baseB + m.nLb + 1, sh);
+    solution_totals(S, S.roff_alt, sh);
     if (S.pen || S.pd || S.gen) {  // summaries of the touched routes, then the totals
         __threadfence_block();
         __syncthreads();

@@ -48,3 +48,61 @@ def test_static_long_routes(tga, problem, lengths):
         assert fields(m) == fields(tga.Solution(I, sol.offsets, sol.customers).eval())
         # another instance's call in between overwrites the scratch
         tga.eval_routes_static(tga.Instance.from_workload(other[0]), other[1].offsets, other[1].customers)
+
+
+def seconds(f, reps=15):
+    """Median time of a call that waits for the device, after one to warm up."""
+    import time
+
+    import torch
+    f()
+    times = []
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        f()
+        torch.cuda.synchronize()
+        times.append(time.perf_counter() - t)
+    return sorted(times)[reps // 2]
+
+
+def spread(n, R):
+    return [n // R + (i < n % R) for i in range(R)]
+
+
+@pytest.mark.parametrize("form", ["plain", "general"])
+@pytest.mark.parametrize("problem", ["cvrp", "vrptw", "vrpspdtw"])
+@pytest.mark.parametrize("lengths", [[9] * 15 + [64] + [9] * 20, [64] * 17, [0] * 20 + [300] + [5] * 30, [1100, 0, 1]])
+def test_reload_long_among_short(tga, problem, lengths, form):
+    """A workgroup's share of the routes with a long one in it, beside workgroups that have none."""
+    inst, sol = make(problem, lengths, 1700 + len(lengths))
+    other = make(problem, lengths[::-1], 1800 + len(lengths))[1]
+    S = tga.Solution(tga.Instance.from_workload(inst), sol.offsets, sol.customers)
+    if form == "general":
+        S.set_general(True)
+    general = form == "general" or problem == "vrpspdtw"
+    print("reload", problem, form, len(lengths), flush=True)
+    for s in (other, sol):
+        S.reload(s.offsets, s.customers)
+        off, cust, cost = S.get()
+        assert np.array_equal(off, s.offsets) and np.array_equal(cust, s.customers)
+        assert cost == oracle.cost(inst, s)[0]
+        for mask in (0x1F, 0xFF) if general else (0x1F,):
+            ob = oracle.eval_neighbourhood(inst, s, mask, threads=0)
+            b = S.eval(mask)
+            assert (b is not None) == bool(ob.found) and (b is None or (b.id, b.delta) == (ob.id, ob.delta))
+        assert int(S.move_counts().sum()) == oracle.eval_neighbourhood(inst, s, 0x1F, threads=0).moves
+        if general:
+            assert S.violations() == oracle.violations(inst, s)
+
+
+def test_reload_time_with_one_long_route(tga):
+    """One route of 64 customers among 500 short ones: the short ones are built as without it (about as fast;
+    4 times as long when every slot of the solution went through one workgroup)."""
+    times = []
+    for lengths in (spread(10000, 500), [64] + spread(9936, 499)):
+        inst, sol = make("cvrp", lengths, 1900)
+        S = tga.Solution(tga.Instance.from_workload(inst), sol.offsets, sol.customers)
+        times.append(seconds(lambda: S.reload(sol.offsets, sol.customers)))
+    print("reload, all short and one of 64: %.1f %.1f us" % (times[0] * 1e6, times[1] * 1e6), flush=True)
+    assert times[1] < 2 * times[0]
