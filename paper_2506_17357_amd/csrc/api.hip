@@ -1148,7 +1148,7 @@ extern "C" int tga_ls_run(tga_solution_t sol, uint32_t op_mask, int32_t max_step
             launch_solution_eval(sol, op_mask | kImprovingOnly, nullptr, nullptr, st);
             if (multi) {
                 k_multi_step<<<1, kApplyThreads, 0, st>>>(sol->h, kModeLS, op_mask);
-                k_build_routes<false><<<(sol->R + kBuildRoutes - 1) / kBuildRoutes, kBuildRoutes * 64, 0, st>>>(
+                k_build_routes<true><<<(sol->R + kBuildRoutes - 1) / kBuildRoutes, kBuildRoutes * 64, 0, st>>>(
                     sol->h, sol->h.roff_alt, (const int32_t *)sol->h.nr_alt, 0, BuildCounts{});
             } else
                 k_finalize_one<<<1, kApplyThreads, 0, st>>>(sol->h, kModeLS, op_mask, nullptr);

@@ -966,7 +966,8 @@ __global__ __launch_bounds__(kBuildRoutes * 64) void k_build_routes(const SolDev
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = blockIdx.x * kBuildRoutes + wave, R = S.R, Q = S.Q;
     const bool gen = S.pen || S.pd || S.gen;
-    if (!fresh && !S.state[kStBuild]) return;  // uniform for the grid
+    const int build = fresh ? (LONG ? 2 : 1) : S.state[kStBuild];
+    if (!build) return;  // uniform for the grid
     long long cost = 0, excess = 0, warps = 0;
     int c0 = 0, L = 0;
     if (r < R) {
@@ -974,7 +975,7 @@ __global__ __launch_bounds__(kBuildRoutes * 64) void k_build_routes(const SolDev
         L = __builtin_amdgcn_readfirstlane(off[r + 1]) - c0;
     }
     const int base = c0 + r;  // one start depot per route before it, and its own
-    if (!LONG || !__syncthreads_or(L >= 64)) {
+    if (!LONG || build < 2 || !__syncthreads_or(L >= 64)) {
         if (r < R) {
             const int node = lane >= 1 && lane <= L ? cust[c0 + lane - 1] : 0;
             const SlotAttr x = route_attr(S, node, r, L);
@@ -4523,10 +4524,10 @@ __global__ __launch_bounds__(kApplyThreads) void k_multi_step(const SolDev S, in
     }
     // 3. the new layout.  Routes are disjoint, so it is the old one with each
     // touched route replaced by its new node sequence, whatever the order of
-    // the moves.  A selection too large for the LDS, or one that makes a route
-    // too long for k_build_routes, is applied move by move instead.
+    // the moves.  A selection too large for the LDS is applied move by move
+    // instead.
     MultiApply &ma = reinterpret_cast<MultiApply &>(ms);
-    bool one_by_one = ns > kMultiMoves;
+    const bool one_by_one = ns > kMultiMoves;
     if (ns > 0 && !one_by_one) {
         int *mov_of = ma.mov_of;
         for (int r = tid; r < R; r += T) mov_of[r] = -1;
@@ -4563,56 +4564,54 @@ __global__ __launch_bounds__(kApplyThreads) void k_multi_step(const SolDev S, in
         }
         if (lane == 63) sh.red[wave][0] = incl;
         __syncthreads();
-        one_by_one = long_sh;
-        if (!one_by_one) {
-            int before = incl - own;
-            for (int w = 0; w < wave; ++w) before += (int)sh.red[w][0];
-            for (int r = r0; r < r1; ++r) {
-                S.roff_alt[r] = before;
-                before += newL(r);
-            }
-            if (tid == 0) S.roff_alt[R] = S.n;
-            __threadfence_block();
-            __syncthreads();
-            // customers of the new layout, one wavefront per route
-            int32_t *cust = (int32_t *)S.nr_alt;
-            for (int r = wave; r < R; r += T / 64) {
-                const int q = mov_of[r], base = S.roff_alt[r], nl = newL(r);
-                if (lane < nl) cust[base + lane] = q < 0 ? old_node(S, r, lane + 1) : new_node(S, ma.mv[q], r, lane + 1);
-            }
-            // |N(S)| changes by the touched routes' terms
-            long long d[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            for (int q = tid; q < ns; q += T) {
-                const MoveInfo &m = ma.mv[q];
-                if (!m.valid) continue;
-                d[0] += 1;
-                if (m.ra == m.rb) continue;
-                const RouteCounts a0 = route_counts(m.La, S.Q), a1 = route_counts(m.nLa, S.Q),
-                                  b0 = route_counts(m.Lb, S.Q), b1 = route_counts(m.nLb, S.Q);
-                d[1] += a1.rel - a0.rel + b1.rel - b0.rel;
-                d[2] -= (a1.star2 - a0.star2 + b1.star2 - b0.star2) / 2;
-                d[3] += a1.two - a0.two + b1.two - b0.two;
-                d[4] += a1.oropt - a0.oropt + b1.oropt - b0.oropt;
-                d[5] += a1.seg - a0.seg + b1.seg - b0.seg;
-                d[6] += a1.k - a0.k + b1.k - b0.k;
-                d[7] += a1.k2 - a0.k2 + b1.k2 - b0.k2;
-            }
-            __syncthreads();
-            for (int i = 0; i < 8; ++i) {
-                long long v = d[i];
-                for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-                if (lane == 0) sh.red[wave][i] = v;
-            }
-            __syncthreads();
-            if (tid < 8) {
-                long long v = 0;
-                for (int w = 0; w < T / 64; ++w) v += sh.red[w][tid];
-                const int to[8] = {-1, kAccCnt0, kAccCnt0 + 2, kAccCnt0 + 3, kAccCnt0 + 4, kAccExtSeg, kAccExtK, kAccExtK2};
-                if (tid == 0) S.state[kStVersion] += (int)v;
-                else S.acc[to[tid]] += v;
-            }
-            if (tid == 0) S.state[kStBuild] = 1;
+        int before = incl - own;
+        for (int w = 0; w < wave; ++w) before += (int)sh.red[w][0];
+        for (int r = r0; r < r1; ++r) {
+            S.roff_alt[r] = before;
+            before += newL(r);
         }
+        if (tid == 0) S.roff_alt[R] = S.n;
+        __threadfence_block();
+        __syncthreads();
+        // customers of the new layout, one wavefront per route
+        int32_t *cust = (int32_t *)S.nr_alt;
+        for (int r = wave; r < R; r += T / 64) {
+            const int q = mov_of[r], base = S.roff_alt[r], nl = newL(r);
+            for (int p = lane; p < nl; p += 64)
+                cust[base + p] = q < 0 ? old_node(S, r, p + 1) : new_node(S, ma.mv[q], r, p + 1);
+        }
+        // |N(S)| changes by the touched routes' terms
+        long long d[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (int q = tid; q < ns; q += T) {
+            const MoveInfo &m = ma.mv[q];
+            if (!m.valid) continue;
+            d[0] += 1;
+            if (m.ra == m.rb) continue;
+            const RouteCounts a0 = route_counts(m.La, S.Q), a1 = route_counts(m.nLa, S.Q),
+                              b0 = route_counts(m.Lb, S.Q), b1 = route_counts(m.nLb, S.Q);
+            d[1] += a1.rel - a0.rel + b1.rel - b0.rel;
+            d[2] -= (a1.star2 - a0.star2 + b1.star2 - b0.star2) / 2;
+            d[3] += a1.two - a0.two + b1.two - b0.two;
+            d[4] += a1.oropt - a0.oropt + b1.oropt - b0.oropt;
+            d[5] += a1.seg - a0.seg + b1.seg - b0.seg;
+            d[6] += a1.k - a0.k + b1.k - b0.k;
+            d[7] += a1.k2 - a0.k2 + b1.k2 - b0.k2;
+        }
+        __syncthreads();
+        for (int i = 0; i < 8; ++i) {
+            long long v = d[i];
+            for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+            if (lane == 0) sh.red[wave][i] = v;
+        }
+        __syncthreads();
+        if (tid < 8) {
+            long long v = 0;
+            for (int w = 0; w < T / 64; ++w) v += sh.red[w][tid];
+            const int to[8] = {-1, kAccCnt0, kAccCnt0 + 2, kAccCnt0 + 3, kAccCnt0 + 4, kAccExtSeg, kAccExtK, kAccExtK2};
+            if (tid == 0) S.state[kStVersion] += (int)v;
+            else S.acc[to[tid]] += v;
+        }
+        if (tid == 0) S.state[kStBuild] = long_sh ? 2 : 1;
     }
     if (one_by_one)
         for (int q = 0; q < ns; ++q) {

@@ -89,7 +89,7 @@ enum {
     kStStatus = 2,     // 0 ok, 1 no admissible move, -1 invalid move
     kStVersion = 3,    // applied moves (host-visible version)
     kStMaxSteps = 4,   // step cap for LS mode
-    kStBuild = 5,      // multi-move: the selection left a new layout for k_build_routes
+    kStBuild = 5,      // multi-move: the selection left a new layout for k_build_routes (2: with a route of 64 or more)
     kStCount
 };
 // acc[] entries

@@ -106,3 +106,40 @@ def test_reload_time_with_one_long_route(tga):
         times.append(seconds(lambda: S.reload(sol.offsets, sol.customers)))
     print("reload, all short and one of 64: %.1f %.1f us" % (times[0] * 1e6, times[1] * 1e6), flush=True)
     assert times[1] < 2 * times[0]
+
+
+@pytest.mark.parametrize("lengths", [[9] * 20 + [90] + [8] * 9, [200, 3, 0, 150, 64], [63, 62, 61, 60] * 5, [70]])
+@pytest.mark.parametrize("problem", ["cvrp", "vrptw", "vrpspdtw"])
+def test_multi_steps_long(tga, problem, lengths):
+    """Multi-move steps with long routes that moves touch and leave alone, in one and in several workgroups."""
+    inst, sol = make(problem, lengths, 2000 + len(lengths))
+    S = tga.Solution(tga.Instance.from_workload(inst), sol.offsets, sol.customers)
+    S.set_multi(True)
+    print("multi", problem, len(lengths), flush=True)
+    fin, applied, per, evaluated = oracle.local_search_multi(inst, sol, 0x1F, max_steps=5)
+    got, moves, cost = S.ls_run(5, 0x1F | tga.OP_MULTI)
+    assert (got, moves) == (len(per), evaluated) and S.multi_stats() == (len(per), len(applied))
+    off, cust, c = S.get()
+    assert np.array_equal(off, fin.offsets) and np.array_equal(cust, fin.customers)
+    assert cost == c == oracle.cost(inst, fin)[0]
+    F = tga.Solution(S.inst, off, cust)
+    F.set_general(True)
+    assert fields(S.eval()) == fields(F.eval())
+    assert np.array_equal(S.move_counts(), F.move_counts()) and S.violations() == F.violations()
+
+
+def test_multi_time_with_one_long_route(tga):
+    """A multi-move step lays every route out once, a long one among them or not (2 to 3 times as long with one of
+    100; 20 times when every selected move was applied by itself)."""
+    times = []
+    for lengths in (spread(1000, 60), [100] + spread(900, 59)):
+        inst, sol = make("cvrp", lengths, 2100)
+        S = tga.Solution(tga.Instance.from_workload(inst), sol.offsets, sol.customers)
+        S.set_multi(True)
+
+        def run():
+            S.reload(sol.offsets, sol.customers)
+            assert S.ls_run(6, 0x1F | tga.OP_MULTI)[0] == 6
+        times.append(seconds(run, reps=7))
+    print("6 multi-move steps, all short and one of 100: %.0f %.0f us" % (times[0] * 1e6, times[1] * 1e6), flush=True)
+    assert times[1] < 6 * times[0]
