@@ -870,7 +870,7 @@ extern "C" int tga_solution_set_penalty(tga_solution_t sol, int32_t w_load, int3
     sol->h.wL = pen ? w_load : 0;
     sol->h.wT = pen ? w_tw : 0;
     hipStream_t st = (hipStream_t)stream;
-    k_pen_init<<<1, kApplyThreads, 0, st>>>(sol->h);
+    k_pen_init<<<(sol->R + kBuildRoutes - 1) / kBuildRoutes, kBuildRoutes * 64, 0, st>>>(sol->h);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
     return TGA_OK;
@@ -882,7 +882,7 @@ extern "C" int tga_solution_set_general(tga_solution_t sol, int32_t on, void *st
     if (on != 0 && on != 1) return fail(TGA_EINVAL, "on must be 0 or 1");
     sol->h.gen = on;
     hipStream_t st = (hipStream_t)stream;
-    k_pen_init<<<1, kApplyThreads, 0, st>>>(sol->h);
+    k_pen_init<<<(sol->R + kBuildRoutes - 1) / kBuildRoutes, kBuildRoutes * 64, 0, st>>>(sol->h);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
     return TGA_OK;
@@ -988,7 +988,7 @@ extern "C" int tga_solution_set_multi(tga_solution_t sol, void *ws, size_t ws_by
         k_fill_u64<<<(int)std::min<size_t>((RR + 255) / 256, 1024), 256, 0, st>>>(sol->h.pairkey, RR);
         HIPCHK(hipGetLastError());
     }
-    k_pen_init<<<1, kApplyThreads, 0, st>>>(sol->h);
+    k_pen_init<<<(sol->R + kBuildRoutes - 1) / kBuildRoutes, kBuildRoutes * 64, 0, st>>>(sol->h);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
     return TGA_OK;

@@ -679,26 +679,6 @@ __device__ __forceinline__ Tw tw_depot(const SolDev &S) {
     return tw_node(q.y, q.z, q.w);
 }
 
-// Prefix and suffix summaries of route r (one thread; TW instances only).
-__device__ __forceinline__ void pen_route(const SolDev &S, int r) {
-    const int off = gld(S.roff + r), L = gld(S.roff + r + 1) - off - 1;
-    const Tw dep = tw_depot(S);
-    Tw f = dep;
-    gst(S.pf4 + off, tw_pack(f));
-    for (int p = 1; p <= L; ++p) {
-        const int4 w = gld(S.w4 + off + p);
-        f = tw_cat(f, gld(S.a4 + off + p - 1).z, tw_node(w.x, w.y, w.z));
-        gst(S.pf4 + off + p, tw_pack(f));
-    }
-    Tw b = dep;
-    for (int p = L; p >= 1; --p) {
-        const int4 w = gld(S.w4 + off + p);
-        b = tw_cat(tw_node(w.x, w.y, w.z), gld(S.a4 + off + p).z, b);
-        gst(S.pb4 + off + p, tw_pack(b));
-    }
-    gst(S.pb4 + off, tw_pack(tw_cat(dep, gld(S.a4 + off).z, b)));
-}
-
 // Load summaries (Section 4.3.2): {L_I delivered, L_O picked up, L_M the
 // largest load on board}; a node is {d, p, max(d, p)}; concatenation keeps
 // the later part's deliveries on board through the earlier part, and the
@@ -717,24 +697,7 @@ __device__ __forceinline__ Ld ld_node_at(const SolDev &S, int x) {
     return Ld{d, p, max(d, p)};
 }
 
-// Prefix and suffix load summaries of route r (one thread; pickups only).
-__device__ __forceinline__ void pd_route(const SolDev &S, int r) {
-    const int off = gld(S.roff + r), L = gld(S.roff + r + 1) - off - 1;
-    Ld f{0, 0, 0};
-    gst(S.pl4 + off, ld_pack(f));
-    for (int p = 1; p <= L; ++p) {
-        f = ld_cat(f, ld_node_at(S, off + p));
-        gst(S.pl4 + off + p, ld_pack(f));
-    }
-    Ld b{0, 0, 0};
-    for (int p = L; p >= 1; --p) {
-        b = ld_cat(ld_node_at(S, off + p), b);
-        gst(S.ql4 + off + p, ld_pack(b));
-    }
-    gst(S.ql4 + off, ld_pack(b));
-}
-
-// The same summaries for one route of at most 64 slots, by one wavefront in
+// The summaries of one route of at most 64 slots, by one wavefront in
 // registers: lane p holds position p (`node` its node).  Concatenation is
 // associative (exactly, in integers), so prefixes and suffixes are wavefront
 // shuffle scans of single nodes, each carrying the edge that enters it.
@@ -818,25 +781,6 @@ __device__ __forceinline__ int2 segment_removal(const SolDev &S, int node, int e
     return v;
 }
 
-// Summaries the general evaluation path reads, of route r, by one thread.
-__device__ __forceinline__ void gen_route(const SolDev &S, int r) {
-    if (S.has_tw) pen_route(S, r);
-    if (S.pd) pd_route(S, r);
-    const int off = gld(S.roff + r), L = gld(S.roff + r + 1) - off - 1;
-    auto node = [&](int p) { return p <= L ? nodeof(gld(S.a4 + off + p).x) : 0; };
-    int4 g = make_int4(0, 0, S.pd ? gld(S.ql4 + off).z : gld(S.b4 + off).z, S.has_tw ? gld(S.pb4 + off).w : 0);
-    for (int p = 0; p <= L; ++p) {
-        g.x = g.y = 0;
-        if (p >= 1) {
-            const int32_t *row = S.D + (size_t)node(p - 1) * S.np1;
-            const int ep = gld(S.a4 + off + p - 1).z;
-            if (p + 1 <= L) g.x = gld(row + node(p + 2)) - ep - gld(S.a4 + off + p + 1).z;
-            if (p + 2 <= L) g.y = gld(row + node(p + 3)) - ep - gld(S.a4 + off + p + 2).z;
-        }
-        gst(S.g4 + off + p, g);
-    }
-}
-
 // Totals of load excess and time warp over the routes (every thread of the
 // block calls it; the summaries must be current).
 __device__ __forceinline__ void pen_totals(const SolDev &S, ApplyShared &sh) {
@@ -897,27 +841,148 @@ __device__ __forceinline__ void gen_route_wave(const SolDev &S, int off, int L, 
     if (lane <= L) gst(S.g4 + off + lane, make_int4(rem.x, rem.y, peak, warp));
 }
 
-// Summaries of route r by one wavefront (one thread of it when the route is
-// too long), from its slots' attributes.
-__device__ __forceinline__ void gen_route_any(const SolDev &S, int r) {
-    const int lane = threadIdx.x & 63;
-    const int off = gld(S.roff + r), L = gld(S.roff + r + 1) - off - 1;
-    if (L >= 64) {
-        if (lane == 0) gen_route(S, r);
-        __threadfence_block();
-        return;
-    }
-    const int4 a = lane <= L ? gld(S.a4 + off + lane) : make_int4(0, 0, 0, 0);
-    int peak, warp;
-    gen_route_wave(S, off, L, nodeof(a.x), a.z, gld(S.b4 + off).z, peak, warp);
+// Removal deltas of the segments of two and three nodes that start at
+// position p of the route whose slots begin at off (L customers), by one
+// thread from the slots' attributes (as segment_removal).
+__device__ __forceinline__ int2 slot_removal(const SolDev &S, int off, int p, int L) {
+    int2 v = make_int2(0, 0);
+    if (p < 1) return v;
+    auto at = [&](int q) { return gld(S.a4 + off + min(q, L)); };
+    const int4 ap = at(p - 1), a1 = at(p + 1), a2 = at(p + 2), a3 = at(p + 3);
+    const int32_t *row = S.D + (size_t)nodeof(ap.x) * S.np1;
+    const int d2 = gld(row + (p + 2 <= L ? nodeof(a2.x) : 0)), d3 = gld(row + (p + 3 <= L ? nodeof(a3.x) : 0));
+    if (p + 1 <= L) v.x = d2 - ap.z - a1.z;
+    if (p + 2 <= L) v.y = d3 - ap.z - a2.z;
+    return v;
 }
 
-// Summaries of every route and the totals (one block).
-__device__ __forceinline__ void pen_all(const SolDev &S, ApplyShared &sh) {
-    for (int r = threadIdx.x >> 6; r < S.R; r += blockDim.x >> 6) gen_route_any(S, r);
-    __threadfence_block();
-    __syncthreads();
-    pen_totals(S, sh);
+// gen_route_wave's prefix and suffix summaries of a route of 64 customers or
+// more, by one wavefront: tiles of 64 positions, each scanned like a short
+// route and joined to what the tiles before (after) it came to.  (One thread
+// per route, a node after the other, took 1.3 ms for routes of 2000 customers
+// and 0.1 ms for routes of 200.)
+__device__ __forceinline__ void gen_route_long(const SolDev &S, int off, int L, int load, int &peak, int &warp) {
+    const int lane = threadIdx.x & 63, last = L & ~63;
+    peak = load;
+    warp = 0;
+    if (S.has_tw) {
+        const Tw dep = tw_depot(S);
+        Tw carry = dep;
+        for (int t0 = 0; t0 <= L; t0 += 64) {
+            const int p = min(t0 + lane, L);
+            const int4 w = gld(S.w4 + off + p);
+            int fin = gld(S.a4 + off + max(p - 1, 0)).z;  // edge entering the lane's node, then its tile's first
+            Tw f = tw_node(w.x, w.y, w.z);
+            for (int d = 1; d < 64; d <<= 1) {
+                const int lo = max(lane - d, 0);
+                const Tw y = shfl_tw(f, lo);
+                const int yi = __shfl(fin, lo);
+                if (lane >= d) {
+                    f = tw_cat(y, fin, f);
+                    fin = yi;
+                }
+            }
+            if (t0 > 0) f = tw_cat(carry, fin, f);
+            carry = shfl_tw(f, 63);
+            if (t0 + lane <= L) gst(S.pf4 + off + p, tw_pack(f));
+        }
+        for (int t0 = last; t0 >= 0; t0 -= 64) {
+            const int p = min(t0 + lane, L), end = min(63, L - t0);
+            const int4 w = gld(S.w4 + off + p);
+            const int in = gld(S.a4 + off + max(p - 1, 0)).z, out = gld(S.a4 + off + p).z;
+            Tw b = tw_node(w.x, w.y, w.z);
+            if (p == L) b = tw_cat(b, out, dep);  // the end depot closes the route
+            for (int d = 1; d < 64; d <<= 1) {
+                const int hi = min(lane + d, 63);
+                const Tw y = shfl_tw(b, hi);
+                const int yi = __shfl(in, hi);
+                if (lane + d <= end) b = tw_cat(b, yi, y);
+            }
+            if (t0 < last) b = tw_cat(b, __shfl(out, 63), carry);
+            carry = shfl_tw(b, 0);
+            if (t0 + lane <= L) gst(S.pb4 + off + p, tw_pack(b));
+        }
+        warp = carry.v;
+    }
+    if (S.pd) {
+        auto shfl_ld = [](const Ld &x, int src) { return Ld{__shfl(x.li, src), __shfl(x.lo, src), __shfl(x.lm, src)}; };
+        Ld carry{0, 0, 0};
+        for (int t0 = 0; t0 <= L; t0 += 64) {
+            const int p = min(t0 + lane, L);
+            Ld f = p ? ld_node_at(S, off + p) : Ld{0, 0, 0};
+            for (int d = 1; d < 64; d <<= 1) {
+                const Ld y = shfl_ld(f, max(lane - d, 0));
+                if (lane >= d) f = ld_cat(y, f);
+            }
+            f = ld_cat(carry, f);
+            carry = shfl_ld(f, 63);
+            if (t0 + lane <= L) gst(S.pl4 + off + p, ld_pack(f));
+        }
+        carry = Ld{0, 0, 0};
+        for (int t0 = last; t0 >= 0; t0 -= 64) {
+            const int p = min(t0 + lane, L), end = min(63, L - t0);
+            Ld b = p ? ld_node_at(S, off + p) : Ld{0, 0, 0};
+            for (int d = 1; d < 64; d <<= 1) {
+                const Ld z = shfl_ld(b, min(lane + d, 63));
+                if (lane + d <= end) b = ld_cat(b, z);
+            }
+            b = ld_cat(b, carry);
+            carry = shfl_ld(b, 0);
+            if (t0 + lane <= L) gst(S.ql4 + off + p, ld_pack(b));
+        }
+        peak = carry.lm;
+    }
+}
+
+// What gen_route_sums leaves for gen_slots and the totals: a route's largest
+// load, time warp, first slot and customers.
+struct GenRoute {
+    int peak, warp, off, len;
+};
+
+// Summaries of route r by one wavefront, from its slots' attributes; g (LDS)
+// receives its totals.  A long route's g4 is left to gen_slots.
+__device__ __forceinline__ void gen_route_sums(const SolDev &S, int r, GenRoute &g) {
+    const int lane = threadIdx.x & 63;
+    const int off = gld(S.roff + r), L = gld(S.roff + r + 1) - off - 1, load = gld(S.b4 + off).z;
+    int peak, warp;
+    if (L < 64) {
+        const int4 a = lane <= L ? gld(S.a4 + off + lane) : make_int4(0, 0, 0, 0);
+        gen_route_wave(S, off, L, nodeof(a.x), a.z, load, peak, warp);
+    } else {
+        gen_route_long(S, off, L, load, peak, warp);
+    }
+    if (lane == 0) {
+        g.peak = peak;
+        g.warp = warp;
+        g.off = off;
+        g.len = L;
+    }
+}
+
+// g4 of the slots [lo, hi) that belong to long routes (routes r0, r0 + 1, ..
+// are entries 0, 1, .. of g), one thread per slot, four at a time.
+__device__ __forceinline__ void gen_slots(const SolDev &S, const GenRoute *g, int r0, int lo, int hi) {
+    constexpr int U = 4;
+    const int T = blockDim.x;
+    for (int s0 = lo + threadIdx.x; s0 < hi; s0 += T * U) {
+        int4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = s0 + u * T;
+            v[u].z = -1;
+            if (s < hi) {
+                const GenRoute &q = g[gld(S.a4 + s).y - r0];
+                if (q.len >= 64) {
+                    const int2 rem = slot_removal(S, q.off, s - q.off, q.len);
+                    v[u] = make_int4(rem.x, rem.y, q.peak, q.warp);
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (v[u].z >= 0) gst(S.g4 + s0 + u * T, v[u]);
+    }
 }
 
 // Local-search state and counters of a solution, for a new run.
@@ -931,6 +996,39 @@ __device__ __forceinline__ void reset_run(const SolDev &S, int max_steps) {
     S.acc[kAccScreenPairs] = 0;
     S.acc[kAccMultiApplied] = 0;
     *S.best_key = ~0ull;
+}
+
+// Sums over the grid of the workgroups' sums (sum_sh, per wavefront): true for
+// threads 0..2 of the last workgroup to finish, t their total; part[0] counts
+// the workgroups and is back at zero then.  Every thread of the block calls it.
+__device__ __forceinline__ bool grid_sums(const SolDev &S, long long (*sum_sh)[3], int &last_sh, long long &t) {
+    __syncthreads();
+    const int nb = gridDim.x;
+    if (threadIdx.x == 0) {
+        long long s[3] = {0, 0, 0};
+        for (int w = 0; w < kBuildRoutes; ++w)
+            for (int i = 0; i < 3; ++i) s[i] += sum_sh[w][i];
+        for (int i = 0; i < 3; ++i) {
+            sum_sh[0][i] = s[i];
+            if (nb > 1)
+                __hip_atomic_store(S.part + 1 + 3 * blockIdx.x + i, s[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        int last = 1;
+        if (nb > 1) {
+            __threadfence();
+            last = atomicAdd((unsigned long long *)S.part, 1ull) == (unsigned long long)(nb - 1);
+            __threadfence();
+        }
+        last_sh = last;
+    }
+    __syncthreads();
+    if (!last_sh || threadIdx.x >= 3) return false;
+    t = nb > 1 ? 0 : sum_sh[0][threadIdx.x];
+    if (nb > 1)
+        for (int b = 0; b < nb; ++b)
+            t += __hip_atomic_load(S.part + 1 + 3 * b + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) S.part[0] = 0;
+    return true;
 }
 
 // Attributes of a new layout: route r holds cust[off[r] .. off[r + 1]).  One
@@ -1012,13 +1110,16 @@ __global__ __launch_bounds__(kBuildRoutes * 64) void k_build_routes(const SolDev
         __threadfence_block();
         __syncthreads();
         rebuild_range<2>(S, nr, S.roff, lo, hi, sh);
-        if (r < R) {
-            cost = gld(S.rdist + r);
-            if (gen) {
-                gen_route_any(S, r);
-                excess = route_excess(S, r);
-                warps = route_warp(S, r);
+        if (r < R) cost = gld(S.rdist + r);
+        if (gen) {
+            __shared__ GenRoute g[kBuildRoutes];
+            if (r < R) {
+                gen_route_sums(S, r, g[wave]);
+                excess = max(g[wave].peak - S.cap, 0);
+                warps = g[wave].warp;
             }
+            __syncthreads();
+            gen_slots(S, g, r0, lo, hi);
         }
     }
     if (r < R && lane == 0 && fresh) gst(S.rblk + (size_t)r * kRouteBlockWords, -1);
@@ -1045,33 +1146,9 @@ __global__ __launch_bounds__(kBuildRoutes * 64) void k_build_routes(const SolDev
         sum_sh[wave][1] = excess;
         sum_sh[wave][2] = warps;
     }
-    __syncthreads();
-    const int nb = gridDim.x;
+    long long t;
+    if (!grid_sums(S, sum_sh, last_sh, t)) return;
     if (threadIdx.x == 0) {
-        long long t[3] = {0, 0, 0};
-        for (int w = 0; w < kBuildRoutes; ++w)
-            for (int i = 0; i < 3; ++i) t[i] += sum_sh[w][i];
-        for (int i = 0; i < 3; ++i) {
-            sum_sh[0][i] = t[i];
-            if (nb > 1)
-                __hip_atomic_store(S.part + 1 + 3 * blockIdx.x + i, t[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        int last = 1;
-        if (nb > 1) {
-            __threadfence();
-            last = atomicAdd((unsigned long long *)S.part, 1ull) == (unsigned long long)(nb - 1);
-            __threadfence();
-        }
-        last_sh = last;
-    }
-    __syncthreads();
-    if (!last_sh || threadIdx.x >= 3) return;
-    long long t = nb > 1 ? 0 : sum_sh[0][threadIdx.x];
-    if (nb > 1)
-        for (int b = 0; b < nb; ++b)
-            t += __hip_atomic_load(S.part + 1 + 3 * b + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (threadIdx.x == 0) {
-        S.part[0] = 0;
         S.acc[kAccCost] = t;
         S.state[kStBuild] = 0;
     } else if (gen) {
@@ -1080,10 +1157,23 @@ __global__ __launch_bounds__(kBuildRoutes * 64) void k_build_routes(const SolDev
 }
 
 // Switch the general path on for a solution whose descriptor now says so:
-// summaries of every route and the totals.
-__global__ __launch_bounds__(kApplyThreads) void k_pen_init(const SolDev S) {
-    __shared__ ApplyShared sh;
-    if (S.pen || S.pd || S.gen) pen_all(S, sh);
+// summaries of every route and the totals, kBuildRoutes routes a workgroup.
+__global__ __launch_bounds__(kBuildRoutes * 64) void k_pen_init(const SolDev S) {
+    __shared__ long long sum_sh[kBuildRoutes][3];
+    __shared__ GenRoute g[kBuildRoutes];
+    __shared__ int last_sh;
+    if (!(S.pen || S.pd || S.gen)) return;  // uniform for the grid
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r0 = blockIdx.x * kBuildRoutes, r = r0 + wave, r1 = min(r0 + kBuildRoutes, S.R);
+    if (r < S.R) gen_route_sums(S, r, g[wave]);
+    if ((threadIdx.x & 63) == 0) {
+        sum_sh[wave][0] = 0;
+        sum_sh[wave][1] = r < S.R ? max(g[wave].peak - S.cap, 0) : 0;
+        sum_sh[wave][2] = r < S.R ? g[wave].warp : 0;
+    }
+    if (__syncthreads_or(r < S.R && g[wave].len >= 64)) gen_slots(S, g, r0, gld(S.roff + r0), gld(S.roff + r1));
+    long long t;
+    if (grid_sums(S, sum_sh, last_sh, t) && threadIdx.x > 0) S.acc[threadIdx.x == 1 ? kAccLoadExcess : kAccTimeWarp] = t;
 }
 
 // The current routes as the caller's arrays: offsets (R + 1), customers (n),
@@ -4034,12 +4124,16 @@ __device__ __forceinline__ void apply_move_block(const SolDev &S, const MoveInfo
     if (inter) rebuild_range<1>(S, S.nr_alt, S.roff_alt, baseB, baseB + m.nLb + 1, sh);
     solution_totals(S, S.roff_alt, sh);
     if (S.pen || S.pd || S.gen) {  // summaries of the touched routes, then the totals
+        __shared__ GenRoute g[2];
         __threadfence_block();
         __syncthreads();
-        if (threadIdx.x == 0) gen_route(S, m.ra);
-        if (threadIdx.x == 64 && inter) gen_route(S, m.rb);
+        const int wave = threadIdx.x >> 6;
+        if (wave == 0) gen_route_sums(S, m.ra, g[0]);
+        if (wave == 1 && inter) gen_route_sums(S, m.rb, g[1]);
         __threadfence_block();
         __syncthreads();
+        if (m.nLa >= 64) gen_slots(S, g, m.ra, baseA, baseA + m.nLa + 1);
+        if (inter && m.nLb >= 64) gen_slots(S, g + 1, m.rb, baseB, baseB + m.nLb + 1);
         pen_totals(S, sh);
     }
 }

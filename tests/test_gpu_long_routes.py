@@ -143,3 +143,47 @@ def test_multi_time_with_one_long_route(tga):
         times.append(seconds(run, reps=7))
     print("6 multi-move steps, all short and one of 100: %.0f %.0f us" % (times[0] * 1e6, times[1] * 1e6), flush=True)
     assert times[1] < 6 * times[0]
+
+
+@pytest.mark.parametrize("problem", ["cvrp", "vrptw", "vrpspdtw"])
+@pytest.mark.parametrize("lengths", [[64], [63, 128, 1, 127, 0, 129], [5] * 30 + [190, 66] + [4] * 7])
+def test_summaries_of_long_routes(tga, problem, lengths):
+    """Every move of the general path, which reads the summaries of every slot: after switching it on, after a reload
+    and after moves into, out of and within long routes."""
+    inst, sol = make(problem, lengths, 2200 + len(lengths))
+    I = tga.Instance.from_workload(inst)
+    S = tga.Solution(I, sol.offsets, sol.customers)
+    pen = (3, 0 if problem == "cvrp" else 2)
+    print("summaries", problem, len(lengths), flush=True)
+
+    def check(s, what):
+        ob, odd, odf = oracle.eval_neighbourhood(inst, s, 0xFF, dump=True, threads=0, penalty=pen)
+        gb, gdd, gdf = S.eval(0xFF, dump=True)
+        assert np.array_equal(gdf.cpu().numpy(), odf) and np.array_equal(gdd.cpu().numpy(), odd), what
+        assert (gb.delta, gb.id) == (ob.delta, ob.id)
+        assert S.violations() == oracle.violations(inst, s), what
+
+    S.set_penalty(*pen)
+    check(sol, "switched on")
+    S.reload(sol.offsets, sol.customers)
+    check(sol, "reloaded")
+    for k in range(3):
+        # the best move under other weights, so that the three are of different kinds
+        m = S.eval((0x1F, 0x60, 0x84)[k])
+        if m is None:
+            continue
+        S.apply(m)
+        sol = oracle.apply_move(inst, sol, m.id)
+        check(sol, "applied %d" % k)
+
+
+def test_summaries_time(tga):
+    """Switching the general path on: routes of 70 customers in tiles of a wavefront, as fast as routes of 60 (25
+    times as long with one thread per route)."""
+    times = []
+    for lengths in ([60] * 117, [70] * 100):
+        inst, sol = make("vrptw", lengths, 2300)
+        S = tga.Solution(tga.Instance.from_workload(inst), sol.offsets, sol.customers)
+        times.append(seconds(lambda: S.set_general(True)))
+    print("set_general, routes of 60 and of 70: %.1f %.1f us" % (times[0] * 1e6, times[1] * 1e6), flush=True)
+    assert times[1] < 4 * times[0]
