@@ -375,50 +375,6 @@ __host__ __device__ __forceinline__ RouteCounts route_counts(long long L, long l
     return c;
 }
 
-// Cost (sum of route distances) and |N(S)| per operator from the route
-// offsets and distances.  Every thread of the block calls it.
-__device__ __forceinline__ void solution_totals(const SolDev &S, const int32_t *roffn, ApplyShared &sh) {
-    const int Q = S.Q, R = S.R, n = S.n;
-    const int tid = threadIdx.x, T = blockDim.x;
-    long long v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int r = tid; r < R; r += T) {
-        const RouteCounts c = route_counts(gld(roffn + r + 1) - gld(roffn + r) - 1, Q);
-        v[0] += gld(S.rdist + r);
-        v[1] += c.rel;
-        v[2] += c.star2;
-        v[3] += c.two;
-        v[4] += c.oropt;
-        v[5] += c.seg;
-        v[6] += c.k;
-        v[7] += c.k2;
-    }
-    for (int i = 0; i < 8; ++i) {
-        long long x = v[i];
-        for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-        v[i] = x;
-    }
-    if ((tid & 63) == 0)
-        for (int i = 0; i < 8; ++i) sh.red[tid >> 6][i] = v[i];
-    __syncthreads();
-    if (tid == 0) {
-        long long t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int w = 0; w < T / 64; ++w)
-            for (int i = 0; i < 8; ++i) t[i] += sh.red[w][i];
-        const long long qq = (long long)Q * Q;
-        S.acc[kAccCost] = t[0];
-        S.acc[kAccCnt0 + 0] = t[1];
-        S.acc[kAccCnt0 + 1] = (long long)n * (n - 1) / 2;
-        S.acc[kAccCnt0 + 2] = (qq - t[2]) / 2;
-        S.acc[kAccCnt0 + 3] = t[3];
-        S.acc[kAccCnt0 + 4] = t[4];
-        S.acc[kAccExtSeg] = t[5];
-        S.acc[kAccExtK] = t[6];
-        S.acc[kAccExtK2] = t[7];
-    }
-    __threadfence_block();
-    __syncthreads();
-}
-
 // Attributes of the slots [lo, hi) of the layout (nr, roffn), a union of
 // whole routes, from their nodes (nr[ST * s] = {node, route} for slot s; it is
 // then reused as scratch for the scans' A and Z), and those routes' distances.
@@ -779,36 +735,6 @@ __device__ __forceinline__ int2 segment_removal(const SolDev &S, int node, int e
     if (lane >= 1 && lane + 1 <= L) v.x = gld(S.D + (size_t)pred * np1 + (lane + 2 <= L ? n2 : 0)) - epred - e1;
     if (lane >= 1 && lane + 2 <= L) v.y = gld(S.D + (size_t)pred * np1 + (lane + 3 <= L ? n3 : 0)) - epred - e2;
     return v;
-}
-
-// Totals of load excess and time warp over the routes (every thread of the
-// block calls it; the summaries must be current).
-__device__ __forceinline__ void pen_totals(const SolDev &S, ApplyShared &sh) {
-    long long lv = 0, tv = 0;
-    for (int r = threadIdx.x; r < S.R; r += blockDim.x) {
-        lv += route_excess(S, r);
-        tv += route_warp(S, r);
-    }
-    for (int off = 32; off >= 1; off >>= 1) {
-        lv += __shfl_xor(lv, off);
-        tv += __shfl_xor(tv, off);
-    }
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
-        sh.red[threadIdx.x >> 6][0] = lv;
-        sh.red[threadIdx.x >> 6][1] = tv;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        long long a = 0, b = 0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
-            a += sh.red[w][0];
-            b += sh.red[w][1];
-        }
-        S.acc[kAccLoadExcess] = a;
-        S.acc[kAccTimeWarp] = b;
-    }
-    __syncthreads();
 }
 
 // The general path's summaries of route r (slots off .., L < 64 customers) by
@@ -4044,15 +3970,47 @@ __device__ __forceinline__ void decode_move(const SolDev &S, uint32_t id, MoveIn
     check_move(S.n, m);
 }
 
+__device__ __forceinline__ void acc_add(const SolDev &S, int k, long long v) {
+    if (v) atomicAdd((unsigned long long *)(S.acc + k), (unsigned long long)v);
+}
+
+// |N(S)| per operator after move m (one thread): the touched routes' terms
+// change.  `acc` holds the accumulators as they were before.
+__device__ __forceinline__ void count_move(const SolDev &S, const MoveInfo &m, const long long *acc) {
+    if (m.ra == m.rb) return;
+    const long long Q = S.Q;
+    const RouteCounts a0 = route_counts(m.La, Q), a1 = route_counts(m.nLa, Q), b0 = route_counts(m.Lb, Q),
+                      b1 = route_counts(m.nLb, Q);
+    S.acc[kAccCnt0 + 0] = acc[kAccCnt0 + 0] + (a1.rel - a0.rel) + (b1.rel - b0.rel);
+    S.acc[kAccCnt0 + 2] = acc[kAccCnt0 + 2] - ((a1.star2 - a0.star2) + (b1.star2 - b0.star2)) / 2;
+    S.acc[kAccCnt0 + 3] = acc[kAccCnt0 + 3] + (a1.two - a0.two) + (b1.two - b0.two);
+    S.acc[kAccCnt0 + 4] = acc[kAccCnt0 + 4] + (a1.oropt - a0.oropt) + (b1.oropt - b0.oropt);
+    S.acc[kAccExtSeg] = acc[kAccExtSeg] + (a1.seg - a0.seg) + (b1.seg - b0.seg);
+    S.acc[kAccExtK] = acc[kAccExtK] + (a1.k - a0.k) + (b1.k - b0.k);
+    S.acc[kAccExtK2] = acc[kAccExtK2] + (a1.k2 - a0.k2) + (b1.k2 - b0.k2);
+}
+
 // Apply m (valid).  All threads of the block participate.  Every slot
 // attribute is route-local, so only the touched routes are rebuilt; the
 // routes strictly between two touched routes of different lengths move as a
 // block by the first one's length change (a plain copy of their records).
+// The cost and the violations change by the touched routes' difference
+// (summing every route again took two rounds of the workgroup's threads and,
+// after each rebuilt route, eight 64-bit reductions); |N(S)| is the caller's.
 __device__ __forceinline__ void apply_move_block(const SolDev &S, const MoveInfo &m, ApplyShared &sh) {
     const int R = S.R, T = blockDim.x, tid = threadIdx.x;
     const bool inter = m.ra != m.rb;
     const int dA = m.nLa - m.La, dB = inter ? m.nLb - m.Lb : 0;
     auto shift = [&](int r) { return (r > m.ra ? dA : 0) + (inter && r > m.rb ? dB : 0); };
+    const bool gen = S.pen || S.pd || S.gen;
+    long long cost = 0, excess = 0, warps = 0;  // thread 0: less what the touched routes came to
+    if (tid == 0) {
+        cost -= gld(S.rdist + m.ra) + (inter ? gld(S.rdist + m.rb) : 0);
+        if (gen) {
+            excess -= route_excess(S, m.ra) + (inter ? route_excess(S, m.rb) : 0);
+            warps -= route_warp(S, m.ra) + (inter ? route_warp(S, m.rb) : 0);
+        }
+    }
     // 1. new offsets, and the touched routes' nodes (read from the old layout)
     for (int r = tid; r <= R; r += T) S.roff_alt[r] = S.roff[r] + shift(r);
     const int baseA = S.roff[m.ra] + shift(m.ra);
@@ -4085,7 +4043,7 @@ __device__ __forceinline__ void apply_move_block(const SolDev &S, const MoveInfo
                     t = S.t4[src];
                     w = S.w4[src];
                     pd = S.pdist[src];
-                    if (S.pen || S.pd || S.gen) {
+                    if (gen) {
                         pf = S.pf4[src];
                         pb = S.pb4[src];
                         pl = S.pl4[src];
@@ -4101,7 +4059,7 @@ __device__ __forceinline__ void apply_move_block(const SolDev &S, const MoveInfo
                     S.t4[dst] = t;
                     S.w4[dst] = w;
                     S.pdist[dst] = pd;
-                    if (S.pen || S.pd || S.gen) {
+                    if (gen) {
                         S.pf4[dst] = pf;
                         S.pb4[dst] = pb;
                         S.pl4[dst] = pl;
@@ -4122,11 +4080,9 @@ __device__ __forceinline__ void apply_move_block(const SolDev &S, const MoveInfo
     // 3. rebuild the touched routes in place
     rebuild_range<1>(S, S.nr_alt, S.roff_alt, baseA, baseA + m.nLa + 1, sh);
     if (inter) rebuild_range<1>(S, S.nr_alt, S.roff_alt, baseB, baseB + m.nLb + 1, sh);
-    solution_totals(S, S.roff_alt, sh);
-    if (S.pen || S.pd || S.gen) {  // summaries of the touched routes, then the totals
+    if (tid == 0) cost += gld(S.rdist + m.ra) + (inter ? gld(S.rdist + m.rb) : 0);
+    if (gen) {  // summaries of the touched routes
         __shared__ GenRoute g[2];
-        __threadfence_block();
-        __syncthreads();
         const int wave = threadIdx.x >> 6;
         if (wave == 0) gen_route_sums(S, m.ra, g[0]);
         if (wave == 1 && inter) gen_route_sums(S, m.rb, g[1]);
@@ -4134,7 +4090,17 @@ __device__ __forceinline__ void apply_move_block(const SolDev &S, const MoveInfo
         __syncthreads();
         if (m.nLa >= 64) gen_slots(S, g, m.ra, baseA, baseA + m.nLa + 1);
         if (inter && m.nLb >= 64) gen_slots(S, g + 1, m.rb, baseB, baseB + m.nLb + 1);
-        pen_totals(S, sh);
+        for (int k = 0; k < (inter ? 2 : 1); ++k) {
+            excess += max(g[k].peak - S.cap, 0);
+            warps += g[k].warp;
+        }
+    }
+    if (tid == 0) {
+        acc_add(S, kAccCost, cost);
+        if (gen) {
+            acc_add(S, kAccLoadExcess, excess);
+            acc_add(S, kAccTimeWarp, warps);
+        }
     }
 }
 
@@ -4161,10 +4127,6 @@ __device__ __forceinline__ void ls_count_moves(const SolDev &S, uint32_t op_mask
     S.acc[kAccMoves] = acc[kAccMoves] + m;
     if ((op_mask & kCountFull) && (op_mask & 7))
         S.acc[kAccScreenPairs] = acc[kAccScreenPairs] + acc[kAccCnt0 + 2];  // = slot pairs of different routes
-}
-
-__device__ __forceinline__ void acc_add(const SolDev &S, int k, long long v) {
-    if (v) atomicAdd((unsigned long long *)(S.acc + k), (unsigned long long)v);
 }
 
 // Moves the records of the slots [lo, hi) by d (routes strictly between the
@@ -4345,17 +4307,7 @@ __device__ __forceinline__ void finalize_block(const SolDev &S, int mode, uint32
         S.state[kStVersion] = version + 1;
         S.state[kStSteps] = steps + 1;
         if (mode == kModeLS && steps + 1 >= max_steps) S.state[kStDone] = 1;
-        if (inter) {
-            const RouteCounts a0 = route_counts(m.La, Q), a1 = route_counts(m.nLa, Q), b0 = route_counts(m.Lb, Q),
-                              b1 = route_counts(m.nLb, Q);
-            S.acc[kAccCnt0 + 0] = acc[kAccCnt0 + 0] + (a1.rel - a0.rel) + (b1.rel - b0.rel);
-            S.acc[kAccCnt0 + 2] = acc[kAccCnt0 + 2] - ((a1.star2 - a0.star2) + (b1.star2 - b0.star2)) / 2;
-            S.acc[kAccCnt0 + 3] = acc[kAccCnt0 + 3] + (a1.two - a0.two) + (b1.two - b0.two);
-            S.acc[kAccCnt0 + 4] = acc[kAccCnt0 + 4] + (a1.oropt - a0.oropt) + (b1.oropt - b0.oropt);
-            S.acc[kAccExtSeg] = acc[kAccExtSeg] + (a1.seg - a0.seg) + (b1.seg - b0.seg);
-            S.acc[kAccExtK] = acc[kAccExtK] + (a1.k - a0.k) + (b1.k - b0.k);
-            S.acc[kAccExtK2] = acc[kAccExtK2] + (a1.k2 - a0.k2) + (b1.k2 - b0.k2);
-        }
+        count_move(S, m, acc);
     }
     if (max(max(m.La, m.Lb), max(m.nLa, m.nLb)) >= 64) {
         __syncthreads();
@@ -4717,7 +4669,10 @@ __global__ __launch_bounds__(kApplyThreads) void k_multi_step(const SolDev S, in
             const MoveInfo m = mi;
             if (m.valid) apply_move_block(S, m, sh);
             __syncthreads();
-            if (tid == 0 && m.valid) S.state[kStVersion] += 1;
+            if (tid == 0 && m.valid) {
+                S.state[kStVersion] += 1;
+                count_move(S, m, S.acc);
+            }
         }
     if (tid == 0) {
         if (ns > 0) {  // the record holds the first (best) selected move

@@ -187,3 +187,61 @@ def test_summaries_time(tga):
         times.append(seconds(lambda: S.set_general(True)))
     print("set_general, routes of 60 and of 70: %.1f %.1f us" % (times[0] * 1e6, times[1] * 1e6), flush=True)
     assert times[1] < 4 * times[0]
+
+
+@pytest.mark.parametrize("form", ["plain", "penalised"])
+@pytest.mark.parametrize("problem", ["cvrp", "vrptw", "vrpspdtw"])
+def test_totals_after_moves_on_long_routes(tga, problem, form):
+    """Cost, violations and move counts after moves that lengthen, shorten, empty and rearrange long routes, one
+    after another, against a solution set from the same routes."""
+    if problem == "vrpspdtw" and form == "plain":
+        pytest.skip("pickups are evaluated on the general path")
+    inst, sol = make(problem, [130, 3, 64, 200, 0], 2400)
+    I = tga.Instance.from_workload(inst)
+
+    def solution(s):
+        S = tga.Solution(I, s.offsets, s.customers)
+        if form == "penalised":
+            S.set_penalty(3, 0 if problem == "cvrp" else 2)
+        return S
+
+    S = solution(sol)
+    Q = inst.n + sol.R
+    rng = np.random.Generator(np.random.PCG64(2400))
+    done = 0
+    print("totals", problem, form, flush=True)
+    while done < 30:
+        op = int(rng.integers(0, 5)) if form == "plain" else int(rng.integers(0, 10))
+        k = {0: 1, 1: 1, 2: 0, 3: 0}.get(op, int(rng.integers(1, 4)))
+        a, b = sorted(rng.integers(0, Q, size=2).tolist()) if op in (1, 2, 3, 7, 8, 9) else rng.integers(0, Q, size=2).tolist()
+        m = tga.Move()
+        m.op, m.k, m.id, m.version, m.feas = op, k, ((op * 4 + k) * Q + a) * Q + b, S.version, 3
+        try:
+            cost = S.apply(m)
+        except tga.TGAError:
+            continue  # not a move of these routes
+        done += 1
+        sol = oracle.apply_move(inst, sol, m.id)
+        F = solution(sol)
+        assert cost == oracle.cost(inst, sol)[0]
+        assert np.array_equal(S.move_counts(), F.move_counts()), (op, k, a, b)
+        if form != "plain":
+            assert S.violations() == F.violations() == oracle.violations(inst, sol), (op, k, a, b)
+        assert fields(S.eval()) == fields(F.eval())
+
+
+def test_multi_selection_beyond_the_lds(tga):
+    """A selection of more moves than a step keeps decoded is applied move by move: routes, cost and counts."""
+    inst, sol = make("cvrp", [2] * 1500, 2500)
+    S = tga.Solution(tga.Instance.from_workload(inst), sol.offsets, sol.customers)
+    S.set_multi(True)
+    print("multi, 1500 routes", flush=True)
+    fin, applied, per, evaluated = oracle.local_search_multi(inst, sol, 0x1F, max_steps=1)
+    assert len(applied) > 700
+    got, moves, cost = S.ls_run(1, 0x1F | tga.OP_MULTI)
+    assert (got, moves) == (len(per), evaluated) and S.multi_stats() == (len(per), len(applied))
+    off, cust, c = S.get()
+    assert np.array_equal(off, fin.offsets) and np.array_equal(cust, fin.customers)
+    assert cost == c == oracle.cost(inst, fin)[0]
+    F = tga.Solution(S.inst, off, cust)
+    assert np.array_equal(S.move_counts(), F.move_counts())
