@@ -800,11 +800,16 @@ static void launch_eval_general(const tga_solution *sol, uint32_t op_mask, int32
     const bool w16 = staged > 0;
     const int rows = w16 ? staged : kGenRows;
     const int strips = std::min(std::max(2 * cus - e.nintra, cus / 2), (sol->Q + 1) / 2);
-    const int grid = e.nintra + ((op_mask & (7 | TGA_OP_VARIANTS)) ? strips : 0);
+    // a solution that cannot hold a route too long to be staged, nor more
+    // customers in a group than lanes, needs no workgroups for such routes
+    // (see gen_slot_block; beyond 4096 slots they would be too many)
+    const int width = sol->Q > 4096 ? 64 : 32;
+    const int nslot = e.nintra && sol->n >= kGenSlotsFrom ? (sol->Q + width - 1) / width : 0;
+    const int grid = nslot + e.nintra + ((op_mask & (7 | TGA_OP_VARIANTS)) ? strips : 0);
     if (!grid) return;
     const size_t lds = std::max(w16 ? general_rows_lds(np1, halo, rows) : 0, (size_t)kGenRegionBytes);
-    if (w16) k_eval_general<TW, PD, EXT, true><<<grid, kInterThreads, lds, st>>>(sol->h, e.nintra, e.G, rows, op_mask, dd, df);
-    else k_eval_general<TW, PD, EXT, false><<<grid, kInterThreads, lds, st>>>(sol->h, e.nintra, e.G, rows, op_mask, dd, df);
+    if (w16) k_eval_general<TW, PD, EXT, true><<<grid, kInterThreads, lds, st>>>(sol->h, nslot, width, e.nintra, e.G, rows, op_mask, dd, df);
+    else k_eval_general<TW, PD, EXT, false><<<grid, kInterThreads, lds, st>>>(sol->h, nslot, width, e.nintra, e.G, rows, op_mask, dd, df);
 }
 
 template <bool TW, bool PD>

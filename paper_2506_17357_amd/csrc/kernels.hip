@@ -3473,7 +3473,10 @@ __device__ __forceinline__ void gen_strip(const SolDev &S, int s0, int s1, uint3
     block_argmin_commit(bd, bid, S.best_key, red);
 }
 
-// Views of a route on the general path: staged (gen_arrays), and direct.
+// Views of a route on the general path: staged (gen_arrays), and direct.  A
+// distance is looked up by two positions, each with its key: on the direct
+// view its node, which the walks read a step ahead (one of the two reads a
+// distance waits for), on the staged one nothing.
 template <bool TW, bool PD>
 struct GenLds {
     const int *b;
@@ -3488,7 +3491,9 @@ struct GenLds {
     __device__ Tw post(int p) const { return sum(11, p + 1); }    // suffix after p
     __device__ Ld lpre(int p) const { return lsum(TW ? 15 : 7, p); }
     __device__ Ld lpost(int p) const { return lsum(TW ? 18 : 10, p + 1); }
-    __device__ int dd(int p, int q) const { return b[gen_arrays<TW, PD>() * P + p * P + q]; }
+    __device__ int key(int) const { return 0; }
+    __device__ int node(int p, int) const { return b[p]; }
+    __device__ int dd(int p, int, int q, int) const { return b[gen_arrays<TW, PD>() * P + p * P + q]; }
 };
 
 struct GenGlobal {
@@ -3502,7 +3507,9 @@ struct GenGlobal {
     __device__ Tw post(int p) const { return p >= L ? tw_depot(S) : tw_of(gld(S.pb4 + off + p + 1)); }
     __device__ Ld lpre(int p) const { return ld_of(gld(S.pl4 + off + p)); }
     __device__ Ld lpost(int p) const { return p >= L ? Ld{0, 0, 0} : ld_of(gld(S.ql4 + off + p + 1)); }
-    __device__ int dd(int p, int q) const { return gld(S.D + (size_t)node(p) * S.np1 + node(q)); }
+    __device__ int key(int p) const { return node(p); }
+    __device__ int node(int, int k) const { return k; }
+    __device__ int dd(int, int kp, int, int kq) const { return gld(S.D + (size_t)kp * S.np1 + kq); }
 };
 
 // Intra-route moves of route r (slots off .., L customers, view V) whose
@@ -3542,27 +3549,31 @@ __device__ __forceinline__ void gen_moves(const SolDev &S, const RV &V, int r, i
     };
     auto excess = [&](const Ld &x) { return PD ? max(x.lm - cap, 0) : lvR; };
     const int eP = V.edge(i - 1), eI = V.edge(i);
+    const int kP = V.key(i - 1), kI = V.key(i);
     const Tw Fi1 = Fpos(i - 1);
     const Ld LFi1 = LFpos(i - 1);
     if (walk == 0 || walk == 7) {  // ---- 2OPT(i, j) or SWAP(i, j), j > i
         if (!op2o && !opSwap) return;
         Tw rev = Npos(i), mid{};
         Ld lrev = LNpos(i), lmid{};
+        const int kI1 = V.key(i + 1);
+        int ejm = eI, kjm = kI, kj = kI1, kj1 = V.key(min(i + 2, L + 1));
 #pragma unroll 1
         for (int j = i + 1; j <= L; ++j) {
-            const int ej = V.edge(j), ejm = V.edge(j - 1);
+            const int ej = V.edge(j), kn = V.key(min(j + 2, L + 1));
             refresh();
             if (TW && op2o) rev = tw_cat(Npos(j), ejm, rev);
             if (PD && op2o) lrev = ld_cat(LNpos(j), lrev);
-            const int d1 = V.dd(i - 1, j), d2 = V.dd(i, j + 1);
+            const int d1 = V.dd(i - 1, kP, j, kj), d2 = V.dd(i, kI, j + 1, kj1);
             const int dO = d1 + d2 - eP - ej;
             int dA = 0, dB = 0, dS = dO;
             if (j > i + 1) {
-                dA = V.dd(j, i + 1);
-                dB = V.dd(j - 1, i);
+                dA = V.dd(j, kj, i + 1, kI1);
+                dB = V.dd(j - 1, kjm, i, kI);
                 dS = d1 + dA + dB + d2 - eP - eI - ejm - ej;
             }
-            const uint32_t lo = min(ref(i), ref(j)), hi = max(ref(i), ref(j));
+            const uint32_t refI = V.node(i, kI) - 1, refJ = V.node(j, kj) - 1;
+            const uint32_t lo = min(refI, refJ), hi = max(refI, refJ);
             if (op2o && can(dO)) {
                 const int tv = TW ? tw_cat(tw_cat(Fi1, d1, rev), d2, Bafter(j)).v : 0;
                 rec(dO, tv, excess(ld_cat(ld_cat(LFi1, lrev), LBafter(j))), (12u * uQ + lo) * uQ + hi);
@@ -3579,6 +3590,10 @@ __device__ __forceinline__ void gen_moves(const SolDev &S, const RV &V, int r, i
             }
             if (TW && opSwap) mid = (j == i + 1) ? Npos(j) : tw_cat(mid, ejm, Npos(j));  // c_{i+1} .. c_j
             if (PD && opSwap) lmid = (j == i + 1) ? LNpos(j) : ld_cat(lmid, LNpos(j));
+            ejm = ej;
+            kjm = kj;
+            kj = kj1;
+            kj1 = kn;
         }
         return;
     }
@@ -3586,7 +3601,8 @@ __device__ __forceinline__ void gen_moves(const SolDev &S, const RV &V, int r, i
     const int k = walk <= 3 ? walk : walk - 3;
     if (!opOr || i + k - 1 > L) return;
     const int gi = i + k - 1, wi = i + k;
-    const int dPW = V.dd(i - 1, wi), base = dPW - eP - V.edge(gi);
+    const int kG = V.key(gi), kW = V.key(wi);
+    const int dPW = V.dd(i - 1, kP, wi, kW), base = dPW - eP - V.edge(gi);
     Tw sig{};
     Ld lsig{};
     if (TW) sig = Npos(i);
@@ -3599,68 +3615,105 @@ __device__ __forceinline__ void gen_moves(const SolDev &S, const RV &V, int r, i
     Tw mid{};
     Ld lmid{};
     if (walk <= 3) {
+        int kj = kW, kj1 = V.key(min(wi + 1, L + 1));
 #pragma unroll 1
         for (int j = wi; j <= L; ++j) {  // forward: middle c_{i+k} .. c_j
+            const int kn = V.key(min(j + 2, L + 1));
             refresh();
             if (TW) mid = (j == wi) ? Npos(j) : tw_cat(mid, V.edge(j - 1), Npos(j));
             if (PD) lmid = (j == wi) ? LNpos(j) : ld_cat(lmid, LNpos(j));
-            const int dVF = V.dd(j, i), dGV = V.dd(gi, j + 1), dO = base + dVF + dGV - V.edge(j);
+            const int dVF = V.dd(j, kj, i, kI), dGV = V.dd(gi, kG, j + 1, kj1), dO = base + dVF + dGV - V.edge(j);
             if (can(dO)) {
                 const int tv = TW ? tw_cat(tw_cat(tw_cat(Fi1, dPW, mid), dVF, sig), dGV, Bafter(j)).v : 0;
                 rec(dO, tv, excess(ld_cat(ld_cat(ld_cat(LFi1, lmid), lsig), LBafter(j))),
                     ((16u + k) * uQ + ref(i)) * uQ + ref(j));
             }
+            kj = kj1;
+            kj1 = kn;
         }
         return;
     }
+    int kj = V.key(max(i - 2, 0)), kj1 = kP;
 #pragma unroll 1
     for (int j = i - 2; j >= 0; --j) {  // backward: middle c_{j+1} .. c_{i-1}
+        const int kn = V.key(max(j - 1, 0));
         refresh();
         if (TW) mid = (j == i - 2) ? Npos(i - 1) : tw_cat(Npos(j + 1), V.edge(j + 1), mid);
         if (PD) lmid = (j == i - 2) ? LNpos(i - 1) : ld_cat(LNpos(j + 1), lmid);
-        const int dVF = V.dd(j, i), dGV = V.dd(gi, j + 1), dO = base + dVF + dGV - V.edge(j);
+        const int dVF = V.dd(j, kj, i, kI), dGV = V.dd(gi, kG, j + 1, kj1), dO = base + dVF + dGV - V.edge(j);
         if (can(dO)) {
             const int tv = TW ? tw_cat(tw_cat(tw_cat(Fpos(j), dVF, sig), dGV, mid), dPW, Bafter(gi)).v : 0;
             rec(dO, tv, excess(ld_cat(ld_cat(ld_cat(LFpos(j), lsig), lmid), LBafter(gi))),
                 ((16u + k) * uQ + ref(i)) * uQ + ref(j));
         }
+        kj1 = kj;
+        kj = kn;
     }
 }
 
 constexpr int kGenRegionBytes = 16384;  // LDS of a staged group on the general path
 
+// Whether a group's routes share one staged region, lane = first position.
+template <bool TW, bool PD>
+__device__ __forceinline__ bool gen_group_fits(int sumL, int words) {
+    return sumL <= 64 && words <= kGenRegionBytes / 4;
+}
+
+// LDS words of a staged route of P positions.
+template <bool TW, bool PD>
+__device__ __forceinline__ int gen_words(int P) { return gen_arrays<TW, PD>() * P + P * P; }
+
+// Fewest customers of a solution that can have routes walked by slots: one
+// route too long for the region (21 arrays), or more than 64 in a group.
+constexpr int kGenSlotsFrom = 50;
+static_assert((7 + 8 + 6) * (kGenSlotsFrom + 1) + (kGenSlotsFrom + 1) * (kGenSlotsFrom + 1) <= kGenRegionBytes / 4,
+              "a route of kGenSlotsFrom - 1 customers is staged");
+
+// In a group that does not fit: whether its routes are walked by slots
+// (gen_slot_block) and not staged one after another.  Two chains of staged
+// steps take about as long as one of steps that gather from memory; more
+// (short routes beside empty ones, whose number sets the groups) longer.
+constexpr int kGenInTurn = 2;
+
+// The moves of one wavefront's walk of route r (slots off .., L customers,
+// view V) whose first position is i, i + step, ..; for a multi-move step also
+// the route's best improving move.
+template <bool TW, bool PD, class RV>
+__device__ __forceinline__ void gen_walk(const SolDev &S, const RV &V, int r, int off, int L, int i, int step,
+                                         uint32_t op_mask, int walk, int32_t *dd, uint8_t *df, int *thr_sh, int &bd,
+                                         uint32_t &bid) {
+    const bool multi = op_mask & kMulti;
+    int b1 = multi ? initial_bound(op_mask) : bd;
+    uint32_t i1 = multi ? 0xFFFFFFFFu : bid;
+#pragma unroll 1
+    for (; i <= L; i += step) gen_moves<TW, PD>(S, V, r, off, L, i, op_mask, walk, dd, df, thr_sh, b1, i1);
+    if (multi) {
+        if (b1 < 0 && i1 != 0xFFFFFFFFu) atomicMin(S.pairkey + (size_t)r * S.R + r, pack_key(b1, i1));
+        if (i1 != 0xFFFFFFFFu) consider(b1, i1, bd, bid);
+    } else {
+        bd = b1;
+        bid = i1;
+    }
+}
+
 // One workgroup evaluates the intra-route moves of the routes [r0, r1) on the
-// general path, wavefront w walk w (as intra_block).
+// general path, wavefront w walk w (as intra_block).  Routes that are not
+// staged are left to gen_slot_block.
 template <bool TW, bool PD>
 __device__ __forceinline__ void gen_intra_block(const SolDev &S, int r0, int r1, uint32_t op_mask,
                                                 int32_t *__restrict__ dd, uint8_t *__restrict__ df, int *region, int *thr_sh) {
     const int lane = threadIdx.x & 63;
     const int walk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool multi = op_mask & kMulti;
     int bd = initial_bound(op_mask);
     if (threadIdx.x == 0) *thr_sh = bd;
-    if (dd || multi) thr_sh = nullptr;  // every move, or every route's best, is wanted
+    if (dd || (op_mask & kMulti)) thr_sh = nullptr;  // every move, or every route's best, is wanted
     __syncthreads();
     uint32_t bid = 0xFFFFFFFFu;
     GroupStage g;
     const int G = r1 - r0;
     constexpr int NA = gen_arrays<TW, PD>();
     group_layout<NA>(S, r0, G, g);
-    // the routes' moves; multi-move: also the route's best improving move
-    auto moves = [&](const auto &V, int r, int off, int L, int i, int step) {
-        int b1 = multi ? initial_bound(op_mask) : bd;
-        uint32_t i1 = multi ? 0xFFFFFFFFu : bid;
-#pragma unroll 1
-        for (; i <= L; i += step) gen_moves<TW, PD>(S, V, r, off, L, i, op_mask, walk, dd, df, thr_sh, b1, i1);
-        if (multi) {
-            if (b1 < 0 && i1 != 0xFFFFFFFFu) atomicMin(S.pairkey + (size_t)r * S.R + r, pack_key(b1, i1));
-            if (i1 != 0xFFFFFFFFu) consider(b1, i1, bd, bid);
-        } else {
-            bd = b1;
-            bid = i1;
-        }
-    };
-    if (g.sumL <= 64 && g.words <= kGenRegionBytes / 4) {
+    if (gen_group_fits<TW, PD>(g.sumL, g.words)) {
         int myk = -1, myi = 0, myP = 0, myAt = 0, myOff = 0, cum = 0;
 #pragma unroll
         for (int k = 0; k < kIntraMaxGroup; ++k) {
@@ -3676,23 +3729,70 @@ __device__ __forceinline__ void gen_intra_block(const SolDev &S, int r0, int r1,
         }
         stage_group<TW, true, PD>(S, g, region);
         const GenLds<TW, PD> V{region + myAt, myP};
-        if (myk >= 0) moves(V, r0 + myk, myOff, myP - 2, myi, 1 << 30);
+        if (myk >= 0)
+            gen_walk<TW, PD>(S, V, r0 + myk, myOff, myP - 2, myi, 1 << 30, op_mask, walk, dd, df, thr_sh, bd, bid);
     } else {
+        int staged = 0;
+#pragma unroll
+        for (int k = 0; k < kIntraMaxGroup; ++k)
+            staged += g.P[k] > 2 && gen_words<TW, PD>(g.P[k]) <= kGenRegionBytes / 4;
+        if (staged > kGenInTurn) return;  // uniform
         for (int k = 0; k < G; ++k) {
             const int r = r0 + k;
             group_layout<NA>(S, r, 1, g);
-            const int off = g.offs[0], P = g.P[0], L = P - 2;
-            if (g.words <= kGenRegionBytes / 4) {
-                __syncthreads();  // the previous route is done with the region
-                stage_group<TW, true, PD>(S, g, region);
-                const GenLds<TW, PD> V{region, P};
-                moves(V, r, off, L, lane + 1, 64);
-            } else {
-                const GenGlobal V{S, off, L};
-                moves(V, r, off, L, lane + 1, 64);
-            }
+            if (g.sumL == 0 || g.words > kGenRegionBytes / 4) continue;
+            __syncthreads();  // the previous route is done with the region
+            stage_group<TW, true, PD>(S, g, region);
+            const GenLds<TW, PD> V{region, g.P[0]};
+            gen_walk<TW, PD>(S, V, r, g.offs[0], g.P[0] - 2, lane + 1, 64, op_mask, walk, dd, df, thr_sh, bd, bid);
         }
     }
+    wave_argmin_commit(bd, bid, S.best_key);
+}
+
+// The routes gen_intra_block leaves (too long for its region, or too many to
+// a group), by slots: one workgroup takes the first positions in the slots
+// [s0, s0 + width), lane = slot, wavefront = walk, all data from memory, so a
+// route of any length is one chain of its length spread over the chip: a
+// penalised step with one route of 1000 customers (CVRP) 0.68 ms, 7.2 ms with
+// all of the route's first positions in turn on one workgroup.  32 slots a
+// workgroup: with 64 the gathers of eight wavefronts keep one compute unit's
+// address path busy (0.78 ms), 16 gain little more (0.62).  With no such route
+// the workgroup ends after two reads.
+template <bool TW, bool PD>
+__device__ __forceinline__ void gen_slot_block(const SolDev &S, int s0, int width, int G, uint32_t op_mask,
+                                               int32_t *__restrict__ dd, uint8_t *__restrict__ df, int *thr_sh) {
+    const int s = s0 + (threadIdx.x & 63);
+    const int4 a = gld(S.a4 + min(s, S.Q));
+    const int r = min(a.y, S.R - 1), r0 = r / G * G;  // (slot Q's route is R)
+    int off = 0, L = 0, sumL = 0, words = 0, staged = 0;
+    int o[kIntraMaxGroup + 1];
+#pragma unroll
+    for (int k = 0; k <= kIntraMaxGroup; ++k) o[k] = gld(S.roff + min(r0 + min(k, G), S.R));
+#pragma unroll
+    for (int k = 0; k < kIntraMaxGroup; ++k) {
+        const int P = o[k + 1] - o[k] + 1;  // 1 beyond the group
+        const int w = P > 1 ? gen_words<TW, PD>(P) : 0;
+        if (r0 + k == r) {
+            off = o[k];
+            L = P - 2;
+        }
+        sumL += max(P - 2, 0);
+        words += w;
+        staged += P > 2 && w <= kGenRegionBytes / 4;
+    }
+    const bool mine = s < min(s0 + width, S.Q) && (flagsof(a.x) & kFlagCustomer) &&
+                      (gen_words<TW, PD>(L + 2) > kGenRegionBytes / 4 ||
+                       (!gen_group_fits<TW, PD>(sumL, words) && staged > kGenInTurn));
+    if (!__builtin_amdgcn_ballot_w64(mine)) return;  // the same slots in every wavefront
+    const int walk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int bd = initial_bound(op_mask);
+    if (threadIdx.x == 0) *thr_sh = bd;
+    if (dd || (op_mask & kMulti)) thr_sh = nullptr;  // as gen_intra_block
+    __syncthreads();
+    uint32_t bid = 0xFFFFFFFFu;
+    const GenGlobal V{S, off, L};
+    if (mine) gen_walk<TW, PD>(S, V, r, off, L, s - off, 1 << 30, op_mask, walk, dd, df, thr_sh, bd, bid);
     wave_argmin_commit(bd, bid, S.best_key);
 }
 
@@ -3706,23 +3806,29 @@ __device__ __forceinline__ int strip_begin(int Q, int k, int n) {
 }
 
 // One evaluation on the general path (as k_eval_solution): workgroups below
-// nintra take the intra-route groups of G routes, the others one strip of row
-// slots each, at most `rows` of them staged at a time.
+// nslot take 64 slots each for the routes that are not staged, the next nintra
+// the intra-route groups of G routes, the others one strip of row slots each,
+// at most `rows` of them staged at a time.
 template <bool TW, bool PD, bool EXT, bool W16>
 __global__ __launch_bounds__(kInterThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_general(
-    const SolDev S, int nintra, int G, int rows, uint32_t op_mask, int32_t *__restrict__ dd,
+    const SolDev S, int nslot, int width, int nintra, int G, int rows, uint32_t op_mask, int32_t *__restrict__ dd,
     uint8_t *__restrict__ df) {
     extern __shared__ int4 smem4[];
     __shared__ unsigned long long red[kInterWaves];
     __shared__ int thr_sh;
     __shared__ GenQueue queues[kInterWaves];
     if (skip_solution(S, op_mask)) return;  // uniform for the grid
-    if ((int)blockIdx.x < nintra) {
-        const int r0 = blockIdx.x * G;
+    const int item = (int)blockIdx.x - nslot;
+    if (item < 0) {
+        gen_slot_block<TW, PD>(S, blockIdx.x * width, width, G, op_mask, dd, df, &thr_sh);
+        return;
+    }
+    if (item < nintra) {
+        const int r0 = item * G;
         gen_intra_block<TW, PD>(S, r0, min(S.R, r0 + G), op_mask, dd, df, (int *)smem4, &thr_sh);
         return;
     }
-    const int k = blockIdx.x - nintra, n = gridDim.x - nintra;
+    const int k = item - nintra, n = (int)gridDim.x - nslot - nintra;
     const int s0 = __builtin_amdgcn_readfirstlane(strip_begin(S.Q, k, n));
     const int s1 = __builtin_amdgcn_readfirstlane(strip_begin(S.Q, k + 1, n));
     for (int x = s0; x < s1; x += rows)

@@ -245,3 +245,46 @@ def test_multi_selection_beyond_the_lds(tga):
     assert cost == c == oracle.cost(inst, fin)[0]
     F = tga.Solution(S.inst, off, cust)
     assert np.array_equal(S.move_counts(), F.move_counts())
+
+
+WALKS = [[200, 3], [70, 0, 55, 64, 30], [17] * 6 + [0] * 90, [12, 0, 13, 0, 11, 0, 9] * 5 + [0] * 60, [52], [48, 1], [120]]
+
+
+@pytest.mark.parametrize("mode", ["hard", "penalised"])
+@pytest.mark.parametrize("problem", ["cvrp", "vrptw", "vrpspdtw"])
+@pytest.mark.parametrize("case", range(len(WALKS)))
+def test_general_walks(tga, case, problem, mode):
+    """Intra-route moves on the general path of routes that are staged in a group, in turn, and not at all (too long,
+    or too many to a group beside empty ones): every move, the best move, and steps."""
+    inst, sol = make(problem, WALKS[case], 2600 + case)
+    pen = None if mode == "hard" else (3, 0 if problem == "cvrp" else 2)
+    S = tga.Solution(tga.Instance.from_workload(inst), sol.offsets, sol.customers)
+    S.set_general(True) if pen is None else S.set_penalty(*pen)
+    print("walks", problem, mode, case, flush=True)
+    for mask in (0x1F, 0x18, 0x02):
+        ob, odd, odf = oracle.eval_neighbourhood(inst, sol, mask, dump=True, threads=0, penalty=pen)
+        gb, gdd, gdf = S.eval(mask, dump=True)
+        assert np.array_equal(gdf.cpu().numpy(), odf) and np.array_equal(gdd.cpu().numpy(), odd)
+        for b in (gb, S.eval(mask)):
+            assert (b is not None) == bool(ob.found) and (b is None or (b.delta, b.id) == (ob.delta, ob.id))
+    fin, ids, _, moves = oracle.local_search(inst, sol, 0x1F, max_steps=12, penalty=pen)
+    steps, mv, _ = S.ls_run(12, 0x1F)
+    off, cust, _ = S.get()
+    assert (steps, mv) == (len(ids), moves)
+    assert np.array_equal(off, fin.offsets) and np.array_equal(cust, fin.customers)
+
+
+def test_general_walks_time(tga):
+    """One route of 1000 customers: the general path spreads its first positions over the chip, the plain path (where
+    a route is one workgroup's) is its measure: an eighth of it, and longer than it when they were one workgroup's."""
+    inst, sol = make("cvrp", [1000], 2700)
+    S = tga.Solution(tga.Instance.from_workload(inst), sol.offsets, sol.customers)
+
+    def run():
+        S.reload(sol.offsets, sol.customers)
+        assert S.ls_run(3)[0] == 3
+    times = [seconds(run, reps=5)]
+    S.set_penalty(10)
+    times.append(seconds(run, reps=5))
+    print("3 steps, plain and penalised: %.0f %.0f us" % (times[0] * 1e6, times[1] * 1e6), flush=True)
+    assert times[1] < 0.5 * times[0]
