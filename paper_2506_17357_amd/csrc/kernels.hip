@@ -3117,6 +3117,14 @@ __device__ __forceinline__ void gen_eval_move(const SolDev &S, int x, int t, int
                bid);
 }
 
+// A wavefront's remaining steps go to gen_dense once it has queued so many
+// moves in all, a quarter of them in the last step (256 is every move of a
+// step of 64 pairs).  Fewer, and steps after which the threshold screens the
+// rest pay for both sides' summaries for nothing (with 128 in one step a
+// query of 1000 customers with pickups 53 us, 50 without); more, and the gain
+// on 2000 empty routes goes (192 in one step: 320 us).
+constexpr int kGenDense = 256, kGenDenseExt = 768;
+
 // Per wavefront: moves waiting to be evaluated (slots and code, lower bound of
 // the score, distance delta).
 constexpr int kGenQueue = 192, kGenSteps = 64;
@@ -3125,6 +3133,273 @@ struct GenQueue {
     int step_min[kGenSteps];  // least lower bound of each of the wavefront's steps
 };
 static_assert(kInterWaves * sizeof(GenQueue) == kGenQueueBytes, "move queues");
+
+// One side of a slot pair as gen_dense reads it: summaries of the prefixes
+// that end before and at the slot, of the suffixes that start 1 .. M after it,
+// and of the segments of 1 .. M customers that start at it, both ways round.
+template <bool TW, bool PD, int M>
+struct GenSide {
+    Tw f0, f1, b[M + 1], seg[M + 1], rev[M + 1];
+    Ld lf0, lf1, lb[M + 1], lseg[M + 1], lrev[M + 1];
+
+    // at(array, slot): the slot's entry; node[k], e[k]: the node k slots on and
+    // the edge leaving it
+    template <class At>
+    __device__ __forceinline__ void read(const SolDev &S, int x, const Tw &dep, At at, const int *node, const int *e) {
+        const int Q = S.Q, xm = max(x - 1, 0);
+#pragma unroll
+        for (int k = 1; k <= M; ++k) {
+            const int y = min(x + k, Q);
+            if (TW) b[k] = node[k] ? tw_of(at(S.pb4, y)) : dep;
+            if (PD) lb[k] = node[k] ? ld_of(at(S.ql4, y)) : Ld{0, 0, 0};
+        }
+        if (TW) {
+            f0 = tw_of(at(S.pf4, xm));
+            f1 = tw_of(at(S.pf4, x));
+        }
+        if (PD) {
+            lf0 = ld_of(at(S.pl4, xm));
+            lf1 = ld_of(at(S.pl4, x));
+        }
+        if (!TW && !PD) return;
+#pragma unroll
+        for (int k = 1; k <= M; ++k) {
+            const int y = min(x + k - 1, Q);
+            const int4 w = at(S.w4, y);
+            if (TW) {
+                const Tw nd = tw_node(w.x, w.y, w.z);
+                seg[k] = k == 1 ? nd : tw_cat(seg[k - 1], e[k - 2], nd);
+                rev[k] = k == 1 ? nd : tw_cat(nd, e[k - 2], rev[k - 1]);
+            }
+            if (PD) {
+                const int dem = at(S.b4, y).x;
+                const Ld nd{dem, w.w, max(dem, w.w)};
+                lseg[k] = k == 1 ? nd : ld_cat(lseg[k - 1], nd);
+                lrev[k] = k == 1 ? nd : ld_cat(nd, lrev[k - 1]);
+            }
+        }
+    }
+    // The new route made of this side's prefix (before the slot, or with it),
+    // the other side's segment k (0: none) and `after`: its time warp (d1, d2:
+    // the distances that join the parts) and its largest load.
+    __device__ __forceinline__ int warp(bool before, const GenSide &o, int k, bool r, int d1, int d2, const Tw &after) const {
+        if (!TW) return 0;
+        const Tw &f = before ? f0 : f1;
+        return k ? tw_cat(tw_cat(f, d1, r ? o.rev[k] : o.seg[k]), d2, after).v : tw_cat(f, d1, after).v;
+    }
+    __device__ __forceinline__ int peak(bool before, const GenSide &o, int k, bool r, const Ld &after) const {
+        const Ld &f = before ? lf0 : lf1;
+        return ld_cat(k ? ld_cat(f, r ? o.lrev[k] : o.lseg[k]) : f, after).lm;
+    }
+};
+
+// The steps [idx, end) of a wavefront of gen_strip (its run begins at `first`)
+// where most moves pass the screens: far from feasible, with ties of many
+// empty routes, and in dumps.  Lane = column, row uniform, every move of a step
+// evaluated in place: both sides' summaries are read once for all moves of the
+// pair (coalesced or uniform), the distances come from the staged rows.  A
+// queue entry's 30 scattered reads are worth it only where few lanes pass:
+// 1000 customers in 60 routes and 2000 empty ones, windows broken, penalised
+// 195 us a step against 592 (264 with one thread per pair), with the variants
+// 660 against 1420 (450); 60 routes, windows broken, a penalised query 73
+// against 92 (79), with the variants 126 against 188 (134).
+template <bool TW, bool PD, bool EXT, bool W16>
+__device__ __forceinline__ void gen_dense(const SolDev &S, int s0, int s1, int first, int idx, int end, uint32_t op_mask,
+                                          int32_t *__restrict__ dd, uint8_t *__restrict__ df, const uint16_t *rows,
+                                          int *thr_sh, const int *step_min, int &bd, uint32_t &bid) {
+    constexpr int M = EXT ? 3 : 1;  // longest segment
+    const int lane = threadIdx.x & 63;
+    const int Q = S.Q, cap = S.cap, wL = S.wL, nr = s1 - s0;
+    const bool pen = S.pen, multi = op_mask & kMulti;
+    const uint32_t uQ = (uint32_t)Q;
+    const Tw dep = TW ? tw_depot(S) : Tw{};
+    auto threshold = [&]() {
+        if (dd) return 0x7FFFFFFF;
+        const int v = min(__hip_atomic_load(thr_sh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP),
+                          initial_bound(op_mask));
+        return multi ? max(v, 0) : v;
+    };
+    // a step none of whose moves can be the best any more
+    auto screened = [&]() {
+        return !dd && !multi && idx - first < kGenSteps && step_min[idx - first] > threshold();
+    };
+    while (true) {
+        while (idx < end && screened()) ++idx;
+        if (idx >= end) return;
+        const int j0 = idx / nr, t = s0 + 1 + 64 * j0 + lane, tc = min(t, Q);
+        const int4 ta = gld(S.a4 + tc), tb = gld(S.b4 + tc), tg = gld(S.g4 + tc);
+        int nt[M + 2], et[M], lt[M + 1] = {};  // nodes of t - 1 .. t + M; edges; deliveries of t's first k customers
+#pragma unroll
+        for (int k = -1; k <= M; ++k) nt[k + 1] = nodeof(gld(S.a4 + min(max(t + k, 0), Q)).x);
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+            et[k] = gld(S.a4 + min(t + k, Q)).z;
+            lt[k + 1] = gld(S.b4 + min(t + k, Q)).y - tb.y + tb.x;
+        }
+        GenSide<TW, PD, M> T;
+        bool have = false;  // T is read
+        const bool ct = flagsof(ta.x) & kFlagCustomer;
+        int kt = ct ? 1 : 0;  // longest segment that starts at t
+#pragma unroll
+        for (int k = 2; k <= M; ++k) kt += kt == k - 1 && nt[k] != 0;
+        const int ept = tb.w - ta.z;
+        const uint32_t refT = ct ? nodeof(ta.x) - 1 : S.n + ta.y;
+#pragma unroll 1
+        for (const int stop = min(end, (j0 + 1) * nr); idx < stop; ++idx) {
+            if (screened()) continue;
+            const int thr = threshold();
+            const int x = s0 + idx - j0 * nr;
+            const int4 ra = sld(S.a4 + x), rb = sld(S.b4 + x), rg = sld(S.g4 + x);
+            const bool valid = t < Q && ta.y > ra.y;
+            if (!__builtin_amdgcn_ballot_w64(valid)) continue;
+            int nx[M + 2], ex[M], lx[M + 1] = {};
+#pragma unroll
+            for (int k = -1; k <= M; ++k) nx[k + 1] = nodeof(sld(S.a4 + min(max(x + k, 0), Q)).x);
+#pragma unroll
+            for (int k = 0; k < M; ++k) {
+                ex[k] = sld(S.a4 + min(x + k, Q)).z;
+                lx[k + 1] = sld(S.b4 + min(x + k, Q)).y - rb.y + rb.x;
+            }
+            const bool cx = flagsof(ra.x) & kFlagCustomer;
+            int kx = cx ? 1 : 0;
+#pragma unroll
+            for (int k = 2; k <= M; ++k) kx += kx == k - 1 && nx[k] != 0;
+            const int epx = rb.w - ra.z;
+            int w[M + 2][M + 2];  // w[1 + a][1 + b]: between x + a and t + b
+#pragma unroll
+            for (int a = 0; a < M + 2; ++a)
+#pragma unroll
+                for (int b = 0; b < M + 2; ++b)
+                    if (EXT || a == 1 || b == 1)
+                        w[a][b] = W16 ? rows[(x + a - s0) * S.stride16 + nt[b]] : gld(S.D + (size_t)nx[a] * S.np1 + nt[b]);
+            // every move of the pair: f(gx, gt, rev, star), gx customers from x
+            // and gt from t change sides
+            auto each_move = [&](auto f) {
+                if (op_mask & 1) {
+                    f(1, 0, false, false);
+                    f(0, 1, false, false);
+                }
+                if (op_mask & 2) f(1, 1, false, false);
+                if (op_mask & 4) f(0, 0, false, true);
+                if constexpr (EXT) {
+                    if (op_mask & 32) {
+                        f(2, 0, false, false);
+                        f(3, 0, false, false);
+                        f(0, 2, false, false);
+                        f(0, 3, false, false);
+                    }
+                    if (op_mask & 64) {
+                        f(2, 0, true, false);
+                        f(3, 0, true, false);
+                        f(0, 2, true, false);
+                        f(0, 3, true, false);
+                    }
+                    if (op_mask & 128) {
+                        f(1, 2, false, false);
+                        f(1, 3, false, false);
+                        f(2, 1, false, false);
+                        f(2, 2, false, false);
+                        f(2, 3, false, false);
+                        f(3, 1, false, false);
+                        f(3, 2, false, false);
+                        f(3, 3, false, false);
+                    }
+                }
+            };
+            // the distances that join the new routes, and the delta
+            struct Join {
+                int dx1, dx2, dt1, dt2, delta;
+            };
+            auto join = [&](int gx, int gt, bool rev, bool star) {
+                Join q{0, 0, 0, 0, 0};
+                if (star) {
+                    q.dx1 = w[1][2];
+                    q.dt1 = w[2][1];
+                    q.delta = q.dx1 + q.dt1 - ex[0] - et[0];
+                    return q;
+                }
+                const int ax = gx ? gx : 1, at = gt ? gt : 1;  // what follows on each side, slots on
+                if (gt) {
+                    q.dx1 = w[gx ? 0 : 1][rev ? gt : 1];
+                    q.dx2 = w[1 + ax][rev ? 1 : gt];
+                } else {
+                    q.dx1 = (gx == 1 ? ra.w : (gx == 2 ? rg.x : rg.y)) + epx + ex[ax - 1];
+                }
+                if (gx) {
+                    q.dt1 = w[rev ? gx : 1][gt ? 0 : 1];
+                    q.dt2 = w[rev ? 1 : gx][1 + at];
+                } else {
+                    q.dt1 = (gt == 1 ? ta.w : (gt == 2 ? tg.x : tg.y)) + ept + et[at - 1];
+                }
+                q.delta = q.dx1 + q.dx2 + q.dt1 + q.dt2 - (gx ? epx + ex[ax - 1] : ex[0]) - (gt ? ept + et[at - 1] : et[0]);
+                return q;
+            };
+            const int Lx = rb.z, Lt = tb.z, lvOld = max(rg.z - cap, 0) + max(tg.z - cap, 0), tvOld = rg.w + tg.w;
+            const int slack = pen ? wL * lvOld + S.wT * tvOld : 0;
+            // whether a move can matter (lower bounds as in gen_strip)
+            auto passes = [&](int gx, int gt, bool star, int delta) {
+                const int load = star ? (Lt - tb.y) - (Lx - rb.y) : lt[gt] - lx[gx];
+                const int over = max(Lx + load - cap, 0) + max(Lt - load - cap, 0);
+                return valid && gx <= kx && gt <= kt &&
+                       (dd || (pen ? delta - slack + wL * over <= thr : !over && delta <= thr));
+            };
+            bool some = false;
+            each_move([&](int gx, int gt, bool rev, bool star) { some |= passes(gx, gt, star, join(gx, gt, rev, star).delta); });
+            if (!__builtin_amdgcn_ballot_w64(some)) continue;
+            if (!have) {
+                T.read(S, tc, dep, [&](const int4 *p, int y) { return gld(p + y); }, nt + 1, et);
+                have = true;
+            }
+            GenSide<TW, PD, M> X;
+            X.read(S, x, dep, [&](const int4 *p, int y) { return sld(p + y); }, nx + 1, ex);
+            const uint32_t refX = cx ? nodeof(ra.x) - 1 : S.n + ra.y;
+            const uint32_t lo = min(refX, refT), hi = max(refX, refT);
+            int b1 = multi ? kAdmissibleBound : bd;
+            uint32_t i1 = multi ? 0xFFFFFFFFu : bid;
+            each_move([&](int gx, int gt, bool rev, bool star) {
+                const Join q = join(gx, gt, rev, star);
+                const bool p = passes(gx, gt, star, q.delta);
+                if (!__builtin_amdgcn_ballot_w64(p)) return;
+                const int ax = gx ? gx : 1, at = gt ? gt : 1;
+                const int tv = X.warp(gx, T, gt, rev, q.dx1, q.dx2, star ? T.b[1] : X.b[ax]) +
+                               T.warp(gt, X, gx, rev, q.dt1, q.dt2, star ? X.b[1] : T.b[at]);
+                const int load = star ? (Lt - tb.y) - (Lx - rb.y) : lt[gt] - lx[gx];
+                int px = Lx + load, pt = Lt - load;
+                if (PD) {
+                    px = X.peak(gx, T, gt, rev, star ? T.lb[1] : X.lb[ax]);
+                    pt = T.peak(gt, X, gx, rev, star ? X.lb[1] : T.lb[at]);
+                }
+                const int lv = max(px - cap, 0) + max(pt - cap, 0);
+                uint32_t opk, a = lo, b = hi;  // ids as in gen_eval_move
+                if (star) {
+                    opk = 8u;
+                } else if (!gx || !gt) {
+                    opk = (gx + gt == 1 ? 0u : (rev ? 24u : 20u)) + (uint32_t)(gx + gt);
+                    a = gx ? refX : refT;
+                    b = gx ? refT : refX;
+                } else if (gx == 1 && gt == 1) {
+                    opk = 5u;
+                } else {
+                    opk = refX < refT ? (6u + gx) * 4u + gt : (6u + gt) * 4u + gx;
+                }
+                if (p) gen_record(S, q.delta, lv - lvOld, tv - tvOld, lv == 0, tv == 0, (opk * uQ + a) * uQ + b, dd, df, b1, i1);
+            });
+            if (multi) {  // the best improving move of each pair of routes
+                if (b1 < 0 && i1 != 0xFFFFFFFFu) atomicMin(S.pairkey + (size_t)ra.y * S.R + ta.y, pack_key(b1, i1));
+                if (i1 != 0xFFFFFFFFu) consider(b1, i1, bd, bid);
+            } else {
+                bd = b1;
+                bid = i1;
+            }
+            if (!dd && __builtin_amdgcn_ballot_w64(bd < thr)) {  // publish what was found
+                int wmin = bd;
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) wmin = min(wmin, __shfl_xor(wmin, off));
+                if (lane == 0) atomicMin(thr_sh, wmin);
+            }
+        }
+    }
+}
 
 // Whole-workgroup evaluation of the inter-route moves of the row slots
 // [s0, s1) (fewer than 256) against every column slot of a later route.
@@ -3190,8 +3465,9 @@ __device__ __forceinline__ void gen_strip(const SolDev &S, int s0, int s1, uint3
               offCross = (op_mask & 128) ? 0 : big;
     // the wavefront's steps, and the columns of the current chunk
     const int nr = s1 - s0, T = ((Q - s0 - 1 + 63) / 64) * nr;
-    const int first = T * wave / kInterWaves, end = T * (wave + 1) / kInterWaves;
-    int idx = first;
+    const int first = T * wave / kInterWaves, last = T * (wave + 1) / kInterWaves;
+    int idx = first, end = last;
+    int pushed = 0, queued = 0;  // moves the current step has queued, and the steps before it
     int cb = s0 + 1 + first / nr * 64;
     int nd[A + 2];  // nodes of t - 1 .. t + A
     int4 ta, tb, tg;
@@ -3368,6 +3644,7 @@ __device__ __forceinline__ void gen_strip(const SolDev &S, int s0, int s1, uint3
                 for (int o = 32; o >= 1; o >>= 1) step = min(step, __shfl_xor(step, o));
                 if (lane == 0 && idx - first < kGenSteps) q.step_min[idx - first] = step;
             } else if (__builtin_amdgcn_ballot_w64(valid && m < exists && m - slack <= thr)) {
+                const int had = cnt;
                 each_move([&](int j, int load, int code) {
                     if (j < m0) return;
                     const int over = max(Lx + load - cap, 0) + max(Lt - load - cap, 0);
@@ -3388,10 +3665,15 @@ __device__ __forceinline__ void gen_strip(const SolDev &S, int s0, int s1, uint3
                     }
                     cnt += __builtin_popcountll(mask);
                 });
+                pushed += cnt - had;
             }
             if (next == 0x7FFFFFFF) {  // on to the next row, or the next chunk
                 m0 = 0;
                 ++idx;
+                constexpr int many = EXT ? kGenDenseExt : kGenDense;
+                queued += pushed;
+                if (queued >= many && 4 * pushed >= many) end = idx;  // gen_dense takes the rest
+                pushed = 0;
                 ra = na;
                 rb = nb;
                 rg = ng;
@@ -3469,6 +3751,17 @@ __device__ __forceinline__ void gen_strip(const SolDev &S, int s0, int s1, uint3
             cb = s0 + 1 + first / nr * 64;
             fresh = fresh_cols = true;
         }
+    }
+    // (out of line where the registers of the loop above are better for it: with
+    // pickups a step 32.9 us so and 34.7 in line, with windows alone 57 and 60
+    // the other way round)
+    auto rest = [&]() {
+        gen_dense<TW, PD, EXT, W16>(S, s0, s1, first, end, last, op_mask, dd, df, rows, thr_sh, q.step_min, bd, bid);
+    };
+    if constexpr (TW && !PD) {
+        if (end < last) rest();
+    } else {
+        if (__builtin_expect(end < last, 0)) rest();
     }
     block_argmin_commit(bd, bid, S.best_key, red);
 }
