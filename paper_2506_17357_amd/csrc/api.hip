@@ -785,7 +785,11 @@ static void to_move(const int32_t *rec, tga_move_t *m) {
 
 // General path (penalised mode, pickups, operator variants, multi-move).
 // The rows go in strips of equal work, as many as let two workgroups share
-// every compute unit with the intra-route groups, as many staged at a time as
+// every compute unit with the intra-route groups and at least one per four
+// rows, as empty routes' rows and groups hold next to no work (2000 empty
+// routes beside 60: 258 of their groups left 254 strips, a hundred of them with
+// all the work; penalised step 195 us, 110 with a strip per four rows; sweep
+// solutions of 5000 customers 174 and 147); as many staged at a time as
 // general_rows says, with their halo (one row before, one after, three with
 // the variants).  Without a 16-bit copy of D, or where one row and its halo do
 // not fit, the distances are gathered from D and nothing is staged.
@@ -799,7 +803,7 @@ static void launch_eval_general(const tga_solution *sol, uint32_t op_mask, int32
     const int staged = sol->h.D16 && known ? general_rows(np1, halo, P.lds_total) : 0;
     const bool w16 = staged > 0;
     const int rows = w16 ? staged : kGenRows;
-    const int strips = std::min(std::max(2 * cus - e.nintra, cus / 2), (sol->Q + 1) / 2);
+    const int strips = std::min(std::max(2 * cus - e.nintra, sol->Q / 4), (sol->Q + 1) / 2);
     // a solution that cannot hold a route too long to be staged, nor more
     // customers in a group than lanes, needs no workgroups for such routes
     // (see gen_slot_block; beyond 4096 slots they would be too many)

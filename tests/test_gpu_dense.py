@@ -74,3 +74,34 @@ def test_dense_steps(tga, case, problem, wide, mode):
     off, cust, _ = S.get()
     assert (steps, mv) == (len(ids), moves)
     assert np.array_equal(off, fin.offsets) and np.array_equal(cust, fin.customers)
+
+
+def test_spare_vehicles_time(tga):
+    """60 routes with broken windows and 2000 spare vehicles: a penalised step takes about as long as the plain path's
+    evaluation of the same routes (4 times as long when every move that passed the screens was a queue entry)."""
+    import torch
+    inst = W.make_vrptw(1000, 1077, capacity=10 ** 6)
+    order = np.asarray(W._angle_order(inst), np.int32)
+    lengths = [17] * 40 + [16] * 20 + [0] * 2000
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    S = tga.Solution(tga.Instance.from_workload(inst), off, order)
+
+    def median(f):
+        return sorted(f() for _ in range(7))[3]
+
+    def plain():
+        t = time.perf_counter()
+        S.eval()
+        return time.perf_counter() - t
+
+    def step():
+        S.reload(off, order)
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        assert S.ls_run(15)[0] == 15
+        return (time.perf_counter() - t) / 15
+    times = [median(plain)]
+    S.set_penalty(10, 10)
+    times.append(median(step))
+    print("plain evaluation, penalised step: %.0f %.0f us" % (times[0] * 1e6, times[1] * 1e6), flush=True)
+    assert times[1] < 2 * times[0]
