@@ -3769,9 +3769,13 @@ __device__ __forceinline__ void gen_strip(const SolDev &S, int s0, int s1, uint3
 // Views of a route on the general path: staged (gen_arrays), and direct.  A
 // distance is looked up by two positions, each with its key: on the direct
 // view its node, which the walks read a step ahead (one of the two reads a
-// distance waits for), on the staged one nothing.
+// distance waits for), on the staged one nothing.  The walks look up the row
+// of a position that stays the same for the lane: on the direct view its 4 KB
+// stay in the cache, where the other way round every step reads new rows (one
+// route of 1000 customers 0.68 ms a step, 0.56).
 template <bool TW, bool PD>
 struct GenLds {
+    static constexpr bool direct = false;
     const int *b;
     int P;
     __device__ int node(int p) const { return b[p]; }
@@ -3790,6 +3794,7 @@ struct GenLds {
 };
 
 struct GenGlobal {
+    static constexpr bool direct = true;
     const SolDev &S;
     int off, L;
     __device__ int node(int p) const { return p <= L ? nodeof(gld(S.a4 + off + p).x) : 0; }
@@ -3824,6 +3829,24 @@ __device__ __forceinline__ void gen_moves(const SolDev &S, const RV &V, int r, i
     auto LNpos = [&](int p) { return PD ? V.load(p) : Ld{}; };
     auto LFpos = [&](int p) { return PD ? V.lpre(p) : Ld{}; };
     auto LBafter = [&](int p) { return PD ? V.lpost(p) : Ld{}; };
+    // on the direct view the part that closes a new route is read beside the
+    // step's distances, not after the test (`at` does it, `use` reads it back)
+    Tw endTw{};
+    Ld endLd{};
+    auto at = [&](auto f, auto lf, int p) {
+        if constexpr (RV::direct) {
+            endTw = f(p);
+            endLd = lf(p);
+        }
+    };
+    auto use = [&](auto f, int p) {
+        if constexpr (RV::direct) return endTw;
+        else return f(p);
+    };
+    auto luse = [&](auto f, int p) {
+        if constexpr (RV::direct) return endLd;
+        else return f(p);
+    };
     const int4 g = gld(S.g4 + off);
     const int lvR = max(g.z - cap, 0), tvR = g.w;
     const int slack = S.pen ? S.wL * lvR + S.wT * tvR : 0;
@@ -3854,6 +3877,7 @@ __device__ __forceinline__ void gen_moves(const SolDev &S, const RV &V, int r, i
 #pragma unroll 1
         for (int j = i + 1; j <= L; ++j) {
             const int ej = V.edge(j), kn = V.key(min(j + 2, L + 1));
+            at(Bafter, LBafter, j);
             refresh();
             if (TW && op2o) rev = tw_cat(Npos(j), ejm, rev);
             if (PD && op2o) lrev = ld_cat(LNpos(j), lrev);
@@ -3861,15 +3885,15 @@ __device__ __forceinline__ void gen_moves(const SolDev &S, const RV &V, int r, i
             const int dO = d1 + d2 - eP - ej;
             int dA = 0, dB = 0, dS = dO;
             if (j > i + 1) {
-                dA = V.dd(j, kj, i + 1, kI1);
-                dB = V.dd(j - 1, kjm, i, kI);
+                dA = V.dd(i + 1, kI1, j, kj);
+                dB = V.dd(i, kI, j - 1, kjm);
                 dS = d1 + dA + dB + d2 - eP - eI - ejm - ej;
             }
             const uint32_t refI = V.node(i, kI) - 1, refJ = V.node(j, kj) - 1;
             const uint32_t lo = min(refI, refJ), hi = max(refI, refJ);
             if (op2o && can(dO)) {
-                const int tv = TW ? tw_cat(tw_cat(Fi1, d1, rev), d2, Bafter(j)).v : 0;
-                rec(dO, tv, excess(ld_cat(ld_cat(LFi1, lrev), LBafter(j))), (12u * uQ + lo) * uQ + hi);
+                const int tv = TW ? tw_cat(tw_cat(Fi1, d1, rev), d2, use(Bafter, j)).v : 0;
+                rec(dO, tv, excess(ld_cat(ld_cat(LFi1, lrev), luse(LBafter, j))), (12u * uQ + lo) * uQ + hi);
             }
             if (opSwap && can(dS)) {
                 Tw f = TW ? tw_cat(Fi1, d1, Npos(j)) : Tw{};
@@ -3878,8 +3902,8 @@ __device__ __forceinline__ void gen_moves(const SolDev &S, const RV &V, int r, i
                     if (TW) f = tw_cat(f, dA, mid);
                     if (PD) lf = ld_cat(lf, lmid);
                 }
-                const int tv = TW ? tw_cat(tw_cat(f, j > i + 1 ? dB : ejm, Npos(i)), d2, Bafter(j)).v : 0;
-                rec(dS, tv, excess(ld_cat(ld_cat(lf, LNpos(i)), LBafter(j))), (5u * uQ + lo) * uQ + hi);
+                const int tv = TW ? tw_cat(tw_cat(f, j > i + 1 ? dB : ejm, Npos(i)), d2, use(Bafter, j)).v : 0;
+                rec(dS, tv, excess(ld_cat(ld_cat(lf, LNpos(i)), luse(LBafter, j))), (5u * uQ + lo) * uQ + hi);
             }
             if (TW && opSwap) mid = (j == i + 1) ? Npos(j) : tw_cat(mid, ejm, Npos(j));  // c_{i+1} .. c_j
             if (PD && opSwap) lmid = (j == i + 1) ? LNpos(j) : ld_cat(lmid, LNpos(j));
@@ -3912,13 +3936,14 @@ __device__ __forceinline__ void gen_moves(const SolDev &S, const RV &V, int r, i
 #pragma unroll 1
         for (int j = wi; j <= L; ++j) {  // forward: middle c_{i+k} .. c_j
             const int kn = V.key(min(j + 2, L + 1));
+            at(Bafter, LBafter, j);
             refresh();
             if (TW) mid = (j == wi) ? Npos(j) : tw_cat(mid, V.edge(j - 1), Npos(j));
             if (PD) lmid = (j == wi) ? LNpos(j) : ld_cat(lmid, LNpos(j));
-            const int dVF = V.dd(j, kj, i, kI), dGV = V.dd(gi, kG, j + 1, kj1), dO = base + dVF + dGV - V.edge(j);
+            const int dVF = V.dd(i, kI, j, kj), dGV = V.dd(gi, kG, j + 1, kj1), dO = base + dVF + dGV - V.edge(j);
             if (can(dO)) {
-                const int tv = TW ? tw_cat(tw_cat(tw_cat(Fi1, dPW, mid), dVF, sig), dGV, Bafter(j)).v : 0;
-                rec(dO, tv, excess(ld_cat(ld_cat(ld_cat(LFi1, lmid), lsig), LBafter(j))),
+                const int tv = TW ? tw_cat(tw_cat(tw_cat(Fi1, dPW, mid), dVF, sig), dGV, use(Bafter, j)).v : 0;
+                rec(dO, tv, excess(ld_cat(ld_cat(ld_cat(LFi1, lmid), lsig), luse(LBafter, j))),
                     ((16u + k) * uQ + ref(i)) * uQ + ref(j));
             }
             kj = kj1;
@@ -3930,13 +3955,14 @@ __device__ __forceinline__ void gen_moves(const SolDev &S, const RV &V, int r, i
 #pragma unroll 1
     for (int j = i - 2; j >= 0; --j) {  // backward: middle c_{j+1} .. c_{i-1}
         const int kn = V.key(max(j - 1, 0));
+        at(Fpos, LFpos, j);
         refresh();
         if (TW) mid = (j == i - 2) ? Npos(i - 1) : tw_cat(Npos(j + 1), V.edge(j + 1), mid);
         if (PD) lmid = (j == i - 2) ? LNpos(i - 1) : ld_cat(LNpos(j + 1), lmid);
-        const int dVF = V.dd(j, kj, i, kI), dGV = V.dd(gi, kG, j + 1, kj1), dO = base + dVF + dGV - V.edge(j);
+        const int dVF = V.dd(i, kI, j, kj), dGV = V.dd(gi, kG, j + 1, kj1), dO = base + dVF + dGV - V.edge(j);
         if (can(dO)) {
-            const int tv = TW ? tw_cat(tw_cat(tw_cat(Fpos(j), dVF, sig), dGV, mid), dPW, Bafter(gi)).v : 0;
-            rec(dO, tv, excess(ld_cat(ld_cat(ld_cat(LFpos(j), lsig), lmid), LBafter(gi))),
+            const int tv = TW ? tw_cat(tw_cat(tw_cat(use(Fpos, j), dVF, sig), dGV, mid), dPW, Bafter(gi)).v : 0;
+            rec(dO, tv, excess(ld_cat(ld_cat(ld_cat(luse(LFpos, j), lsig), lmid), LBafter(gi))),
                 ((16u + k) * uQ + ref(i)) * uQ + ref(j));
         }
         kj1 = kj;
@@ -4047,10 +4073,10 @@ __device__ __forceinline__ void gen_intra_block(const SolDev &S, int r0, int r1,
 // a group), by slots: one workgroup takes the first positions in the slots
 // [s0, s0 + width), lane = slot, wavefront = walk, all data from memory, so a
 // route of any length is one chain of its length spread over the chip: a
-// penalised step with one route of 1000 customers (CVRP) 0.68 ms, 7.2 ms with
+// penalised step with one route of 1000 customers (CVRP) 0.56 ms, 7.2 ms with
 // all of the route's first positions in turn on one workgroup.  32 slots a
-// workgroup: with 64 the gathers of eight wavefronts keep one compute unit's
-// address path busy (0.78 ms), 16 gain little more (0.62).  With no such route
+// workgroup: with 64 the gathers of eight wavefronts kept one compute unit's
+// address path busy (0.78 ms when 32 took 0.68), 16 gained little more (0.62).  With no such route
 // the workgroup ends after two reads.
 template <bool TW, bool PD>
 __device__ __forceinline__ void gen_slot_block(const SolDev &S, int s0, int width, int G, uint32_t op_mask,
