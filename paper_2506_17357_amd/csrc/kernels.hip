@@ -3424,8 +3424,10 @@ __device__ __forceinline__ void gen_dense(const SolDev &S, int s0, int s1, int f
 // best queued.  The queue is evaluated 64 moves at a time, one per lane, so
 // the long concatenations run on full wavefronts whatever the share of lanes
 // that passed.  A queue that fills up in the middle of a step is drained and
-// the step taken again from the move that did not fit.  Dumps and multi-move
-// steps (which need every improving move) start with the second pass.
+// the step taken again from the move that did not fit.  A wavefront that has
+// queued as many moves as a whole step holds leaves its remaining steps to
+// gen_dense.  Dumps and multi-move steps (which need every improving move)
+// start with the second pass.
 //
 // The evaluation launch (with the intra-route groups) against one thread per
 // pair evaluating all of its moves, and one per walk gathering from memory, in
